@@ -1139,6 +1139,12 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
     }
     {
       const ColMap cm{nullptr, slot, pos0, 0};
+      // Transposed copy of the V rows of earlier calls and blocks, from the cache.  Before the append
+      // kernel, which writes the block's own columns of the copy: the transpose stores whole groups
+      // of 64 positions and pos0 may lie inside the last one.
+      if (pos0 > 0)
+        RUN(FAM_MISC, pos0 * Dkv * 2.0 * w, 0,
+            launch_v_transpose(s, L.vc, slot, nkv, c.max_seq, pos0, m->pb_vt, m->pb_vt_stride));
       RUN(FAM_QKROPE, T * Nqkv * 4.0, 0,
           launch_qknorm_rope_append(s, m->dt, m->pb_qkv, nq, nkv, L.g_q, L.g_k, c.rms_eps, m->rope, cm, (int)n, L.kc,
                                     L.vc, c.max_batch, c.max_seq, nullptr, m->pb_vt, m->pb_vt_stride));
@@ -1149,11 +1155,6 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       // slot's V rows (positions of earlier blocks included)
       double rows = 0;
       for (uint32_t i = 0; i < n; ++i) rows += pos0 + i + 1.0;
-      // the block's own V rows were written transposed by the append kernel; rows of earlier
-      // blocks come from the cache
-      if (pos0 > 0)
-        RUN(FAM_MISC, pos0 * Dkv * 2.0 * w, 0,
-            launch_v_transpose(s, L.vc, slot, nkv, c.max_seq, pos0, m->pb_vt, m->pb_vt_stride));
       RUN(FAM_PATTN, (pos0 + T) * 2.0 * Dkv * w + T * Dq * 6.0, rows * 4.0 * Dq,
           launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n,
                               pieces, m->pb_fb, m->n_cus, m->opt_prefill_attn));

@@ -143,6 +143,23 @@ def test_large_block_prefill_lengths(nnc, n):
         assert int(ng.item()) == t
 
 
+@pytest.mark.parametrize("turns", [(70, 41), (64, 33), (1, 20), (37, 90, 65), (100, 600)], ids=str)
+def test_prompt_continued_at_any_position(nnc, turns):
+    """A prompt call that continues a slot at a position inside a group of 64: the transposed V copy of
+    the earlier rows must not overwrite the columns of the call's own rows."""
+    print(f"case: prompt in turns of {turns}", flush=True)
+    shape = SMALL_G4
+    g, o = _pair(nnc, shape, 1, 800, exact_prefill=False)
+    toks = synth.tokens(sum(turns), shape.vocab, stream=700)
+    at = 0
+    for n in turns:
+        lg, ng = g.prefill(0, toks[at:at + n])
+        lo, no = oracle_prefill_like_library(o, 0, toks[at:at + n], shape)
+        _check_logits(shape, lg, lo, BF16_ABS_PROMPT if n > 512 else BF16_ABS_TIGHT)
+        assert int(ng.item()) == no
+        at += n
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("n", [47, 300, 700])
 def test_large_block_prefill_every_block_tile(nnc, n, tile):
