@@ -101,6 +101,7 @@ struct nnc_model {
   float *pb_x = nullptr, *pb_qkv = nullptr;
   float* pb_part = nullptr;                 // k-slice partial sums of short blocks' O / down projections
   void *pb_fa = nullptr, *pb_fb = nullptr;  // fragment-order bf16 operands: K = H, K = max(Dq, F)
+  float* pb_ssq = nullptr;  // partial sums of squares of a short block's rows (nnc_small.hip)
   void* pb_w = nullptr;  // byte-weight models: the matrix of the next prompt GEMM, widened to bf16 tiles
   int32_t* pb_tok = nullptr;
   void* pb_vt = nullptr;  // transposed V copy of the slot being prefilled
@@ -289,6 +290,7 @@ struct Launch {
 // at most PB_SPLIT_TOKENS tokens on the 64-row tiles under the fixed rules.
 constexpr int PB_SPLIT_MAX = 4;
 constexpr uint32_t PB_SPLIT_TOKENS = 512;
+constexpr uint32_t PB_SMALL_TOKENS = 512;  // longest block the kernels of nnc_small.hip are chosen for
 constexpr int MAX_KSPLIT = 8;  // the norm kernel folds at most eight pending partials
 int pick_kts(int n_tiles, int KT) {
   int ksplit = 512 / (n_tiles > 0 ? n_tiles : 1);
@@ -846,6 +848,7 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
     if (m->w8) ALLOC(m->pb_w, void*, std::max(std::max(Dq + 2 * Dkv, 2 * F) * H, H * std::max(Dq, F)) * 2);
     // k-slice partials of the narrow projections (up to PB_SPLIT_MAX - 1 buffers of a whole block)
     ALLOC(m->pb_part, float*, (size_t)(PB_SPLIT_MAX - 1) * pb * H * 4);
+    ALLOC(m->pb_ssq, float*, (H / 16) * (size_t)std::min<uint32_t>(pb, PB_SMALL_TOKENS) * 4);
     // transposed V copy of one slot: [kv head][128][positions, padded to a multiple of 32];
     // zero-filled once so that positions never written read as finite values
     m->pb_vt_stride = (c.max_seq + 31) / 32 * 32;
@@ -1029,13 +1032,130 @@ nnc_status nnc_set_option(nnc_model* m, nnc_option opt, int32_t value) {
   return fail(NNC_E_ARG, "unknown option %d", (int)opt);
 }
 
+// Logits of a prompt block's last token (row n - 1 of pb_x): fp32-grade (three-piece) GEMV over the LM
+// head.  pending: k-slice partials of the last projection still to be added to that row.
+static nnc_status prefill_head(nnc_model* m, uint32_t n, int pending, float* logits_out, int32_t* next_dev) {
+  const nnc_config& c = m->c;
+  hipStream_t s = m->stream;
+  const int H = m->H(), V = m->V();
+  const long part_stride = (long)m->pb_max * H;
+  const double w = 2.0;
+  RUN(FAM_NORM, H * 8.0, 0,
+      launch_rmsnorm_pack(s, m->dt, m->pb_x + (size_t)(n - 1) * H, H, m->pb_part + (size_t)(n - 1) * H, pending,
+                          part_stride, m->g_final, H, c.rms_eps, 1, m->Xp, 3, 3));
+  GemmArgs a{};
+  a.Wp = m->lm_head; a.n_tiles = V / 16; a.KT = H / 32; a.kts_per_split = H / 32;
+  a.Xp = m->Xp; a.NC = 3; a.ncols = 3; a.nsplit = 3; a.nseq = 1;
+  a.out = logits_out ? logits_out : m->logits; a.ldo = V;
+  RUN(FAM_GEMM_HEAD, (double)V * H * w, 2.0 * V * H, launch_gemm(s, m->dt, EPI_STORE, a));
+  if (next_dev)
+    RUN(FAM_ARGMAX, V * 4.0, 0, launch_argmax(s, a.out, V, V, 1, nullptr, 0, m->am_val, m->am_idx, next_dev));
+  return NNC_OK;
+}
+
+// Whether a block of n tokens runs through the kernels of nnc_small.hip.  They save three kernels per
+// layer (12 us with their gaps) but re-read the weights from L2 once per 32 - 64 operand columns, which
+// costs more than that from n * (weight bytes of a layer) = 16e9 on.  Measured, us per layer, block
+// tiles / short-block kernels: 0.6B 66 / 53 at 128 tokens, 111 / 106 at 512; 1.7B 101 / 94 at 128, 127 / 127
+// at 256, 153 / 202 at 333; 4B 130 / 122 at 64, 141 / 158 at 128.  binary16 keeps its norm kernels (0.6B 83 / 78
+// at 256, 111 / 112 at 512): half the limit.  One row block per head leaves the q|k|v GEMM of the 4096-wide
+// shape on 48 CUs (33 us at 16 tokens, 14 on the block tiles): hidden sizes up to 2560.  Byte weights need no
+// widened copy here: 8B 303 / 202 at 128 tokens, 383 / 360 at 256, 484 / 494 at 333; 1.7B 148 / 126 and 174 / 186.
+static bool short_block(const nnc_model* m, uint32_t n) {
+  if (n > PB_SMALL_TOKENS || m->opt_prefill_exact == 1) return false;
+  if (m->w8) return n <= 256;
+  const double H = m->H(), layer = 2.0 * (H * (2.0 * m->Dq() + 2.0 * m->Dkv()) + 3.0 * H * m->F());
+  return H <= 2560 && n * layer <= (m->dt == NNC_F16 ? 8e9 : 16e9);
+}
+
+// Prompt pass over one short block (two pieces per activation) with the kernels of nnc_small.hip.
+static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t* tokens, uint32_t n, uint32_t pos0,
+                                      bool want_head, float* logits_out, int32_t* next_dev) {
+  const nnc_config& c = m->c;
+  hipStream_t s = m->stream;
+  const int H = m->H(), Dq = m->Dq(), Dkv = m->Dkv(), F = m->F();
+  const int nq = c.n_q_heads, nkv = c.n_kv_heads, Nqkv = Dq + 2 * Dkv;
+  const bool f16 = m->dt == NNC_F16;
+  const int tt = (int)((n + 15) / 16), xt = m->w8 ? 2 : 1, kt = m->wktile();
+  const double w = 2.0, lw = (double)m->wsz(), T = n;
+  const Machine mc = machine_mi355x(m->n_cus);
+  const SmallGemmPlan pq = plan_small_gemm(mc, SEPI_QKV, Nqkv / 16, H / kt, 2 * tt, xt),
+                      po = plan_small_gemm(mc, SEPI_RESID, H / 16, Dq / kt, 2 * tt, xt),
+                      pg = plan_small_gemm(mc, SEPI_SWIGLU, 2 * F / 16, H / kt, 2 * tt, xt),
+                      pd = plan_small_gemm(mc, SEPI_RESID, H / 16, F / kt, 2 * tt, xt);
+  int blocks = 1;  // partial sums of squares per token that the next GEMM adds up
+  auto gemm = [&](const void* W, const float* scale, int rows, int K, const void* X) {
+    SmallGemmArgs a;
+    a.Wp = W; a.wscale = scale; a.n_tiles = rows / 16; a.KT = K / kt;
+    a.Xf = X; a.t_tiles = 2 * tt; a.n_tokens = (int)n;
+    a.ssq_stride = 16 * tt; a.H = H; a.eps = c.rms_eps;
+    return a;
+  };
+  auto normed_by = [&](SmallGemmArgs& a) {
+    if (f16) return;
+    a.ssq = m->pb_ssq; a.ssq_blocks = blocks;
+  };
+  auto resid = [&](SmallGemmArgs& a, const SmallGemmPlan& p, const float* gain) {
+    a.x = m->pb_x;
+    if (f16 || !gain) return;
+    a.gain = gain; a.Xn = m->pb_fa; a.ssq_out = m->pb_ssq;
+    blocks = (a.n_tiles + p.nt - 1) / p.nt;
+  };
+  HIP_TRY(hipMemcpyAsync(m->pb_tok, tokens, (size_t)n * 4, hipMemcpyHostToDevice, s));
+  if (f16 || !c.n_layers)
+    RUN(FAM_EMBED, T * H * w, 0, launch_embed_rows(s, f16, m->embed, H, m->pb_tok, (int)n, m->pb_x));
+  else
+    RUN(FAM_EMBED, T * H * w, 0,
+        launch_embed_rows_pack(s, m->embed, H, m->pb_tok, (int)n, m->L[0].g_in, m->pb_x, m->pb_fa, m->pb_ssq));
+  for (uint32_t li = 0; li < c.n_layers; ++li) {
+    const LayerW& L = m->L[li];
+    if (f16) RUN(FAM_NORM, T * H * 6.0, 0, launch_rmsnorm_frag(s, f16, m->pb_x, nullptr, 0, 0, L.g_in, H, c.rms_eps, (int)n, tt, 2, m->pb_fa));
+    if (pos0 > 0)
+      RUN(FAM_MISC, pos0 * Dkv * 2.0 * w, 0,
+          launch_v_transpose(s, L.vc, slot, nkv, c.max_seq, pos0, m->pb_vt, m->pb_vt_stride));
+    {
+      SmallGemmArgs a = gemm(L.wqkv, L.sqkv, Nqkv, H, m->pb_fa);
+      normed_by(a);
+      a.gq = L.g_q; a.gk = L.g_k; a.rope = m->rope; a.slot = slot; a.pos0 = pos0; a.max_seq = c.max_seq;
+      a.nq = nq; a.nkv = nkv; a.q = m->pb_qkv; a.ldq = Nqkv; a.kc = L.kc; a.vc = L.vc; a.vt = m->pb_vt; a.vt_stride = m->pb_vt_stride;
+      RUN(FAM_PGEMM, (double)Nqkv * H * lw, 2.0 * Nqkv * H * T, launch_gemm_small(s, f16, SEPI_QKV, a, pq.nt, pq.ct));
+    }
+    if (m->record_layers) HIP_TRY(hipEventRecord(m->layer_done[li], s));
+    double rows = 0;
+    for (uint32_t i = 0; i < n; ++i) rows += pos0 + i + 1.0;
+    RUN(FAM_PATTN, (pos0 + T) * 2.0 * Dkv * w + T * Dq * 6.0, rows * 4.0 * Dq,
+        launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n, 2,
+                            m->pb_fb, m->n_cus, m->opt_prefill_attn));
+    {
+      SmallGemmArgs a = gemm(L.wo, L.so, H, Dq, m->pb_fb);
+      resid(a, po, L.g_post);
+      RUN(FAM_PGEMM_O, (double)H * Dq * lw, 2.0 * H * Dq * T, launch_gemm_small(s, f16, SEPI_RESID, a, po.nt, po.ct));
+    }
+    if (f16) RUN(FAM_NORM, T * H * 6.0, 0, launch_rmsnorm_frag(s, f16, m->pb_x, nullptr, 0, 0, L.g_post, H, c.rms_eps, (int)n, tt, 2, m->pb_fa));
+    {
+      SmallGemmArgs a = gemm(L.wgu, L.sgu, 2 * F, H, m->pb_fa);
+      normed_by(a);
+      a.packed_out = m->pb_fb;
+      RUN(FAM_PGEMM_GU, 2.0 * F * H * lw, 4.0 * F * H * T, launch_gemm_small(s, f16, SEPI_SWIGLU, a, pg.nt, pg.ct));
+    }
+    {
+      SmallGemmArgs a = gemm(L.wd, L.sd, H, F, m->pb_fb);
+      resid(a, pd, li + 1 < c.n_layers ? m->L[li + 1].g_in : nullptr);
+      RUN(FAM_PGEMM_D, (double)H * F * lw, 2.0 * H * F * T, launch_gemm_small(s, f16, SEPI_RESID, a, pd.nt, pd.ct));
+    }
+  }
+  return want_head ? prefill_head(m, n, 0, logits_out, next_dev) : NNC_OK;
+}
+
 // Prompt pass over one block of up to pb_max tokens of one slot with the LDS-staged
 // matrix-core GEMMs.  Activations entering a GEMM are rounded to bf16 once.
 static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* tokens, uint32_t n, uint32_t pos0,
                                 bool want_head, float* logits_out, int32_t* next_dev) {
   const nnc_config& c = m->c;
+  if (m->opt_planner && m->opt_prefill_tile < 0 && short_block(m, n))
+    return prefill_block_small(m, slot, tokens, n, pos0, want_head, logits_out, next_dev);
   hipStream_t s = m->stream;
-  const int H = m->H(), Dq = m->Dq(), Dkv = m->Dkv(), F = m->F(), V = m->V();
+  const int H = m->H(), Dq = m->Dq(), Dkv = m->Dkv(), F = m->F();
   const int nq = c.n_q_heads, nkv = c.n_kv_heads, Nqkv = Dq + 2 * Dkv;
   const bool f16 = m->dt == NNC_F16;
   const int tt = (int)((n + 15) / 16);  // token tiles; rows up to 16 * tt exist in every buffer
@@ -1184,20 +1304,7 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       RUN(FAM_PGEMM_D, (double)H * F * w, 2.0 * H * F * T, launch_gemm_prefill(s, f16, EPI_RESID, a, pieces, shape));
     }
   }
-  if (want_head) {
-    // logits of the block's last token: fp32-grade (three-piece) GEMV over the LM head
-    RUN(FAM_NORM, H * 8.0, 0,
-        launch_rmsnorm_pack(s, m->dt, m->pb_x + (size_t)(n - 1) * H, H, m->pb_part + (size_t)(n - 1) * H, pending,
-                            part_stride, m->g_final, H, c.rms_eps, 1, m->Xp, 3, 3));
-    GemmArgs a{};
-    a.Wp = m->lm_head; a.n_tiles = V / 16; a.KT = H / 32; a.kts_per_split = H / 32;
-    a.Xp = m->Xp; a.NC = 3; a.ncols = 3; a.nsplit = 3; a.nseq = 1;
-    a.out = logits_out ? logits_out : m->logits; a.ldo = V;
-    RUN(FAM_GEMM_HEAD, (double)V * H * w, 2.0 * V * H, launch_gemm(s, m->dt, EPI_STORE, a));
-    if (next_dev)
-      RUN(FAM_ARGMAX, V * 4.0, 0, launch_argmax(s, a.out, V, V, 1, nullptr, 0, m->am_val, m->am_idx, next_dev));
-  }
-  return NNC_OK;
+  return want_head ? prefill_head(m, n, pending, logits_out, next_dev) : NNC_OK;
 }
 
 // Second stream and per-layer events for the tail of a long prompt; false if they cannot be had

@@ -179,6 +179,48 @@ struct PrefillGemmArgs {
   long part_stride = 0;
 };
 hipError_t launch_gemm_prefill(hipStream_t s, bool f16, int epi, const PrefillGemmArgs& a, int pieces, int shape);
+
+// ---- prompt GEMMs of short blocks (two pieces per activation; nnc_small.hip) ----
+// Y[t, n] = sum_k X[t, k] W[n, k], X in fragment order with two pieces per activation, W packed
+// 16-bit tiles or byte tiles (wscale != NULL; KT then counts 64-wide k tiles).
+enum SmallEpilogue { SEPI_QKV = 0, SEPI_RESID = 1, SEPI_SWIGLU = 2 };
+struct SmallGemmArgs {
+  const void* Wp = nullptr;
+  const float* wscale = nullptr;
+  int n_tiles = 0, KT = 0;
+  const void* Xf = nullptr;
+  int t_tiles = 0, n_tokens = 0;  // operand column tiles = token tiles x 2
+  // The operand is gain * x, not yet divided by its root mean square: outputs are multiplied by
+  // 1 / sqrt(mean x^2 + eps), the mean from ssq[block * ssq_stride + token] (ssq_blocks partial sums per
+  // token).  NULL: the operand is already normed.
+  const float* ssq = nullptr;
+  int ssq_blocks = 0;
+  long ssq_stride = 0;  // also of ssq_out
+  int H = 0;            // hidden size (mean above; row stride of x)
+  float eps = 0.f;
+  // SEPI_QKV: QK norm, rotary embedding, cache append; rotated queries to q[t * ldq + head * 128]
+  const float *gq = nullptr, *gk = nullptr;
+  const float2* rope = nullptr;
+  uint32_t slot = 0, pos0 = 0, max_seq = 0;
+  int nq = 0, nkv = 0;
+  float* q = nullptr;
+  long ldq = 0;
+  void *kc = nullptr, *vc = nullptr, *vt = nullptr;
+  uint32_t vt_stride = 0;
+  // SEPI_RESID: x += y; with a gain, gain * x goes to Xn (two pieces, fragment order) and the sum of
+  // x^2 over row block b of nt tiles to ssq_out[b * ssq_stride + token]
+  float* x = nullptr;
+  const float* gain = nullptr;
+  void* Xn = nullptr;
+  float* ssq_out = nullptr;
+  // SEPI_SWIGLU: silu(gate) * up in fragment order, two pieces
+  void* packed_out = nullptr;
+};
+// nt x ct: row tiles x column tiles per workgroup
+hipError_t launch_gemm_small(hipStream_t s, bool f16, int epi, const SmallGemmArgs& a, int nt, int ct);
+hipError_t launch_embed_rows_pack(hipStream_t s, const void* Ep, int H, const int32_t* tokens_dev, int n, const float* gain,
+                                  float* x, void* Xn, float* ssq);
+
 // packed byte tiles (n_tiles x KT8 of 16 rows x 64 k) -> bf16 tiles of 16 rows x 32 k in the same tile order
 // (exact: |byte| <= 127), the operand the block-tile prompt GEMMs copy into LDS
 hipError_t launch_widen_w8(hipStream_t s, const void* src, void* dst, int n_tiles, int KT8);

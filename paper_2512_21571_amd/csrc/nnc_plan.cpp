@@ -161,4 +161,26 @@ SkinnyGemmPlan plan_skinny_gemm(const Machine& mc, int n_tiles, int KT, int ncol
   return best;
 }
 
+SmallGemmPlan plan_small_gemm(const Machine& mc, int epi, int n_tiles, int KT, int col_tiles, int xt) {
+  static const int tiles[3][5][2] = {{{8, 2}, {8, 4}}, {{1, 2}, {2, 2}, {4, 2}, {2, 4}, {4, 4}}, {{2, 2}, {4, 2}, {4, 4}, {6, 4}, {8, 4}}};
+  SmallGemmPlan best{};
+  best.t_us = 1e30;
+  for (const auto& t : tiles[epi]) {
+    const int nt = t[0], ct = t[1];
+    if (!nt) continue;
+    const int wgs = ceil_div(n_tiles, nt) * ceil_div(col_tiles, ct), rounds = ceil_div(wgs, mc.cus);
+    const double bytes = (double)KT * (nt + ct * xt) * 1024.0;
+    // what the busiest CU pulls out of L2 (a loads-only kernel reaches 100 - 120 GB/s per CU, these 55 - 90),
+    // the matrix-core time, the weights from HBM; an epilogue per workgroup; launch
+    const double t_cu = rounds * bytes / 100e3;
+    const double t_mfma = (double)rounds * KT * xt * nt * ct / 4 * 16 / 2200.0;
+    const double t_hbm = (double)n_tiles * KT * 1024.0 / mc.hbm_bytes_per_us;
+    const double total = std::max(std::max(t_cu, t_mfma), t_hbm) + 0.15 * nt * ct / 2 * rounds + 3.0;
+    if (total < best.t_us) {
+      best.nt = nt; best.ct = ct; best.workgroups = wgs; best.t_us = total;
+    }
+  }
+  return best;
+}
+
 }  // namespace nnc

@@ -74,4 +74,12 @@ struct SkinnyGemmPlan {
 SkinnyGemmPlan plan_skinny_gemm(const Machine& mc, int n_tiles, int KT, int ncols, int nseq, int rt_choices,
                                 int max_k_slices);
 
+// GEMM of a short prompt block (k_gemm_small): nt x ct row / column tiles per workgroup.
+struct SmallGemmPlan {
+  int nt, ct, workgroups;
+  double t_us;
+};
+// epi: 0 q|k|v, 1 residual, 2 SwiGLU; xt: operand k tiles per weight tile (2 for byte weights)
+SmallGemmPlan plan_small_gemm(const Machine& m, int epi, int n_tiles, int KT, int col_tiles, int xt);
+
 }  // namespace nnc

@@ -160,6 +160,35 @@ def test_prompt_continued_at_any_position(nnc, turns):
         at += n
 
 
+@pytest.mark.parametrize("n", [16, 17, 33, 100, 129, 250])
+@pytest.mark.parametrize("dtype,dims", [(synth.BF16, (1024, 16, 8, 3072)), (synth.F16, (1024, 16, 8, 3072)), (synth.BF16, (2560, 32, 8, 1216)),
+                                        (synth.W8, (2048, 16, 8, 6144)), (synth.BF16, (352, 6, 3, 736))], ids=str)
+def test_short_block_kernels(nnc, dtype, dims, n):
+    """The GEMMs of short prompt blocks on layer shapes that make the tile model pick their different tiles
+    (remainders of token tiles, column blocks and row blocks among them), against the block-tile kernels
+    (the library without its tile model) on the same prompt, continued at an odd position.  Both carry two pieces
+    per activation: the logits differ by what a cached element rounding the other way moves, as in the
+    other comparisons of two-piece paths."""
+    H, nq, nkv, F = dims
+    print(f"case: short block of {n} tokens, dtype {dtype}, {dims}", flush=True)
+    shape = synth.ModelShape("short", hidden=H, n_layers=2, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, ffn=F,
+                             vocab=1024, dtype=dtype)
+    g = nnc.Model(shape, synth.make_blob(shape, gain_jitter=0.1), 1, 320)
+    toks = synth.tokens(n + 37, shape.vocab, stream=800 + n)
+    got = {}
+    for planner in (1, 0):
+        g.set_option(nnc.OPT_PLANNER, planner)
+        g.kv_reset(0)
+        a, _ = g.prefill(0, toks[:37])
+        b, _ = g.prefill(0, toks[37:])
+        got[planner] = (a.cpu().numpy(), b.cpu().numpy(), g.kv_read(1, 0, 1, 0, n + 37).cpu().numpy())
+    for x, y in zip(got[1], got[0]):
+        assert np.isfinite(x).all() and np.abs(y).max() > 0.5
+    assert max(np.abs(got[1][i] - got[0][i]).max() for i in (0, 1)) <= BF16_ABS_TIGHT
+    # one 16-bit ulp (2^-8 relative for bf16) of a cached row, plus the upstream noise of the KV-row test above
+    assert np.all(np.abs(got[1][2] - got[0][2]) <= 2.0 ** -7 * np.abs(got[0][2]) + 3e-3)
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("n", [47, 300, 700])
 def test_large_block_prefill_every_block_tile(nnc, n, tile):
