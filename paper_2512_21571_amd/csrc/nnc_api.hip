@@ -336,6 +336,7 @@ struct Pass {
   const uint32_t* step_ptr = nullptr;
   long step_stride = 0;
   int32_t* next = nullptr;  // arg-max output (device) or NULL
+  bool finish = false;      // greedy loop: the arg-max also feeds the tokens back and logs them (needs `next`)
   int grid_chunks = 1;
   double kv_rows = 0;       // sum over columns of (position + 1): cached rows attention must read
   bool one_slot = false;    // the columns are consecutive positions of one slot (prompt chunk)
@@ -353,7 +354,8 @@ nnc_status run_pass(nnc_model* m, const Pass& p) {
   const int KTH = H / m->wktile(), KTQ = Dq / m->wktile(), KTF = F / m->wktile();
   const int Nqkv = Dq + 2 * Dkv;
 
-  if (p.tokens) RUN(FAM_EMBED, n * H * hw, 0, launch_embed(s, dt, m->embed, H, m->st, n, m->x));
+  // (the first layer's norm gathers the embedding rows itself)
+  if (p.tokens && c.n_layers == 0) RUN(FAM_EMBED, n * H * hw, 0, launch_embed(s, dt, m->embed, H, m->st, n, m->x));
 
   const ColMap cm{m->st, 0, 0, 0};
   // k-slice partials of the previous projection still to be added to x
@@ -376,7 +378,10 @@ nnc_status run_pass(nnc_model* m, const Pass& p) {
   for (uint32_t li = 0; li < c.n_layers; ++li) {
     const LayerW& L = m->L[li];
     if (m->wait_layers) HIP_TRY(hipStreamWaitEvent(s, m->layer_done[li], 0));
-    if (!normed)
+    if (p.tokens && li == 0)
+      RUN(FAM_NORM, n * H * (8.0 + hw), 0,
+          launch_embed_rmsnorm_pack(s, dt, m->embed, m->st, m->x, L.g_in, H, c.rms_eps, n, m->Xp, nc, ns));
+    else if (!normed)
       RUN(FAM_NORM, n * H * 8.0, 0,
           launch_rmsnorm_pack(s, dt, m->x, H, m->rpart, pending, pstride, L.g_in, H, c.rms_eps, n, m->Xp, nc, ns));
     normed = false;
@@ -459,7 +464,7 @@ nnc_status run_pass(nnc_model* m, const Pass& p) {
     if (p.next)
       RUN(FAM_ARGMAX, hn * V * 4.0, 0,
           launch_argmax(s, p.logits, p.logits_ld, V, hn, p.step_ptr, p.step_stride, m->am_val, m->am_idx,
-                        p.next));
+                        p.next, p.finish ? m->st : nullptr, m->token_log));
   } else if (!c.has_embed_and_head && pending > 0) {
     // hidden-state models return x itself: add the last projection's partials now
     RUN(FAM_MISC, 0, 0, launch_fold_residual(s, m->x, m->rpart, pending, pstride, (size_t)n * H));
@@ -531,12 +536,11 @@ nnc_status greedy_step(nnc_model* m, uint32_t batch, int nsplit, int grid_chunks
   p.logits = m->logits;
   p.logits_ld = m->V();
   p.next = m->next;
+  p.finish = true;
   p.grid_chunks = grid_chunks;
   const bool graph = allow_graph && m->opt_graph && !m->profiling && m->stream != nullptr;
   if (!graph) {
-    if (nnc_status st = run_pass(m, p)) return st;
-    HIP_TRY(launch_finish_step(m->stream, m->st, (int)batch, m->next, m->token_log));
-    return NNC_OK;
+    return run_pass(m, p);
   }
   const auto key = std::make_tuple((int)batch, nsplit, grid_chunks);
   auto it = m->graphs.find(key);
@@ -544,14 +548,11 @@ nnc_status greedy_step(nnc_model* m, uint32_t batch, int nsplit, int grid_chunks
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));
     nnc_status st = run_pass(m, p);
-    hipError_t e1 = st == NNC_OK ? launch_finish_step(m->stream, m->st, (int)batch, m->next, m->token_log)
-                                 : hipSuccess;
     hipError_t e2 = hipStreamEndCapture(m->stream, &g);
     if (st != NNC_OK) {
       if (g) (void)hipGraphDestroy(g);
       return st;
     }
-    if (e1 != hipSuccess) return dev_fail(e1, "capture finish_step");
     if (e2 != hipSuccess) return dev_fail(e2, "hipStreamEndCapture");
     hipGraphExec_t ge = nullptr;
     hipError_t e3 = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
@@ -1632,10 +1633,10 @@ nnc_status nnc_decode_greedy(nnc_model* m, const uint32_t* slots, const int32_t*
       p.logits = logits_out + (size_t)step * batch * m->V();
       p.logits_ld = m->V();
       p.next = m->next;
+      p.finish = true;
       p.grid_chunks = gc;
       p.kv_rows = kv_rows + (double)step * batch;
       if (nnc_status st = run_pass(m, p)) return st;
-      HIP_TRY(launch_finish_step(m->stream, m->st, (int)batch, m->next, m->token_log));
     } else {
       if (nnc_status st = greedy_step(m, batch, nsplit, gc, true, kv_rows + (double)step * batch)) return st;
     }

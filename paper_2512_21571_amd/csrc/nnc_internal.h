@@ -122,6 +122,8 @@ hipError_t launch_embed(hipStream_t s, int dt, const void* Ep, int H, const ColS
 hipError_t launch_rmsnorm_pack(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
                                long part_stride, const float* gain, int H, float eps, int ncols, void* Xp,
                                int NC, int nsplit);
+hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, const ColState* st, float* x, const float* gain,
+                                     int H, float eps, int ncols, void* Xp, int NC, int nsplit);
 // n 32-bit words = 0 (a fill kernel: safe under graph capture)
 hipError_t launch_zero_words(hipStream_t s, uint32_t* p, int n);
 hipError_t launch_fold_residual(hipStream_t s, float* x, const float* part, int nparts, long part_stride,
@@ -236,11 +238,11 @@ hipError_t launch_attn_prefill(hipStream_t s, bool f16, const float* qkv, int nq
                                uint32_t S, uint32_t slot, uint32_t max_seq, uint32_t pos0, int n, int pieces, void* Of,
                                int n_cus, int shape);
 hipError_t launch_embed_rows(hipStream_t s, bool f16, const void* Ep, int H, const int32_t* tokens_dev, int n, float* x);
+// finish: also feed the tokens back, advance the positions and log the tokens (greedy loop)
 hipError_t launch_argmax(hipStream_t s, const float* logits, long ld, int V, int ncols,
                          const uint32_t* step_ptr, long step_stride, float* scratch_val,
-                         int32_t* scratch_idx, int32_t* next);
-hipError_t launch_finish_step(hipStream_t s, ColState* st, int ncols, const int32_t* next,
-                              int32_t* token_log);
+                         int32_t* scratch_idx, int32_t* next, ColState* finish = nullptr,
+                         int32_t* token_log = nullptr);
 hipError_t launch_kv_read(hipStream_t s, int dt, const void* cache, uint32_t max_seq, int nkv,
                           uint32_t pos0, uint32_t n, float* out);
 hipError_t launch_copy_rows(hipStream_t s, const float* src, float* dst, size_t n);

@@ -174,26 +174,6 @@ hipError_t launch_set_state(hipStream_t s, ColState* st, int ncols, const int32_
   return hipGetLastError();
 }
 
-// After a greedy step: feed the chosen token back, advance positions, log the token.
-__global__ void k_finish_step(ColState* st, int ncols, const int32_t* next, int32_t* token_log) {
-  const int i = threadIdx.x;
-  const uint32_t step = st->step;
-  __syncthreads();
-  if (i < ncols) {
-    const int32_t t = next[i];
-    st->tok[i] = t;
-    st->pos[i] += 1;
-    token_log[(size_t)step * ncols + i] = t;
-  }
-  if (i == 0) st->step = step + 1;
-}
-
-hipError_t launch_finish_step(hipStream_t s, ColState* st, int ncols, const int32_t* next,
-                              int32_t* token_log) {
-  k_finish_step<<<1, MAX_COLS, 0, s>>>(st, ncols, next, token_log);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // embedding gather from the packed matrix: x[col][k] = E[tok[col]][k]
 // ---------------------------------------------------------------------------
@@ -289,13 +269,17 @@ __device__ __forceinline__ void store_normed4(void* Xp, int NC, int nsplit, int 
 // corresponds to blockIdx.x == 0 (the LM head norms a sub-range of the columns).
 // NV = float4 groups per thread: the whole row (H <= 1024 * NV) lives in registers, every load
 // (row, pending partials, gains) is issued before the first use, and the row is neither
-// re-read nor re-written more than once.
-template <bool F32, int NV, class HF>
+// re-read nor re-written more than once.  (A row on 1024 threads instead of 256 measured the same, 4.7 against
+// 4.8 us for 8 rows of 2560 with three partials: the kernel is memory latency from start to end.)
+// EMB: the row comes from the packed embedding matrix (token of the column) and is written to x; a
+// gather kernel of its own in front of the first layer cost a greedy step 6.5 us (8 x 2560).
+template <bool F32, int NV, bool EMB, class HF>
 __global__ __launch_bounds__(256) void k_rmsnorm_pack(float* __restrict__ x, long ldx,
                                                       const float* __restrict__ part, int nparts,
                                                       long part_stride, const float* __restrict__ gain,
                                                       int H, float eps, void* __restrict__ Xp, int NC,
-                                                      int nsplit) {
+                                                      int nsplit, const void* __restrict__ Ep,
+                                                      const ColState* __restrict__ st) {
   __shared__ float sm[4];
   const int seq = blockIdx.x;
   float* xr = x + (size_t)seq * ldx;
@@ -306,7 +290,19 @@ __global__ __launch_bounds__(256) void k_rmsnorm_pack(float* __restrict__ x, lon
     const int i = (threadIdx.x + 256 * q) * 4;
     v[q] = g[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < H) {
-      v[q] = *reinterpret_cast<const float4*>(xr + i);
+      if constexpr (EMB) {
+        const int r = st->tok[seq];
+        if constexpr (F32) {
+          v[q] = static_cast<const float4*>(Ep)[((size_t)(r >> 4) * (H / 16) + (i >> 4)) * 64 + (r & 15) + 16 * ((i & 15) >> 2)];
+        } else {
+          const size_t e = (((size_t)(r >> 4) * (H / 32) + (i >> 5)) * 64 + (r & 15) + 16 * ((i & 31) >> 3)) * 8 + (i & 7);
+          const uint2 w = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(Ep) + e);
+          v[q] = make_float4(HF::lo(w.x), HF::hi(w.x), HF::lo(w.y), HF::hi(w.y));
+        }
+        *reinterpret_cast<float4*>(xr + i) = v[q];
+      } else {
+        v[q] = *reinterpret_cast<const float4*>(xr + i);
+      }
       g[q] = *reinterpret_cast<const float4*>(gain + i);
 #pragma unroll
       for (int p = 0; p < MAXP; ++p)
@@ -337,18 +333,32 @@ __global__ __launch_bounds__(256) void k_rmsnorm_pack(float* __restrict__ x, lon
   }
 }
 
-hipError_t launch_rmsnorm_pack(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
-                               long part_stride, const float* gain, int H, float eps, int ncols, void* Xp,
-                               int NC, int nsplit) {
+template <bool EMB>
+static hipError_t rmsnorm_pack_dispatch(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
+                                        long part_stride, const float* gain, int H, float eps, int ncols, void* Xp,
+                                        int NC, int nsplit, const void* Ep, const ColState* st) {
   if (H % 4 || H > 8192 || nparts > 8 || nparts < 0 || ldx % 4) return hipErrorInvalidValue;
-#define RN_LAUNCH(NV) \
-  NNC_FOR_DTYPE(dt, k_rmsnorm_pack<F32, NV, HF><<<ncols, 256, 0, s>>>(x, ldx, part, nparts, part_stride, gain, H, eps, Xp, NC, nsplit))
+#define RN_LAUNCH(NV)                                                                                                 \
+  NNC_FOR_DTYPE(dt, k_rmsnorm_pack<F32, NV, EMB, HF><<<ncols, 256, 0, s>>>(x, ldx, part, nparts, part_stride, gain, H, eps, \
+                                                                           Xp, NC, nsplit, Ep, st))
   if (H <= 1024) RN_LAUNCH(1);
   else if (H <= 2048) RN_LAUNCH(2);
   else if (H <= 4096) RN_LAUNCH(4);
   else RN_LAUNCH(8);
 #undef RN_LAUNCH
   return hipGetLastError();
+}
+
+hipError_t launch_rmsnorm_pack(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
+                               long part_stride, const float* gain, int H, float eps, int ncols, void* Xp,
+                               int NC, int nsplit) {
+  return rmsnorm_pack_dispatch<false>(s, dt, x, ldx, part, nparts, part_stride, gain, H, eps, ncols, Xp, NC, nsplit, nullptr, nullptr);
+}
+
+// the same with x[col] = E[tok[col]] first (x is written)
+hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, const ColState* st, float* x, const float* gain,
+                                     int H, float eps, int ncols, void* Xp, int NC, int nsplit) {
+  return rmsnorm_pack_dispatch<true>(s, dt, x, H, nullptr, 0, 0, gain, H, eps, ncols, Xp, NC, nsplit, Ep, st);
 }
 
 __global__ void k_zero_words(uint32_t* p, int n) {
@@ -402,15 +412,16 @@ __device__ __forceinline__ void gemm_norm_tail(const NormTail& t, const float* p
     int role = -1;
     if (done_before + takers >= total) {
       role = (int)(done_before - (total - takers));
-      // at most takers - 1 workgroups are still running: the others among the takers
-      unsigned polls = 0;
-      while (__hip_atomic_load(t.counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < total) {
-        if (++polls > t.spin_limit) {
+      // at most takers - 1 workgroups are still running: the others among the takers.  The count that
+      // the arrival returned is the first poll.
+      for (unsigned polls = 1, seen = done_before + 1; seen < total; ++polls) {
+        if (polls >= t.spin_limit) {
           __hip_atomic_store(t.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           role = -1;
           break;
         }
-        __builtin_amdgcn_s_sleep(4);
+        if (polls > 1) __builtin_amdgcn_s_sleep(4);
+        seen = __hip_atomic_load(t.counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
     si[4] = role;
@@ -1548,28 +1559,44 @@ __global__ __launch_bounds__(256) void k_argmax_part(const float* __restrict__ l
   }
 }
 
-__global__ __launch_bounds__(64) void k_argmax_final(const float* __restrict__ pv,
-                                                     const int32_t* __restrict__ pi,
-                                                     int32_t* __restrict__ next) {
-  const int col = blockIdx.x;
-  float best = pv[col * ARGMAX_BLOCKS + threadIdx.x];
-  int32_t bi = pi[col * ARGMAX_BLOCKS + threadIdx.x];
+// Best of the partial winners, one wave per column; with st, the greedy loop's bookkeeping too: the
+// token is fed back, positions advance, the token is logged at the step's row.
+__global__ __launch_bounds__(1024) void k_argmax_final(const float* __restrict__ pv, const int32_t* __restrict__ pi,
+                                                       int ncols, int32_t* __restrict__ next, ColState* st,
+                                                       int32_t* __restrict__ token_log) {
+  const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const uint32_t step = st ? st->step : 0u;
+  for (int col = threadIdx.x >> 6; col < ncols; col += waves) {
+    float best = pv[col * ARGMAX_BLOCKS + lane];
+    int32_t bi = pi[col * ARGMAX_BLOCKS + lane];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(best, o, 64);
-    const int32_t oi = __shfl_xor(bi, o, 64);
-    argmax_merge(best, bi, ov, oi);
+    for (int o = 32; o > 0; o >>= 1) {
+      const float ov = __shfl_xor(best, o, 64);
+      const int32_t oi = __shfl_xor(bi, o, 64);
+      argmax_merge(best, bi, ov, oi);
+    }
+    if (lane == 0) {
+      const int32_t t = bi == 0x7fffffff ? 0 : bi;
+      next[col] = t;
+      if (st) {
+        st->tok[col] = t;
+        st->pos[col] += 1;
+        token_log[(size_t)step * ncols + col] = t;
+      }
+    }
   }
-  if (threadIdx.x == 0) next[col] = bi == 0x7fffffff ? 0 : bi;
+  __syncthreads();  // every wave has read the step
+  if (st && threadIdx.x == 0) st->step = step + 1;
 }
 
 hipError_t launch_argmax(hipStream_t s, const float* logits, long ld, int V, int ncols,
                          const uint32_t* step_ptr, long step_stride, float* scratch_val,
-                         int32_t* scratch_idx, int32_t* next) {
+                         int32_t* scratch_idx, int32_t* next, ColState* finish, int32_t* token_log) {
   static_assert(ARGMAX_BLOCKS == 64, "final pass assumes one wave of partials");
+  if (finish && !token_log) return hipErrorInvalidValue;
   k_argmax_part<<<dim3(ARGMAX_BLOCKS, ncols), 256, 0, s>>>(logits, ld, V, step_ptr, step_stride,
                                                            scratch_val, scratch_idx);
-  k_argmax_final<<<ncols, 64, 0, s>>>(scratch_val, scratch_idx, next);
+  k_argmax_final<<<1, 64 * (ncols < 16 ? ncols : 16), 0, s>>>(scratch_val, scratch_idx, ncols, next, finish, token_log);
   return hipGetLastError();
 }
 
