@@ -225,7 +225,8 @@ typedef enum {
                                matrix-core work of long blocks).
                                1: 21-token chunks through the decode kernels, three bf16 pieces
                                (fp32-grade) */
-  NNC_OPT_PERSISTENT = 2,   /* 1 (default): batch-1 decode steps of bf16 models run in one
+  NNC_OPT_PERSISTENT = 2,   /* 1 (default): batch-1 decode steps of 16-bit models, and nnc_decode_greedy
+                               runs of two to four sequences of the smaller shapes, run in one
                                resident kernel per call (all steps of nnc_decode_greedy in a
                                single launch); 0: one kernel per stage */
   NNC_OPT_PREFILL_TILE = 4, /* block tile of the large-block prompt GEMMs: -1 (default) chosen from

@@ -111,6 +111,7 @@ struct nnc_model {
   bool mk_ok = false;
   int n_cus = 256;
   int mk_nwg = 0, mk_ks_o = 1, mk_ks_d = 1;
+  uint32_t mk_seqs = 1;  // most sequences the resident kernel decodes together
   unsigned mk_tag = 1;  // next unused exchange tag
   void* mk_layers = nullptr;
   unsigned* mk_error = nullptr;
@@ -567,9 +568,26 @@ nnc_status greedy_step(nnc_model* m, uint32_t batch, int nsplit, int grid_chunks
 bool use_persistent(const nnc_model* m, uint32_t batch) {
   return m->mk_ok && m->opt_persistent && !m->profiling && batch == 1;
 }
+// Greedy runs of two to four sequences.  (Single steps of a batch keep the per-stage kernels, whose bits
+// nnc_decode_step_static promises; so do runs that ask for a variant of those kernels.)
+// Measured, us per step of 7 layers, resident / per-stage: 0.6B at 128 positions 180 / 278 (2 sequences),
+// 227 / 282 (3), 261 / 285 (4); 1.7B 323 / 387 (2).  Every sequence more adds 5 us per layer, most of it the
+// two residual exchanges, which every workgroup reads whole past the caches.  The attention units (64
+// positions of one kv head of one sequence) are walked by one workgroup per CU, the per-stage kernel keeps
+// six there: beyond two units per workgroup that decides (0.6B at 1024 positions 259 / 302 with 3 sequences = 1.6
+// units, 311 / 307 with 4 = 2.1; at 3000 positions 358 / 336 with 3 = 4.5).
+bool use_persistent_greedy(const nnc_model* m, const uint32_t* slots, uint32_t batch, uint32_t n_steps) {
+  if (use_persistent(m, batch)) return true;
+  if (!m->mk_ok || !m->opt_persistent || m->profiling || batch > m->mk_seqs || m->opt_fuse_norm || !m->opt_fuse_qk ||
+      m->opt_decode_pieces == 2)
+    return false;
+  long units = 0;
+  for (uint32_t i = 0; i < batch; ++i) units += (long)m->c.n_kv_heads * ((m->len[slots[i]] + n_steps - 1) / ATT_CHUNK + 1);
+  return units <= 2L * m->mk_nwg;
+}
 
-// n_steps greedy decode steps of one sequence in one resident kernel, starting from
-// `token` at the slot's current length.  Tokens land in token_log [n_steps].
+// n_steps greedy decode steps of one to mk_seqs sequences in one resident kernel, starting from
+// `tokens` at the slots' current lengths.  Tokens land in token_log [n_steps][batch].
 // The give-up flag of the kernels that wait for other workgroups (the resident decode kernel, the
 // norm tails of decode GEMMs) travels to pinned host memory behind the launches; the next call on
 // this model that finds the copy complete looks at it (resident_failed).
@@ -581,14 +599,18 @@ nnc_status fetch_wait_flag(nnc_model* m) {
   return NNC_OK;
 }
 
-nnc_status persistent_steps(nnc_model* m, uint32_t slot, int32_t token, uint32_t n_steps, float* logits_out) {
+nnc_status persistent_steps(nnc_model* m, const uint32_t* slots, const int32_t* tokens, uint32_t batch, uint32_t n_steps,
+                            float* logits_out) {
   const nnc_config& c = m->c;
   MkPlan p{};
   p.nwg = m->mk_nwg;
   p.n_layers = (int)c.n_layers; p.H = (int)m->H(); p.nq = (int)c.n_q_heads; p.nkv = (int)c.n_kv_heads;
   p.F = (int)m->F(); p.V = (int)m->V();
   p.eps = c.rms_eps; p.max_seq = c.max_seq; p.max_chunks = m->max_chunks;
-  p.tok0 = token; p.pos0 = m->len[slot]; p.slot = slot;
+  p.nseq = (int)batch;
+  for (uint32_t b = 0; b < batch; ++b) {
+    p.tok0[b] = tokens[b]; p.pos0[b] = m->len[slots[b]]; p.slot[b] = slots[b];
+  }
   p.n_steps = (int)n_steps;
   p.tag_base = m->mk_tag;
   p.ks_o = m->mk_ks_o; p.ks_d = m->mk_ks_d;
@@ -598,7 +620,9 @@ nnc_status persistent_steps(nnc_model* m, uint32_t slot, int32_t token, uint32_t
     // nothing to prefetch before they wait for q); output-projection units end at the last
     // workgroup; down-projection units start after the attention workgroups
     const int o_units = (int)(m->H() / 16) * p.ks_o;
-    const int att_units = (int)c.n_kv_heads * ((int)(m->len[slot] + n_steps - 1) / ATT_CHUNK + 1);
+    int att_units = 0;
+    for (uint32_t b = 0; b < batch; ++b)
+      att_units += (int)c.n_kv_heads * ((int)(m->len[slots[b]] + n_steps - 1) / ATT_CHUNK + 1);
     auto wrap = [&](int v) { return ((v % p.nwg) + p.nwg) % p.nwg; };
     p.off_att = 0;
     p.off_o = wrap(p.nwg - o_units);
@@ -900,6 +924,7 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
     plan.H = (int)H; plan.nq = (int)c.n_q_heads; plan.nkv = (int)c.n_kv_heads; plan.F = (int)F;
     plan.ks_o = m->mk_ks_o; plan.ks_d = m->mk_ks_d;
     plan.f16 = m->dt == NNC_F16;
+    plan.nseq = 1;
     // The grid's workgroups wait for each other, so all of them must be resident at once: ask
     // the runtime how many fit (registers, LDS).  If the grid does not fit, batch-1 decode
     // falls back to the per-stage kernels; it is not an error.
@@ -918,14 +943,22 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
         if (!ptr) return hipErrorOutOfMemory;
         return hipMemsetAsync(ptr, 0, bytes, s);
       };
-      TRY_OR_BAIL(zeroed(m->mk_xq, (Dq + 2 * Dkv) * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xatt, (size_t)c.n_q_heads * m->max_chunks * 132 * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xo, Dq * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xop, 4 * H * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xact, F * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xdp, 4 * H * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xamv, (size_t)m->mk_nwg * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xami, (size_t)m->mk_nwg * 8));
+      // several sequences at once, where an instance exists, its operand fits and the grid is resident
+      for (int nseq : {MK_MAX_SEQ, 2}) {
+        plan.nseq = nseq;
+        if (m->mk_seqs == 1 && mk_opnd_bytes(plan) <= 96 * 1024 && mk_max_resident_workgroups(plan, m->n_cus) >= m->mk_nwg)
+          m->mk_seqs = (uint32_t)nseq;
+      }
+      m->mk_seqs = std::min(m->mk_seqs, c.max_batch);
+      const size_t ns = m->mk_seqs;
+      TRY_OR_BAIL(zeroed(m->mk_xq, ns * (Dq + 2 * Dkv) * 8));
+      TRY_OR_BAIL(zeroed(m->mk_xatt, ns * c.n_q_heads * m->max_chunks * 132 * 8));
+      TRY_OR_BAIL(zeroed(m->mk_xo, ns * Dq * 8));
+      TRY_OR_BAIL(zeroed(m->mk_xop, ns * 4 * H * 8));
+      TRY_OR_BAIL(zeroed(m->mk_xact, ns * F * 8));
+      TRY_OR_BAIL(zeroed(m->mk_xdp, ns * 4 * H * 8));
+      TRY_OR_BAIL(zeroed(m->mk_xamv, ns * m->mk_nwg * 8));
+      TRY_OR_BAIL(zeroed(m->mk_xami, ns * m->mk_nwg * 8));
       void* tr = nullptr;
       TRY_OR_BAIL(zeroed(tr, (size_t)m->mk_nwg * mk_trace_points((int)c.n_layers) * 8));
       m->mk_trace = static_cast<unsigned long long*>(tr);
@@ -1469,7 +1502,7 @@ nnc_status nnc_decode_step(nnc_model* m, const uint32_t* slots, const int32_t* t
   if (nnc_status st = set_decode_state(m, slots, tokens, batch, &max_pos, &kv_rows)) return st;
   const int nsplit = decode_nsplit(m, batch);
   if (use_persistent(m, batch)) {
-    if (nnc_status st = persistent_steps(m, slots[0], tokens[0], 1, logits_out)) return st;
+    if (nnc_status st = persistent_steps(m, slots, tokens, 1, 1, logits_out)) return st;
     if (next_out) HIP_TRY(hipMemcpyAsync(next_out, m->token_log, batch * 4, hipMemcpyDeviceToDevice, m->stream));
     for (uint32_t i = 0; i < batch; ++i) m->len[slots[i]] += 1;
     return NNC_OK;
@@ -1616,8 +1649,8 @@ nnc_status nnc_decode_greedy(nnc_model* m, const uint32_t* slots, const int32_t*
   double kv_rows = 0;
   if (nnc_status st = set_decode_state(m, slots, first_tokens, batch, &max_pos, &kv_rows)) return st;
   const int nsplit = decode_nsplit(m, batch);
-  if (use_persistent(m, batch)) {
-    if (nnc_status st = persistent_steps(m, slots[0], first_tokens[0], n_steps, logits_out)) return st;
+  if (use_persistent_greedy(m, slots, batch, n_steps)) {
+    if (nnc_status st = persistent_steps(m, slots, first_tokens, batch, n_steps, logits_out)) return st;
     HIP_TRY(hipMemcpyAsync(tokens_out, m->token_log, (size_t)n_steps * batch * 4, hipMemcpyDeviceToDevice, m->stream));
     for (uint32_t i = 0; i < batch; ++i) m->len[slots[i]] += n_steps;
     return NNC_OK;

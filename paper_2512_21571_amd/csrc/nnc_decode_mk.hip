@@ -1,4 +1,4 @@
-// Resident whole-step decode kernel for batch 1 (bf16 models).
+// Resident whole-step decode kernel for one to four sequences (16-bit models).
 //
 // Batch-1 decode of a 0.6B-shaped model moves ~1.2 GB per token: 150 us at HBM
 // speed, spread over ~140 dependent matmul / attention stages of about 1 us each.
@@ -75,6 +75,24 @@ __device__ __forceinline__ u64 ld_t(const u64* p) {
 __device__ __forceinline__ void st_t(u64* p, float v, unsigned tag) {
   __hip_atomic_store(p, (u64)__float_as_uint(v) | ((u64)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Two adjacent (value, tag) words in one 16-byte load past the caches (cache policy 16 = sc1, agent
+// scope).  The halves need no common atomicity: each carries its own tag.  Against two 8-byte loads
+// per pair this halves the requests of every poll: 0.6B 153 -> 149 us per step of 7 layers, 1.7B 300 -> 290.
+// The loads are ordinary to the compiler: a poll loop begins with poll_again().
+struct TWord2 {
+  u32x4 v;
+  __device__ __forceinline__ bool ok(unsigned tag) const { return v[1] == tag && v[3] == tag; }
+  __device__ __forceinline__ float2 val() const { return make_float2(__uint_as_float(v[0]), __uint_as_float(v[2])); }
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t t_buffer(const u64* p, int words) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<u64*>(p), 0, words * 8, 0x00020000);
+}
+// words i and i + 1 (i even) at `voff` bytes per lane + `soff` bytes (scalar)
+__device__ __forceinline__ TWord2 ld_t2(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  return TWord2{__builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 16)};
+}
+// keeps the loads of one poll from being merged with or moved across those of another
+__device__ __forceinline__ void poll_again() { asm volatile("" ::: "memory"); }
 __device__ __forceinline__ float t_val(u64 w) { return __uint_as_float((unsigned)w); }
 __device__ __forceinline__ bool t_ok(u64 w, unsigned tag) { return (unsigned)(w >> 32) == tag; }
 
@@ -114,8 +132,9 @@ struct MkArgs {
   uint32_t max_seq;
   unsigned* error;
   unsigned spin_max;    // polls of one wait before the launch gives up
-  int tok0;             // first token
-  uint32_t pos0, slot;  // position of the first step, KV slot
+  int nseq;                       // sequences decoded together
+  int tok0[MK_MAX_SEQ];           // first tokens
+  uint32_t pos0[MK_MAX_SEQ], slot[MK_MAX_SEQ];  // positions of the first step, KV slots
   int n_steps;
   unsigned tag_base;
   int ks_o, ks_d;  // k slices of the output / down projections
@@ -124,17 +143,17 @@ struct MkArgs {
   // workgroups, so that a workgroup's weight prefetch for its next role is issued early.
   int off_att, off_o, off_d;
   // exchange buffers of (value, tag) words
-  u64* xq;    // [Dq + 2 Dkv] raw q | k | v
-  u64* xatt;  // [nq][max_chunks][132] attention partials: 128 sums, max, sum
+  u64* xq;    // [nseq][Dq + 2 Dkv] raw q | k | v
+  u64* xatt;  // [nseq][nq][max_chunks][132] attention partials: 128 sums, max, sum
   int max_chunks;
-  u64* xo;    // [Dq] merged attention output (used when the context spans many chunks)
-  u64* xop;   // [ks_o][H]
-  u64* xact;  // [F]
-  u64* xdp;   // [ks_d][H]
-  u64* xamv;  // [workgroups] best logit
-  u64* xami;  // [workgroups] its index
-  float* logits;       // [n_steps][V] or NULL
-  int32_t* token_log;  // [n_steps]
+  u64* xo;    // [nseq][Dq] merged attention output (one sequence: only when the context spans many chunks)
+  u64* xop;   // [ks_o][nseq][H]
+  u64* xact;  // [nseq][F]
+  u64* xdp;   // [ks_d][nseq][H]
+  u64* xamv;  // [nseq][workgroups] best logit
+  u64* xami;  // [nseq][workgroups] its index
+  float* logits;       // [n_steps][nseq][V] or NULL
+  int32_t* token_log;  // [n_steps][nseq]
   unsigned long long* trace;  // [workgroups][trace_points] wall-clock stamps of one step, or NULL
   int trace_step, trace_points;
 };
@@ -149,16 +168,16 @@ struct Smem {
     uint32_t Vs[ATT_CHUNK][MK_VS];        // attention: the chunk's V rows, two bf16 per word
     float mrg[MK_WAVES][128];             // merge stage: per-wave weighted sums of one head
   };
-  float wsum[MK_WAVES];
+  float wsum[MK_MAX_SEQ][MK_WAVES];
   float sc[16][ATT_CHUNK];                                          // scores per head
   __attribute__((aligned(16))) uint16_t qp[3][16][128];            // rotated queries, three bf16 pieces
   __attribute__((aligned(16))) uint16_t pw[3][16][ATT_CHUNK];      // softmax weights, three bf16 pieces
   __attribute__((aligned(16))) uint16_t knew[128], vnew[128];      // this step's K and V rows (bf16 bits)
   float att_m[16], att_l[16];
   __attribute__((aligned(16))) float outv[16][128];                // value sums of the chunk per head, for publication
-  float bestv[MK_WAVES];
-  int besti[MK_WAVES];
-  int tok;
+  float bestv[MK_MAX_SEQ][MK_WAVES];
+  int besti[MK_MAX_SEQ][MK_WAVES];
+  int tok[MK_MAX_SEQ];
   int abort;
 };
 
@@ -172,13 +191,15 @@ __device__ __forceinline__ bool spin_over(const MkArgs& a, unsigned& spins) {
   return spins > a.spin_max || ((spins & 255u) == 0 && ld_u32(a.error) != 0);
 }
 
-// bf16 pieces of the pair (v.x, v.y) = activations k, k+1 (k even, relative to the
-// operand's first k) into the packed LDS operand: 4 columns of 16 bytes per 8 k
-// (three pieces and one unused column).
-template <class HF>
-__device__ __forceinline__ void put_pair(uint4* opnd, int k, float2 v) {
+// Operand columns of 16 bytes per 8 k in LDS: three pieces per sequence, rounded up to four.
+constexpr int mk_cols(int ns) { return (3 * ns + 3) / 4 * 4; }
+
+// bf16 pieces of the pair (v.x, v.y) = activations k, k+1 of sequence b (k even, relative to the
+// operand's first k) into the packed LDS operand.
+template <class HF, int NS>
+__device__ __forceinline__ void put_pair(uint4* opnd, int b, int k, float2 v) {
   float rx = v.x, ry = v.y;
-  uint32_t* base = reinterpret_cast<uint32_t*>(opnd + (size_t)(k >> 3) * 4) + ((k & 7) >> 1);
+  uint32_t* base = reinterpret_cast<uint32_t*>(opnd + (size_t)(k >> 3) * mk_cols(NS) + 3 * b) + ((k & 7) >> 1);
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     const uint32_t bx = HF::bits(rx), by = HF::bits(ry);
@@ -211,13 +232,15 @@ __device__ __forceinline__ void pf_issue(Pf<RT>& pf, const uint4* __restrict__ W
 // One GEMM unit: RT adjacent 16-row tiles x k tiles [kt_begin, kt_end), the
 // waves taking k tiles round-robin; the operand in LDS starts at k tile opnd_kt0.
 // Every wave leaves its partial tile in red[wave][rt]; the caller synchronises.
-template <int RT, bool USE_PF, class HF>
+template <int RT, bool USE_PF, int NS, class HF>
 __device__ __forceinline__ void gemm_unit(Smem& sm, const uint4* __restrict__ W, size_t tile0, int KT, int kt_begin,
                                           int kt_end, const Pf<RT>& pf, const uint4* opnd, int opnd_kt0) {
   const int tid = opaque(threadIdx.x);
   const int wave = tid >> 6, lane = tid & 63;
   const int c16 = lane & 15, g = lane >> 4;
-  const bool colok = c16 < 3;
+  // one sequence: lanes without a column feed zeros; several: they repeat the last column (never read)
+  const bool colok = NS > 1 || c16 < 3;
+  const int cc = NS > 1 ? min(c16, mk_cols(NS) - 1) : c16;
   f32x4 acc[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -227,7 +250,7 @@ __device__ __forceinline__ void gemm_unit(Smem& sm, const uint4* __restrict__ W,
     for (int u = 0; u < U; ++u) {
       const int kt = kt0 + MK_WAVES * u;
       uint4 bv = uint4{0, 0, 0, 0};
-      if (kt < kt_end && colok) bv = opnd[((size_t)(kt - opnd_kt0) * 4 + g) * 4 + c16];
+      if (kt < kt_end && colok) bv = opnd[((size_t)(kt - opnd_kt0) * 4 + g) * mk_cols(NS) + cc];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
         acc[rt] = HF::mfma(__builtin_bit_cast(u32x4, av[u][rt]), __builtin_bit_cast(u32x4, bv), acc[rt]);
@@ -261,13 +284,13 @@ __device__ __forceinline__ void gemm_unit(Smem& sm, const uint4* __restrict__ W,
 }
 
 // Sum of the waves' partial tiles and of the three bf16 pieces for output row
-// `row` of tile rt; call after wg_sync().  Accumulator element i of lane l is output
+// `row` of tile rt, sequence b; call after wg_sync().  Accumulator element i of lane l is output
 // row (l / 16) * 4 + i, operand column l % 16.
-__device__ __forceinline__ float tile_total(const Smem& sm, int rt, int row) {
+__device__ __forceinline__ float tile_total(const Smem& sm, int rt, int row, int b) {
   float v = 0.f;
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
-    const int idx = (row & 3) * 64 + (row >> 2) * 16 + s;
+    const int idx = (row & 3) * 64 + (row >> 2) * 16 + 3 * b + s;
     float t = 0.f;
 #pragma unroll
     for (int w = 0; w < MK_WAVES; ++w) t += sm.red[w][rt][idx];
@@ -276,62 +299,120 @@ __device__ __forceinline__ float tile_total(const Smem& sm, int rt, int row) {
   return v;
 }
 
-// x[j] += sum over `ks` slices of the exchanged vector `buf` ([ks][H] tagged words), for
+// x[b][j] += sum over `ks` slices of the exchanged vectors `buf` ([ks][ns][H] tagged words), for
 // the pairs k = 2 * (tid + MK_THREADS * j) this thread owns.  Loads are repeated until
-// every word carries `tag`.
-template <int NP>
-__device__ __forceinline__ void add_exchanged(const MkArgs& a, Smem& sm, float2 (&x)[NP], int H, const u64* buf, int ks,
-                                              unsigned tag) {
-  constexpr int JB = NP < 4 ? NP : 4;  // pairs per thread whose words are in flight together
+// every word carries `tag`; the words of all sequences are in flight together.
+// Most k slices an instance adds up (several sequences: their words share the registers).
+constexpr int mk_max_ks(int ns) { return ns == 1 ? MK_MAX_KS : 3; }
+
+template <int NP, int NS>
+__device__ __forceinline__ void add_exchanged(const MkArgs& a, Smem& sm, float2 (&x)[NS][NP], int H, const u64* buf, int ks,
+                                              int ns, unsigned tag) {
+  constexpr int JM = NS > 1 ? 2 : 4;
+  constexpr int KS = mk_max_ks(NS);
+  constexpr int JB = NP < JM ? NP : JM;  // pairs per thread and sequence whose words are in flight together
   const int tid = opaque(threadIdx.x);
+  const __amdgpu_buffer_rsrc_t rs = t_buffer(buf, ks * ns * H);
 #pragma unroll
   for (int j0 = 0; j0 < NP; j0 += JB) {
     unsigned spins = 0;
     for (;;) {
-      u64 w[JB][MK_MAX_KS][2];
+      poll_again();
+      TWord2 w[NS][JB][KS];
 #pragma unroll
-      for (int j = 0; j < JB; ++j) {
-        const int k = 2 * (tid + MK_THREADS * (j0 + j));
-        if (k < H) {
+      for (int b = 0; b < NS; ++b)
+        if (NS == 1 || b < ns) {
 #pragma unroll
-          for (int p = 0; p < MK_MAX_KS; ++p)
-            if (p < ks) {
-              w[j][p][0] = ld_t(buf + (size_t)p * H + k);
-              w[j][p][1] = ld_t(buf + (size_t)p * H + k + 1);
+          for (int j = 0; j < JB; ++j)
+            if (2 * (tid + MK_THREADS * (j0 + j)) < H) {
+#pragma unroll
+              for (int p = 0; p < KS; ++p)
+                if (p < ks) w[b][j][p] = ld_t2(rs, tid * 16, ((p * ns + b) * H + 2 * MK_THREADS * (j0 + j)) * 8);
             }
         }
-      }
       bool ok = true;
 #pragma unroll
-      for (int j = 0; j < JB; ++j) {
-        const int k = 2 * ((int)threadIdx.x + MK_THREADS * (j0 + j));
-        if (k < H) {
+      for (int b = 0; b < NS; ++b)
+        if (NS == 1 || b < ns) {
 #pragma unroll
-          for (int p = 0; p < MK_MAX_KS; ++p)
-            if (p < ks) ok = ok && t_ok(w[j][p][0], tag) && t_ok(w[j][p][1], tag);
+          for (int j = 0; j < JB; ++j)
+            if (2 * ((int)threadIdx.x + MK_THREADS * (j0 + j)) < H) {
+#pragma unroll
+              for (int p = 0; p < KS; ++p)
+                if (p < ks) ok = ok && w[b][j][p].ok(tag);
+            }
         }
-      }
       if (ok) {
 #pragma unroll
-        for (int j = 0; j < JB; ++j) {
-          const int k = 2 * ((int)threadIdx.x + MK_THREADS * (j0 + j));
-          if (k < H) {
-            float2 add = make_float2(t_val(w[j][0][0]), t_val(w[j][0][1]));
+        for (int b = 0; b < NS; ++b)
+          if (NS == 1 || b < ns) {
 #pragma unroll
-            for (int p = 1; p < MK_MAX_KS; ++p)
-              if (p < ks) {
-                add.x += t_val(w[j][p][0]);
-                add.y += t_val(w[j][p][1]);
+            for (int j = 0; j < JB; ++j)
+              if (2 * ((int)threadIdx.x + MK_THREADS * (j0 + j)) < H) {
+                float2 add = w[b][j][0].val();
+#pragma unroll
+                for (int p = 1; p < KS; ++p)
+                  if (p < ks) {
+                    const float2 v = w[b][j][p].val();
+                    add.x += v.x;
+                    add.y += v.y;
+                  }
+                x[b][j0 + j].x += add.x;
+                x[b][j0 + j].y += add.y;
               }
-            x[j0 + j].x += add.x;
-            x[j0 + j].y += add.y;
           }
-        }
         break;
       }
       if (spin_over(a, spins)) {
         give_up(a, sm);
         return;
+      }
+    }
+  }
+}
+
+// An exchanged vector per sequence (src + b * stride, k in [k0, k1)) -> the packed operand: four (k, k+1)
+// pairs per thread and sequence at a time, loaded together, repeated until every word carries `tag`.
+template <int NS, class HF>
+__device__ __forceinline__ void load_operand(const MkArgs& a, Smem& sm, uint4* opnd, const u64* src, size_t stride, int k0,
+                                             int k1, int ns, unsigned tag) {
+  const int tid = threadIdx.x;
+  const __amdgpu_buffer_rsrc_t rs = t_buffer(src, (int)stride * ns);
+  for (int kb = k0 + 2 * tid; kb < k1; kb += 8 * MK_THREADS) {
+    unsigned spins = 0;
+    for (;;) {
+      poll_again();
+      TWord2 w[NS][4];
+      bool ok = true;
+#pragma unroll
+      for (int b = 0; b < NS; ++b)
+        if (NS == 1 || b < ns) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (kb + 2 * MK_THREADS * j < k1) w[b][j] = ld_t2(rs, kb * 8, (b * (int)stride + 2 * MK_THREADS * j) * 8);
+        }
+#pragma unroll
+      for (int b = 0; b < NS; ++b)
+        if (NS == 1 || b < ns) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (kb + 2 * MK_THREADS * j < k1) ok = ok && w[b][j].ok(tag);
+        }
+      if (ok) {
+#pragma unroll
+        for (int b = 0; b < NS; ++b)
+          if (NS == 1 || b < ns) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int k = kb + 2 * MK_THREADS * j;
+              if (k < k1) put_pair<HF, NS>(opnd, b, k - k0, w[b][j].val());
+            }
+          }
+        break;
+      }
+      if (spin_over(a, spins)) {
+        give_up(a, sm);
+        break;
       }
     }
   }
@@ -369,48 +450,55 @@ __device__ __forceinline__ void load_gain(float2 (&gg)[NP], int H, const float* 
 }
 
 // 1 / sqrt(mean(x^2) + eps) from the per-wave sums of squares (after a workgroup barrier).
-__device__ __forceinline__ float rms_from_sums(const Smem& sm, int H, float eps) {
+__device__ __forceinline__ float rms_from_sums(const Smem& sm, int b, int H, float eps) {
   float t = 0.f;
 #pragma unroll
-  for (int w = 0; w < MK_WAVES; ++w) t += sm.wsum[w];
+  for (int w = 0; w < MK_WAVES; ++w) t += sm.wsum[b][w];
   return 1.0f / sqrtf(t / (float)H + eps);
 }
 
 // A format with a narrow exponent range (binary16) cannot split an un-normalised row of small
 // magnitude into pieces without losing bits, so there the row is normalised first (one more
 // workgroup barrier) and the epilogues multiply by one.
-template <int NP, class HF>
-__device__ __forceinline__ void norm_pack(Smem& sm, uint4* opnd, int H, float eps, const float2 (&x)[NP],
+template <int NP, int NS, class HF>
+__device__ __forceinline__ void norm_pack(Smem& sm, uint4* opnd, int H, float eps, int ns, const float2 (&x)[NS][NP],
                                           const float2 (&gg)[NP]) {
-  float ss = 0.f;
 #pragma unroll
-  for (int j = 0; j < NP; ++j) ss += x[j].x * x[j].x + x[j].y * x[j].y;  // unowned pairs are zero
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) sm.wsum[threadIdx.x >> 6] = ss;
-  float r = 1.0f;
-  if constexpr (HF::kNarrowRange) {
-    wg_sync();
-    r = rms_from_sums(sm, H, eps);
-  }
+  for (int b = 0; b < NS; ++b)
+    if (NS == 1 || b < ns) {
+      float ss = 0.f;
 #pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    const int k = 2 * ((int)threadIdx.x + MK_THREADS * j);
-    if (k < H) put_pair<HF>(opnd, k, make_float2(x[j].x * gg[j].x * r, x[j].y * gg[j].y * r));
-  }
+      for (int j = 0; j < NP; ++j) ss += x[b][j].x * x[b][j].x + x[b][j].y * x[b][j].y;  // unowned pairs are zero
+      ss = wave_sum(ss);
+      if ((threadIdx.x & 63) == 0) sm.wsum[b][threadIdx.x >> 6] = ss;
+    }
+  if constexpr (HF::kNarrowRange) wg_sync();
+#pragma unroll
+  for (int b = 0; b < NS; ++b)
+    if (NS == 1 || b < ns) {
+      float r = 1.0f;
+      if constexpr (HF::kNarrowRange) r = rms_from_sums(sm, b, H, eps);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        const int k = 2 * ((int)threadIdx.x + MK_THREADS * j);
+        if (k < H) put_pair<HF, NS>(opnd, b, k, make_float2(x[b][j].x * gg[j].x * r, x[b][j].y * gg[j].y * r));
+      }
+    }
 }
 
 // What the GEMM epilogues after norm_pack multiply their outputs by (after the workgroup barrier).
 template <class HF>
-__device__ __forceinline__ float rms_scale(const Smem& sm, int H, float eps) {
+__device__ __forceinline__ float rms_scale(const Smem& sm, int b, int H, float eps) {
   if constexpr (HF::kNarrowRange) return 1.0f;
-  else return rms_from_sums(sm, H, eps);
+  else return rms_from_sums(sm, b, H, eps);
 }
 
 }  // namespace
 
-// GH = query heads sharing one kv head that a workgroup handles together (divides nq/nkv).
 // NP = (k, k+1) pairs of a hidden-state row per thread: hidden <= 2 * MK_THREADS * NP.
-template <int GH, int NP, class HF>
+// NS = most sequences the instance decodes together (their 3 NS operand columns fit the 16 the matrix
+// cores multiply anyway): the exchanges and weights of a step then serve all of them.
+template <int NP, int NS, class HF>
 __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
   extern __shared__ uint4 opnd[];  // packed activation operand of the current GEMM stage
   __shared__ Smem sm;
@@ -420,6 +508,10 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
   const int Dq = nq * 128, Dkv = nkv * 128, Nqkv = Dq + 2 * Dkv;
   const int KTH = H / 32, KTQ = Dq / 32, KTF = F / 32;
   const int G = nq / nkv;
+  const int ns = NS == 1 ? 1 : a.nseq;
+  // this thread's share of a GEMM epilogue: row epi_row of the tile for sequence epi_seq
+  const int epi_row = tid & 15, epi_seq = NS == 1 ? 0 : tid >> 4;
+  const bool epi_on = tid < 16 * ns;
 
   if (ld_u32(a.error)) return;
   if (tid == 0) sm.abort = 0;
@@ -451,11 +543,12 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
   Pf<2> pf4;
   if (wg < qkv_tiles) pf_issue<1>(pf1, a.layers[0].wqkv, (size_t)wg, KTH, 0, KTH);
 
-  float2 x[NP];  // this workgroup's copy of the residual stream (pairs owned by the thread)
-  int tok = a.tok0;
+  float2 x[NS][NP];  // this workgroup's copy of the residual streams (pairs owned by the thread)
+  int tok[NS];
+#pragma unroll
+  for (int b = 0; b < NS; ++b) tok[b] = a.tok0[b];
 
   for (int step = 0; step < a.n_steps; ++step) {
-    const uint32_t pos = a.pos0 + step;
     const unsigned t_step = a.tag_base + (unsigned)step * tags_per_step;
     for (int li = 0; li < a.n_layers; ++li) {
       const MkLayer L = a.layers[li];
@@ -465,21 +558,26 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       // ============ stage 1: residual update + input norm + QKV projection ============
       float2 gg[NP];
       load_gain<NP>(gg, H, L.g_in);
-      if (li == 0)
-        gather_embed<NP, HF>(x, H, a.embed, tok);
-      else
-        add_exchanged<NP>(a, sm, x, H, a.xdp, a.ks_d, t_dp - 5u);
-      norm_pack<NP, HF>(sm, opnd, H, a.eps, x, gg);
+      if (li == 0) {
+#pragma unroll
+        for (int b = 0; b < NS; ++b)
+          if (NS == 1 || b < ns) gather_embed<NP, HF>(x[b], H, a.embed, tok[b]);
+      } else {
+        add_exchanged<NP, NS>(a, sm, x, H, a.xdp, a.ks_d, ns, t_dp - 5u);
+      }
+      norm_pack<NP, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
       wg_sync();
       if (sm.abort) return;
       stamp(step);  // 1: operand ready
       for (int t = wg; t < qkv_tiles; t += nwg) {
         if (t == wg)
-          gemm_unit<1, true, HF>(sm, L.wqkv, (size_t)t, KTH, 0, KTH, pf1, opnd, 0);
+          gemm_unit<1, true, NS, HF>(sm, L.wqkv, (size_t)t, KTH, 0, KTH, pf1, opnd, 0);
         else
-          gemm_unit<1, false, HF>(sm, L.wqkv, (size_t)t, KTH, 0, KTH, pf1, opnd, 0);
+          gemm_unit<1, false, NS, HF>(sm, L.wqkv, (size_t)t, KTH, 0, KTH, pf1, opnd, 0);
         wg_sync();
-        if (tid < 16) st_t(a.xq + t * 16 + tid, tile_total(sm, 0, tid) * rms_scale<HF>(sm, H, a.eps), t_q);
+        if (epi_on)
+          st_t(a.xq + (size_t)epi_seq * Nqkv + t * 16 + epi_row,
+               tile_total(sm, 0, epi_row, epi_seq) * rms_scale<HF>(sm, epi_seq, H, a.eps), t_q);
         wg_sync();
       }
       // prefetch point A (a long wait follows: attention has to run first): output projection
@@ -498,12 +596,26 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       //                 LDS, B = the softmax weights (three pieces, split once per head).
       // The step's own K / V row is not in the cache when the loads are issued: the lane /
       // LDS row that stands for position `pos` takes it from the role waves instead.
-      const int nch = (int)(pos / ATT_CHUNK) + 1;  // chunks that hold positions 0 .. pos
-      for (int u = wg_att; u < nkv * nch; u += nwg) {
-        const int chunk = u % nch, kvh = u / nch;
+      // (several sequences: their units one after the other)
+      int att_units = 0, first_unit[NS], chunks[NS];  // chunks that hold a sequence's positions 0 .. pos
+#pragma unroll
+      for (int b = 0; b < NS; ++b) {
+        first_unit[b] = att_units;
+        chunks[b] = (int)((a.pos0[b] + step) / ATT_CHUNK) + 1;
+        if (NS == 1 || b < ns) att_units += nkv * chunks[b];
+      }
+      for (int u = wg_att; u < att_units; u += nwg) {
+        int seq = 0, nch = chunks[0], u0 = 0;
+#pragma unroll
+        for (int b = 1; b < NS; ++b)
+          if (b < ns && u >= first_unit[b]) seq = b, nch = chunks[b], u0 = first_unit[b];
+        const uint32_t pos = a.pos0[seq] + step;
+        const u64* xq = a.xq + (size_t)seq * Nqkv;
+        u64* xatt = a.xatt + (size_t)seq * nq * a.max_chunks * 132;
+        const int chunk = (u - u0) % nch, kvh = (u - u0) / nch;
         const uint32_t j0 = (uint32_t)chunk * ATT_CHUNK;
         const bool owns_new = pos - j0 < ATT_CHUNK;
-        const size_t cbase = ((size_t)a.slot * nkv + kvh) * a.max_seq * 128;
+        const size_t cbase = ((size_t)a.slot[seq] * nkv + kvh) * a.max_seq * 128;
         const int c16 = lane & 15, g = lane >> 4;
         const int head0 = kvh * G;
         // cached rows of the chunk, loaded up front (rows from `pos` on re-read an older row:
@@ -529,8 +641,8 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         // roles 0..G-1: q heads; role G: the step's k row; role G+1: its v row
         for (int role = wave; role < G + 2; role += MK_WAVES) {
           if (role >= G && !owns_new) continue;
-          const u64* src = role < G ? a.xq + (size_t)(head0 + role) * 128
-                                    : a.xq + Dq + (size_t)(role == G ? 0 : Dkv) + (size_t)kvh * 128;
+          const u64* src = role < G ? xq + (size_t)(head0 + role) * 128
+                                    : xq + Dq + (size_t)(role == G ? 0 : Dkv) + (size_t)kvh * 128;
           // rotary factors and norm gains first: their loads overlap with the wait for q
           const float* gsrc = role < G ? L.g_q : L.g_k;
           const float g0 = gsrc[lane], g1 = gsrc[lane + 64];
@@ -685,7 +797,7 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         if (owns_new) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), the other counters left alone
         for (int o = tid; o < G * 128; o += MK_THREADS) {
           const int h = o >> 7, i = o & 127;
-          u64* rec = a.xatt + ((size_t)(head0 + h) * a.max_chunks + chunk) * 132;
+          u64* rec = xatt + ((size_t)(head0 + h) * a.max_chunks + chunk) * 132;
           st_t(rec + i, sm.outv[h][i], t_att);
           if (i == 0) {
             st_t(rec + 128, sm.att_m[h], t_att);
@@ -706,9 +818,15 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       // (no extra exchange).  Many chunks: that repeated merge would dominate, so one workgroup
       // per query head merges its records once and publishes the head's output, at the cost of
       // one more exchange.
-      const bool merged = nch > MK_DIRECT_MERGE_MAX;
+      // (Several sequences always take that exchange: the direct merge reads every record of every
+      // sequence in every output-projection unit.)
+      const bool merged = NS > 1 || chunks[0] > MK_DIRECT_MERGE_MAX;
       if (merged) {
-        for (int h = nwg - 1 - wg_att; h < nq; h += nwg) {
+        for (int h = nwg - 1 - wg_att; h < ns * nq; h += nwg) {  // h = sequence * query heads + head
+          int nch = chunks[0];
+#pragma unroll
+          for (int b = 1; b < NS; ++b)
+            if (h >= b * nq) nch = chunks[b];
           wg_sync();
           // wave w takes chunks w, w + 4, ...; lane l the sums of dimensions l and l + 64
           const u64* rec0 = a.xatt + (size_t)h * a.max_chunks * 132;
@@ -786,40 +904,10 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         if (s == s_loaded) {
           // operand already in LDS
         } else if (merged) {
-          // four (k, k+1) pairs of the merged output per thread at a time, loaded together
-          for (int kb = kt0 * 32 + 2 * tid; kb < kt1 * 32; kb += 8 * MK_THREADS) {
-            unsigned spins = 0;
-            for (;;) {
-              u64 w[4][2];
-              bool ok = true;
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const int k = kb + 2 * MK_THREADS * j;
-                if (k < kt1 * 32) {
-                  w[j][0] = ld_t(a.xo + k);
-                  w[j][1] = ld_t(a.xo + k + 1);
-                }
-              }
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const int k = kb + 2 * MK_THREADS * j;
-                if (k < kt1 * 32) ok = ok && t_ok(w[j][0], t_att) && t_ok(w[j][1], t_att);
-              }
-              if (ok) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                  const int k = kb + 2 * MK_THREADS * j;
-                  if (k < kt1 * 32) put_pair<HF>(opnd, k - kt0 * 32, make_float2(t_val(w[j][0]), t_val(w[j][1])));
-                }
-                break;
-              }
-              if (spin_over(a, spins)) {
-                give_up(a, sm);
-                break;
-              }
-            }
-          }
-        } else {
+          load_operand<NS, HF>(a, sm, opnd, a.xo, (size_t)Dq, kt0 * 32, kt1 * 32, ns, t_att);
+        } else if constexpr (NS == 1) {
+          const int nch = chunks[0];
+          const __amdgpu_buffer_rsrc_t ratt = t_buffer(a.xatt, nq * a.max_chunks * 132);
           // two (k, k+1) pairs per thread at a time, four chunk records each, all in flight together
           for (int kb = kt0 * 32 + 2 * tid; kb < kt1 * 32; kb += 4 * MK_THREADS) {
             float M[2], n0[2], n1[2], den[2];
@@ -829,22 +917,21 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
               n0[r] = n1[r] = den[r] = 0.f;
             }
             for (int c0 = 0; c0 < nch; c0 += 4) {
-              u64 wm[2][4], wl[2][4], wa[2][4], wb[2][4];
+              TWord2 wml[2][4], wab[2][4];  // (max, sum), (sums of dimensions k, k + 1)
               unsigned spins = 0;
               for (;;) {
+                poll_again();
                 bool ok = true;
   #pragma unroll
                 for (int r = 0; r < 2; ++r) {
                   const int k = kb + 2 * MK_THREADS * r;
                   if (k < kt1 * 32) {
-                    const u64* rec0 = a.xatt + (size_t)(k >> 7) * a.max_chunks * 132;
+                    const int rec0 = (k >> 7) * a.max_chunks * 132;
   #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                      const u64* rec = rec0 + (size_t)min(c0 + q, nch - 1) * 132;
-                      wm[r][q] = ld_t(rec + 128);
-                      wl[r][q] = ld_t(rec + 129);
-                      wa[r][q] = ld_t(rec + (k & 127));
-                      wb[r][q] = ld_t(rec + (k & 127) + 1);
+                      const int rec = rec0 + min(c0 + q, nch - 1) * 132;
+                      wml[r][q] = ld_t2(ratt, (rec + 128) * 8, 0);
+                      wab[r][q] = ld_t2(ratt, (rec + (k & 127)) * 8, 0);
                     }
                   }
                 }
@@ -853,8 +940,7 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
                   if (kb + 2 * MK_THREADS * r < kt1 * 32) {
   #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                      ok = ok && t_ok(wm[r][q], t_att) && t_ok(wl[r][q], t_att) && t_ok(wa[r][q], t_att) &&
-                           t_ok(wb[r][q], t_att);
+                      ok = ok && wml[r][q].ok(t_att) && wab[r][q].ok(t_att);
                   }
                 if (ok) break;
                 if (spin_over(a, spins)) {
@@ -869,7 +955,7 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
                   float Mn = M[r];
   #pragma unroll
                   for (int q = 0; q < 4; ++q)
-                    if (c0 + q < nch) Mn = fmaxf(Mn, t_val(wm[r][q]));
+                    if (c0 + q < nch) Mn = fmaxf(Mn, wml[r][q].val().x);
                   const float sc = expf(M[r] - Mn);  // 0 on the first group (M = -inf)
                   n0[r] *= sc;
                   n1[r] *= sc;
@@ -877,10 +963,11 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
   #pragma unroll
                   for (int q = 0; q < 4; ++q)
                     if (c0 + q < nch) {
-                      const float f = expf(t_val(wm[r][q]) - Mn);
-                      n0[r] += f * t_val(wa[r][q]);
-                      n1[r] += f * t_val(wb[r][q]);
-                      den[r] += f * t_val(wl[r][q]);
+                      const float2 ml = wml[r][q].val(), ab = wab[r][q].val();
+                      const float f = expf(ml.x - Mn);
+                      n0[r] += f * ab.x;
+                      n1[r] += f * ab.y;
+                      den[r] += f * ml.y;
                     }
                   M[r] = Mn;
                 }
@@ -888,7 +975,7 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
   #pragma unroll
             for (int r = 0; r < 2; ++r) {
               const int k = kb + 2 * MK_THREADS * r;
-              if (k < kt1 * 32) put_pair<HF>(opnd, k - kt0 * 32, make_float2(n0[r] / den[r], n1[r] / den[r]));
+              if (k < kt1 * 32) put_pair<HF, NS>(opnd, 0, k - kt0 * 32, make_float2(n0[r] / den[r], n1[r] / den[r]));
             }
           }
         }
@@ -896,31 +983,32 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         wg_sync();
         if (sm.abort) return;
         if (u == wg_o)
-          gemm_unit<1, true, HF>(sm, L.wo, (size_t)t, KTQ, kt0, kt1, pf3, opnd, kt0);
+          gemm_unit<1, true, NS, HF>(sm, L.wo, (size_t)t, KTQ, kt0, kt1, pf3, opnd, kt0);
         else
-          gemm_unit<1, false, HF>(sm, L.wo, (size_t)t, KTQ, kt0, kt1, pf3, opnd, kt0);
+          gemm_unit<1, false, NS, HF>(sm, L.wo, (size_t)t, KTQ, kt0, kt1, pf3, opnd, kt0);
         wg_sync();
-        if (tid < 16) st_t(a.xop + (size_t)s * H + t * 16 + tid, tile_total(sm, 0, tid), t_op);
+        if (epi_on)
+          st_t(a.xop + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row, tile_total(sm, 0, epi_row, epi_seq), t_op);
       }
       stamp(step);  // 4: attention block output published
 
       // ============ stage 4: residual update + post-attention norm + gate/up + SwiGLU ============
       load_gain<NP>(gg, H, L.g_post);
-      add_exchanged<NP>(a, sm, x, H, a.xop, a.ks_o, t_op);
-      norm_pack<NP, HF>(sm, opnd, H, a.eps, x, gg);
+      add_exchanged<NP, NS>(a, sm, x, H, a.xop, a.ks_o, ns, t_op);
+      norm_pack<NP, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
       wg_sync();
       if (sm.abort) return;
       stamp(step);  // 5: operand ready
       for (int pr = wg; pr < gu_pairs; pr += nwg) {
         if (pr == wg)
-          gemm_unit<2, true, HF>(sm, L.wgu, (size_t)pr * 2, KTH, 0, KTH, pf4, opnd, 0);
+          gemm_unit<2, true, NS, HF>(sm, L.wgu, (size_t)pr * 2, KTH, 0, KTH, pf4, opnd, 0);
         else
-          gemm_unit<2, false, HF>(sm, L.wgu, (size_t)pr * 2, KTH, 0, KTH, pf4, opnd, 0);
+          gemm_unit<2, false, NS, HF>(sm, L.wgu, (size_t)pr * 2, KTH, 0, KTH, pf4, opnd, 0);
         wg_sync();
-        if (tid < 16) {
-          const float r = rms_scale<HF>(sm, H, a.eps);
-          const float gate = tile_total(sm, 0, tid) * r, up = tile_total(sm, 1, tid) * r;
-          st_t(a.xact + pr * 16 + tid, gate / (1.0f + expf(-gate)) * up, t_act);
+        if (epi_on) {
+          const float r = rms_scale<HF>(sm, epi_seq, H, a.eps);
+          const float gate = tile_total(sm, 0, epi_row, epi_seq) * r, up = tile_total(sm, 1, epi_row, epi_seq) * r;
+          st_t(a.xact + (size_t)epi_seq * F + pr * 16 + epi_row, gate / (1.0f + expf(-gate)) * up, t_act);
         }
         wg_sync();
       }
@@ -935,48 +1023,17 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         const int t = u / a.ks_d, s = u % a.ks_d;
         const int kt0 = s * kts_d, kt1 = min(KTF, (s + 1) * kts_d);
         wg_sync();
-        // four (k, k+1) pairs per thread at a time, loaded together
-        for (int kb = kt0 * 32 + 2 * tid; s != s_loaded && kb < kt1 * 32; kb += 8 * MK_THREADS) {
-          unsigned spins = 0;
-          for (;;) {
-            u64 w[4][2];
-            bool ok = true;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int k = kb + 2 * MK_THREADS * j;
-              if (k < kt1 * 32) {
-                w[j][0] = ld_t(a.xact + k);
-                w[j][1] = ld_t(a.xact + k + 1);
-              }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int k = kb + 2 * MK_THREADS * j;
-              if (k < kt1 * 32) ok = ok && t_ok(w[j][0], t_act) && t_ok(w[j][1], t_act);
-            }
-            if (ok) {
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const int k = kb + 2 * MK_THREADS * j;
-                if (k < kt1 * 32) put_pair<HF>(opnd, k - kt0 * 32, make_float2(t_val(w[j][0]), t_val(w[j][1])));
-              }
-              break;
-            }
-            if (spin_over(a, spins)) {
-              give_up(a, sm);
-              break;
-            }
-          }
-        }
+        if (s != s_loaded) load_operand<NS, HF>(a, sm, opnd, a.xact, (size_t)F, kt0 * 32, kt1 * 32, ns, t_act);
         s_loaded = s;
         wg_sync();
         if (sm.abort) return;
         if (u == wg_d)
-          gemm_unit<1, true, HF>(sm, L.wd, (size_t)t, KTF, kt0, kt1, pf5, opnd, kt0);
+          gemm_unit<1, true, NS, HF>(sm, L.wd, (size_t)t, KTF, kt0, kt1, pf5, opnd, kt0);
         else
-          gemm_unit<1, false, HF>(sm, L.wd, (size_t)t, KTF, kt0, kt1, pf5, opnd, kt0);
+          gemm_unit<1, false, NS, HF>(sm, L.wd, (size_t)t, KTF, kt0, kt1, pf5, opnd, kt0);
         wg_sync();
-        if (tid < 16) st_t(a.xdp + (size_t)s * H + t * 16 + tid, tile_total(sm, 0, tid), t_dp);
+        if (epi_on)
+          st_t(a.xdp + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row, tile_total(sm, 0, epi_row, epi_seq), t_dp);
       }
       stamp(step);  // 7: MLP output published
     }
@@ -986,8 +1043,8 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
     {
       float2 gg[NP];
       load_gain<NP>(gg, H, a.g_final);
-      add_exchanged<NP>(a, sm, x, H, a.xdp, a.ks_d, t_am - 1u);
-      norm_pack<NP, HF>(sm, opnd, H, a.eps, x, gg);
+      add_exchanged<NP, NS>(a, sm, x, H, a.xdp, a.ks_d, ns, t_am - 1u);
+      norm_pack<NP, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
     }
     wg_sync();
     if (sm.abort) return;
@@ -996,11 +1053,15 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       // every wave walks whole 16-row tiles of the vocabulary on its own (no k split,
       // no workgroup synchronisation): tile = global wave index, stride = all waves
       const int c16 = lane & 15, g = lane >> 4;
-      const bool colok = c16 < 3;
+      const bool colok = NS > 1 || c16 < 3;
+      const int cc = NS > 1 ? min(c16, mk_cols(NS) - 1) : c16;
+      // lanes c16 = 3 b collect sequence b
+      const int seq = NS == 1 ? 0 : min(c16 / 3, ns - 1);
+      const bool owner = NS == 1 ? c16 == 0 : c16 == 3 * seq;
       float best = -INFINITY;
       int besti = 0x7fffffff;
-      const float rms = rms_scale<HF>(sm, H, a.eps);
-      float* lg = a.logits ? a.logits + (size_t)step * V : nullptr;
+      const float rms = rms_scale<HF>(sm, seq, H, a.eps);
+      float* lg = a.logits ? a.logits + ((size_t)step * ns + seq) * V : nullptr;
       for (int t = wg * MK_WAVES + wave; t < v_tiles; t += nwg * MK_WAVES) {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
         const uint4* Wt = a.lm_head + (size_t)t * KTH * 64 + lane;
@@ -1011,15 +1072,15 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
 #pragma unroll
           for (int u = 0; u < 16; ++u) {
             uint4 bv = uint4{0, 0, 0, 0};
-            if (kt0 + u < KTH && colok) bv = opnd[((size_t)(kt0 + u) * 4 + g) * 4 + c16];
+            if (kt0 + u < KTH && colok) bv = opnd[((size_t)(kt0 + u) * 4 + g) * mk_cols(NS) + cc];
             acc = HF::mfma(__builtin_bit_cast(u32x4, av[u]), __builtin_bit_cast(u32x4, bv), acc);
           }
         }
-        // add the three pieces: columns 0, 1, 2 sit in adjacent lanes
+        // add the three pieces of a sequence: their columns sit in adjacent lanes
         f32x4 s;
 #pragma unroll
         for (int i = 0; i < 4; ++i) s[i] = (acc[i] + __shfl_down(acc[i], 1, 64) + __shfl_down(acc[i], 2, 64)) * rms;
-        if (c16 == 0) {
+        if (owner) {
           const int row0 = t * 16 + g * 4;
           if (lg) *reinterpret_cast<float4*>(lg + row0) = make_float4(s[0], s[1], s[2], s[3]);
 #pragma unroll
@@ -1030,8 +1091,9 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
             }
         }
       }
+      // over the four lanes that hold a column
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
+      for (int o = 32; o >= 16; o >>= 1) {
         const float ov = __shfl_xor(best, o, 64);
         const int oi = __shfl_xor(besti, o, 64);
         if (ov > best || (ov == best && oi < besti)) {
@@ -1039,28 +1101,30 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
           besti = oi;
         }
       }
-      if (lane == 0) {
-        sm.bestv[wave] = best;
-        sm.besti[wave] = besti;
+      if (g == 0 && owner) {
+        sm.bestv[seq][wave] = best;
+        sm.besti[seq][wave] = besti;
       }
       wg_sync();
-      if (tid == 0) {
-        float v = sm.bestv[0];
-        int i = sm.besti[0];
+      if (tid < ns) {
+        float v = sm.bestv[tid][0];
+        int i = sm.besti[tid][0];
         for (int w = 1; w < MK_WAVES; ++w)
-          if (sm.bestv[w] > v || (sm.bestv[w] == v && sm.besti[w] < i)) {
-            v = sm.bestv[w];
-            i = sm.besti[w];
+          if (sm.bestv[tid][w] > v || (sm.bestv[tid][w] == v && sm.besti[tid][w] < i)) {
+            v = sm.bestv[tid][w];
+            i = sm.besti[tid][w];
           }
-        st_t(a.xamv + wg, v, t_am);
-        st_t(a.xami + wg, __int_as_float(i), t_am);
+        st_t(a.xamv + (size_t)tid * nwg + wg, v, t_am);
+        st_t(a.xami + (size_t)tid * nwg + wg, __int_as_float(i), t_am);
       }
     }
     stamp(step);  // winners published
 
     // every workgroup reduces the per-workgroup winners itself: the next token needs no
     // further exchange
-    if (wave == 0) {
+    // (one wave per sequence)
+    for (int b = wave; b < ns; b += MK_WAVES) {
+      const u64 *xv = a.xamv + (size_t)b * nwg, *xi = a.xami + (size_t)b * nwg;
       float v = -INFINITY;
       int i = 0x7fffffff;
       for (int w0 = lane; w0 < nwg; w0 += 256) {
@@ -1071,8 +1135,8 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int w = min(w0 + 64 * q, nwg - 1);
-            wv[q] = ld_t(a.xamv + w);
-            wi[q] = ld_t(a.xami + w);
+            wv[q] = ld_t(xv + w);
+            wi[q] = ld_t(xi + w);
           }
 #pragma unroll
           for (int q = 0; q < 4; ++q) ok = ok && t_ok(wv[q], t_am) && t_ok(wi[q], t_am);
@@ -1103,13 +1167,15 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       }
       if (lane == 0) {
         const int t = i == 0x7fffffff ? 0 : i;
-        sm.tok = t;
-        if (wg == 0) a.token_log[step] = t;
+        sm.tok[b] = t;
+        if (wg == 0) a.token_log[(size_t)step * ns + b] = t;
       }
     }
     wg_sync();
     if (sm.abort) return;
-    tok = sm.tok;
+#pragma unroll
+    for (int b = 0; b < NS; ++b)
+      if (NS == 1 || b < ns) tok[b] = sm.tok[b];
     stamp(step);  // token known
   }
 }
@@ -1135,47 +1201,56 @@ void mk_fill_layer(void* dst, const void* wqkv, const void* wo, const void* wgu,
   memcpy(dst, &l, sizeof l);
 }
 
-// Operand bytes in LDS: the widest k range any stage holds at once (4 columns of 16 bytes per 8 k).
+// Instances: one sequence, two, up to four (the last only for hidden sizes up to 1024).
+static int mk_instance(int nseq) { return nseq <= 2 ? nseq : 4; }
+
+// Operand bytes in LDS: the widest k range any stage holds at once (mk_cols columns of 16 bytes per 8 k).
 size_t mk_opnd_bytes(const MkPlan& p) {
   const int kts_o = (p.nq * 128 / 32 + p.ks_o - 1) / p.ks_o, kts_d = (p.F / 32 + p.ks_d - 1) / p.ks_d;
   int kt = p.H / 32;
   if (kts_o > kt) kt = kts_o;
   if (kts_d > kt) kt = kts_d;
-  return (size_t)kt * 4 * 4 * 16;
+  return (size_t)kt * 4 * mk_cols(mk_instance(p.nseq)) * 16;
 }
 
 // Workgroups of the resident kernel (for this plan's template instance and LDS size) that the
 // device can hold at once, 0 on error: the grid must fit, since its workgroups wait for each other.
+// f(kernel) for the instance a plan runs with; false if there is none
+template <class F>
+static bool mk_with_kernel(const MkPlan& p, F&& f) {
+  const int ns = mk_instance(p.nseq);
+#define MK_CASE(NP, NS)                                              \
+  do {                                                               \
+    if (p.f16) f(&k_decode_resident<NP, NS, Fp16>);                  \
+    else f(&k_decode_resident<NP, NS, Bf16>);                        \
+    return true;                                                     \
+  } while (0)
+  if (p.nseq < 1 || p.nseq > MK_MAX_SEQ) return false;
+  const int ks = p.ks_o > p.ks_d ? p.ks_o : p.ks_d;
+  if (ks > mk_max_ks(ns)) return false;
+  if (ns == 1) {
+    if (p.H <= 1024) MK_CASE(2, 1);
+    if (p.H <= 2048) MK_CASE(4, 1);
+    if (p.H <= 4096) MK_CASE(8, 1);
+  } else if (ns == 2) {
+    if (p.H <= 1024) MK_CASE(2, 2);
+    if (p.H <= 2048) MK_CASE(4, 2);
+  } else {
+    if (p.H <= 1024) MK_CASE(2, 4);
+  }
+#undef MK_CASE
+  return false;
+}
+
 int mk_max_resident_workgroups(const MkPlan& p, int n_cus) {
-  const int G = p.nkv > 0 ? p.nq / p.nkv : 0;
   const size_t dyn = mk_opnd_bytes(p);
   int per_cu = 0;
   hipError_t e = hipErrorInvalidValue;
-#define MK_OCC(GH, NP)                                                                                        \
-  do {                                                                                                        \
-    if (p.f16) {                                                                                              \
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_resident<GH, NP, Fp16>),                \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);                          \
-      if (e == hipSuccess)                                                                                    \
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_decode_resident<GH, NP, Fp16>, MK_THREADS, dyn); \
-    } else {                                                                                                  \
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_resident<GH, NP, Bf16>),                \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);                          \
-      if (e == hipSuccess)                                                                                    \
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_decode_resident<GH, NP, Bf16>, MK_THREADS, dyn); \
-    }                                                                                                         \
-  } while (0)
-#define MK_OCC_NP(GH)                    \
-  do {                                   \
-    if (p.H <= 1024) MK_OCC(GH, 2);      \
-    else if (p.H <= 2048) MK_OCC(GH, 4); \
-    else MK_OCC(GH, 8);                  \
-  } while (0)
-  if (G % 4 == 0) MK_OCC_NP(4);
-  else MK_OCC_NP(2);
-#undef MK_OCC_NP
-#undef MK_OCC
-  if (e != hipSuccess || per_cu < 1) return 0;
+  const bool have = mk_with_kernel(p, [&](auto* k) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, MK_THREADS, dyn);
+  });
+  if (!have || e != hipSuccess || per_cu < 1) return 0;
   return per_cu * n_cus;
 }
 
@@ -1195,7 +1270,13 @@ hipError_t launch_decode_resident(hipStream_t s, const MkPlan& p, const MkBuffer
   a.max_seq = p.max_seq;
   a.error = bf.error;
   a.spin_max = p.spin_max ? p.spin_max : MK_SPIN_MAX;
-  a.tok0 = p.tok0; a.pos0 = p.pos0; a.slot = p.slot;
+  a.nseq = p.nseq;
+  for (int b = 0; b < MK_MAX_SEQ; ++b) {
+    // (unused entries repeat the first: they are read, not used)
+    a.tok0[b] = p.tok0[b < p.nseq ? b : 0];
+    a.pos0[b] = p.pos0[b < p.nseq ? b : 0];
+    a.slot[b] = p.slot[b < p.nseq ? b : 0];
+  }
   a.n_steps = p.n_steps;
   a.tag_base = p.tag_base;
   a.ks_o = p.ks_o; a.ks_d = p.ks_d;
@@ -1207,31 +1288,12 @@ hipError_t launch_decode_resident(hipStream_t s, const MkPlan& p, const MkBuffer
   a.logits = bf.logits; a.token_log = bf.token_log;
   a.trace = bf.trace; a.trace_step = bf.trace_step; a.trace_points = bf.trace_points;
   const size_t dyn = mk_opnd_bytes(p);
-  hipError_t e;
-#define MK_LAUNCH(GH, NP)                                                                                     \
-  do {                                                                                                        \
-    if (p.f16) {                                                                                              \
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_resident<GH, NP, Fp16>),                \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);                          \
-      if (e != hipSuccess) return e;                                                                          \
-      k_decode_resident<GH, NP, Fp16><<<p.nwg, MK_THREADS, dyn, s>>>(a);                                      \
-    } else {                                                                                                  \
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_resident<GH, NP, Bf16>),                \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);                          \
-      if (e != hipSuccess) return e;                                                                          \
-      k_decode_resident<GH, NP, Bf16><<<p.nwg, MK_THREADS, dyn, s>>>(a);                                      \
-    }                                                                                                         \
-  } while (0)
-#define MK_LAUNCH_NP(GH)                    \
-  do {                                      \
-    if (p.H <= 1024) MK_LAUNCH(GH, 2);      \
-    else if (p.H <= 2048) MK_LAUNCH(GH, 4); \
-    else MK_LAUNCH(GH, 8);                  \
-  } while (0)
-  if (G % 4 == 0) MK_LAUNCH_NP(4);
-  else MK_LAUNCH_NP(2);
-#undef MK_LAUNCH_NP
-#undef MK_LAUNCH
+  hipError_t e = hipErrorInvalidValue;
+  const bool have = mk_with_kernel(p, [&](auto* k) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    if (e == hipSuccess) k<<<p.nwg, MK_THREADS, dyn, s>>>(a);
+  });
+  if (!have || e != hipSuccess) return have ? e : hipErrorInvalidValue;
   return hipGetLastError();
 }
 

@@ -247,15 +247,17 @@ hipError_t launch_kv_read(hipStream_t s, int dt, const void* cache, uint32_t max
                           uint32_t pos0, uint32_t n, float* out);
 hipError_t launch_copy_rows(hipStream_t s, const float* src, float* dst, size_t n);
 
-// ---- resident whole-step decode kernel (bf16 models, batch 1) ----
+// ---- resident whole-step decode kernel (16-bit models, one to four sequences) ----
+constexpr int MK_MAX_SEQ = 4;  // 3 pieces each: 12 of the 16 operand columns of a matrix-core instruction
 struct MkPlan {
   int nwg;  // resident workgroups: min(compute units, QKV tiles)
   int n_layers, H, nq, nkv, F, V;
   float eps;
   uint32_t max_seq;
   int max_chunks;
-  int tok0;             // token fed to the first step
-  uint32_t pos0, slot;  // its position and KV slot
+  int nseq;
+  int tok0[MK_MAX_SEQ];                        // tokens fed to the first step
+  uint32_t pos0[MK_MAX_SEQ], slot[MK_MAX_SEQ];  // their positions and KV slots
   int n_steps;
   unsigned tag_base;    // first exchange tag of this launch (tags must never repeat)
   int ks_o, ks_d;       // k slices of the output / down projections
@@ -273,8 +275,8 @@ struct MkBuffers {
   unsigned* error;  // single word, zero-initialised once
   // exchange buffers of 64-bit (value, tag) words, zero-initialised once
   void *xq, *xatt, *xo, *xop, *xact, *xdp, *xamv, *xami;
-  float* logits;       // [n_steps][V] or NULL
-  int32_t* token_log;  // [n_steps]
+  float* logits;       // [n_steps][nseq][V] or NULL
+  int32_t* token_log;  // [n_steps][nseq]
   unsigned long long* trace;  // [nwg][trace_points] or NULL
   int trace_step, trace_points;
 };

@@ -11,7 +11,7 @@ import pytest
 
 import oracle
 import synth
-from parity_util import (SMALL_BF16, SMALL_F32, SMALL_G4, SMALL_LAYER_F32, oracle_flags,
+from parity_util import (SMALL_BF16, SMALL_F16, SMALL_F32, SMALL_G4, SMALL_LAYER_F32, oracle_flags,
                          oracle_prefill_like_library, prefill_blocks, rel_inf)
 
 pytestmark = pytest.mark.gpu
@@ -25,6 +25,9 @@ BF16_ABS_TIGHT = 4e-3
 # fp32-grade path, and every shorter prompt carries two bf16 pieces per activation.
 BF16_ABS_PROMPT = 2.5e-2
 F32_REL = 1e-4
+# hidden size of the resident kernel's second instance of two sequences (residual rows in two rounds)
+WIDE_BF16 = synth.ModelShape("wide-bf16", hidden=1536, n_layers=3, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=2048,
+                             vocab=1024, dtype=synth.BF16)
 
 
 @pytest.fixture(scope="module")
@@ -294,6 +297,39 @@ def test_large_block_prefill_every_attention_shape(nnc, n, attn):
     lo, no = oracle_prefill_like_library(o, 0, toks, shape)
     _check_logits(shape, lg, lo, BF16_ABS_PROMPT if one_piece else BF16_ABS_TIGHT)
     assert int(ng.item()) == no
+
+
+@pytest.mark.parametrize("shape", [SMALL_BF16, SMALL_G4, SMALL_F16, WIDE_BF16], ids=lambda s: s.name)
+@pytest.mark.parametrize("batch", [2, 3, 4, 5])
+def test_resident_greedy_of_a_few_sequences(nnc, shape, batch):
+    """Greedy runs of two to four sequences (five stay per-stage) in the resident kernel against the per-stage kernels: ragged
+    contexts from one position to several chunks, runs that cross chunk boundaries, slots out of order and
+    with gaps, with and without logits.  Both are fp32-grade up to the rounding of cached rows, as in the
+    comparison of the fused and the separate kernels above; greedy margins here are far larger."""
+    print(f"case: resident greedy, {shape.name}, B={batch}", flush=True)
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    lens, slots = [57, 1, 120, 320, 63][:batch], [6, 0, 3, 5, 1][:batch]
+    runs = []
+    for resident in (1, 0):
+        g = nnc.Model(shape, blob, 7, 400)
+        g.set_option(nnc.OPT_PREFILL_EXACT, 1)
+        g.set_option(nnc.OPT_PERSISTENT, resident)
+        firsts = []
+        for sl, n in zip(slots, lens):
+            _, nx = g.prefill(sl, synth.tokens(n, shape.vocab, stream=900 + sl))
+            firsts.append(int(nx.item()))
+        toks, logits = g.decode_greedy(slots, firsts, 13, want_logits=True)
+        toks2, _ = g.decode_greedy(slots, toks[-1].cpu().numpy().tolist(), 40)
+        lg, _ = g.decode_step(slots, toks2[-1].cpu().numpy().tolist())
+        g.synchronize()
+        assert [g.slot_len(sl) for sl in slots] == [n + 54 for n in lens]
+        kv = [g.kv_read(shape.n_layers - 1, sl, w, 0, n + 54).cpu().numpy() for sl, n in zip(slots, lens) for w in (0, 1)]
+        runs.append((toks.cpu().numpy(), toks2.cpu().numpy(), logits.cpu().numpy(), lg.cpu().numpy(), kv))
+    (t0, u0, l0, s0, k0), (t1, u1, l1, s1, k1) = runs
+    assert np.array_equal(t0, t1) and np.array_equal(u0, u1)
+    assert np.isfinite(l0).all() and np.abs(l0 - l1).max() <= BF16_ABS_TIGHT and np.abs(s0 - s1).max() <= BF16_ABS_TIGHT
+    for a, b in zip(k0, k1):
+        assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
 
 
 @pytest.mark.parametrize("planner", [0, 1], ids=["hand-rules", "planner"])
