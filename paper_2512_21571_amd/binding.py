@@ -167,6 +167,7 @@ class Model:
         self.device = torch.device(device)
         torch.cuda.set_device(self.device)
         self.stream = torch.cuda.Stream(device=self.device)
+        self._ev_in, self._ev_out = torch.cuda.Event(), torch.cuda.Event()
         self.cfg = make_config(shape, max_batch, max_seq, compute_dtype)
         self._held = {}
 
@@ -203,20 +204,25 @@ class Model:
             pass
 
     def _empty(self, shape, dtype):
-        with self.torch.cuda.stream(self.stream):
-            return self.torch.empty(shape, dtype=dtype, device=self.device)
+        # a tensor of the caller's current stream: the model's stream waits for that stream before it
+        # writes (_before), and that stream waits for the model's before anything it runs later (_after)
+        return self.torch.empty(shape, dtype=dtype, device=self.device)
 
     def synchronize(self):
         """Wait for the model's stream; raises NncError if a resident decode launch gave up."""
         _check(lib().nnc_synchronize(self.h))
 
     def _before(self):
-        # inputs may have been produced on the caller's current stream
-        self.stream.wait_stream(self.torch.cuda.current_stream(self.device))
+        # inputs may have been produced on the caller's current stream (two events kept for the hand-over:
+        # recording one again does not disturb a wait that was already enqueued)
+        self._caller = self.torch.cuda.current_stream(self.device)
+        self._ev_in.record(self._caller)
+        self.stream.wait_event(self._ev_in)
 
     def _after(self):
         # outputs are consumed on the caller's current stream
-        self.torch.cuda.current_stream(self.device).wait_stream(self.stream)
+        self._ev_out.record(self.stream)
+        self._caller.wait_event(self._ev_out)
 
     # -- forward pass ---------------------------------------------------------------
     def prefill(self, slot: int, tokens, want_logits: bool = True):
@@ -296,8 +302,8 @@ class Model:
         torch = self.torch
         if not isinstance(x, torch.Tensor):
             x = torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32))
-        with torch.cuda.stream(self.stream):
-            x = x.to(self.device, dtype=torch.float32, non_blocking=False).contiguous()
+        # (a conversion runs on the caller's stream, which _before waits for)
+        x = x.to(self.device, dtype=torch.float32, non_blocking=False).contiguous()
         if x.dim() == 1:
             x = x[None]
         return x

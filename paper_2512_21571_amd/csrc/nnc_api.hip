@@ -136,6 +136,13 @@ struct nnc_model {
   uint32_t* tail_counters = nullptr;  // one per GEMM launch with a norm tail in a pass (2 per layer), zeroed per pass
   bool opt_planner = true;    // tile sizes from the analytic model (nnc_plan.h); false: the earlier hand rules
   std::map<std::tuple<int, int, int>, hipGraphExec_t> graphs;
+  // hidden-state decode steps: the layers of one step, captured at a key's third use (a model that is
+  // stepped once or twice pays for no capture); what follows the graph needs the number of partials it left
+  struct HiddenGraph {
+    hipGraphExec_t exec = nullptr;
+    int pending = 0, uses = 0;
+  };
+  std::map<std::tuple<int, int, int>, HiddenGraph> hidden_graphs;
 
   bool profiling = false;
   // Long prompts: the fp32-grade tail pass runs on a second stream, one layer behind the last
@@ -226,6 +233,14 @@ void* dev_alloc(nnc_model* m, size_t bytes) {
   return p;
 }
 
+void clear_graphs(nnc_model* m) {
+  for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
+  m->graphs.clear();
+  for (auto& kv : m->hidden_graphs)
+    if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
+  m->hidden_graphs.clear();
+}
+
 void release_all(nnc_model* m) {
   if (m->tail_stream) {
     (void)hipStreamSynchronize(m->tail_stream);
@@ -234,8 +249,7 @@ void release_all(nnc_model* m) {
   }
   for (hipEvent_t e : m->layer_done) (void)hipEventDestroy(e);
   m->layer_done.clear();
-  for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
-  m->graphs.clear();
+  clear_graphs(m);
   for (auto& r : m->prof) {
     (void)hipEventDestroy(r.e0);
     (void)hipEventDestroy(r.e1);
@@ -341,6 +355,7 @@ struct Pass {
   int grid_chunks = 1;
   double kv_rows = 0;       // sum over columns of (position + 1): cached rows attention must read
   bool one_slot = false;    // the columns are consecutive positions of one slot (prompt chunk)
+  int* pending_out = nullptr;  // hidden-state models: leave the last projection's partials unadded and say how many
   bool decode = false;      // every column is a different slot: QK-norm, RoPE and the cache append may run inside the attention kernel
 };
 
@@ -466,9 +481,8 @@ nnc_status run_pass(nnc_model* m, const Pass& p) {
       RUN(FAM_ARGMAX, hn * V * 4.0, 0,
           launch_argmax(s, p.logits, p.logits_ld, V, hn, p.step_ptr, p.step_stride, m->am_val, m->am_idx,
                         p.next, p.finish ? m->st : nullptr, m->token_log));
-  } else if (!c.has_embed_and_head && pending > 0) {
-    // hidden-state models return x itself: add the last projection's partials now
-    RUN(FAM_MISC, 0, 0, launch_fold_residual(s, m->x, m->rpart, pending, pstride, (size_t)n * H));
+  } else if (p.pending_out) {
+    *p.pending_out = pending;  // the caller adds them on the way out
   }
   return NNC_OK;
 }
@@ -509,7 +523,7 @@ nnc_status check_slots(const nnc_model* m, const uint32_t* slots, uint32_t batch
 }
 
 nnc_status set_decode_state(nnc_model* m, const uint32_t* slots, const int32_t* tokens, uint32_t batch,
-                            uint32_t* max_pos_out, double* kv_rows_out) {
+                            uint32_t* max_pos_out, double* kv_rows_out, const float* x_rows = nullptr) {
   uint32_t pos[MAX_COLS];
   uint32_t mx = 0;
   double rows = 0;
@@ -520,7 +534,8 @@ nnc_status set_decode_state(nnc_model* m, const uint32_t* slots, const int32_t* 
   }
   *max_pos_out = mx;
   *kv_rows_out = rows;
-  HIP_TRY(launch_set_state(m->stream, m->st, (int)batch, tokens, slots, pos, 0));
+  // (x_rows: hidden-state input, copied to x by the same launch)
+  HIP_TRY(launch_set_state(m->stream, m->st, (int)batch, tokens, slots, pos, 0, x_rows, m->x, x_rows ? (size_t)batch * m->H() : 0));
   return NNC_OK;
 }
 
@@ -598,6 +613,9 @@ nnc_status fetch_wait_flag(nnc_model* m) {
   m->mk_error_pending = true;
   return NNC_OK;
 }
+
+// after per-stage passes: only norm tails wait there
+nnc_status fetch_tail_flag(nnc_model* m) { return m->opt_fuse_norm ? fetch_wait_flag(m) : NNC_OK; }
 
 nnc_status persistent_steps(nnc_model* m, const uint32_t* slots, const int32_t* tokens, uint32_t batch, uint32_t n_steps,
                             float* logits_out) {
@@ -1028,8 +1046,7 @@ nnc_status nnc_set_option(nnc_model* m, nnc_option opt, int32_t value) {
     case NNC_OPT_PLANNER:
       m->opt_planner = value != 0;
       // captured decode graphs contain the launches of one or the other choice
-      for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
-      m->graphs.clear();
+      clear_graphs(m);
       return NNC_OK;
     case NNC_OPT_PREFILL_BLOCK:
       if (value != 0 && (value < 128 || value % 128)) return fail(NNC_E_ARG, "prefill block must be 0 (largest) or a multiple of 128");
@@ -1042,13 +1059,11 @@ nnc_status nnc_set_option(nnc_model* m, nnc_option opt, int32_t value) {
     case NNC_OPT_FUSE_QK:
       m->opt_fuse_qk = value != 0;
       // captured decode graphs contain one or the other set of kernels
-      for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
-      m->graphs.clear();
+      clear_graphs(m);
       return NNC_OK;
     case NNC_OPT_FUSE_NORM:
       m->opt_fuse_norm = value != 0;
-      for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
-      m->graphs.clear();
+      clear_graphs(m);
       return NNC_OK;
     case NNC_OPT_DECODE_PIECES:
       if (value != 0 && value != 2 && value != 3) return fail(NNC_E_ARG, "decode pieces must be 0 (default), 2 or 3");
@@ -1450,8 +1465,11 @@ static nnc_status prefill_common(nnc_model* m, uint32_t slot, const int32_t* tok
     p.one_slot = true;
     for (uint32_t i = 0; i < nc; ++i) p.kv_rows += pos[i] + 1.0;
     const bool last = t0 + nc == n;
-    if (!tokens)
+    int pending = 0;
+    if (!tokens) {
       HIP_TRY(launch_copy_rows(m->stream, x + (size_t)t0 * H, m->x, (size_t)nc * H));
+      p.pending_out = &pending;
+    }
     if (last && tokens && (logits_out || next_out)) {
       p.head_col0 = (int)nc - 1;
       p.head_ncols = 1;
@@ -1460,7 +1478,8 @@ static nnc_status prefill_common(nnc_model* m, uint32_t slot, const int32_t* tok
       p.next = next_out ? m->next : nullptr;
     }
     if (nnc_status st = run_pass(m, p)) return st;
-    if (!tokens) HIP_TRY(launch_copy_rows(m->stream, m->x, y + (size_t)t0 * H, (size_t)nc * H));
+    if (!tokens)
+      HIP_TRY(launch_fold_residual(m->stream, m->x, m->rpart, pending, (long)nc * H, y + (size_t)t0 * H, (size_t)nc * H));
     if (last && next_out && tokens)
       HIP_TRY(hipMemcpyAsync(next_out, m->next, 4, hipMemcpyDeviceToDevice, m->stream));
   }
@@ -1524,7 +1543,7 @@ nnc_status nnc_decode_step(nnc_model* m, const uint32_t* slots, const int32_t* t
   }
   if (next_out) HIP_TRY(hipMemcpyAsync(next_out, m->next, batch * 4, hipMemcpyDeviceToDevice, m->stream));
   for (uint32_t i = 0; i < batch; ++i) m->len[slots[i]] += 1;
-  return fetch_wait_flag(m);
+  return fetch_tail_flag(m);
 }
 
 // ---- decode step for callers that cannot allocate -------------------------------
@@ -1630,7 +1649,7 @@ nnc_status nnc_decode_step_static(nnc_model* m, const uint32_t* slots, const int
   if (nnc_status st = run_pass(m, p)) return st;
   if (next_out) HIP_TRY(hipMemcpyAsync(next_out, m->next, batch * 4, hipMemcpyDeviceToDevice, m->stream));
   for (uint32_t i = 0; i < batch; ++i) m->len[slots[i]] += 1;
-  return fetch_wait_flag(m);
+  return fetch_tail_flag(m);
 }
 
 nnc_status nnc_decode_greedy(nnc_model* m, const uint32_t* slots, const int32_t* first_tokens, uint32_t batch,
@@ -1676,7 +1695,7 @@ nnc_status nnc_decode_greedy(nnc_model* m, const uint32_t* slots, const int32_t*
   }
   HIP_TRY(hipMemcpyAsync(tokens_out, m->token_log, (size_t)n_steps * batch * 4, hipMemcpyDeviceToDevice, m->stream));
   for (uint32_t i = 0; i < batch; ++i) m->len[slots[i]] += n_steps;
-  return fetch_wait_flag(m);
+  return fetch_tail_flag(m);
 }
 
 nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const float* x, uint32_t batch, float* y) {
@@ -1685,8 +1704,7 @@ nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const flo
   if (nnc_status st = check_slots(m, slots, batch, 1)) return st;
   uint32_t max_pos = 0;
   double kv_rows = 0;
-  if (nnc_status st = set_decode_state(m, slots, nullptr, batch, &max_pos, &kv_rows)) return st;
-  HIP_TRY(launch_copy_rows(m->stream, x, m->x, (size_t)batch * m->H()));
+  if (nnc_status st = set_decode_state(m, slots, nullptr, batch, &max_pos, &kv_rows, x)) return st;
   Pass p;
   p.decode = true;
   p.kv_rows = kv_rows;
@@ -1694,10 +1712,40 @@ nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const flo
   p.nsplit = decode_nsplit(m, batch);
   p.tokens = false;
   p.grid_chunks = chunks_grid(max_pos);
-  if (nnc_status st = run_pass(m, p)) return st;
-  HIP_TRY(launch_copy_rows(m->stream, m->x, y, (size_t)batch * m->H()));
+  int pending = 0;
+  p.pending_out = &pending;
+  // One small layer is eight kernels of a few microseconds: launched one by one they are bound by the
+  // host (41 us per call), replayed as a graph by the GPU.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const bool graph = m->opt_graph && !m->profiling && m->stream != nullptr &&
+                     hipStreamIsCapturing(m->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  nnc_model::HiddenGraph* hg = graph ? &m->hidden_graphs[std::make_tuple((int)batch, p.nsplit, p.grid_chunks)] : nullptr;
+  if (hg && !hg->exec && ++hg->uses > 2) {
+    hipGraph_t g = nullptr;
+    HIP_TRY(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));
+    const nnc_status st = run_pass(m, p);
+    const hipError_t e = hipStreamEndCapture(m->stream, &g);
+    if (st != NNC_OK || e != hipSuccess) {
+      if (g) (void)hipGraphDestroy(g);
+      return st != NNC_OK ? st : dev_fail(e, "hipStreamEndCapture");
+    }
+    const hipError_t e2 = hipGraphInstantiate(&hg->exec, g, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(g);
+    if (e2 != hipSuccess) {
+      hg->exec = nullptr;
+      return dev_fail(e2, "hipGraphInstantiate");
+    }
+    hg->pending = pending;
+  }
+  if (hg && hg->exec) {
+    HIP_TRY(hipGraphLaunch(hg->exec, m->stream));
+    pending = hg->pending;
+  } else if (nnc_status st = run_pass(m, p)) {
+    return st;
+  }
+  HIP_TRY(launch_fold_residual(m->stream, m->x, m->rpart, pending, (long)batch * m->H(), y, (size_t)batch * m->H()));
   for (uint32_t i = 0; i < batch; ++i) m->len[slots[i]] += 1;
-  return fetch_wait_flag(m);
+  return fetch_tail_flag(m);
 }
 
 nnc_status nnc_kv_read(nnc_model* m, uint32_t layer, uint32_t slot, uint32_t which, uint32_t pos0, uint32_t n,

@@ -115,8 +115,10 @@ hipError_t launch_repack(hipStream_t s, bool src_f32, int dst_dt, const void* sr
 // row-major signed bytes [rows, K] -> byte tiles of 16 rows x 64 k (K a multiple of 64)
 hipError_t launch_repack_w8(hipStream_t s, const void* src, void* dst, int rows, int K, int tile_stride,
                             int tile_offset);
+// rows != NULL: also x[0 .. n) = rows[0 .. n)
 hipError_t launch_set_state(hipStream_t s, ColState* st, int ncols, const int32_t* tok,
-                            const uint32_t* slot, const uint32_t* pos, uint32_t step);
+                            const uint32_t* slot, const uint32_t* pos, uint32_t step, const float* rows = nullptr,
+                            float* x = nullptr, size_t n = 0);
 hipError_t launch_embed(hipStream_t s, int dt, const void* Ep, int H, const ColState* st,
                         int ncols, float* x);
 hipError_t launch_rmsnorm_pack(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
@@ -126,8 +128,9 @@ hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, cons
                                      int H, float eps, int ncols, void* Xp, int NC, int nsplit);
 // n 32-bit words = 0 (a fill kernel: safe under graph capture)
 hipError_t launch_zero_words(hipStream_t s, uint32_t* p, int n);
-hipError_t launch_fold_residual(hipStream_t s, float* x, const float* part, int nparts, long part_stride,
-                                size_t n);
+// y = x + part[0] + ... + part[nparts - 1], n contiguous floats
+hipError_t launch_fold_residual(hipStream_t s, const float* x, const float* part, int nparts, long part_stride,
+                                float* y, size_t n);
 hipError_t launch_gemm(hipStream_t s, int dt, int epi, const GemmArgs& a);
 hipError_t launch_qknorm_rope_append(hipStream_t s, int dt, float* qkv, int nq, int nkv,
                                      const float* gq, const float* gk, float eps,

@@ -152,7 +152,10 @@ struct StateInit {
   uint32_t pos[MAX_COLS];
 };
 
-__global__ void k_set_state(ColState* st, StateInit init, int ncols, uint32_t step) {
+__global__ __launch_bounds__(256) void k_set_state(ColState* st, StateInit init, int ncols, uint32_t step,
+                                                   const float* __restrict__ rows, float* __restrict__ x, size_t n) {
+  for (size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (size_t)gridDim.x * blockDim.x) x[j] = rows[j];
+  if (blockIdx.x) return;
   const int i = threadIdx.x;
   if (i < ncols) {
     st->tok[i] = init.tok[i];
@@ -163,14 +166,17 @@ __global__ void k_set_state(ColState* st, StateInit init, int ncols, uint32_t st
 }
 
 hipError_t launch_set_state(hipStream_t s, ColState* st, int ncols, const int32_t* tok,
-                            const uint32_t* slot, const uint32_t* pos, uint32_t step) {
+                            const uint32_t* slot, const uint32_t* pos, uint32_t step, const float* rows, float* x,
+                            size_t n) {
   StateInit init;
   for (int i = 0; i < MAX_COLS; ++i) {
     init.tok[i] = (i < ncols && tok) ? tok[i] : 0;
     init.slot[i] = i < ncols ? slot[i] : 0;
     init.pos[i] = i < ncols ? pos[i] : 0;
   }
-  k_set_state<<<1, MAX_COLS, 0, s>>>(st, init, ncols, step);
+  if (!rows) n = 0;
+  const unsigned grid = (unsigned)((n + 255) / 256 < 256 ? (n + 255) / 256 : 256);
+  k_set_state<<<grid ? grid : 1, n ? 256 : MAX_COLS, 0, s>>>(st, init, ncols, step, rows, x, n);
   return hipGetLastError();
 }
 
@@ -370,20 +376,24 @@ hipError_t launch_zero_words(hipStream_t s, uint32_t* p, int n) {
   return hipGetLastError();
 }
 
-// x += part[0] + part[1] + ... for n contiguous floats (all columns), fixed order.
-__global__ __launch_bounds__(256) void k_fold_residual(float* __restrict__ x, const float* __restrict__ part,
-                                                       int nparts, long part_stride, size_t n) {
+// y = x + (part[0] + part[1] + ...) for n contiguous floats (all columns), fixed order.
+__global__ __launch_bounds__(256) void k_fold_residual(const float* __restrict__ x, const float* __restrict__ part,
+                                                       int nparts, long part_stride, float* __restrict__ y, size_t n) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    float add = part[i];
-    for (int p = 1; p < nparts; ++p) add += part[(size_t)p * part_stride + i];
-    x[i] += add;
+    float v = x[i];
+    if (nparts > 0) {
+      float add = part[i];
+      for (int p = 1; p < nparts; ++p) add += part[(size_t)p * part_stride + i];
+      v += add;
+    }
+    y[i] = v;
   }
 }
 
-hipError_t launch_fold_residual(hipStream_t s, float* x, const float* part, int nparts, long part_stride,
-                                size_t n) {
+hipError_t launch_fold_residual(hipStream_t s, const float* x, const float* part, int nparts, long part_stride,
+                                float* y, size_t n) {
   const unsigned grid = (unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-  k_fold_residual<<<grid ? grid : 1, 256, 0, s>>>(x, part, nparts, part_stride, n);
+  k_fold_residual<<<grid ? grid : 1, 256, 0, s>>>(x, part, nparts, part_stride, y, n);
   return hipGetLastError();
 }
 
