@@ -242,7 +242,9 @@ typedef enum {
   NNC_OPT_PREFILL_ATTN = 6, /* launch shape of the large-block prompt attention: -1 (default) chosen
                                from each launch's size; else bit 0: every workgroup takes a long
                                and a short 64-token block, bit 1: two query heads per wave; results
-                               are bit-identical for all (a wave's arithmetic per head is the same) */
+                               are bit-identical for all (a wave's arithmetic per head is the same).
+                               Short blocks with few workgroups use a kernel of their own, whatever
+                               this says, while NNC_OPT_PLANNER is 1 */
   NNC_OPT_FUSE_QK = 7,      /* 1 (default): per-stage decode passes of bf16 models do QK-norm, RoPE and
                                the cache append inside the attention kernel (one kernel less per
                                layer); 0: in a kernel of their own.  Bit-identical results */

@@ -1117,6 +1117,13 @@ static bool short_block(const nnc_model* m, uint32_t n) {
   return H <= 2560 && n * layer <= (m->dt == NNC_F16 ? 8e9 : 16e9);
 }
 
+// Two-piece blocks of up to 512 tokens whose attention launch is small (forced launch shapes concern the
+// large-block kernel, which such a block then does not use).
+static bool small_attn(const nnc_model* m, uint32_t n) {
+  return m->opt_planner && n <= PB_SMALL_TOKENS &&
+         attn_small_heads((int)m->c.n_q_heads, (int)m->c.n_kv_heads, (int)n, m->n_cus) > 0;
+}
+
 // Prompt pass over one short block (two pieces per activation) with the kernels of nnc_small.hip.
 static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t* tokens, uint32_t n, uint32_t pos0,
                                       bool want_head, float* logits_out, int32_t* next_dev) {
@@ -1173,8 +1180,10 @@ static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t
     double rows = 0;
     for (uint32_t i = 0; i < n; ++i) rows += pos0 + i + 1.0;
     RUN(FAM_PATTN, (pos0 + T) * 2.0 * Dkv * w + T * Dq * 6.0, rows * 4.0 * Dq,
-        launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n, 2,
-                            m->pb_fb, m->n_cus, m->opt_prefill_attn));
+        small_attn(m, n) ? launch_attn_small(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0,
+                                          (int)n, m->pb_fb, m->n_cus)
+                      : launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq,
+                                            pos0, (int)n, 2, m->pb_fb, m->n_cus, m->opt_prefill_attn));
     {
       SmallGemmArgs a = gemm(L.wo, L.so, H, Dq, m->pb_fb);
       resid(a, po, L.g_post);
@@ -1325,8 +1334,11 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       double rows = 0;
       for (uint32_t i = 0; i < n; ++i) rows += pos0 + i + 1.0;
       RUN(FAM_PATTN, (pos0 + T) * 2.0 * Dkv * w + T * Dq * 6.0, rows * 4.0 * Dq,
-          launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n,
-                              pieces, m->pb_fb, m->n_cus, m->opt_prefill_attn));
+          pieces == 2 && small_attn(m, n)
+              ? launch_attn_small(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n,
+                                  m->pb_fb, m->n_cus)
+              : launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0,
+                                    (int)n, pieces, m->pb_fb, m->n_cus, m->opt_prefill_attn));
     }
     {
       PrefillGemmArgs a{};

@@ -223,6 +223,10 @@ struct SmallGemmArgs {
 };
 // nt x ct: row tiles x column tiles per workgroup
 hipError_t launch_gemm_small(hipStream_t s, bool f16, int epi, const SmallGemmArgs& a, int nt, int ct);
+int attn_small_heads(int nq, int nkv, int n, int n_cus);
+// causal attention of a short block, arguments as launch_attn_prefill with two pieces
+hipError_t launch_attn_small(hipStream_t s, bool f16, const float* qkv, int nq, int nkv, const void* kc, const void* vt,
+                             uint32_t S, uint32_t slot, uint32_t max_seq, uint32_t pos0, int n, void* Of, int n_cus);
 hipError_t launch_embed_rows_pack(hipStream_t s, const void* Ep, int H, const int32_t* tokens_dev, int n, const float* gain,
                                   float* x, void* Xn, float* ssq);
 

@@ -422,4 +422,225 @@ hipError_t launch_embed_rows_pack(hipStream_t s, const void* Ep, int H, const in
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// causal attention of short blocks
+// ---------------------------------------------------------------------------
+// The arithmetic of k_attn_prefill (both products transposed, base-2 softmax with a running bound of the
+// maximum, weights and queries in two pieces), for launches too small to fill the chip with 64-token
+// workgroups: a workgroup takes 16 tokens x GH query heads of one kv head and its four waves take the
+// 32-position chunks round-robin, merging their (maximum, sum, value sums) in LDS at the end.  Four times
+// the workgroups, a quarter of the serial chunks (each about 1.2 us of dependent products and softmax), no
+// barrier in the loop; the K and V^T fragments come straight from L2, the next chunk's K and this chunk's V^T in
+// flight while the products run.
+template <int GH, class HF>
+__global__ __launch_bounds__(256) void k_attn_small(const float* __restrict__ qkv, int nq, int nkv,
+                                                    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vt,
+                                                    uint32_t S, uint32_t slot, uint32_t max_seq, uint32_t pos0, int n,
+                                                    void* __restrict__ Of) {
+  __shared__ f32x4 red[4][GH][8][64];
+  __shared__ float smm[4][GH][16], sml[4][GH][16];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int c16 = lane & 15, g = lane >> 4;
+  const int G = nq / nkv;
+  const int kvh = blockIdx.y / (G / GH), head0 = kvh * G + (blockIdx.y % (G / GH)) * GH;
+  const int tq = (int)gridDim.x - 1 - (int)blockIdx.x;  // token tile, longest first
+  const int ld = (nq + 2 * nkv) * 128;
+  const int t = min(tq * 16 + c16, n - 1);  // rows past the prompt repeat the last token (never stored)
+  const uint32_t p = pos0 + (uint32_t)t, p_first = pos0 + (uint32_t)tq * 16, p_last = pos0 + (uint32_t)min(tq * 16 + 15, n - 1);
+
+  const uint16_t* kbase = kc + ((size_t)slot * nkv + kvh) * max_seq * 128;
+  const uint16_t* vbase = vt + (size_t)kvh * 128 * S;
+  const uint32_t r4 = (uint32_t)((c16 >> 2) * 8 + (c16 & 3));  // K row of tile a for A-operand row c16; tile b: + 4
+  u32x4 ka[4], kb[4], vf[8];
+  auto load_k = [&](uint32_t kv0) __attribute__((always_inline)) {  // rows past the cache's end repeat its last (masked)
+    const uint16_t* ra = kbase + (size_t)min(kv0 + r4, max_seq - 1) * 128 + g * 8;
+    const uint16_t* rb = kbase + (size_t)min(kv0 + r4 + 4, max_seq - 1) * 128 + g * 8;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      ka[ks] = *reinterpret_cast<const u32x4*>(ra + ks * 32);
+      kb[ks] = *reinterpret_cast<const u32x4*>(rb + ks * 32);
+    }
+  };
+  auto load_v = [&](uint32_t kv0) __attribute__((always_inline)) {  // kv0 + 31 < S
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+      vf[dt] = *reinterpret_cast<const u32x4*>(vbase + (size_t)(dt * 16 + c16) * S + kv0 + g * 8);
+  };
+  uint32_t kv0 = (uint32_t)wave * 32;
+  if (kv0 <= p_last) load_k(kv0);
+
+  u32x4 qf[GH][4][2];
+#pragma unroll
+  for (int h = 0; h < GH; ++h)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const float* src = qkv + (size_t)t * ld + (size_t)(head0 + h) * 128 + ks * 32 + g * 8;
+      const float4 x0 = *reinterpret_cast<const float4*>(src), x1 = *reinterpret_cast<const float4*>(src + 4);
+      float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+      for (int pc = 0; pc < 2; ++pc) {
+        uint32_t b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          b[e] = HF::pack2(v[2 * e], v[2 * e + 1]);
+          v[2 * e] -= HF::lo(b[e]);
+          v[2 * e + 1] -= HF::hi(b[e]);
+        }
+        qf[h][ks][pc] = u32x4{b[0], b[1], b[2], b[3]};
+      }
+    }
+
+  f32x4 acc[GH][8], lacc[GH];
+  float mrun[GH];
+#pragma unroll
+  for (int h = 0; h < GH; ++h) {
+    mrun[h] = -INFINITY;
+    lacc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) acc[h][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const u32x4 ones = u32x4{HF::kOnes2, HF::kOnes2, HF::kOnes2, HF::kOnes2};
+  for (; kv0 <= p_last; kv0 += 128) {
+    load_v(kv0);
+    f32x4 sa[GH], sb[GH];
+#pragma unroll
+    for (int h = 0; h < GH; ++h) {
+      sa[h] = sb[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int pc = 0; pc < 2; ++pc) {
+          sa[h] = HF::mfma(ka[ks], qf[h][ks][pc], sa[h]);
+          sb[h] = HF::mfma(kb[ks], qf[h][ks][pc], sb[h]);
+        }
+    }
+    if (kv0 + 128 <= p_last) load_k(kv0 + 128);
+    u32x4 pf[GH][2];
+#pragma unroll
+    for (int h = 0; h < GH; ++h) {
+      float sc[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sc[i] = i < 4 ? sa[h][i] : sb[h][i - 4];
+      if (kv0 + 31 > p_first) {  // the chunk reaches past the tile's first token: mask per lane
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sc[i] = kv0 + g * 8 + i <= p ? sc[i] : -INFINITY;
+      }
+      constexpr float kScale = 0.12751743082459868f;  // log2(e) / sqrt(128)
+      float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7]))) * kScale;
+      if (__any(mx > mrun[h])) {
+        const float mn = fmaxf(mrun[h], col4_max(mx));
+        // a token that sees nothing of this wave's chunks yet keeps maximum -inf and sums of zero
+        const float alpha = __builtin_amdgcn_exp2f(mrun[h] - (mn == -INFINITY ? 0.f : mn));
+        mrun[h] = mn;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lacc[h][e] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[h][dt][e] *= alpha;
+      }
+      const float mn = mrun[h] == -INFINITY ? 0.f : mrun[h];
+      uint32_t pw[2][4];
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) {
+        float w0 = __builtin_amdgcn_exp2f(fmaf(sc[i], kScale, -mn));
+        float w1 = __builtin_amdgcn_exp2f(fmaf(sc[i + 1], kScale, -mn));
+        pw[0][i / 2] = HF::pack2(w0, w1);
+        w0 -= HF::lo(pw[0][i / 2]);
+        w1 -= HF::hi(pw[0][i / 2]);
+        pw[1][i / 2] = HF::pack2(w0, w1);
+      }
+#pragma unroll
+      for (int pc = 0; pc < 2; ++pc) {
+        pf[h][pc] = u32x4{pw[pc][0], pw[pc][1], pw[pc][2], pw[pc][3]};
+        lacc[h] = HF::mfma(ones, pf[h][pc], lacc[h]);
+      }
+    }
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int h = 0; h < GH; ++h)
+#pragma unroll
+        for (int pc = 0; pc < 2; ++pc) acc[h][dt] = HF::mfma(vf[dt], pf[h][pc], acc[h][dt]);
+  }
+
+  // merge of the four waves (fixed order)
+#pragma unroll
+  for (int h = 0; h < GH; ++h) {
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) red[wave][h][dt][lane] = acc[h][dt];
+    if (g == 0) {
+      smm[wave][h][c16] = mrun[h];
+      sml[wave][h][c16] = lacc[h][0];
+    }
+  }
+  __syncthreads();
+  if (tq * 16 + c16 >= n) return;
+  const int KTQ = nq * 4;
+#pragma unroll
+  for (int h = 0; h < GH; ++h) {
+    float M = smm[0][h][c16], f[4], l = 0.f;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) M = fmaxf(M, smm[w][h][c16]);  // finite: wave 0 sees position 0
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      f[w] = __builtin_amdgcn_exp2f(smm[w][h][c16] - M);
+      l += f[w] * sml[w][h][c16];
+    }
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int d2 = 0; d2 < 2; ++d2) {
+      const int dt = wave * 2 + d2, k0 = (head0 + h) * 128 + dt * 16 + g * 4;
+      float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const f32x4 o = red[w][h][dt][lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += f[w] * o[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] *= inv;
+#pragma unroll
+      for (int pc = 0; pc < 2; ++pc) {
+        const uint32_t b0 = HF::pack2(v[0], v[1]), b1 = HF::pack2(v[2], v[3]);
+        v[0] -= HF::lo(b0);
+        v[1] -= HF::hi(b0);
+        v[2] -= HF::lo(b1);
+        v[3] -= HF::hi(b1);
+        const size_t el = (((size_t)(tq * 2 + pc) * KTQ + (k0 >> 5)) * 64 + c16 + 16 * ((k0 & 31) >> 3)) * 8 + (k0 & 7);
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(Of) + el) = make_uint2(b0, b1);
+      }
+    }
+  }
+}
+
+// Query heads per workgroup for a block, 0 where k_attn_prefill is the better kernel: as long as one
+// workgroup per CU holds the launch, first with one head each, then with two.  Beyond, the fragment loads
+// of the extra workgroups cost more than the shorter chains save.  us per launch, k_attn_prefill / one
+// head / two heads: 16 heads, 128 tokens 7.9 / 5.3 / 7.0; 256 10.6 / 7.4 / 9.1; 333 12.1 / 13.6 / 10.2; 512 16.9 / 19 / 13;
+// 32 heads, 128 tokens 7.2 / 5.4 / 7.2; 256 11.4 / 12.6 / 10.0; 333 13.4 / 18.7 / 17.7.
+int attn_small_heads(int nq, int nkv, int n, int n_cus) {
+  const int tt = (n + 15) / 16;
+  if (tt * nq <= n_cus) return 1;
+  return nq / nkv % 2 == 0 && tt * (nq / 2) <= n_cus ? 2 : 0;
+}
+
+hipError_t launch_attn_small(hipStream_t s, bool f16, const float* qkv, int nq, int nkv, const void* kc, const void* vt,
+                             uint32_t S, uint32_t slot, uint32_t max_seq, uint32_t pos0, int n, void* Of, int n_cus) {
+  if (n <= 0 || nkv <= 0 || nq % nkv || S % 32 || pos0 + (uint32_t)n > max_seq || max_seq > S) return hipErrorInvalidValue;
+  const int GH = attn_small_heads(nq, nkv, n, n_cus) == 2 ? 2 : 1;
+  dim3 grid((n + 15) / 16, nq / GH);
+  const uint16_t *k = static_cast<const uint16_t*>(kc), *v = static_cast<const uint16_t*>(vt);
+#define AS(GHV, HF) k_attn_small<GHV, HF><<<grid, 256, 0, s>>>(qkv, nq, nkv, k, v, S, slot, max_seq, pos0, n, Of)
+  if (GH == 2) {
+    if (f16) AS(2, Fp16);
+    else AS(2, Bf16);
+  } else {
+    if (f16) AS(1, Fp16);
+    else AS(1, Bf16);
+  }
+#undef AS
+  return hipGetLastError();
+}
+
 }  // namespace nnc

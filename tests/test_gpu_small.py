@@ -187,6 +187,12 @@ def test_short_block_kernels(nnc, dtype, dims, n):
         got[planner] = (a.cpu().numpy(), b.cpu().numpy(), g.kv_read(1, 0, 1, 0, n + 37).cpu().numpy())
     for x, y in zip(got[1], got[0]):
         assert np.isfinite(x).all() and np.abs(y).max() > 0.5
+    # (without the tile model the block runs k_attn_prefill: its launch shapes give the same bits)
+    for attn in (0, 1, 2, 3):
+        g.set_option(nnc.OPT_PREFILL_ATTN, attn)
+        g.kv_reset(0)
+        g.prefill(0, toks[:37])
+        assert np.array_equal(g.prefill(0, toks[37:])[0].cpu().numpy(), got[0][1]), attn
     assert max(np.abs(got[1][i] - got[0][i]).max() for i in (0, 1)) <= BF16_ABS_TIGHT
     # one 16-bit ulp (2^-8 relative for bf16) of a cached row, plus the upstream noise of the KV-row test above
     assert np.all(np.abs(got[1][2] - got[0][2]) <= 2.0 ** -7 * np.abs(got[0][2]) + 3e-3)
