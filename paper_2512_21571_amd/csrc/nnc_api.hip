@@ -417,7 +417,7 @@ nnc_status run_pass(nnc_model* m, const Pass& p) {
     if (!fuse)
       RUN(FAM_QKROPE, n * Nqkv * 4.0, 0,
           launch_qknorm_rope_append(s, dt, m->qkv, nq, nkv, L.g_q, L.g_k, c.rms_eps, m->rope, cm, n,
-                                    L.kc, L.vc, c.max_batch, c.max_seq, m->qsplit, nullptr, 0));
+                                    L.kc, L.vc, c.max_batch, c.max_seq, m->qsplit));
     RUN(FAM_ATTN, p.kv_rows * 2.0 * Dkv * hw, p.kv_rows * 4.0 * Dq,
         launch_attn_partial(s, dt, m->qkv, m->qsplit, nq, nkv, L.kc, L.vc, c.max_batch, c.max_seq, cm, n,
                             p.grid_chunks, m->partial, m->max_chunks, fuse ? &fz : nullptr, p.one_slot));
@@ -1316,7 +1316,6 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       RUN(FAM_PGEMM, (double)Nqkv * H * w, 2.0 * Nqkv * H * T, launch_gemm_prefill(s, f16, EPI_STORE, a, pieces, plan_gemm(a, EPI_STORE, nullptr)));
     }
     {
-      const ColMap cm{nullptr, slot, pos0, 0};
       // Transposed copy of the V rows of earlier calls and blocks, from the cache.  Before the append
       // kernel, which writes the block's own columns of the copy: the transpose stores whole groups
       // of 64 positions and pos0 may lie inside the last one.
@@ -1324,8 +1323,8 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
         RUN(FAM_MISC, pos0 * Dkv * 2.0 * w, 0,
             launch_v_transpose(s, L.vc, slot, nkv, c.max_seq, pos0, m->pb_vt, m->pb_vt_stride));
       RUN(FAM_QKROPE, T * Nqkv * 4.0, 0,
-          launch_qknorm_rope_append(s, m->dt, m->pb_qkv, nq, nkv, L.g_q, L.g_k, c.rms_eps, m->rope, cm, (int)n, L.kc,
-                                    L.vc, c.max_batch, c.max_seq, nullptr, m->pb_vt, m->pb_vt_stride));
+          launch_qknorm_rope_block(s, f16, m->pb_qkv, nq, nkv, L.g_q, L.g_k, c.rms_eps, m->rope, slot, pos0, (int)n, L.kc,
+                                   L.vc, c.max_seq, m->pb_vt, m->pb_vt_stride));
       if (m->record_layers) HIP_TRY(hipEventRecord(m->layer_done[li], s));
     }
     {

@@ -135,8 +135,11 @@ hipError_t launch_gemm(hipStream_t s, int dt, int epi, const GemmArgs& a);
 hipError_t launch_qknorm_rope_append(hipStream_t s, int dt, float* qkv, int nq, int nkv,
                                      const float* gq, const float* gk, float eps,
                                      const float2* rope, const ColMap& cm, int ncols, void* kc,
-                                     void* vc, uint32_t max_batch, uint32_t max_seq, void* qsplit, void* vt,
-                                     uint32_t vt_stride);
+                                     void* vc, uint32_t max_batch, uint32_t max_seq, void* qsplit);
+// the same for n consecutive positions of one slot (16-bit prompt blocks), plus the transposed V copy
+hipError_t launch_qknorm_rope_block(hipStream_t s, bool f16, float* qkv, int nq, int nkv, const float* gq, const float* gk,
+                                    float eps, const float2* rope, uint32_t slot, uint32_t pos0, int n, void* kc, void* vc,
+                                    uint32_t max_seq, void* vt, uint32_t vt_stride);
 // Fused QK-norm + RoPE + append inside the batched decode attention (bf16, at most 8 query heads
 // per kv head, every column a different slot): what the kernel needs besides the raw projection.
 struct AttnFuseArgs {

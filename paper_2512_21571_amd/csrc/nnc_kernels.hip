@@ -810,8 +810,7 @@ template <bool F32, class HF>
 __global__ __launch_bounds__(64) void k_qknorm_rope_append(
     float* __restrict__ qkv, int nq, int nkv, const float* __restrict__ gq, const float* __restrict__ gk,
     float eps, const float2* __restrict__ rope, ColMap cm, void* __restrict__ kc,
-    void* __restrict__ vc, uint32_t max_seq, uint16_t* __restrict__ qsplit, uint16_t* __restrict__ vt,
-    uint32_t vt_stride) {
+    void* __restrict__ vc, uint32_t max_seq, uint16_t* __restrict__ qsplit) {
   const int col = blockIdx.y, hh = blockIdx.x, lane = threadIdx.x;
   const int ld = (nq + 2 * nkv) * 128;
   float* p = qkv + (size_t)(cm.row0 + col) * ld + (size_t)hh * 128;
@@ -849,30 +848,114 @@ __global__ __launch_bounds__(64) void k_qknorm_rope_append(
   } else {
     static_cast<uint16_t*>(dst)[row + lane] = (uint16_t)HF::bits(a);
     static_cast<uint16_t*>(dst)[row + lane + 64] = (uint16_t)HF::bits(b);
-    if (is_v && vt) {
-      // prompt blocks: also the transposed copy [kv head][dim][position] that the
-      // matrix-core prompt attention reads
-      vt[((size_t)kvh * 128 + lane) * vt_stride + pos] = (uint16_t)HF::bits(a);
-      vt[((size_t)kvh * 128 + lane + 64) * vt_stride + pos] = (uint16_t)HF::bits(b);
-    }
   }
 }
 
 hipError_t launch_qknorm_rope_append(hipStream_t s, int dt, float* qkv, int nq, int nkv,
                                      const float* gq, const float* gk, float eps,
                                      const float2* rope, const ColMap& cm, int ncols, void* kc,
-                                     void* vc, uint32_t max_batch, uint32_t max_seq, void* qsplit, void* vt,
-                                     uint32_t vt_stride) {
+                                     void* vc, uint32_t max_batch, uint32_t max_seq, void* qsplit) {
   (void)max_batch;
   dim3 grid(nq + 2 * nkv, ncols);
   uint16_t* qs = static_cast<uint16_t*>(qsplit);
-  if (dt == DT_F32) {
-    qs = nullptr;
-    vt = nullptr;
-    vt_stride = 0;
+  if (dt == DT_F32) qs = nullptr;
+  NNC_FOR_DTYPE(dt, k_qknorm_rope_append<F32, HF><<<grid, 64, 0, s>>>(qkv, nq, nkv, gq, gk, eps, rope, cm, kc, vc, max_seq, qs));
+  return hipGetLastError();
+}
+
+// The same for a prompt block (16-bit models, consecutive positions of one slot), plus the transposed copy
+// of the V rows, [kv head][dim][position], that the matrix-core prompt attention reads.  Bound by memory
+// traffic; two kinds of workgroup:
+//   q / k: four waves x QT tokens of one head, all loads of a wave in flight before the first norm;
+//   v: 64 positions of one kv head, turned through LDS, so that the transposed copy is stored 8 positions (16
+//      bytes) at a time.  One wave per row storing its 128 values of that copy two bytes at a time, each in a
+//      cache line of its own, was what set the time of the kernel this replaces.
+constexpr int QB_TOKENS = 4;  // tokens per wave
+template <class HF>
+__global__ __launch_bounds__(256) void k_qknorm_rope_block(float* __restrict__ qkv, int nq, int nkv,
+                                                           const float* __restrict__ gq, const float* __restrict__ gk,
+                                                           float eps, const float2* __restrict__ rope, uint32_t slot,
+                                                           uint32_t pos0, int n, uint16_t* __restrict__ kc,
+                                                           uint16_t* __restrict__ vc, uint32_t max_seq,
+                                                           uint16_t* __restrict__ vt, uint32_t vt_stride, int v_blocks) {
+  __shared__ uint16_t tile[64][130];  // V: 64 positions x 128 dims, rows padded to 65 words
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int ld = (nq + 2 * nkv) * 128;
+  if ((int)blockIdx.x >= v_blocks) {
+    const int u = blockIdx.x - v_blocks, hh = u % (nq + nkv), t0 = (u / (nq + nkv) * 4 + wave) * QB_TOKENS;
+    if (t0 >= n) return;
+    float* p = qkv + (size_t)t0 * ld + (size_t)hh * 128;
+    const float* gg = hh < nq ? gq : gk;
+    const float g0 = gg[lane], g1 = gg[lane + 64];
+    float a[QB_TOKENS], b[QB_TOKENS];
+    float2 cs[QB_TOKENS];
+#pragma unroll
+    for (int i = 0; i < QB_TOKENS; ++i) {
+      const int d = min(i, n - 1 - t0);
+      a[i] = p[(size_t)d * ld + lane];
+      b[i] = p[(size_t)d * ld + lane + 64];
+      cs[i] = rope[(size_t)(pos0 + t0 + d) * 64 + lane];
+    }
+#pragma unroll
+    for (int i = 0; i < QB_TOKENS; ++i) {
+      if (t0 + i >= n) break;
+      qk_norm_rope(a[i], b[i], eps, g0, g1, cs[i]);
+      if (hh < nq) {
+        p[(size_t)i * ld + lane] = a[i];
+        p[(size_t)i * ld + lane + 64] = b[i];
+      } else {
+        uint16_t* row = kc + (((size_t)slot * nkv + hh - nq) * max_seq + pos0 + t0 + i) * 128;
+        row[lane] = (uint16_t)HF::bits(a[i]);
+        row[lane + 64] = (uint16_t)HF::bits(b[i]);
+      }
+    }
+    return;
   }
-  NNC_FOR_DTYPE(dt, k_qknorm_rope_append<F32, HF><<<grid, 64, 0, s>>>(qkv, nq, nkv, gq, gk, eps, rope, cm, kc, vc, max_seq,
-                                                                       qs, static_cast<uint16_t*>(vt), vt_stride));
+  // groups of 64 absolute positions, so that the 8-position stores are aligned wherever the block starts
+  const int kvh = blockIdx.x % nkv;
+  const uint32_t p0 = (pos0 / 64 + blockIdx.x / nkv) * 64, p1 = pos0 + (uint32_t)n;
+  for (int q = tid; q < 64 * 16; q += 256) {
+    const int pr = q >> 4, dc = (q & 15) * 8;
+    const uint32_t pos = p0 + (uint32_t)pr;
+    if (pos < pos0 || pos >= p1) continue;
+    const float* src = qkv + (size_t)(pos - pos0) * ld + (size_t)(nq + nkv + kvh) * 128 + dc;
+    const float4 x = *reinterpret_cast<const float4*>(src), y = *reinterpret_cast<const float4*>(src + 4);
+    const uint4 w = make_uint4(HF::bits(x.x) | (HF::bits(x.y) << 16), HF::bits(x.z) | (HF::bits(x.w) << 16),
+                               HF::bits(y.x) | (HF::bits(y.y) << 16), HF::bits(y.z) | (HF::bits(y.w) << 16));
+    *reinterpret_cast<uint4*>(vc + (((size_t)slot * nkv + kvh) * max_seq + pos) * 128 + dc) = w;
+    uint32_t* d = reinterpret_cast<uint32_t*>(&tile[pr][dc]);
+    d[0] = w.x; d[1] = w.y; d[2] = w.z; d[3] = w.w;
+  }
+  __syncthreads();
+  for (int q = tid; q < 128 * 8; q += 256) {
+    const int d = q >> 3, seg = (q & 7) * 8;
+    const uint32_t pa = p0 + (uint32_t)seg;
+    uint16_t* dst = vt + ((size_t)kvh * 128 + d) * vt_stride + pa;
+    if (pa >= pos0 && pa + 8 <= p1) {
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = tile[seg + 2 * e][d] | ((uint32_t)tile[seg + 2 * e + 1][d] << 16);
+      *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (pa + e >= pos0 && pa + e < p1) dst[e] = tile[seg + e][d];
+    }
+  }
+}
+
+hipError_t launch_qknorm_rope_block(hipStream_t s, bool f16, float* qkv, int nq, int nkv, const float* gq, const float* gk,
+                                    float eps, const float2* rope, uint32_t slot, uint32_t pos0, int n, void* kc, void* vc,
+                                    uint32_t max_seq, void* vt, uint32_t vt_stride) {
+  if (n <= 0 || pos0 + (uint32_t)n > max_seq || max_seq > vt_stride || vt_stride % 8) return hipErrorInvalidValue;
+  const int groups = (int)((pos0 + (uint32_t)n - 1) / 64 - pos0 / 64) + 1, v_blocks = groups * nkv;
+  const unsigned grid = (unsigned)v_blocks + (unsigned)((n + 4 * QB_TOKENS - 1) / (4 * QB_TOKENS)) * (unsigned)(nq + nkv);
+#define QB(HF)                                                                                                            \
+  k_qknorm_rope_block<HF><<<grid, 256, 0, s>>>(qkv, nq, nkv, gq, gk, eps, rope, slot, pos0, n, static_cast<uint16_t*>(kc), \
+                                               static_cast<uint16_t*>(vc), max_seq, static_cast<uint16_t*>(vt), vt_stride, v_blocks)
+  if (f16) QB(Fp16);
+  else QB(Bf16);
+#undef QB
   return hipGetLastError();
 }
 
