@@ -869,7 +869,8 @@ hipError_t launch_qknorm_rope_append(hipStream_t s, int dt, float* qkv, int nq, 
 //   q / k: four waves x QT tokens of one head, all loads of a wave in flight before the first norm;
 //   v: 64 positions of one kv head, turned through LDS, so that the transposed copy is stored 8 positions (16
 //      bytes) at a time.  One wave per row storing its 128 values of that copy two bytes at a time, each in a
-//      cache line of its own, was what set the time of the kernel this replaces.
+//      cache line of its own, was what set the time of the kernel this replaces: 48 heads x 4080 tokens
+//      65 -> 38.7 us (4.9 TB/s), 32 heads x 512 tokens 11.7 -> 6.1.
 constexpr int QB_TOKENS = 4;  // tokens per wave
 template <class HF>
 __global__ __launch_bounds__(256) void k_qknorm_rope_block(float* __restrict__ qkv, int nq, int nkv,

@@ -677,7 +677,11 @@ __global__ __launch_bounds__(256) void k_rmsnorm_frag(float* __restrict__ x, con
                                                       const float* __restrict__ gain, int H, float eps, int n_rows,
                                                       int pieces, void* __restrict__ Xf) {
   __shared__ float sm[4];
-  const int t = blockIdx.x, KT = H / 32;
+  // The 16 rows of a token tile share its cache lines (a row's elements are 16 bytes of every 256): give
+  // them to consecutive workgroups of one XCD (workgroups go to the 8 XCDs in turn), whose L2 then
+  // writes whole lines: 4080 x 4096 37 -> 23.8 us (4.2 TB/s), 512 x 2048 in two pieces 9.0 -> 7.1.
+  const int b = blockIdx.x, full = (int)gridDim.x / 128 * 128;
+  const int t = b < full ? b / 128 * 128 + (b & 7) * 16 + ((b >> 3) & 15) : b, KT = H / 32;
   uint4* out = static_cast<uint4*>(Xf) + ((size_t)(t >> 4) * pieces * KT) * 64 + (t & 15);
   const size_t piece_stride = (size_t)KT * 64;
   if (t >= n_rows) {
