@@ -276,6 +276,12 @@ typedef enum {
   NNC_OPT_SPIN_LIMIT = 5,   /* polls after which a wait inside the resident kernel gives up (sets
                                the failure flag and lets every workgroup exit); 0 (default):
                                2^20, about a second.  A tiny value makes the give-up path testable */
+  NNC_OPT_TAG_LIMIT = 14,   /* the resident kernel marks every exchanged word with a 32-bit tag, 5 x layers + 1
+                               tags per decode step; when they reach this limit, the exchange buffers are
+                               cleared (on the model's stream) and the tags start again: no run of calls ends
+                               there.  0 (default): 2^32 - 1.  A small value makes the restart testable; one
+                               run that needs more tags by itself is NNC_E_STATE at batch 1 and runs one
+                               kernel per stage at larger batches */
   NNC_OPT_STAGE_TRACE = 3   /* s + 1: the resident kernel stamps the 100 MHz wall clock at every
                                stage boundary of decode step s of each following launch (read them
                                with nnc_stage_trace); 0 (default): off */

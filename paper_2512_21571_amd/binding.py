@@ -23,6 +23,7 @@ OPT_PLANNER = 10
 OPT_FUSE_NORM = 11
 OPT_DECODE_PIECES = 12
 OPT_PREFILL_KSLICES = 13
+OPT_TAG_LIMIT = 14
 
 # every symbol include/nnc.h declares
 EXPORTS = [

@@ -113,6 +113,8 @@ struct nnc_model {
   int mk_nwg = 0, mk_ks_o = 1, mk_ks_d = 1;
   uint32_t mk_seqs = 1;  // most sequences the resident kernel decodes together
   unsigned mk_tag = 1;  // next unused exchange tag
+  unsigned mk_tag_limit = 0xffffffffu;  // tags stay below it: then the exchange buffers are cleared and the tags start again
+  std::vector<std::pair<void*, size_t>> mk_exchange;  // the exchange buffers and their 32-bit words
   void* mk_layers = nullptr;
   unsigned* mk_error = nullptr;
   unsigned* mk_error_host = nullptr;   // pinned copy of the flag, refreshed after every resident launch
@@ -596,6 +598,8 @@ bool use_persistent_greedy(const nnc_model* m, const uint32_t* slots, uint32_t b
   if (!m->mk_ok || !m->opt_persistent || m->profiling || batch > m->mk_seqs || m->opt_fuse_norm || !m->opt_fuse_qk ||
       m->opt_decode_pieces == 2)
     return false;
+  // (a single run beyond the tag space, which the resident kernel would have to refuse)
+  if ((uint64_t)n_steps * mk_tags_per_step((int)m->c.n_layers) + 1 >= m->mk_tag_limit) return false;
   long units = 0;
   for (uint32_t i = 0; i < batch; ++i) units += (long)m->c.n_kv_heads * ((m->len[slots[i]] + n_steps - 1) / ATT_CHUNK + 1);
   return units <= 2L * m->mk_nwg;
@@ -630,7 +634,6 @@ nnc_status persistent_steps(nnc_model* m, const uint32_t* slots, const int32_t* 
     p.tok0[b] = tokens[b]; p.pos0[b] = m->len[slots[b]]; p.slot[b] = slots[b];
   }
   p.n_steps = (int)n_steps;
-  p.tag_base = m->mk_tag;
   p.ks_o = m->mk_ks_o; p.ks_d = m->mk_ks_d;
   p.f16 = m->dt == NNC_F16;
   {
@@ -646,10 +649,16 @@ nnc_status persistent_steps(nnc_model* m, const uint32_t* slots, const int32_t* 
     p.off_o = wrap(p.nwg - o_units);
     p.off_d = wrap(att_units);
   }
+  // A tag must not meet a word that an earlier launch left under the same tag: before the 32 bits run out
+  // (30 million steps of 28 layers), behind every launch so far, the buffers are cleared and the tags start again.
   const uint64_t tags = (uint64_t)n_steps * mk_tags_per_step((int)c.n_layers);
-  if ((uint64_t)m->mk_tag + tags >= 0xffffffffull)
-    return fail(NNC_E_STATE, "exchange tags exhausted (after ~2^32 / %u decode steps); recreate the model",
-                mk_tags_per_step((int)c.n_layers));
+  if (1 + tags >= m->mk_tag_limit)
+    return fail(NNC_E_STATE, "one run needs %llu exchange tags, there are %u", (unsigned long long)tags, m->mk_tag_limit - 1);
+  if (m->mk_tag + tags >= m->mk_tag_limit) {
+    for (const auto& b : m->mk_exchange) HIP_TRY(launch_zero_words(m->stream, static_cast<uint32_t*>(b.first), (int)b.second));
+    m->mk_tag = 1;
+  }
+  p.tag_base = m->mk_tag;
   MkBuffers b{};
   b.layers = m->mk_layers; b.embed = m->embed; b.lm_head = m->lm_head; b.g_final = m->g_final; b.rope = m->rope;
   b.error = m->mk_error;
@@ -959,6 +968,7 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
       auto zeroed = [&](void*& ptr, size_t bytes) -> hipError_t {
         ptr = dev_alloc(m, bytes);
         if (!ptr) return hipErrorOutOfMemory;
+        m->mk_exchange.emplace_back(ptr, bytes / 4);
         return hipMemsetAsync(ptr, 0, bytes, s);
       };
       // several sequences at once, where an instance exists, its operand fits and the grid is resident
@@ -980,6 +990,7 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
       void* tr = nullptr;
       TRY_OR_BAIL(zeroed(tr, (size_t)m->mk_nwg * mk_trace_points((int)c.n_layers) * 8));
       m->mk_trace = static_cast<unsigned long long*>(tr);
+      m->mk_exchange.pop_back();  // (the trace is no exchange buffer)
       TRY_OR_BAIL(hipStreamSynchronize(s));  // table goes out of scope
       m->mk_ok = true;
     }
@@ -1072,6 +1083,10 @@ nnc_status nnc_set_option(nnc_model* m, nnc_option opt, int32_t value) {
     case NNC_OPT_SPIN_LIMIT:
       if (value < 0) return fail(NNC_E_ARG, "spin limit must be >= 0");
       m->mk_spin_limit = (unsigned)value;
+      return NNC_OK;
+    case NNC_OPT_TAG_LIMIT:
+      if (value < 0) return fail(NNC_E_ARG, "tag limit must be >= 0");
+      m->mk_tag_limit = value ? (unsigned)value : 0xffffffffu;
       return NNC_OK;
     case NNC_OPT_STAGE_TRACE:
       if (!m->mk_ok) return fail(NNC_E_STATE, "the resident decode kernel is not available for this model");

@@ -338,6 +338,38 @@ def test_resident_greedy_of_a_few_sequences(nnc, shape, batch):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
 
 
+@pytest.mark.parametrize("batch", [1, 2, 4])
+def test_resident_exchange_tags_start_again(nnc, batch):
+    """When the tags of the exchanged words reach their limit, the exchange buffers are cleared and the tags
+    start again: many runs on few tags give the bits of the same runs on all of them.  A run that
+    needs more tags than there are is refused at batch 1 and runs per stage at larger batches."""
+    print(f"case: exchange tags start again, B={batch}", flush=True)
+    shape = SMALL_BF16                                    # 11 tags per step
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    slots, runs = list(range(batch)), []
+    for limit in (0, 11 * 5 + 2, 11 * 7):                 # room for one run of five steps, exactly and with some to spare
+        g = nnc.Model(shape, blob, batch, 100)
+        g.set_option(nnc.OPT_TAG_LIMIT, limit)
+        cur = [int(g.prefill(s, synth.tokens(20 + 9 * s, shape.vocab, stream=60 + s))[1].item()) for s in slots]
+        got = []
+        for _ in range(6):
+            toks, logits = g.decode_greedy(slots, cur, 5, want_logits=True)
+            got += [toks.cpu().numpy(), logits.cpu().numpy()]
+            cur = [int(v) for v in got[-2][-1]]
+        g.synchronize()
+        runs.append(got)
+        if limit:
+            if batch == 1:
+                with pytest.raises(nnc.NncError) as e:
+                    g.decode_greedy(slots, cur, 8)
+                assert e.value.status == nnc.E_STATE and g.slot_len(0) == 50
+            else:
+                assert g.decode_greedy(slots, cur, 8)[0].shape == (8, batch)
+                g.synchronize()
+    for got in runs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(got, runs[0]))
+
+
 @pytest.mark.parametrize("planner", [0, 1], ids=["hand-rules", "planner"])
 @pytest.mark.parametrize("batch", [1, 3, 16])
 def test_fused_qk_norm_rope_append_equals_separate_kernel(nnc, batch, planner):
