@@ -228,7 +228,12 @@ typedef enum {
   NNC_OPT_PERSISTENT = 2,   /* 1 (default): batch-1 decode steps of 16-bit models, and nnc_decode_greedy
                                runs of two to four sequences of the smaller shapes, run in one
                                resident kernel per call (all steps of nnc_decode_greedy in a
-                               single launch); 0: one kernel per stage */
+                               single launch); 0: one kernel per stage.
+                               That kernel takes every compute unit, and its workgroups wait for each
+                               other (NNC_OPT_SPIN_LIMIT bounds the wait).  Launches of one process, of
+                               whatever model and stream, take turns on a GPU; nothing orders them with
+                               the kernels of other processes, or with kernels of the caller's own that stay
+                               on the GPU for as long as that bound: where such share the GPU, set 0 */
   NNC_OPT_PREFILL_TILE = 4, /* block tile of the large-block prompt GEMMs: -1 (default) chosen from
                                each launch's size; 0: 64 x 128, 1: 256 x 128, 2: 128 x 128, 3: 64 x 64,
                                4: 192 x 128, 5: 256 x 256, 6: 192 x 256 (rows x operand columns).  Same k order per output

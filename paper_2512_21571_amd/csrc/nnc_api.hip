@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 #include <tuple>
@@ -243,7 +244,28 @@ void clear_graphs(nnc_model* m) {
   m->hidden_graphs.clear();
 }
 
+constexpr int MAX_DEVICES = 64;
+
+// Resident grids on one GPU take turns.  A grid takes every CU and its workgroups wait for each other: two of
+// them side by side (two models on two streams) could each hold CUs that the other waits for.  So a launch
+// waits, in its stream, for the last launch of another model; the event is the one that follows every launch anyway.
+struct ResidentTurn {
+  std::mutex mutex;                      // held from that wait to the record of the launch's own event
+  nnc_model* last[MAX_DEVICES] = {};     // by device: the model of the last launch (NULL: none, or destroyed since)
+};
+ResidentTurn g_turn;
+
+// Whether the caller is capturing the model's stream into a graph of its own.
+bool being_captured(const nnc_model* m) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return m->stream && hipStreamIsCapturing(m->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 void release_all(nnc_model* m) {
+  if (m->device >= 0 && m->device < MAX_DEVICES) {
+    std::lock_guard<std::mutex> lock(g_turn.mutex);
+    if (g_turn.last[m->device] == m) g_turn.last[m->device] = nullptr;  // (its stream has been waited for)
+  }
   if (m->tail_stream) {
     (void)hipStreamSynchronize(m->tail_stream);
     (void)hipStreamDestroy(m->tail_stream);
@@ -613,6 +635,7 @@ bool use_persistent_greedy(const nnc_model* m, const uint32_t* slots, uint32_t b
 nnc_status fetch_wait_flag(nnc_model* m) {
   if (!m->mk_error) return NNC_OK;
   HIP_TRY(hipMemcpyAsync(m->mk_error_host, m->mk_error, sizeof(unsigned), hipMemcpyDeviceToHost, m->stream));
+  if (being_captured(m)) return NNC_OK;  // an event recorded into a caller's graph says nothing outside it
   HIP_TRY(hipEventRecord(m->mk_error_event, m->stream));
   m->mk_error_pending = true;
   return NNC_OK;
@@ -669,7 +692,15 @@ nnc_status persistent_steps(nnc_model* m, const uint32_t* slots, const int32_t* 
   b.trace_step = m->mk_trace_step;
   b.trace_points = mk_trace_points((int)c.n_layers);
   p.spin_max = m->mk_spin_limit;
+  std::unique_lock<std::mutex> turn(g_turn.mutex, std::defer_lock);
+  nnc_model** last = nullptr;
+  if (m->device < MAX_DEVICES && !being_captured(m)) {
+    turn.lock();
+    last = &g_turn.last[m->device];
+    if (*last && *last != m) HIP_TRY(hipStreamWaitEvent(m->stream, (*last)->mk_error_event, 0));
+  }
   HIP_TRY(launch_decode_resident(m->stream, p, b));
+  if (last) *last = m;
   m->mk_tag += (unsigned)tags;
   // the kernel's give-up flag travels to pinned host memory behind the launch; the next call
   // on this model that finds the copy complete looks at it (resident_failed)
@@ -1581,7 +1612,6 @@ constexpr size_t STATIC_SCRATCH_BYTES = (size_t)NNC_STATIC_SCRATCH_MIB << 20;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
 namespace {
-constexpr int MAX_DEVICES = 64;
 unsigned char* g_scratch_ptr[MAX_DEVICES] = {};  // this device's copy of `scratch`, by device ordinal
 
 // Workspace pointers of the model while a pass runs out of the static array; restored on exit.
@@ -1742,9 +1772,7 @@ nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const flo
   p.pending_out = &pending;
   // One small layer is eight kernels of a few microseconds: launched one by one they are bound by the
   // host (41 us per call), replayed as a graph by the GPU.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool graph = m->opt_graph && !m->profiling && m->stream != nullptr &&
-                     hipStreamIsCapturing(m->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  const bool graph = m->opt_graph && !m->profiling && m->stream != nullptr && !being_captured(m);
   nnc_model::HiddenGraph* hg = graph ? &m->hidden_graphs[std::make_tuple((int)batch, p.nsplit, p.grid_chunks)] : nullptr;
   if (hg && !hg->exec && ++hg->uses > 2) {
     hipGraph_t g = nullptr;

@@ -370,6 +370,58 @@ def test_resident_exchange_tags_start_again(nnc, batch):
         assert all(np.array_equal(a, b) for a, b in zip(got, runs[0]))
 
 
+# widths of the smallest model: its resident grid is one workgroup per CU, with k slices in both residual projections
+FULL_GRID = synth.ModelShape("full-grid", hidden=1024, n_layers=2, n_q_heads=16, n_kv_heads=8, head_dim=128, ffn=3072,
+                             vocab=1024, dtype=synth.BF16)
+
+
+@pytest.mark.parametrize("batches", [(2, 2), (1, 4)], ids=str)
+def test_resident_grids_of_two_models_take_turns(nnc, batches):
+    """Greedy runs of two models on two streams, enqueued by two threads with nothing between them: a resident grid
+    takes every CU, so the launches have to follow one another; no wait may run out, and every
+    run gives the tokens and logits it gives alone."""
+    import threading
+    print(f"case: two models' resident greedy runs side by side, batches {batches}", flush=True)
+    blob = synth.make_blob(FULL_GRID, gain_jitter=0.1)
+    models = []
+    for k, b in enumerate(batches):
+        g = nnc.Model(FULL_GRID, blob, b, 256)
+        firsts = [int(g.prefill(s, synth.tokens(30 + 11 * s, 1024, stream=10 * k + s))[1].item()) for s in range(b)]
+        models.append((g, list(range(b)), firsts))
+
+    def runs(g, slots, firsts, out):
+        for _ in range(6):
+            toks, logits = g.decode_greedy(slots, firsts, 20, want_logits=True)
+            out.append((toks, logits))
+
+    def again(side_by_side):
+        outs = [[] for _ in models]
+        for (g, slots, _) in models:
+            g.kv_reset()
+            for s in slots:
+                g.prefill(s, synth.tokens(30 + 11 * s, 1024, stream=s), want_logits=False)
+        threads = [threading.Thread(target=runs, args=(*m, o)) for m, o in zip(models, outs)]
+        for t in threads:
+            t.start()
+            if not side_by_side:
+                t.join()
+        for t in threads:
+            t.join()
+        for g, _, _ in models:
+            g.synchronize()
+        return [[(a.cpu().numpy(), b.cpu().numpy()) for a, b in o] for o in outs]
+
+    alone, together = again(False), again(True)
+    for x, y in zip(alone, together):
+        assert len(x) == len(y) == 6
+        for (t0, l0), (t1, l1) in zip(x, y):
+            assert np.array_equal(t0, t1) and np.array_equal(l0, l1)
+    models[0][0].close()                                    # the other model goes on without it
+    g, slots, firsts = models[1]
+    g.decode_greedy(slots, firsts, 2)
+    g.synchronize()
+
+
 @pytest.mark.parametrize("planner", [0, 1], ids=["hand-rules", "planner"])
 @pytest.mark.parametrize("batch", [1, 3, 16])
 def test_fused_qk_norm_rope_append_equals_separate_kernel(nnc, batch, planner):
