@@ -620,6 +620,8 @@ bool use_persistent_greedy(const nnc_model* m, const uint32_t* slots, uint32_t b
   if (!m->mk_ok || !m->opt_persistent || m->profiling || batch > m->mk_seqs || m->opt_fuse_norm || !m->opt_fuse_qk ||
       m->opt_decode_pieces == 2)
     return false;
+  // (a replay of a caller's graph would meet the tags of the replay before)
+  if (being_captured(m)) return false;
   // (a single run beyond the tag space, which the resident kernel would have to refuse)
   if ((uint64_t)n_steps * mk_tags_per_step((int)m->c.n_layers) + 1 >= m->mk_tag_limit) return false;
   long units = 0;

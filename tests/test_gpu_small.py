@@ -422,6 +422,35 @@ def test_resident_grids_of_two_models_take_turns(nnc, batches):
     g.synchronize()
 
 
+def test_greedy_run_of_two_in_a_callers_graph(nnc):
+    """A greedy run of two sequences captured by the caller is one kernel per stage (a replayed resident launch
+    would meet its own tags): every replay gives the tokens and logits of the eager run."""
+    import torch
+    print("case: greedy run of two sequences in a caller's graph", flush=True)
+    shape, slots = SMALL_BF16, [0, 1]
+    g = nnc.Model(shape, synth.make_blob(shape, weight_std=0.05), 2, 100)
+    g.set_option(nnc.OPT_GRAPH, 0)
+    prompts = [synth.tokens(21 + s, shape.vocab, stream=s) for s in slots]
+    firsts = [int(g.prefill(s, p)[1].item()) for s, p in zip(slots, prompts)]
+    g.set_option(nnc.OPT_PERSISTENT, 0)
+    want = [t.cpu().numpy() for t in g.decode_greedy(slots, firsts, 4, want_logits=True)]
+    g.set_option(nnc.OPT_PERSISTENT, 1)
+    g.kv_reset()
+    for s, p in zip(slots, prompts):
+        g.prefill(s, p, want_logits=False)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=g.stream):
+        toks, logits = g.decode_greedy(slots, firsts, 4, want_logits=True)
+    for _ in range(3):
+        toks.zero_()
+        logits.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(toks.cpu().numpy(), want[0]) and np.array_equal(logits.cpu().numpy(), want[1])
+
+
 @pytest.mark.parametrize("planner", [0, 1], ids=["hand-rules", "planner"])
 @pytest.mark.parametrize("batch", [1, 3, 16])
 def test_fused_qk_norm_rope_append_equals_separate_kernel(nnc, batch, planner):
