@@ -6,6 +6,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 
 import numpy as np
 
@@ -157,7 +158,9 @@ def _u32(a):
 
 class Model:
     """A model on cuda:0.  Device memory comes from torch's allocator, work runs on a
-    torch stream of default priority; outputs are torch tensors on that stream."""
+    torch stream of default priority (`stream`), which waits for the caller's current stream; outputs are
+    tensors of the caller's current stream, which waits for the model's before anything it runs later.
+    Calls on one model, from whatever threads, must not overlap inside the library."""
 
     def __init__(self, shape, blob: np.ndarray, max_batch: int, max_seq: int,
                  compute_dtype: int | None = None, device: str = "cuda:0"):
@@ -168,7 +171,7 @@ class Model:
         self.device = torch.device(device)
         torch.cuda.set_device(self.device)
         self.stream = torch.cuda.Stream(device=self.device)
-        self._ev_in, self._ev_out = torch.cuda.Event(), torch.cuda.Event()
+        self._local = threading.local()  # the hand-over of a thread's call: its stream and two events
         self.cfg = make_config(shape, max_batch, max_seq, compute_dtype)
         self._held = {}
 
@@ -214,16 +217,20 @@ class Model:
         _check(lib().nnc_synchronize(self.h))
 
     def _before(self):
-        # inputs may have been produced on the caller's current stream (two events kept for the hand-over:
-        # recording one again does not disturb a wait that was already enqueued)
-        self._caller = self.torch.cuda.current_stream(self.device)
-        self._ev_in.record(self._caller)
-        self.stream.wait_event(self._ev_in)
+        # inputs may have been produced on the caller's current stream (two events kept per thread for the
+        # hand-over: recording one again does not disturb a wait that was already enqueued)
+        here = self._local
+        if not hasattr(here, "ev_in"):
+            here.ev_in, here.ev_out = self.torch.cuda.Event(), self.torch.cuda.Event()
+        here.caller = self.torch.cuda.current_stream(self.device)
+        here.ev_in.record(here.caller)
+        self.stream.wait_event(here.ev_in)
 
     def _after(self):
         # outputs are consumed on the caller's current stream
-        self._ev_out.record(self.stream)
-        self._caller.wait_event(self._ev_out)
+        here = self._local
+        here.ev_out.record(self.stream)
+        here.caller.wait_event(here.ev_out)
 
     # -- forward pass ---------------------------------------------------------------
     def prefill(self, slot: int, tokens, want_logits: bool = True):
