@@ -82,8 +82,9 @@ typedef struct {
                                   once, at create).  An NNC_W8 blob computes in NNC_BF16: the decode
                                   GEMMs stream the bytes, widen them to bf16 exactly in registers and
                                   multiply the row sums by the scales; bf16 KV cache, embedding and
-                                  LM head.  Prompt blocks of more than 256 tokens widen each matrix (exactly) into a
-                                  scratch matrix of bf16 tiles first and scale the rows in the GEMM's epilogue;
+                                  LM head.  Prompt blocks widen each matrix (exactly) into a scratch matrix of
+                                  bf16 tiles first and scale the rows in the GEMM's epilogue, short ones (up to
+                                  256 tokens, see NNC_OPT_PLANNER) stream the bytes as decode does;
                                   batch-1 decode runs through the per-stage kernels (the resident decode
                                   kernel takes 16-bit weights only). */
   uint32_t max_batch;          /* number of KV slots */

@@ -1151,18 +1151,36 @@ static nnc_status prefill_head(nnc_model* m, uint32_t n, int pending, float* log
 }
 
 // Whether a block of n tokens runs through the kernels of nnc_small.hip.  They save three kernels per
-// layer (12 us with their gaps) but re-read the weights from L2 once per 32 - 64 operand columns, which
-// costs more than that from n * (weight bytes of a layer) = 16e9 on.  Measured, us per layer, block
-// tiles / short-block kernels: 0.6B 66 / 53 at 128 tokens, 111 / 106 at 512; 1.7B 101 / 94 at 128, 127 / 127
-// at 256, 153 / 202 at 333; 4B 130 / 122 at 64, 141 / 158 at 128.  binary16 keeps its norm kernels (0.6B 83 / 78
-// at 256, 111 / 112 at 512): half the limit.  One row block per head leaves the q|k|v GEMM of the 4096-wide
-// shape on 48 CUs (33 us at 16 tokens, 14 on the block tiles): hidden sizes up to 2560.  Byte weights need no
-// widened copy here: 8B 303 / 202 at 128 tokens, 383 / 360 at 256, 484 / 494 at 333; 1.7B 148 / 126 and 174 / 186.
+// layer but re-read the weights from L2 once per 32 - 64 operand columns, which costs more than that from
+// n * H^2 = 2^29 on, in binary16 (which keeps its norm kernels) 2^28.  Measured, us per layer, block tiles /
+// short-block kernels: 0.6B 55.5 / 44.1 at 128 tokens, 96.6 / 90.1 at 512; 1.7B 92.8 / 87.8 at 128, 99.9 / 102.0 at
+// 144, 117.5 / 119.5 at 256; 4B 116.5 / 104.6 at 33, 120.2 / 118.6 at 79, 131.2 / 145.2 at 112; binary16: 0.6B 70.7 / 63.3
+// at 256, 80.5 / 79.5 at 288; 1.7B 78.3 / 73.4 at 64, 88.1 / 91.2 at 79; 4B 117.8 / 106.0 at 39, 121.2 / 122.9 at 80.
+// One row block per head leaves the q|k|v GEMM of the 4096-wide shape on 48 CUs (33 us at 16 tokens, 14 on the block
+// tiles): hidden sizes up to 2560.
+// Byte weights need no widened copy here, so the limit lies further out and depends on how many rounds
+// of workgroups the short GEMMs take; the tile models know that.  A layer takes 1.75 - 2 times the short GEMMs'
+// model time, against the block-tile GEMMs' model time + 25 us + a pass over the weights at 2.4 TB/s.
+// Measured as above: 0.6B 86.9 / 64.2 at 256; 1.7B 144.8 / 123.0 at 256, 166.7 / 168.7 at 300; 4B 209.0 / 189.8 at 192,
+// 219.6 / 228.6 at 208, 227.0 / 241.8 at 256; 8B 286 / 196 at 128, 351 / 306 at 192, 338 / 324 at 208, 370 / 357 and (another
+// card) 344 / 357 at 256, 423 / 424 at 288.
 static bool short_block(const nnc_model* m, uint32_t n) {
   if (n > PB_SMALL_TOKENS || m->opt_prefill_exact == 1) return false;
-  if (m->w8) return n <= 256;
-  const double H = m->H(), layer = 2.0 * (H * (2.0 * m->Dq() + 2.0 * m->Dkv()) + 3.0 * H * m->F());
-  return H <= 2560 && n * layer <= (m->dt == NNC_F16 ? 8e9 : 16e9);
+  const double H = m->H();
+  if (!m->w8) return H <= 2560 && n * H * H <= (m->dt == NNC_F16 ? 0x1p28 : 0x1p29);
+  if (n > 256) return false;
+  const Machine mc = machine_mi355x(m->n_cus);
+  const int tt = 2 * (int)((n + 15) / 16);
+  const struct { int small, block, rows, K; } gemms[4] = {
+      {SEPI_QKV, PLAN_EPI_STORE, (int)(m->Dq() + 2 * m->Dkv()), (int)m->H()}, {SEPI_RESID, PLAN_EPI_RESID, (int)m->H(), (int)m->Dq()},
+      {SEPI_SWIGLU, PLAN_EPI_SWIGLU, (int)(2 * m->F()), (int)m->H()}, {SEPI_RESID, PLAN_EPI_RESID, (int)m->H(), (int)m->F()}};
+  double small = 0.0, block = 25.0;
+  for (const auto& g : gemms) {
+    small += 1.75 * plan_small_gemm(mc, g.small, g.rows / 16, g.K / 64, tt, 2).t_us;
+    block += plan_prefill_gemm(mc, g.rows / 16, g.K / 32, tt, (int)n, 2, g.block, g.block == PLAN_EPI_RESID ? PB_SPLIT_MAX : 1).t_us +
+             (double)g.rows * g.K / 2.4e6;
+  }
+  return small <= block;
 }
 
 // Two-piece blocks of up to 512 tokens whose attention launch is small (forced launch shapes concern the

@@ -198,6 +198,38 @@ def test_short_block_kernels(nnc, dtype, dims, n):
     assert np.all(np.abs(got[1][2] - got[0][2]) <= 2.0 ** -7 * np.abs(got[0][2]) + 3e-3)
 
 
+@pytest.mark.parametrize("dtype,dims,n", [(synth.BF16, (1024, 16, 8, 3072), 512), (synth.F16, (1024, 16, 8, 3072), 256),
+                                          (synth.BF16, (2048, 16, 8, 6144), 128), (synth.F16, (2048, 16, 8, 6144), 64),
+                                          (synth.BF16, (2560, 32, 8, 9728), 81), (synth.W8, (2560, 32, 8, 9728), 192)], ids=str)
+def test_largest_short_blocks(nnc, dtype, dims, n):
+    """The largest block that the short-block kernels take on a shape, and the next size, which they leave to the
+    block tiles; the largest against the library without its tile model, as above."""
+    H, nq, nkv, F = dims
+    print(f"case: largest short block, dtype {dtype}, {dims}, {n} tokens", flush=True)
+    shape = synth.ModelShape("short", hidden=H, n_layers=1, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, ffn=F,
+                             vocab=1024, dtype=dtype)
+    g = nnc.Model(shape, synth.make_blob(shape, gain_jitter=0.1), 1, 640)
+    toks = synth.tokens(n + 16, shape.vocab, stream=850 + n)
+    for m, separate in ((n, False), (n + 16, True)):       # (16: the next token tile)
+        if m > 512:                                         # (one piece per activation from here on)
+            continue
+        g.kv_reset(0)
+        g.profile_begin()
+        g.prefill(0, toks[:m])
+        names = {r["name"] for r in g.profile_end() if r["launches"]}
+        # the block tiles leave QK norm, rotary embedding and append to a kernel of their own
+        assert ("qknorm_rope_append" in names) == separate, (m, names)
+    got = []
+    for planner in (1, 0):
+        g.set_option(nnc.OPT_PLANNER, planner)
+        g.kv_reset(0)
+        lg, _ = g.prefill(0, toks[:n])
+        got.append([lg.cpu().numpy()] + [g.kv_read(0, 0, w, 0, n).cpu().numpy() for w in (0, 1)])
+    assert np.abs(got[1][0]).max() > 0.5 and np.abs(got[0][0] - got[1][0]).max() <= BF16_ABS_TIGHT
+    for a, b in zip(got[0][1:], got[1][1:]):
+        assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(b) + 3e-3)
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("n", [47, 300, 700])
 def test_large_block_prefill_every_block_tile(nnc, n, tile):
