@@ -1116,6 +1116,7 @@ nnc_status nnc_set_option(nnc_model* m, nnc_option opt, int32_t value) {
     case NNC_OPT_SPIN_LIMIT:
       if (value < 0) return fail(NNC_E_ARG, "spin limit must be >= 0");
       m->mk_spin_limit = (unsigned)value;
+      clear_graphs(m);  // captured passes with norm tails hold the limit they were captured under
       return NNC_OK;
     case NNC_OPT_TAG_LIMIT:
       if (value < 0) return fail(NNC_E_ARG, "tag limit must be >= 0");

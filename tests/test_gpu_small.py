@@ -817,6 +817,38 @@ def test_hidden_state_layer_fp32(nnc):
         assert rel_inf(yg, want) <= F32_REL
 
 
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16, synth.F16])
+def test_hidden_state_steps_replayed_equal_eager(nnc, dtype):
+    """Hidden-state steps replayed as graphs (a key's third use captures) against the same steps launched one by
+    one: the same bits, over batches of one and two in turn, contexts that pass 512 positions (another
+    key), and options that change the launches or the number of partial sums a step leaves."""
+    print(f"case: hidden-state steps, graph and eager, dtype {dtype}", flush=True)
+    shape = synth.ModelShape("hidden", hidden=256, n_layers=2, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=512, vocab=0,
+                             has_embed_and_head=False, tied_lm_head=False, dtype=dtype)
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    rows = synth.activations(700, shape.hidden)
+    options = [(), (nnc.OPT_FUSE_NORM, 1), (nnc.OPT_FUSE_QK, 0), (nnc.OPT_PLANNER, 0), (nnc.OPT_DECODE_PIECES, 2), (nnc.OPT_FUSE_NORM, 0)]
+    runs = []
+    for graph in (1, 0):
+        g = nnc.Model(shape, blob, 3, 600)
+        g.set_option(nnc.OPT_GRAPH, graph)
+        got = [g.prefill_hidden(sl, rows[:n]) for sl, n in enumerate((500, 20, 494))]
+        at = 500
+        for opt in options:
+            if opt:
+                g.set_option(*opt)
+            for _ in range(5):
+                got.append(g.decode_step_hidden([0], rows[at:at + 1]))
+                got.append(g.decode_step_hidden([2, 1], rows[at + 1:at + 3]))
+                at += 3
+        g.synchronize()
+        assert [g.slot_len(s) for s in range(3)] == [530, 50, 524]
+        got += [g.kv_read(1, s, w, 0, 50) for s in range(3) for w in (0, 1)]
+        runs.append([y.cpu().numpy() for y in got])
+    assert all(np.isfinite(y).all() for y in runs[0])
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
+
+
 def test_greedy_loop_graph_and_eager_agree_with_oracle(nnc):
     print("case: greedy loop graph/eager", flush=True)
     shape = SMALL_BF16
@@ -935,6 +967,30 @@ def test_norm_tail_gives_up_cleanly_and_reports_it(nnc):
     assert ei.value.status == nnc.E_DEVICE
     with pytest.raises(nnc.NncError):
         g.decode_step(list(range(16)), firsts)
+
+
+@pytest.mark.parametrize("shape", [SMALL_BF16, SMALL_LAYER_F32], ids=lambda s: s.name)
+def test_spin_limit_reaches_replayed_steps(nnc, shape):
+    """The give-up path of the norm tail, forced as above, after the steps have been captured under the
+    default limit: a new limit drops those graphs."""
+    print(f"case: spin limit after capture, {shape.name}", flush=True)
+    g = nnc.Model(shape, synth.make_blob(shape, weight_std=0.05), 16, 64)
+    g.set_option(nnc.OPT_FUSE_NORM, 1)
+    slots = list(range(16))
+
+    def steps():
+        if shape.has_embed_and_head:
+            g.decode_greedy(slots, [1] * 16, 4)
+        else:
+            for _ in range(4):
+                g.decode_step_hidden(slots, synth.activations(16, shape.hidden))
+        g.synchronize()
+
+    steps()
+    g.set_option(nnc.OPT_SPIN_LIMIT, 1)
+    with pytest.raises(nnc.NncError) as ei:
+        steps()
+    assert ei.value.status == nnc.E_DEVICE
 
 
 def test_resident_kernel_gives_up_cleanly_and_reports_it(nnc):
