@@ -321,10 +321,12 @@ def test_large_block_prefill_every_attention_shape(nnc, n, attn):
     """Prompt attention launch shapes (one or two 64-token blocks per workgroup, one or two
     heads per wave) forced on prompts with an odd and an even number of blocks: a wave's
     arithmetic per head is the same in all of them, so the logits are bit-identical to the
-    automatic choice, and they match the oracle."""
+    automatic choice, and they match the oracle.  (Without the tile model, which would give blocks of up to 512
+    tokens of this shape to the short-block attention, whatever shape is forced.)"""
     print(f"case: large-block prefill length {n}, forced attention shape {attn}", flush=True)
     shape = SMALL_G4
     g, o = _pair(nnc, shape, 1, 800, exact_prefill=False)
+    g.set_option(nnc.OPT_PLANNER, int(n > 512))
     toks = synth.tokens(n, shape.vocab, stream=500 + n)
     one_piece = any(pc == 1 for _, _, pc in prefill_blocks(n))
     ref, _ = g.prefill(0, toks)
