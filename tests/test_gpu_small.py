@@ -6,6 +6,8 @@ All calls go through the C ABI (ctypes binding).  Tolerances:
                  also held to 4e-3: fp32 accumulation plus an occasional one-ulp bf16
                  difference in a cached K/V element gives ~1e-3 here.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -344,7 +346,7 @@ def test_large_block_prefill_every_attention_shape(nnc, n, attn):
 def test_resident_greedy_of_a_few_sequences(nnc, shape, batch):
     """Greedy runs of two to four sequences (five stay per-stage) in the resident kernel against the per-stage kernels: ragged
     contexts from one position to several chunks, runs that cross chunk boundaries, slots out of order and
-    with gaps, with and without logits.  Both are fp32-grade up to the rounding of cached rows, as in the
+    with gaps, with and without logits.  (The wide shape's instance takes two.)  Both are fp32-grade up to the rounding of cached rows, as in the
     comparison of the fused and the separate kernels above; greedy margins here are far larger."""
     print(f"case: resident greedy, {shape.name}, B={batch}", flush=True)
     blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
@@ -354,11 +356,13 @@ def test_resident_greedy_of_a_few_sequences(nnc, shape, batch):
         g = nnc.Model(shape, blob, 7, 400)
         g.set_option(nnc.OPT_PREFILL_EXACT, 1)
         g.set_option(nnc.OPT_PERSISTENT, resident)
+        g.set_option(nnc.OPT_STAGE_TRACE, 1)                # stamps only where the resident kernel runs
         firsts = []
         for sl, n in zip(slots, lens):
             _, nx = g.prefill(sl, synth.tokens(n, shape.vocab, stream=900 + sl))
             firsts.append(int(nx.item()))
         toks, logits = g.decode_greedy(slots, firsts, 13, want_logits=True)
+        assert g.stage_trace().any() == (resident and batch <= (2 if shape is WIDE_BF16 else 4))
         toks2, _ = g.decode_greedy(slots, toks[-1].cpu().numpy().tolist(), 40)
         lg, _ = g.decode_step(slots, toks2[-1].cpu().numpy().tolist())
         g.synchronize()
@@ -368,6 +372,48 @@ def test_resident_greedy_of_a_few_sequences(nnc, shape, batch):
     (t0, u0, l0, s0, k0), (t1, u1, l1, s1, k1) = runs
     assert np.array_equal(t0, t1) and np.array_equal(u0, u1)
     assert np.isfinite(l0).all() and np.abs(l0 - l1).max() <= BF16_ABS_TIGHT and np.abs(s0 - s1).max() <= BF16_ABS_TIGHT
+    for a, b in zip(k0, k1):
+        assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
+
+
+# widths of the smallest model: its resident grid is one workgroup per CU, with k slices in both residual projections
+FULL_GRID = synth.ModelShape("full-grid", hidden=1024, n_layers=2, n_q_heads=16, n_kv_heads=8, head_dim=128, ffn=3072,
+                             vocab=1024, dtype=synth.BF16)
+
+
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
+@pytest.mark.parametrize("lens", [(1010, 1100), (700, 1213, 900), (1000, 895, 1060, 960)], ids=str)
+def test_resident_greedy_on_the_full_grid(nnc, lens, dtype):
+    """The same on the smallest model's widths: 256 workgroups, two k slices in the output projection and three in the
+    down projection, and contexts that give a workgroup up to two attention units; one
+    more chunk than that, and the run is per stage."""
+    print(f"case: resident greedy on the full grid, contexts {lens}, dtype {dtype}", flush=True)
+    shape = dataclasses.replace(FULL_GRID, name="full-grid", dtype=dtype)
+    blob, batch, n_steps = synth.make_blob(shape, gain_jitter=0.1), len(lens), 24
+    slots = [3, 0, 2, 1][:batch]
+    units = 8 * sum((n + n_steps - 1) // 64 + 1 for n in lens)
+    assert 256 < units <= 512
+    runs = []
+    for resident in (1, 0):
+        g = nnc.Model(shape, blob, 4, 3200)
+        g.set_option(nnc.OPT_PREFILL_EXACT, 1)
+        g.set_option(nnc.OPT_PERSISTENT, resident)
+        g.set_option(nnc.OPT_STAGE_TRACE, 1)
+        firsts = [int(g.prefill(sl, synth.tokens(n, shape.vocab, stream=950 + sl))[1].item()) for sl, n in zip(slots, lens)]
+        toks, logits = g.decode_greedy(slots, firsts, n_steps, want_logits=True)
+        assert g.stage_trace().any() == bool(resident)
+        kv = [g.kv_read(1, sl, w, 0, n + n_steps).cpu().numpy() for sl, n in zip(slots, lens) for w in (0, 1)]
+        # the longest context grows until the units are more than two per workgroup
+        before = g.stage_trace()
+        more = (512 - units) // 8 * 64 + 64
+        g.prefill(slots[1], synth.tokens(more, shape.vocab, stream=990), want_logits=False)
+        g.decode_greedy(slots, firsts, n_steps)
+        assert np.array_equal(g.stage_trace(), before)
+        g.synchronize()
+        runs.append((toks.cpu().numpy(), logits.cpu().numpy(), kv))
+    (t0, l0, k0), (t1, l1, k1) = runs
+    assert np.array_equal(t0, t1)
+    assert np.isfinite(l0).all() and np.abs(l1).max() > 0.5 and np.abs(l0 - l1).max() <= BF16_ABS_TIGHT
     for a, b in zip(k0, k1):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
 
@@ -402,11 +448,6 @@ def test_resident_exchange_tags_start_again(nnc, batch):
                 g.synchronize()
     for got in runs[1:]:
         assert all(np.array_equal(a, b) for a, b in zip(got, runs[0]))
-
-
-# widths of the smallest model: its resident grid is one workgroup per CU, with k slices in both residual projections
-FULL_GRID = synth.ModelShape("full-grid", hidden=1024, n_layers=2, n_q_heads=16, n_kv_heads=8, head_dim=128, ffn=3072,
-                             vocab=1024, dtype=synth.BF16)
 
 
 @pytest.mark.parametrize("batches", [(2, 2), (1, 4)], ids=str)
