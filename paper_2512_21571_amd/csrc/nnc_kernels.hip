@@ -810,7 +810,8 @@ template <bool F32, class HF>
 __global__ __launch_bounds__(64) void k_qknorm_rope_append(
     float* __restrict__ qkv, int nq, int nkv, const float* __restrict__ gq, const float* __restrict__ gk,
     float eps, const float2* __restrict__ rope, ColMap cm, void* __restrict__ kc,
-    void* __restrict__ vc, uint32_t max_seq, uint16_t* __restrict__ qsplit) {
+    void* __restrict__ vc, uint32_t max_seq, uint16_t* __restrict__ qsplit, uint16_t* __restrict__ vt,
+    uint32_t vt_stride) {
   const int col = blockIdx.y, hh = blockIdx.x, lane = threadIdx.x;
   const int ld = (nq + 2 * nkv) * 128;
   float* p = qkv + (size_t)(cm.row0 + col) * ld + (size_t)hh * 128;
@@ -848,6 +849,10 @@ __global__ __launch_bounds__(64) void k_qknorm_rope_append(
   } else {
     static_cast<uint16_t*>(dst)[row + lane] = (uint16_t)HF::bits(a);
     static_cast<uint16_t*>(dst)[row + lane + 64] = (uint16_t)HF::bits(b);
+    if (is_v && vt) {  // short prompt blocks: also the transposed copy (below)
+      vt[((size_t)kvh * 128 + lane) * vt_stride + pos] = (uint16_t)HF::bits(a);
+      vt[((size_t)kvh * 128 + lane + 64) * vt_stride + pos] = (uint16_t)HF::bits(b);
+    }
   }
 }
 
@@ -859,7 +864,8 @@ hipError_t launch_qknorm_rope_append(hipStream_t s, int dt, float* qkv, int nq, 
   dim3 grid(nq + 2 * nkv, ncols);
   uint16_t* qs = static_cast<uint16_t*>(qsplit);
   if (dt == DT_F32) qs = nullptr;
-  NNC_FOR_DTYPE(dt, k_qknorm_rope_append<F32, HF><<<grid, 64, 0, s>>>(qkv, nq, nkv, gq, gk, eps, rope, cm, kc, vc, max_seq, qs));
+  NNC_FOR_DTYPE(dt, k_qknorm_rope_append<F32, HF><<<grid, 64, 0, s>>>(qkv, nq, nkv, gq, gk, eps, rope, cm, kc, vc, max_seq, qs,
+                                                                       nullptr, 0));
   return hipGetLastError();
 }
 
@@ -871,7 +877,11 @@ hipError_t launch_qknorm_rope_append(hipStream_t s, int dt, float* qkv, int nq, 
 //      bytes) at a time.  One wave per row storing its 128 values of that copy two bytes at a time, each in a
 //      cache line of its own, was what set the time of the kernel this replaces: 48 heads x 4080 tokens
 //      65 -> 38.7 us (4.9 TB/s), 32 heads x 512 tokens 11.7 -> 6.1.
+// Blocks of up to 192 tokens keep that kernel, a wave per row: more and shorter workgroups, and the stores do not count
+// yet.  us per layer of the whole prompt, this kernel / wave per row: 48 heads x 9 tokens 132.8 / 131.4, 33 159.8 / 157.5,
+// 128 206.3 / 204.9, 200 255.9 / 255.5; 32 heads x 140 103.8 / 103.2, 200 115.4 / 115.6, 256 122.1 / 123.4, 400 163.9 / 166.2.
 constexpr int QB_TOKENS = 4;  // tokens per wave
+constexpr int QB_ROWWISE = 192;
 template <class HF>
 __global__ __launch_bounds__(256) void k_qknorm_rope_block(float* __restrict__ qkv, int nq, int nkv,
                                                            const float* __restrict__ gq, const float* __restrict__ gk,
@@ -949,6 +959,17 @@ hipError_t launch_qknorm_rope_block(hipStream_t s, bool f16, float* qkv, int nq,
                                     float eps, const float2* rope, uint32_t slot, uint32_t pos0, int n, void* kc, void* vc,
                                     uint32_t max_seq, void* vt, uint32_t vt_stride) {
   if (n <= 0 || pos0 + (uint32_t)n > max_seq || max_seq > vt_stride || vt_stride % 8) return hipErrorInvalidValue;
+  if (n <= QB_ROWWISE) {
+    const ColMap cm{nullptr, slot, pos0, 0};
+    const dim3 grid(nq + 2 * nkv, n);
+#define QR(HF)                                                                                                         \
+  k_qknorm_rope_append<false, HF><<<grid, 64, 0, s>>>(qkv, nq, nkv, gq, gk, eps, rope, cm, kc, vc, max_seq, nullptr, \
+                                                      static_cast<uint16_t*>(vt), vt_stride)
+    if (f16) QR(Fp16);
+    else QR(Bf16);
+#undef QR
+    return hipGetLastError();
+  }
   const int groups = (int)((pos0 + (uint32_t)n - 1) / 64 - pos0 / 64) + 1, v_blocks = groups * nkv;
   const unsigned grid = (unsigned)v_blocks + (unsigned)((n + 4 * QB_TOKENS - 1) / (4 * QB_TOKENS)) * (unsigned)(nq + nkv);
 #define QB(HF)                                                                                                            \

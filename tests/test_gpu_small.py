@@ -165,6 +165,30 @@ def test_prompt_continued_at_any_position(nnc, turns):
         at += n
 
 
+@pytest.mark.parametrize("at", [0, 37, 64])
+@pytest.mark.parametrize("n", [193, 250, 321])
+@pytest.mark.parametrize("shape", [SMALL_G4, SMALL_F16], ids=lambda s: s.name)
+def test_append_kernels_of_prompt_blocks(nnc, shape, n, at):
+    """QK norm, rotary embedding and append of a prompt block: the kernel of blocks beyond 192 tokens against the
+    one-wave-per-row kernel of shorter ones, on the same rows in one call and in two.  The same arithmetic,
+    so the first layer's cached rows have the same bits; the transposed V copy shows in the logits."""
+    print(f"case: append kernels, {shape.name}, {n} tokens at {at}", flush=True)
+    g = nnc.Model(shape, synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1), 1, 400)
+    g.set_option(nnc.OPT_PLANNER, 0)
+    g.set_option(nnc.OPT_PREFILL_TILE, 1)                   # one k order whatever the block's length
+    toks = synth.tokens(at + n, shape.vocab, stream=77)
+    runs = []
+    for cuts in ((n,), (n - 150, 150)):
+        g.kv_reset(0)
+        done = 0
+        for m in ((at,) if at else ()) + cuts:
+            lg, _ = g.prefill(0, toks[done:done + m])
+            done += m
+        runs.append([g.kv_read(0, 0, w, 0, at + n).cpu().numpy() for w in (0, 1)] + [lg.cpu().numpy()])
+    assert all(np.array_equal(a, b) for a, b in zip(runs[0][:2], runs[1][:2]))
+    assert np.abs(runs[0][2]).max() > 0.5 and np.abs(runs[0][2] - runs[1][2]).max() <= BF16_ABS_TIGHT
+
+
 @pytest.mark.parametrize("n", [16, 17, 33, 100, 129, 250])
 @pytest.mark.parametrize("dtype,dims", [(synth.BF16, (1024, 16, 8, 3072)), (synth.F16, (1024, 16, 8, 3072)), (synth.BF16, (2560, 32, 8, 1216)),
                                         (synth.W8, (2048, 16, 8, 6144)), (synth.BF16, (352, 6, 3, 736))], ids=str)
