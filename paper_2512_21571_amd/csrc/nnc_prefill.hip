@@ -675,12 +675,14 @@ template <class HF>
 __global__ __launch_bounds__(256) void k_rmsnorm_frag(float* __restrict__ x, const float* __restrict__ part,
                                                       int nparts, long part_stride,
                                                       const float* __restrict__ gain, int H, float eps, int n_rows,
-                                                      int pieces, void* __restrict__ Xf) {
+                                                      int pieces, void* __restrict__ Xf, int full) {
   __shared__ float sm[4];
   // The 16 rows of a token tile share its cache lines (a row's elements are 16 bytes of every 256): give
   // them to consecutive workgroups of one XCD (workgroups go to the 8 XCDs in turn), whose L2 then
   // writes whole lines: 4080 x 4096 37 -> 23.8 us (4.2 TB/s), 512 x 2048 in two pieces 9.0 -> 7.1.
-  const int b = blockIdx.x, full = (int)gridDim.x / 128 * 128;
+  // (full: the workgroups in whole groups of 128, an argument: gridDim comes out of the launch packet by a load of
+  // its own, 0.2 us in front of everything else)
+  const int b = blockIdx.x;
   const int t = b < full ? b / 128 * 128 + (b & 7) * 16 + ((b >> 3) & 15) : b, KT = H / 32;
   uint4* out = static_cast<uint4*>(Xf) + ((size_t)(t >> 4) * pieces * KT) * 64 + (t & 15);
   const size_t piece_stride = (size_t)KT * 64;
@@ -752,9 +754,9 @@ hipError_t launch_rmsnorm_frag(hipStream_t s, bool f16, float* x, const float* p
                                void* Xf) {
   if (H % 32 || H > 8192 || nparts < 0 || (nparts > 0 && !part) || n_rows <= 0) return hipErrorInvalidValue;
   if (f16)
-    k_rmsnorm_frag<Fp16><<<token_tiles * 16, 256, 0, s>>>(x, part, nparts, part_stride, gain, H, eps, n_rows, pieces, Xf);
+    k_rmsnorm_frag<Fp16><<<token_tiles * 16, 256, 0, s>>>(x, part, nparts, part_stride, gain, H, eps, n_rows, pieces, Xf, token_tiles / 8 * 128);
   else
-    k_rmsnorm_frag<Bf16><<<token_tiles * 16, 256, 0, s>>>(x, part, nparts, part_stride, gain, H, eps, n_rows, pieces, Xf);
+    k_rmsnorm_frag<Bf16><<<token_tiles * 16, 256, 0, s>>>(x, part, nparts, part_stride, gain, H, eps, n_rows, pieces, Xf, token_tiles / 8 * 128);
   return hipGetLastError();
 }
 

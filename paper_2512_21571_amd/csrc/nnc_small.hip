@@ -443,7 +443,7 @@ __global__ __launch_bounds__(256) void k_attn_small(const float* __restrict__ qk
   const int c16 = lane & 15, g = lane >> 4;
   const int G = nq / nkv;
   const int kvh = blockIdx.y / (G / GH), head0 = kvh * G + (blockIdx.y % (G / GH)) * GH;
-  const int tq = (int)gridDim.x - 1 - (int)blockIdx.x;  // token tile, longest first
+  const int tq = (n + 15) / 16 - 1 - (int)blockIdx.x;  // token tile, longest first (gridDim would be a load of its own)
   const int ld = (nq + 2 * nkv) * 128;
   const int t = min(tq * 16 + c16, n - 1);  // rows past the prompt repeat the last token (never stored)
   const uint32_t p = pos0 + (uint32_t)t, p_first = pos0 + (uint32_t)tq * 16, p_last = pos0 + (uint32_t)min(tq * 16 + 15, n - 1);
