@@ -144,6 +144,10 @@ nnc_status nnc_decode_step(nnc_model *m, const uint32_t *slots, const int32_t *t
  * synchronisation between steps.  tokens_out: device [n_steps, batch] int32, the
  * token produced by each step.  logits_out: device [n_steps, batch, vocab] floats
  * or NULL.  NNC_E_KV_FULL if any slot would exceed max_seq during the run.
+ * A run of two to four sequences that the resident kernel takes (NNC_OPT_PERSISTENT; its choice looks at the
+ * contexts at the end of the run) computes what the same steps by nnc_decode_step compute, to fp32 rounding
+ * but not bit for bit: those run one kernel per stage, and a value that is cached may round the other way
+ * in its last bit.  With NNC_OPT_PERSISTENT 0 a run gives the same bits however it is cut into calls.
  */
 nnc_status nnc_decode_greedy(nnc_model *m, const uint32_t *slots, const int32_t *first_tokens,
                              uint32_t batch, uint32_t n_steps, int32_t *tokens_out,
@@ -227,7 +231,8 @@ typedef enum {
                                1: 21-token chunks through the decode kernels, three bf16 pieces
                                (fp32-grade) */
   NNC_OPT_PERSISTENT = 2,   /* 1 (default): batch-1 decode steps of 16-bit models, and nnc_decode_greedy
-                               runs of two to four sequences of the smaller shapes, run in one
+                               runs of two to four sequences of the smaller shapes (hidden sizes up to
+                               1024, two sequences up to 2048) whose contexts are not too long, run in one
                                resident kernel per call (all steps of nnc_decode_greedy in a
                                single launch); 0: one kernel per stage.
                                That kernel takes every compute unit, and its workgroups wait for each
@@ -240,10 +245,13 @@ typedef enum {
   NNC_OPT_PREFILL_TILE = 4, /* block tile of the large-block prompt GEMMs: -1 (default) chosen from
                                each launch's size; 0: 64 x 128, 1: 256 x 128, 2: 128 x 128, 3: 64 x 64,
                                4: 192 x 128, 5: 256 x 256, 6: 192 x 256 (rows x operand columns).  Same k order per output
-                               element in all, hence bit-identical results, except where the k range of
+                               element in all of 0 .. 6, hence bit-identical results, except where the k range of
                                a narrow (residual) projection is split over several workgroups (partial
                                sums added in a fixed order): with a forced tile only the 64-row tiles do
-                               that by themselves, for short blocks; see NNC_OPT_PREFILL_KSLICES */
+                               that by themselves, for short blocks; see NNC_OPT_PREFILL_KSLICES.
+                               With -1 and NNC_OPT_PLANNER 1, blocks of up to 512 tokens (the smaller the
+                               hidden size, the longer) run through kernels of their own, which sum k in
+                               another order: two pieces as well, equal to the tiles' to rounding */
   NNC_OPT_PREFILL_KSLICES = 13, /* with a forced NNC_OPT_PREFILL_TILE: k slices (1 .. 4) of the output and
                                down projections of a large prompt block, 0 (default): by the rule above.
                                Without a forced tile the tile model picks tile and slices together */
@@ -268,8 +276,10 @@ typedef enum {
                                largest block tile; the blocking does not change which inputs are rounded
                                (every block of more than 512 tokens carries one bf16 piece) */
   NNC_OPT_PLANNER = 10,     /* 1 (default): block tiles, row tiles per workgroup and k slices of the GEMM
-                               launches come from the analytic model behind nnc_plan_*_query; 0: from the
-                               hand-written rules that preceded it (kept for comparison) */
+                               launches come from the analytic model behind nnc_plan_*_query, and short
+                               prompt blocks have kernels of their own (see NNC_OPT_PREFILL_TILE and
+                               NNC_OPT_PREFILL_ATTN); 0: from the hand-written rules that preceded it, the
+                               block tiles at every length (kept for comparison) */
   NNC_OPT_FUSE_NORM = 11,   /* 1: in per-stage decode passes the RMSNorm after an output / down
                                projection runs in the tail of that GEMM launch (its last workgroups to
                                finish wait for the others, one per sequence, and norm the rows): two

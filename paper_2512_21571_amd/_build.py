@@ -20,7 +20,8 @@ HIPCC_FLAGS = [
     # the direct-to-LDS copies set m0 inside inline assembly and list it as clobbered
     "-Wno-inline-asm",
     # k_gemm_prefill_big keeps its accumulators in accumulation registers it names itself in inline
-    # assembly: the compiler must never park values of its own there (it would, as a cheaper spill)
+    # assembly: the compiler must never park values of its own there (it would, as a cheaper spill).
+    # nnc_decode_mk.hip needs the flag too: its spilled scalars came back wrong from accumulation registers
     "-mllvm", "-amdgpu-spill-vgpr-to-agpr=0",
 ]
 

@@ -1154,17 +1154,17 @@ static nnc_status prefill_head(nnc_model* m, uint32_t n, int pending, float* log
 // Whether a block of n tokens runs through the kernels of nnc_small.hip.  They save three kernels per
 // layer but re-read the weights from L2 once per 32 - 64 operand columns, which costs more than that from
 // n * H^2 = 2^29 on, in binary16 (which keeps its norm kernels) 2^28.  Measured, us per layer, block tiles /
-// short-block kernels: 0.6B 55.5 / 44.1 at 128 tokens, 96.6 / 90.1 at 512; 1.7B 92.8 / 87.8 at 128, 99.9 / 102.0 at
-// 144, 117.5 / 119.5 at 256; 4B 116.5 / 104.6 at 33, 120.2 / 118.6 at 79, 131.2 / 145.2 at 112; binary16: 0.6B 70.7 / 63.3
-// at 256, 80.5 / 79.5 at 288; 1.7B 78.3 / 73.4 at 64, 88.1 / 91.2 at 79; 4B 117.8 / 106.0 at 39, 121.2 / 122.9 at 80.
+// short-block kernels: 0.6B 55.2 / 44.3 at 128 tokens, 96.4 / 90.5 at 512; 1.7B 92.2 / 87.9 at 128, 99.8 / 102.0 at
+// 144, 116.6 / 119.0 at 256; 4B 114.3 / 104.8 at 33, 118.3 / 118.4 at 79, 129.9 / 145.4 at 112; binary16: 0.6B 69.5 / 62.8
+// at 256, 78.6 / 79.1 at 288; 1.7B 77.4 / 73.4 at 64, 86.9 / 90.9 at 79; 4B 115.1 / 106.1 at 39, 119.0 / 123.1 at 80.
 // One row block per head leaves the q|k|v GEMM of the 4096-wide shape on 48 CUs (33 us at 16 tokens, 14 on the block
 // tiles): hidden sizes up to 2560.
 // Byte weights need no widened copy here, so the limit lies further out and depends on how many rounds
 // of workgroups the short GEMMs take; the tile models know that.  A layer takes 1.75 - 2 times the short GEMMs'
 // model time, against the block-tile GEMMs' model time + 25 us + a pass over the weights at 2.4 TB/s.
-// Measured as above: 0.6B 86.9 / 64.2 at 256; 1.7B 144.8 / 123.0 at 256, 166.7 / 168.7 at 300; 4B 209.0 / 189.8 at 192,
-// 219.6 / 228.6 at 208, 227.0 / 241.8 at 256; 8B 286 / 196 at 128, 351 / 306 at 192, 338 / 324 at 208, 370 / 357 and (another
-// card) 344 / 357 at 256, 423 / 424 at 288.
+// Measured as above: 0.6B 86.0 / 63.8 at 256; 1.7B 144.6 / 122.9 at 256, 165.4 / 169.1 at 300; 4B 206.8 / 190.7 at 192,
+// 219.6 / 228.6 at 208, 226.1 / 243.0 at 256; 8B 288 / 197 at 128, 337 / 307 at 192, 338 / 324 at 208, 344 - 370 (three cards) /
+// 357 at 256, 417 / 424 at 288.
 static bool short_block(const nnc_model* m, uint32_t n) {
   if (n > PB_SMALL_TOKENS || m->opt_prefill_exact == 1) return false;
   const double H = m->H();

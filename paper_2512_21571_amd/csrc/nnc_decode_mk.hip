@@ -30,6 +30,11 @@
 // needs every workgroup to own at least one QKV tile per layer, so the grid is
 // min(compute units, QKV tiles).
 //
+// The instances hold more scalars than there are registers for (the compiler reports 280 - 460 spilled ones), kept
+// in lanes of vector registers.  Built without -amdgpu-spill-vgpr-to-agpr=0 those were parked in accumulation
+// registers under a partial execution mask, and once in about a hundred steps a wave of the several-sequence
+// instances went on with a wrong sequence count: this file must not be built without that flag.
+//
 // Weights, gains, the rotary table and cached K/V rows older than the current
 // step are immutable during a launch and use ordinary loads.
 #include <cstring>
@@ -76,7 +81,11 @@ __device__ __forceinline__ void st_t(u64* p, float v, unsigned tag) {
   __hip_atomic_store(p, (u64)__float_as_uint(v) | ((u64)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Two adjacent (value, tag) words in one 16-byte load past the caches (cache policy 16 = sc1, agent
-// scope).  The halves need no common atomicity: each carries its own tag.  Against two 8-byte loads
+// scope).  The halves need no common atomicity: each carries its own tag.  But each half has to arrive whole, which
+// the language promises for an 8-byte atomic load and not for a part of this one.  It does: an aligned half lies
+// in one segment of one cache line, which the request reads at once, and its producer writes it with one 8-byte
+// store.  Checked by 2e10 halves loaded like this while other workgroups kept storing them, 3.9e9 of them
+// changed since the load before: none was torn.  Against two 8-byte loads
 // per pair this halves the requests of every poll: 0.6B 153 -> 149 us per step of 7 layers, 1.7B 300 -> 290.
 // The loads are ordinary to the compiler: a poll loop begins with poll_again().
 struct TWord2 {

@@ -3,7 +3,7 @@
 //
 // Five kernels per layer instead of eight:
 //   q|k|v GEMM + per-head QK norm + rotary embedding + cache append   (k_gemm_small<EPI_QKV>)
-//   attention                                                          (k_attn_prefill)
+//   attention                                    (k_attn_small; k_attn_prefill for larger launches)
 //   output projection + residual + operand of the next GEMM            (k_gemm_small<EPI_RESID>)
 //   gate|up GEMM + SwiGLU                                              (k_gemm_small<EPI_SWIGLU>)
 //   down projection + residual + operand of the next GEMM              (k_gemm_small<EPI_RESID>)
@@ -618,7 +618,10 @@ __global__ __launch_bounds__(256) void k_attn_small(const float* __restrict__ qk
 // workgroup per CU holds the launch, first with one head each, then with two.  Beyond, the fragment loads
 // of the extra workgroups cost more than the shorter chains save.  us per launch, k_attn_prefill / one
 // head / two heads: 16 heads, 128 tokens 7.9 / 5.3 / 7.0; 256 10.6 / 7.4 / 9.1; 333 12.1 / 13.6 / 10.2; 512 16.9 / 19 / 13;
-// 32 heads, 128 tokens 7.2 / 5.4 / 7.2; 256 11.4 / 12.6 / 10.0; 333 13.4 / 18.7 / 17.7.
+// 32 heads, 128 tokens 7.2 / 5.4 / 7.2; 256 11.4 / 12.6 / 10.0; 333 13.4 / 18.7 / 17.7.  The line does not move with the
+// position the block starts at (timed by events, which add 2 us): at 256, 1024 and 4000 earlier positions 16
+// heads, 128 tokens 16.2 / 11.4 / 13.4, 34.0 / 21.7 / 23.5, 132 / 63 / 65; 400 tokens 22.3 / 24.3 / 18.2, 40.5 / 45.1 / 28.7,
+// 137 / 128 / 72; 32 heads, 256 tokens 20.7 / 21.5 / 15.8, 44.2 / 43.1 / 27.8, 138 / 131 / 74.
 int attn_small_heads(int nq, int nkv, int n, int n_cus) {
   const int tt = (n + 15) / 16;
   if (tt * nq <= n_cus) return 1;

@@ -90,3 +90,12 @@ def test_null_model_arguments(nnc):
     assert L.nnc_decode_step(None, None, None, 1, None, None) == nnc.E_ARG
     assert L.nnc_profile_begin(None) == nnc.E_ARG
     L.nnc_model_destroy(None)
+
+
+def test_every_source_is_built_with_the_flags_it_relies_on():
+    """One list for all sources: no packed fp32 instructions, and no spills into accumulation registers, which the
+    256 x 256 prompt tile owns and from which the resident decode kernel's spilled scalars came back wrong."""
+    from paper_2512_21571_amd._build import HIPCC_FLAGS as flags
+    pairs = list(zip(flags, flags[1:]))
+    assert ("-mllvm", "-amdgpu-spill-vgpr-to-agpr=0") in pairs
+    assert ("-Xclang", "-packed-fp32-ops") in pairs
