@@ -269,7 +269,7 @@ struct MkPlan {
   int tok0[MK_MAX_SEQ];                        // tokens fed to the first step
   uint32_t pos0[MK_MAX_SEQ], slot[MK_MAX_SEQ];  // their positions and KV slots
   int n_steps;
-  unsigned tag_base;    // first exchange tag of this launch (tags must never repeat)
+  unsigned tag_base;    // first exchange tag of this launch (no tag may repeat while the buffers may hold a word under it)
   int ks_o, ks_d;       // k slices of the output / down projections
   int off_att, off_o, off_d;  // first workgroup of the attention / output / down projection units
   unsigned spin_max;    // polls of one wait before the launch gives up (0 = default)

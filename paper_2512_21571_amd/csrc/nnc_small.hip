@@ -2,11 +2,11 @@
 // bound by latency and by what one CU pulls out of L2, not by the matrix cores.
 //
 // Five kernels per layer instead of eight:
-//   q|k|v GEMM + per-head QK norm + rotary embedding + cache append   (k_gemm_small<EPI_QKV>)
+//   q|k|v GEMM + per-head QK norm + rotary embedding + cache append   (k_gemm_small<SEPI_QKV>)
 //   attention                                    (k_attn_small; k_attn_prefill for larger launches)
-//   output projection + residual + operand of the next GEMM            (k_gemm_small<EPI_RESID>)
-//   gate|up GEMM + SwiGLU                                              (k_gemm_small<EPI_SWIGLU>)
-//   down projection + residual + operand of the next GEMM              (k_gemm_small<EPI_RESID>)
+//   output projection + residual + operand of the next GEMM            (k_gemm_small<SEPI_RESID>)
+//   gate|up GEMM + SwiGLU                                              (k_gemm_small<SEPI_SWIGLU>)
+//   down projection + residual + operand of the next GEMM              (k_gemm_small<SEPI_RESID>)
 // The RMSNorm between a residual projection and the GEMM it feeds needs no kernel: the projection's
 // epilogue writes gain * x as the next operand and, per row block and token, the sum of x^2; the
 // next GEMM multiplies its outputs by 1 / rms, which is exact because the matmul is linear.
