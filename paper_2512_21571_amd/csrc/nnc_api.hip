@@ -1014,10 +1014,16 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
       const size_t ns = m->mk_seqs;
       TRY_OR_BAIL(zeroed(m->mk_xq, ns * (Dq + 2 * Dkv) * 8));
       TRY_OR_BAIL(zeroed(m->mk_xatt, ns * c.n_q_heads * m->max_chunks * 132 * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xo, ns * Dq * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xop, ns * 4 * H * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xact, ns * F * 8));
-      TRY_OR_BAIL(zeroed(m->mk_xdp, ns * 4 * H * 8));
+      // (the untagged ones start empty, and every launch leaves them so)
+      auto emptied = [&](void*& ptr, size_t words) -> hipError_t {
+        ptr = dev_alloc(m, words * 4);
+        return ptr ? hipMemsetAsync(ptr, 0xff, words * 4, s) : hipErrorOutOfMemory;
+      };
+      const MkExchangeWords xw = mk_exchange_words(ns, Dq, F, H);
+      TRY_OR_BAIL(emptied(m->mk_xo, xw.xo));
+      TRY_OR_BAIL(emptied(m->mk_xop, xw.xop));
+      TRY_OR_BAIL(emptied(m->mk_xact, xw.xact));
+      TRY_OR_BAIL(emptied(m->mk_xdp, xw.xdp));
       TRY_OR_BAIL(zeroed(m->mk_xamv, ns * m->mk_nwg * 8));
       TRY_OR_BAIL(zeroed(m->mk_xami, ns * m->mk_nwg * 8));
       void* tr = nullptr;

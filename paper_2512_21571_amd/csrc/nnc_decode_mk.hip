@@ -11,11 +11,12 @@
 //
 //   * every stage is statically partitioned over the workgroups;
 //   * there are no grid barriers.  Whatever one workgroup produces for others is
-//     written as 64-bit words (fp32 value, 32-bit tag) with relaxed agent-scope
-//     atomic stores, which go to the memory side past the per-XCD L2s; the tag
-//     names the (step, layer, stage) that produced it.  A consumer simply loads
-//     the words it needs (relaxed agent-scope atomic loads) and repeats until
-//     every tag is the one it expects.  Synchronisation and data transfer are
+//     written with relaxed agent-scope atomic stores, which go to the memory side past
+//     the per-XCD L2s: as 64-bit words (fp32 value, 32-bit tag), the tag naming the (step,
+//     layer, stage) that produced it, or, where many workgroups read the whole vector, as
+//     32-bit words into a buffer known to be empty (Word4 below).  A consumer simply loads
+//     the words it needs (relaxed agent-scope loads) and repeats until
+//     every tag is the one it expects and no word is empty.  Synchronisation and data transfer are
 //     one and the same memory round trip (~1.7 us for an all-to-all of a hidden
 //     vector among 256 workgroups, measured), and no cache write-back or
 //     invalidate is ever issued (those cost ~10 us each on this part);
@@ -24,7 +25,7 @@
 //   * the residual stream never goes through memory: every workgroup keeps its own
 //     copy in registers and adds the exchanged projection outputs to it.
 //
-// Why a producer may overwrite an exchange buffer without asking: each buffer is
+// Why a producer may overwrite a tagged buffer without asking: each buffer is
 // rewritten one layer later at the same stage, and before that can happen its
 // readers have produced something the writer (transitively) waited for.  This
 // needs every workgroup to own at least one QKV tile per layer, so the grid is
@@ -100,6 +101,44 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t t_buffer(const u64* p, int wor
 __device__ __forceinline__ TWord2 ld_t2(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
   return TWord2{__builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 16)};
 }
+// Words without a tag.  The vectors that many workgroups read whole (residual partials, activations, merged
+// attention output) are plain fp32 words: a word that holds MK_EMPTY has not been written yet (the one NaN with
+// these bits is published as another), and one 16-byte load takes four of them.  Half the bytes of a tagged word,
+// past the caches, by every workgroup, on every poll.  Each vector rotates through MK_ROT buffers,
+// one per layer; a workgroup empties its own words of the next buffer before it waits for the operand of the
+// unit that will write the current one, and publishes only after those stores are acknowledged.
+//   * Nobody still reads the buffer being emptied: it was written two layers ago (layer l - 2).  A workgroup that
+//     empties it has consumed the down projections of layer l - 1; those waited for activations whose
+//     producers consumed every output-projection word of l - 1, thus all heads, thus every workgroup's QKV
+//     tile of l - 1 (each workgroup owns one), which comes after its reads of layer l - 2.
+//   * Nobody polls it before it is empty: who polls for layer l + 1 has, through the same chain, consumed
+//     what this workgroup published for layer l.
+// A launch leaves all buffers empty: it clears its words after the last token exchange, when every
+// workgroup has read everything.  Measured against (value, tag) words, us per layer: 0.6B at 128 positions 18.3 -> 17.8 (one
+// sequence), 33.5 -> 29.1 (four); 1.7B at 512 35.2 -> 33.1; 8B at 512 93.0 -> 89.8.
+constexpr unsigned MK_EMPTY = 0xffffffffu;
+constexpr int MK_ROT = 3;
+struct Word4 {
+  u32x4 v;
+  __device__ __forceinline__ bool ok() const { return v[0] != MK_EMPTY && v[1] != MK_EMPTY && v[2] != MK_EMPTY && v[3] != MK_EMPTY; }
+  __device__ __forceinline__ float4 val() const {
+    return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+  }
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t w_buffer(const float* p, int words) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, words * 4, 0x00020000);
+}
+// words i .. i + 3 (i a multiple of four) at `voff` bytes per lane + `soff` bytes (scalar)
+__device__ __forceinline__ Word4 ld_w4(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  return Word4{__builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 16)};
+}
+__device__ __forceinline__ void st_w(float* p, float v) {
+  const unsigned b = __float_as_uint(v);
+  st_u32(reinterpret_cast<unsigned*>(p), b == MK_EMPTY ? 0x7fc00000u : b);
+}
+__device__ __forceinline__ void st_empty(float* p) { st_u32(reinterpret_cast<unsigned*>(p), MK_EMPTY); }
+// every memory operation of this wave so far is complete
+__device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0), the other counters left alone
 // keeps the loads of one poll from being merged with or moved across those of another
 __device__ __forceinline__ void poll_again() { asm volatile("" ::: "memory"); }
 __device__ __forceinline__ float t_val(u64 w) { return __uint_as_float((unsigned)w); }
@@ -155,10 +194,12 @@ struct MkArgs {
   u64* xq;    // [nseq][Dq + 2 Dkv] raw q | k | v
   u64* xatt;  // [nseq][nq][max_chunks][132] attention partials: 128 sums, max, sum
   int max_chunks;
-  u64* xo;    // [nseq][Dq] merged attention output (one sequence: only when the context spans many chunks)
-  u64* xop;   // [ks_o][nseq][H]
-  u64* xact;  // [nseq][F]
-  u64* xdp;   // [ks_d][nseq][H]
+  // words without a tag, MK_ROT buffers each, `s_...` words apart
+  float* xo;    // [nseq][Dq] merged attention output (one sequence: only when the context spans many chunks)
+  float* xop;   // [ks_o][nseq][H]
+  float* xact;  // [nseq][F]
+  float* xdp;   // [ks_d][nseq][H]
+  int s_o, s_op, s_act, s_dp;
   u64* xamv;  // [nseq][workgroups] best logit
   u64* xami;  // [nseq][workgroups] its index
   float* logits;       // [n_steps][nseq][V] or NULL
@@ -215,6 +256,23 @@ __device__ __forceinline__ void put_pair(uint4* opnd, int b, int k, float2 v) {
     base[s * 4] = bx | (by << 16);
     rx -= HF::widen(bx);
     ry -= HF::widen(by);
+  }
+}
+
+// the same for the four activations k .. k + 3 (k a multiple of four)
+template <class HF, int NS>
+__device__ __forceinline__ void put_quad(uint4* opnd, int b, int k, float4 v) {
+  float r[4] = {v.x, v.y, v.z, v.w};
+  uint2* base = reinterpret_cast<uint2*>(opnd + (size_t)(k >> 3) * mk_cols(NS) + 3 * b) + ((k & 7) >> 2);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    uint32_t bt[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      bt[e] = HF::bits(r[e]);
+      r[e] -= HF::widen(bt[e]);
+    }
+    base[s * 2] = make_uint2(bt[0] | (bt[1] << 16), bt[2] | (bt[3] << 16));
   }
 }
 
@@ -308,35 +366,35 @@ __device__ __forceinline__ float tile_total(const Smem& sm, int rt, int row, int
   return v;
 }
 
-// x[b][j] += sum over `ks` slices of the exchanged vectors `buf` ([ks][ns][H] tagged words), for
-// the pairs k = 2 * (tid + MK_THREADS * j) this thread owns.  Loads are repeated until
-// every word carries `tag`; the words of all sequences are in flight together.
+// x[b][j] += sum over `ks` slices of the exchanged vectors `buf` ([ks][ns][H] words), for
+// the quads k = 4 * (tid + MK_THREADS * j) this thread owns.  Loads are repeated until
+// every word is there; the words of all sequences are in flight together.
 // Most k slices an instance adds up (several sequences: their words share the registers).
 constexpr int mk_max_ks(int ns) { return ns == 1 ? MK_MAX_KS : 3; }
 
-template <int NP, int NS>
-__device__ __forceinline__ void add_exchanged(const MkArgs& a, Smem& sm, float2 (&x)[NS][NP], int H, const u64* buf, int ks,
-                                              int ns, unsigned tag) {
-  constexpr int JM = NS > 1 ? 2 : 4;
+template <int NQ, int NS>
+__device__ __forceinline__ void add_exchanged(const MkArgs& a, Smem& sm, float4 (&x)[NS][NQ], int H, const float* buf, int ks,
+                                              int ns) {
+  constexpr int JM = NS > 1 ? 1 : 2;
   constexpr int KS = mk_max_ks(NS);
-  constexpr int JB = NP < JM ? NP : JM;  // pairs per thread and sequence whose words are in flight together
+  constexpr int JB = NQ < JM ? NQ : JM;  // quads per thread and sequence whose words are in flight together
   const int tid = opaque(threadIdx.x);
-  const __amdgpu_buffer_rsrc_t rs = t_buffer(buf, ks * ns * H);
+  const __amdgpu_buffer_rsrc_t rs = w_buffer(buf, ks * ns * H);
 #pragma unroll
-  for (int j0 = 0; j0 < NP; j0 += JB) {
+  for (int j0 = 0; j0 < NQ; j0 += JB) {
     unsigned spins = 0;
     for (;;) {
       poll_again();
-      TWord2 w[NS][JB][KS];
+      Word4 w[NS][JB][KS];
 #pragma unroll
       for (int b = 0; b < NS; ++b)
         if (NS == 1 || b < ns) {
 #pragma unroll
           for (int j = 0; j < JB; ++j)
-            if (2 * (tid + MK_THREADS * (j0 + j)) < H) {
+            if (4 * (tid + MK_THREADS * (j0 + j)) < H) {
 #pragma unroll
               for (int p = 0; p < KS; ++p)
-                if (p < ks) w[b][j][p] = ld_t2(rs, tid * 16, ((p * ns + b) * H + 2 * MK_THREADS * (j0 + j)) * 8);
+                if (p < ks) w[b][j][p] = ld_w4(rs, tid * 16, ((p * ns + b) * H + 4 * MK_THREADS * (j0 + j)) * 4);
             }
         }
       bool ok = true;
@@ -345,10 +403,10 @@ __device__ __forceinline__ void add_exchanged(const MkArgs& a, Smem& sm, float2 
         if (NS == 1 || b < ns) {
 #pragma unroll
           for (int j = 0; j < JB; ++j)
-            if (2 * ((int)threadIdx.x + MK_THREADS * (j0 + j)) < H) {
+            if (4 * ((int)threadIdx.x + MK_THREADS * (j0 + j)) < H) {
 #pragma unroll
               for (int p = 0; p < KS; ++p)
-                if (p < ks) ok = ok && w[b][j][p].ok(tag);
+                if (p < ks) ok = ok && w[b][j][p].ok();
             }
         }
       if (ok) {
@@ -357,17 +415,16 @@ __device__ __forceinline__ void add_exchanged(const MkArgs& a, Smem& sm, float2 
           if (NS == 1 || b < ns) {
 #pragma unroll
             for (int j = 0; j < JB; ++j)
-              if (2 * ((int)threadIdx.x + MK_THREADS * (j0 + j)) < H) {
-                float2 add = w[b][j][0].val();
+              if (4 * ((int)threadIdx.x + MK_THREADS * (j0 + j)) < H) {
+                float4 add = w[b][j][0].val();
 #pragma unroll
                 for (int p = 1; p < KS; ++p)
                   if (p < ks) {
-                    const float2 v = w[b][j][p].val();
-                    add.x += v.x;
-                    add.y += v.y;
+                    const float4 v = w[b][j][p].val();
+                    add = make_float4(add.x + v.x, add.y + v.y, add.z + v.z, add.w + v.w);
                   }
-                x[b][j0 + j].x += add.x;
-                x[b][j0 + j].y += add.y;
+                float4& xx = x[b][j0 + j];
+                xx = make_float4(xx.x + add.x, xx.y + add.y, xx.z + add.z, xx.w + add.w);
               }
           }
         break;
@@ -380,41 +437,41 @@ __device__ __forceinline__ void add_exchanged(const MkArgs& a, Smem& sm, float2 
   }
 }
 
-// An exchanged vector per sequence (src + b * stride, k in [k0, k1)) -> the packed operand: four (k, k+1)
-// pairs per thread and sequence at a time, loaded together, repeated until every word carries `tag`.
+// An exchanged vector per sequence (src + b * stride, k in [k0, k1), multiples of four) -> the packed operand: two
+// quads per thread and sequence at a time, loaded together, repeated until every word is there.
 template <int NS, class HF>
-__device__ __forceinline__ void load_operand(const MkArgs& a, Smem& sm, uint4* opnd, const u64* src, size_t stride, int k0,
-                                             int k1, int ns, unsigned tag) {
+__device__ __forceinline__ void load_operand(const MkArgs& a, Smem& sm, uint4* opnd, const float* src, int stride, int k0,
+                                             int k1, int ns) {
   const int tid = threadIdx.x;
-  const __amdgpu_buffer_rsrc_t rs = t_buffer(src, (int)stride * ns);
-  for (int kb = k0 + 2 * tid; kb < k1; kb += 8 * MK_THREADS) {
+  const __amdgpu_buffer_rsrc_t rs = w_buffer(src, stride * ns);
+  for (int kb = k0 + 4 * tid; kb < k1; kb += 8 * MK_THREADS) {
     unsigned spins = 0;
     for (;;) {
       poll_again();
-      TWord2 w[NS][4];
+      Word4 w[NS][2];
       bool ok = true;
 #pragma unroll
       for (int b = 0; b < NS; ++b)
         if (NS == 1 || b < ns) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (kb + 2 * MK_THREADS * j < k1) w[b][j] = ld_t2(rs, kb * 8, (b * (int)stride + 2 * MK_THREADS * j) * 8);
+          for (int j = 0; j < 2; ++j)
+            if (kb + 4 * MK_THREADS * j < k1) w[b][j] = ld_w4(rs, kb * 4, (b * stride + 4 * MK_THREADS * j) * 4);
         }
 #pragma unroll
       for (int b = 0; b < NS; ++b)
         if (NS == 1 || b < ns) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (kb + 2 * MK_THREADS * j < k1) ok = ok && w[b][j].ok(tag);
+          for (int j = 0; j < 2; ++j)
+            if (kb + 4 * MK_THREADS * j < k1) ok = ok && w[b][j].ok();
         }
       if (ok) {
 #pragma unroll
         for (int b = 0; b < NS; ++b)
           if (NS == 1 || b < ns) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int k = kb + 2 * MK_THREADS * j;
-              if (k < k1) put_pair<HF, NS>(opnd, b, k - k0, w[b][j].val());
+            for (int j = 0; j < 2; ++j) {
+              const int k = kb + 4 * MK_THREADS * j;
+              if (k < k1) put_quad<HF, NS>(opnd, b, k - k0, w[b][j].val());
             }
           }
         break;
@@ -427,18 +484,18 @@ __device__ __forceinline__ void load_operand(const MkArgs& a, Smem& sm, uint4* o
   }
 }
 
-// Row r of the packed embedding matrix, pairs owned by this thread.
-template <int NP, class HF>
-__device__ __forceinline__ void gather_embed(float2 (&x)[NP], int H, const uint4* embed, int r) {
+// Row r of the packed embedding matrix, quads owned by this thread.
+template <int NQ, class HF>
+__device__ __forceinline__ void gather_embed(float4 (&x)[NQ], int H, const uint4* embed, int r) {
   const int KTH = H / 32;
 #pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    const int k = 2 * ((int)threadIdx.x + MK_THREADS * j);
-    x[j] = make_float2(0.f, 0.f);
+  for (int j = 0; j < NQ; ++j) {
+    const int k = 4 * ((int)threadIdx.x + MK_THREADS * j);
+    x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (k < H) {
       const size_t e = (((size_t)(r >> 4) * KTH + (k >> 5)) * 64 + (r & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
-      const uint32_t two = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint16_t*>(embed) + e);
-      x[j] = make_float2(HF::lo(two), HF::hi(two));
+      const uint2 w = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(embed) + e);
+      x[j] = make_float4(HF::lo(w.x), HF::hi(w.x), HF::lo(w.y), HF::hi(w.y));
     }
   }
 }
@@ -447,14 +504,14 @@ __device__ __forceinline__ void gather_embed(float2 (&x)[NP], int H, const uint4
 // x * gain (not yet divided by the root mean square); each wave leaves its sum of squares in
 // sm.wsum, and the GEMM epilogues multiply their outputs by rms_scale(), which is exact
 // because the matmul is linear.  Caller synchronises before the GEMM as it must anyway.
-// Gains of the pairs this thread owns.  Loaded before the wait for the exchanged vector, so
+// Gains of the quads this thread owns.  Loaded before the wait for the exchanged vector, so
 // that their latency (an L2 hit, ~0.7 us) overlaps with it instead of following it.
-template <int NP>
-__device__ __forceinline__ void load_gain(float2 (&gg)[NP], int H, const float* gain) {
+template <int NQ>
+__device__ __forceinline__ void load_gain(float4 (&gg)[NQ], int H, const float* gain) {
 #pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    const int k = 2 * ((int)threadIdx.x + MK_THREADS * j);
-    gg[j] = k < H ? *reinterpret_cast<const float2*>(gain + k) : make_float2(0.f, 0.f);
+  for (int j = 0; j < NQ; ++j) {
+    const int k = 4 * ((int)threadIdx.x + MK_THREADS * j);
+    gg[j] = k < H ? *reinterpret_cast<const float4*>(gain + k) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 }
 
@@ -469,15 +526,16 @@ __device__ __forceinline__ float rms_from_sums(const Smem& sm, int b, int H, flo
 // A format with a narrow exponent range (binary16) cannot split an un-normalised row of small
 // magnitude into pieces without losing bits, so there the row is normalised first (one more
 // workgroup barrier) and the epilogues multiply by one.
-template <int NP, int NS, class HF>
-__device__ __forceinline__ void norm_pack(Smem& sm, uint4* opnd, int H, float eps, int ns, const float2 (&x)[NS][NP],
-                                          const float2 (&gg)[NP]) {
+template <int NQ, int NS, class HF>
+__device__ __forceinline__ void norm_pack(Smem& sm, uint4* opnd, int H, float eps, int ns, const float4 (&x)[NS][NQ],
+                                          const float4 (&gg)[NQ]) {
 #pragma unroll
   for (int b = 0; b < NS; ++b)
     if (NS == 1 || b < ns) {
       float ss = 0.f;
 #pragma unroll
-      for (int j = 0; j < NP; ++j) ss += x[b][j].x * x[b][j].x + x[b][j].y * x[b][j].y;  // unowned pairs are zero
+      for (int j = 0; j < NQ; ++j)  // unowned quads are zero
+        ss += (x[b][j].x * x[b][j].x + x[b][j].y * x[b][j].y) + (x[b][j].z * x[b][j].z + x[b][j].w * x[b][j].w);
       ss = wave_sum(ss);
       if ((threadIdx.x & 63) == 0) sm.wsum[b][threadIdx.x >> 6] = ss;
     }
@@ -488,9 +546,11 @@ __device__ __forceinline__ void norm_pack(Smem& sm, uint4* opnd, int H, float ep
       float r = 1.0f;
       if constexpr (HF::kNarrowRange) r = rms_from_sums(sm, b, H, eps);
 #pragma unroll
-      for (int j = 0; j < NP; ++j) {
-        const int k = 2 * ((int)threadIdx.x + MK_THREADS * j);
-        if (k < H) put_pair<HF, NS>(opnd, b, k, make_float2(x[b][j].x * gg[j].x * r, x[b][j].y * gg[j].y * r));
+      for (int j = 0; j < NQ; ++j) {
+        const int k = 4 * ((int)threadIdx.x + MK_THREADS * j);
+        if (k < H)
+          put_quad<HF, NS>(opnd, b, k, make_float4(x[b][j].x * gg[j].x * r, x[b][j].y * gg[j].y * r, x[b][j].z * gg[j].z * r,
+                                                   x[b][j].w * gg[j].w * r));
       }
     }
 }
@@ -504,10 +564,10 @@ __device__ __forceinline__ float rms_scale(const Smem& sm, int b, int H, float e
 
 }  // namespace
 
-// NP = (k, k+1) pairs of a hidden-state row per thread: hidden <= 2 * MK_THREADS * NP.
+// NQ = quads (k .. k + 3) of a hidden-state row per thread: hidden <= 4 * MK_THREADS * NQ.
 // NS = most sequences the instance decodes together (their 3 NS operand columns fit the 16 the matrix
 // cores multiply anyway): the exchanges and weights of a step then serve all of them.
-template <int NP, int NS, class HF>
+template <int NQ, int NS, class HF>
 __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
   extern __shared__ uint4 opnd[];  // packed activation operand of the current GEMM stage
   __shared__ Smem sm;
@@ -552,7 +612,8 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
   Pf<2> pf4;
   if (wg < qkv_tiles) pf_issue<1>(pf1, a.layers[0].wqkv, (size_t)wg, KTH, 0, KTH);
 
-  float2 x[NS][NP];  // this workgroup's copy of the residual streams (pairs owned by the thread)
+  float4 x[NS][NQ];  // this workgroup's copy of the residual streams (quads owned by the thread)
+  int rot = 0;       // buffer of this layer's untagged vectors
   int tok[NS];
 #pragma unroll
   for (int b = 0; b < NS; ++b) tok[b] = a.tok0[b];
@@ -561,20 +622,21 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
     const unsigned t_step = a.tag_base + (unsigned)step * tags_per_step;
     for (int li = 0; li < a.n_layers; ++li) {
       const MkLayer L = a.layers[li];
-      const unsigned t_q = t_step + 5u * li, t_att = t_q + 1, t_op = t_q + 2, t_act = t_q + 3, t_dp = t_q + 4;
+      const unsigned t_q = t_step + 5u * li, t_att = t_q + 1;
+      const int rot_next = rot == MK_ROT - 1 ? 0 : rot + 1, rot_prev = rot == 0 ? MK_ROT - 1 : rot - 1;
       stamp(step);  // 0: layer start
 
       // ============ stage 1: residual update + input norm + QKV projection ============
-      float2 gg[NP];
-      load_gain<NP>(gg, H, L.g_in);
+      float4 gg[NQ];
+      load_gain<NQ>(gg, H, L.g_in);
       if (li == 0) {
 #pragma unroll
         for (int b = 0; b < NS; ++b)
-          if (NS == 1 || b < ns) gather_embed<NP, HF>(x[b], H, a.embed, tok[b]);
+          if (NS == 1 || b < ns) gather_embed<NQ, HF>(x[b], H, a.embed, tok[b]);
       } else {
-        add_exchanged<NP, NS>(a, sm, x, H, a.xdp, a.ks_d, ns, t_dp - 5u);
+        add_exchanged<NQ, NS>(a, sm, x, H, a.xdp + rot_prev * a.s_dp, a.ks_d, ns);
       }
-      norm_pack<NP, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
+      norm_pack<NQ, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
       wg_sync();
       if (sm.abort) return;
       stamp(step);  // 1: operand ready
@@ -830,7 +892,16 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       // (Several sequences always take that exchange: the direct merge reads every record of every
       // sequence in every output-projection unit.)
       const bool merged = NS > 1 || chunks[0] > MK_DIRECT_MERGE_MAX;
+      float* const xo = a.xo + rot * a.s_o;
+      float* const xop = a.xop + rot * a.s_op;
+      if (epi_on)
+        for (int u = wg_o; u < o_units; u += nwg) {
+          const int t = u / a.ks_o, s = u % a.ks_o;
+          st_empty(a.xop + rot_next * a.s_op + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row);
+        }
       if (merged) {
+        if (tid < 128)
+          for (int h = nwg - 1 - wg_att; h < ns * nq; h += nwg) st_empty(a.xo + rot_next * a.s_o + (size_t)h * 128 + tid);
         for (int h = nwg - 1 - wg_att; h < ns * nq; h += nwg) {  // h = sequence * query heads + head
           int nch = chunks[0];
 #pragma unroll
@@ -899,7 +970,8 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
               num += f * sm.mrg[w][tid];
               dn += f * sm.att_l[w];
             }
-            st_t(a.xo + (size_t)h * 128 + tid, num / dn, t_att);
+            wait_stores();  // (this thread's empty words, stored before the chunk records came in)
+            st_w(xo + (size_t)h * 128 + tid, num / dn);
           }
         }
       }
@@ -913,7 +985,7 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         if (s == s_loaded) {
           // operand already in LDS
         } else if (merged) {
-          load_operand<NS, HF>(a, sm, opnd, a.xo, (size_t)Dq, kt0 * 32, kt1 * 32, ns, t_att);
+          load_operand<NS, HF>(a, sm, opnd, xo, Dq, kt0 * 32, kt1 * 32, ns);
         } else if constexpr (NS == 1) {
           const int nch = chunks[0];
           const __amdgpu_buffer_rsrc_t ratt = t_buffer(a.xatt, nq * a.max_chunks * 132);
@@ -996,15 +1068,20 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         else
           gemm_unit<1, false, NS, HF>(sm, L.wo, (size_t)t, KTQ, kt0, kt1, pf3, opnd, kt0);
         wg_sync();
-        if (epi_on)
-          st_t(a.xop + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row, tile_total(sm, 0, epi_row, epi_seq), t_op);
+        if (epi_on) {
+          if (u == wg_o) wait_stores();
+          st_w(xop + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row, tile_total(sm, 0, epi_row, epi_seq));
+        }
       }
       stamp(step);  // 4: attention block output published
 
       // ============ stage 4: residual update + post-attention norm + gate/up + SwiGLU ============
-      load_gain<NP>(gg, H, L.g_post);
-      add_exchanged<NP, NS>(a, sm, x, H, a.xop, a.ks_o, ns, t_op);
-      norm_pack<NP, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
+      load_gain<NQ>(gg, H, L.g_post);
+      float* const xact = a.xact + rot * a.s_act;
+      if (epi_on)
+        for (int pr = wg; pr < gu_pairs; pr += nwg) st_empty(a.xact + rot_next * a.s_act + (size_t)epi_seq * F + pr * 16 + epi_row);
+      add_exchanged<NQ, NS>(a, sm, x, H, xop, a.ks_o, ns);
+      norm_pack<NQ, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
       wg_sync();
       if (sm.abort) return;
       stamp(step);  // 5: operand ready
@@ -1017,7 +1094,8 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         if (epi_on) {
           const float r = rms_scale<HF>(sm, epi_seq, H, a.eps);
           const float gate = tile_total(sm, 0, epi_row, epi_seq) * r, up = tile_total(sm, 1, epi_row, epi_seq) * r;
-          st_t(a.xact + (size_t)epi_seq * F + pr * 16 + epi_row, gate / (1.0f + expf(-gate)) * up, t_act);
+          if (pr == wg) wait_stores();
+          st_w(xact + (size_t)epi_seq * F + pr * 16 + epi_row, gate / (1.0f + expf(-gate)) * up);
         }
         wg_sync();
       }
@@ -1027,12 +1105,18 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       if (wg < qkv_tiles && (li + 1 < a.n_layers || step + 1 < a.n_steps))
         pf_issue<1>(pf1, a.layers[li + 1 < a.n_layers ? li + 1 : 0].wqkv, (size_t)wg, KTH, 0, KTH);
       // ============ stage 5: down projection (k slices) ============
+      float* const xdp = a.xdp + rot * a.s_dp;
+      if (epi_on)
+        for (int u = wg_d; u < d_units; u += nwg) {
+          const int t = u / a.ks_d, s = u % a.ks_d;
+          st_empty(a.xdp + rot_next * a.s_dp + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row);
+        }
       s_loaded = -1;
       for (int u = wg_d; u < d_units; u += nwg) {
         const int t = u / a.ks_d, s = u % a.ks_d;
         const int kt0 = s * kts_d, kt1 = min(KTF, (s + 1) * kts_d);
         wg_sync();
-        if (s != s_loaded) load_operand<NS, HF>(a, sm, opnd, a.xact, (size_t)F, kt0 * 32, kt1 * 32, ns, t_act);
+        if (s != s_loaded) load_operand<NS, HF>(a, sm, opnd, xact, F, kt0 * 32, kt1 * 32, ns);
         s_loaded = s;
         wg_sync();
         if (sm.abort) return;
@@ -1041,19 +1125,22 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         else
           gemm_unit<1, false, NS, HF>(sm, L.wd, (size_t)t, KTF, kt0, kt1, pf5, opnd, kt0);
         wg_sync();
-        if (epi_on)
-          st_t(a.xdp + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row, tile_total(sm, 0, epi_row, epi_seq), t_dp);
+        if (epi_on) {
+          if (u == wg_d) wait_stores();
+          st_w(xdp + ((size_t)s * ns + epi_seq) * H + t * 16 + epi_row, tile_total(sm, 0, epi_row, epi_seq));
+        }
       }
       stamp(step);  // 7: MLP output published
+      rot = rot_next;
     }
 
     // ============ final norm + LM head + arg-max ============
     const unsigned t_am = t_step + tags_per_step - 1u;
     {
-      float2 gg[NP];
-      load_gain<NP>(gg, H, a.g_final);
-      add_exchanged<NP, NS>(a, sm, x, H, a.xdp, a.ks_d, ns, t_am - 1u);
-      norm_pack<NP, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
+      float4 gg[NQ];
+      load_gain<NQ>(gg, H, a.g_final);
+      add_exchanged<NQ, NS>(a, sm, x, H, a.xdp + (rot == 0 ? MK_ROT - 1 : rot - 1) * a.s_dp, a.ks_d, ns);
+      norm_pack<NQ, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
     }
     wg_sync();
     if (sm.abort) return;
@@ -1187,11 +1274,27 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       if (NS == 1 || b < ns) tok[b] = sm.tok[b];
     stamp(step);  // token known
   }
+
+  // all winners are in, so every workgroup has read every vector: leave the untagged words empty
+  for (int r = 0; r < MK_ROT; ++r) {
+    if (tid < 128)
+      for (int h = nwg - 1 - wg_att; h < ns * nq; h += nwg) st_empty(a.xo + r * a.s_o + (size_t)h * 128 + tid);
+    if (!epi_on) continue;
+    for (int u = wg_o; u < o_units; u += nwg)
+      st_empty(a.xop + r * a.s_op + ((size_t)(u % a.ks_o) * ns + epi_seq) * H + u / a.ks_o * 16 + epi_row);
+    for (int pr = wg; pr < gu_pairs; pr += nwg) st_empty(a.xact + r * a.s_act + (size_t)epi_seq * F + pr * 16 + epi_row);
+    for (int u = wg_d; u < d_units; u += nwg)
+      st_empty(a.xdp + r * a.s_dp + ((size_t)(u % a.ks_d) * ns + epi_seq) * H + u / a.ks_d * 16 + epi_row);
+  }
 }
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+MkExchangeWords mk_exchange_words(size_t nseq, size_t Dq, size_t F, size_t H) {
+  return {MK_ROT * nseq * Dq, MK_ROT * nseq * MK_MAX_KS * H, MK_ROT * nseq * F, MK_ROT * nseq * MK_MAX_KS * H};
+}
+
 size_t mk_layer_bytes() { return sizeof(MkLayer); }
 
 void mk_fill_layer(void* dst, const void* wqkv, const void* wo, const void* wgu, const void* wd, const float* g_in,
@@ -1228,24 +1331,24 @@ size_t mk_opnd_bytes(const MkPlan& p) {
 template <class F>
 static bool mk_with_kernel(const MkPlan& p, F&& f) {
   const int ns = mk_instance(p.nseq);
-#define MK_CASE(NP, NS)                                              \
+#define MK_CASE(NQ, NS)                                              \
   do {                                                               \
-    if (p.f16) f(&k_decode_resident<NP, NS, Fp16>);                  \
-    else f(&k_decode_resident<NP, NS, Bf16>);                        \
+    if (p.f16) f(&k_decode_resident<NQ, NS, Fp16>);                  \
+    else f(&k_decode_resident<NQ, NS, Bf16>);                        \
     return true;                                                     \
   } while (0)
   if (p.nseq < 1 || p.nseq > MK_MAX_SEQ) return false;
   const int ks = p.ks_o > p.ks_d ? p.ks_o : p.ks_d;
   if (ks > mk_max_ks(ns)) return false;
   if (ns == 1) {
-    if (p.H <= 1024) MK_CASE(2, 1);
-    if (p.H <= 2048) MK_CASE(4, 1);
-    if (p.H <= 4096) MK_CASE(8, 1);
+    if (p.H <= 1024) MK_CASE(1, 1);
+    if (p.H <= 2048) MK_CASE(2, 1);
+    if (p.H <= 4096) MK_CASE(4, 1);
   } else if (ns == 2) {
-    if (p.H <= 1024) MK_CASE(2, 2);
-    if (p.H <= 2048) MK_CASE(4, 2);
+    if (p.H <= 1024) MK_CASE(1, 2);
+    if (p.H <= 2048) MK_CASE(2, 2);
   } else {
-    if (p.H <= 1024) MK_CASE(2, 4);
+    if (p.H <= 1024) MK_CASE(1, 4);
   }
 #undef MK_CASE
   return false;
@@ -1291,8 +1394,9 @@ hipError_t launch_decode_resident(hipStream_t s, const MkPlan& p, const MkBuffer
   a.ks_o = p.ks_o; a.ks_d = p.ks_d;
   a.off_att = p.off_att % p.nwg; a.off_o = p.off_o % p.nwg; a.off_d = p.off_d % p.nwg;
   a.xq = static_cast<u64*>(bf.xq); a.xatt = static_cast<u64*>(bf.xatt); a.max_chunks = p.max_chunks;
-  a.xo = static_cast<u64*>(bf.xo);
-  a.xop = static_cast<u64*>(bf.xop); a.xact = static_cast<u64*>(bf.xact); a.xdp = static_cast<u64*>(bf.xdp);
+  a.xo = static_cast<float*>(bf.xo);
+  a.xop = static_cast<float*>(bf.xop); a.xact = static_cast<float*>(bf.xact); a.xdp = static_cast<float*>(bf.xdp);
+  a.s_o = p.nseq * p.nq * 128; a.s_op = p.ks_o * p.nseq * p.H; a.s_act = p.nseq * p.F; a.s_dp = p.ks_d * p.nseq * p.H;
   a.xamv = static_cast<u64*>(bf.xamv); a.xami = static_cast<u64*>(bf.xami);
   a.logits = bf.logits; a.token_log = bf.token_log;
   a.trace = bf.trace; a.trace_step = bf.trace_step; a.trace_points = bf.trace_points;

@@ -284,7 +284,9 @@ struct MkBuffers {
   const float2* rope;
   unsigned* error;  // single word, zero-initialised once
   // exchange buffers of 64-bit (value, tag) words, zero-initialised once
-  void *xq, *xatt, *xo, *xop, *xact, *xdp, *xamv, *xami;
+  void *xq, *xatt, *xamv, *xami;
+  // exchange buffers of 32-bit words without a tag (mk_exchange_words), every byte 0xff before the first launch
+  void *xo, *xop, *xact, *xdp;
   float* logits;       // [n_steps][nseq][V] or NULL
   int32_t* token_log;  // [n_steps][nseq]
   unsigned long long* trace;  // [nwg][trace_points] or NULL
@@ -298,6 +300,11 @@ inline int mk_trace_points(int n_layers) { return 8 * n_layers + 3; }
 // exchange tags one decode step consumes
 inline unsigned mk_tags_per_step(int n_layers) { return 5u * (unsigned)n_layers + 1u; }
 
+// 32-bit words of the untagged exchange buffers for launches of up to nseq sequences
+struct MkExchangeWords {
+  size_t xo, xop, xact, xdp;
+};
+MkExchangeWords mk_exchange_words(size_t nseq, size_t Dq, size_t F, size_t H);
 size_t mk_layer_bytes();
 void mk_fill_layer(void* dst, const void* wqkv, const void* wo, const void* wgu, const void* wd, const float* g_in,
                    const float* g_q, const float* g_k, const float* g_post, void* kc, void* vc);

@@ -442,6 +442,29 @@ def test_resident_greedy_on_the_full_grid(nnc, lens, dtype):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
 
 
+@pytest.mark.parametrize("shape", [SMALL_BF16, FULL_GRID], ids=lambda s: s.name)
+def test_resident_runs_leave_the_exchange_words_empty(nnc, shape):
+    """Runs of one to four sequences and of one to five steps (shorter and longer than the rotation of the exchange
+    buffers) one after the other on one model give the bits of the same runs on models of their own: every run
+    leaves the untagged exchange words empty for the next, whatever that one's layout of them."""
+    print(f"case: resident runs one after the other, {shape.name}", flush=True)
+    shape = dataclasses.replace(shape, n_layers=1 if shape is FULL_GRID else 2)
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    runs = [(1, 1), (4, 2), (1, 3), (2, 1), (3, 5), (4, 1), (1, 2), (2, 4)]
+
+    def one(g, batch, n):
+        g.kv_reset()
+        cur = [int(g.prefill(s, synth.tokens(20 + 100 * s, shape.vocab, stream=70 + s))[1].item()) for s in range(batch)]
+        toks, logits = g.decode_greedy(list(range(batch)), cur, n, want_logits=True)
+        g.synchronize()
+        return toks.cpu().numpy(), logits.cpu().numpy()
+
+    shared = nnc.Model(shape, blob, 4, 400)
+    for batch, n in runs:
+        got, want = one(shared, batch, n), one(nnc.Model(shape, blob, 4, 400), batch, n)
+        assert np.isfinite(want[1]).all() and all(np.array_equal(a, b) for a, b in zip(got, want)), (batch, n)
+
+
 @pytest.mark.parametrize("batch", [1, 2, 4])
 def test_resident_exchange_tags_start_again(nnc, batch):
     """When the tags of the exchanged words reach their limit, the exchange buffers are cleared and the tags
