@@ -289,6 +289,33 @@ __device__ __forceinline__ void pf_issue(Pf<RT>& pf, const uint4* __restrict__ W
   }
 }
 
+// The weights of a unit brought into this XCD's L2: one word per 64 bytes, so that a wave needs a register per 16 KiB of
+// the workgroup's range.  For the last unit of the workgroups that have one more than others, just before a wait:
+// loads return in order, so the wait lasts at least until these have landed.  In front of the two waits for the residual stream
+// (3 - 8 us in which nothing streams): 4B, 608 gate|up pairs and 384 QKV tiles on 256 workgroups, 277 -> 261 us per step of 4
+// layers; 1.7B 266 -> 259 (7 layers); 8B 364 -> 362.  Touching the last unit of every workgroup, or more
+// of it in front of the output and down projections, is slower (4B 263 - 270, 8B 365 - 378): those waits are shorter.
+constexpr int MK_TOUCH = 10;  // most registers: 160 KiB
+struct Touch {
+  uint32_t v[MK_TOUCH];
+  __device__ __forceinline__ void issue(const uint4* W, size_t tile0, int tiles) {
+    const int tid = opaque(threadIdx.x);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(W + tile0 * 64), 0, tiles * 1024, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < MK_TOUCH; ++i)  // (past the range: zero)
+      v[i] = i * 16 < tiles ? __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 64, i * 16384, 0) : 0u;
+  }
+  __device__ __forceinline__ void done() {
+#pragma unroll
+    for (int i = 0; i < MK_TOUCH; ++i) asm volatile("" ::"v"(v[i]));
+  }
+};
+// a workgroup's last unit of a stage where some workgroups have one more than others (-1: it is none of those)
+__device__ __forceinline__ int extra_unit(int first, int units, int nwg) {
+  const int last = units - 1 - (units - 1) % nwg + first;  // in the last round
+  return units % nwg != 0 && units > nwg && first < units % nwg ? last : -1;
+}
+
 // One GEMM unit: RT adjacent 16-row tiles x k tiles [kt_begin, kt_end), the
 // waves taking k tiles round-robin; the operand in LDS starts at k tile opnd_kt0.
 // Every wave leaves its partial tile in red[wave][rt]; the caller synchronises.
@@ -627,7 +654,11 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
         for (int b = 0; b < NS; ++b)
           if (NS == 1 || b < ns) gather_embed<NQ, HF>(x[b], H, a.embed, tok[b]);
       } else {
+        const int ex = extra_unit(wg, qkv_tiles, nwg);
+        Touch th;
+        if (ex >= 0) th.issue(L.wqkv, (size_t)ex * KTH, KTH);
         add_exchanged<NQ, NS>(a, sm, x, H, a.xdp + rot_prev * a.s_dp, a.ks_d, ns);
+        if (ex >= 0) th.done();
       }
       norm_pack<NQ, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
       wg_sync();
@@ -1073,7 +1104,13 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
       float* const xact = a.xact + rot * a.s_act;
       if (epi_on)
         for (int pr = wg; pr < gu_pairs; pr += nwg) st_empty(a.xact + rot_next * a.s_act + (size_t)epi_seq * F + pr * 16 + epi_row);
-      add_exchanged<NQ, NS>(a, sm, x, H, xop, a.ks_o, ns);
+      {
+        const int ex = extra_unit(wg, gu_pairs, nwg);
+        Touch th;
+        if (ex >= 0) th.issue(L.wgu, (size_t)ex * 2 * KTH, 2 * KTH);
+        add_exchanged<NQ, NS>(a, sm, x, H, xop, a.ks_o, ns);
+        if (ex >= 0) th.done();
+      }
       norm_pack<NQ, NS, HF>(sm, opnd, H, a.eps, ns, x, gg);
       wg_sync();
       if (sm.abort) return;

@@ -442,6 +442,33 @@ def test_resident_greedy_on_the_full_grid(nnc, lens, dtype):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
 
 
+@pytest.mark.parametrize("ffn", [4864, 8448])
+@pytest.mark.parametrize("batch", [1, 3])
+def test_resident_greedy_with_uneven_units(nnc, batch, ffn):
+    """Some workgroups of the resident grid have one QKV tile and one gate|up pair more than others (320 tiles, 304 or 528
+    pairs on 256 workgroups), whose weights they touch ahead: the tokens, logits and cache rows of the per-stage kernels."""
+    print(f"case: resident greedy with uneven units, B={batch}, ffn {ffn}", flush=True)
+    shape = synth.ModelShape("uneven", hidden=1024, n_layers=2, n_q_heads=20, n_kv_heads=10, head_dim=128, ffn=ffn, vocab=1024,
+                             dtype=synth.BF16)
+    blob, slots, runs = synth.make_blob(shape, gain_jitter=0.1), list(range(batch)), []
+    for resident in (1, 0):
+        g = nnc.Model(shape, blob, batch, 200)
+        g.set_option(nnc.OPT_PREFILL_EXACT, 1)
+        g.set_option(nnc.OPT_PERSISTENT, resident)
+        g.set_option(nnc.OPT_STAGE_TRACE, 1)
+        firsts = [int(g.prefill(sl, synth.tokens(30 + 17 * sl, shape.vocab, stream=970 + sl))[1].item()) for sl in slots]
+        toks, logits = g.decode_greedy(slots, firsts, 12, want_logits=True)
+        assert g.stage_trace().any() == bool(resident)
+        kv = [g.kv_read(1, sl, w, 0, 42 + 17 * sl).cpu().numpy() for sl in slots for w in (0, 1)]
+        g.synchronize()
+        runs.append((toks.cpu().numpy(), logits.cpu().numpy(), kv))
+    (t0, l0, k0), (t1, l1, k1) = runs
+    assert np.array_equal(t0, t1)
+    assert np.isfinite(l0).all() and np.abs(l1).max() > 0.5 and np.abs(l0 - l1).max() <= BF16_ABS_TIGHT
+    for a, b in zip(k0, k1):
+        assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
+
+
 @pytest.mark.parametrize("shape", [SMALL_BF16, FULL_GRID], ids=lambda s: s.name)
 def test_resident_runs_leave_the_exchange_words_empty(nnc, shape):
     """Runs of one to four sequences and of one to five steps (shorter and longer than the rotation of the exchange
