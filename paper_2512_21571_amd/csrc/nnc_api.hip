@@ -1197,6 +1197,40 @@ static bool small_attn(const nnc_model* m, uint32_t n) {
          attn_small_heads((int)m->c.n_q_heads, (int)m->c.n_kv_heads, (int)n, m->n_cus) > 0;
 }
 
+// Attention of a prompt block on 32 x 32 products (k_attn_block): workgroups over the positions, 0 where another kernel is
+// the better one.  One piece: from 80 workgroups of 128 tokens on (16 heads: 513 tokens); below, the 64-token
+// workgroups of k_attn_prefill are twice as many.  Two pieces: k_attn_block alone is slower than k_attn_prefill
+// (333 tokens of 32 heads behind 2048 positions: 88 us against 80), with its positions split over idle CUs it is faster,
+// from about 1600 positions on (us, the better other kernel / split: 16 heads, 333 tokens behind 512 21.9 / 22.5; 32 heads,
+// 200 behind 1024 28.6 / 28.8; figures beyond stand at the kernel): as many workgroups as fit the chip twice,
+// each with at least ten chunks of 32 positions.
+static size_t attn_part_floats(const nnc_model* m) { return (size_t)(PB_SPLIT_MAX - 1) * m->pb_max * m->H(); }
+static int attn_block_splits(const nnc_model* m, uint32_t n, uint32_t pos0, int pieces) {
+  if (!m->opt_planner || m->opt_prefill_attn >= 0) return 0;
+  const long wgs = (long)((n + 127) / 128) * m->c.n_q_heads;
+  if (pieces == 1) return wgs >= 80 ? 1 : 0;
+  const long positions = (long)pos0 + n;
+  if (positions < 1600) return 0;
+  long splits = std::min({2L * m->n_cus / wgs, (long)ATTN_MAX_SPLITS, positions / 320});
+  while (splits > 1 && attn_split_floats((int)n, (int)m->c.n_q_heads, (int)splits) > attn_part_floats(m)) --splits;
+  return splits > 1 ? (int)splits : 0;
+}
+
+static hipError_t prompt_attention(nnc_model* m, const LayerW& L, uint32_t slot, uint32_t pos0, uint32_t n, int pieces) {
+  const nnc_config& c = m->c;
+  const bool f16 = m->dt == NNC_F16;
+  const int nq = c.n_q_heads, nkv = c.n_kv_heads;
+  // (the partial records use the k-slice buffers, which are free between a projection's norm and the next projection)
+  if (const int splits = attn_block_splits(m, n, pos0, pieces))
+    return launch_attn_block(m->stream, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n, pieces,
+                             splits, m->pb_part, attn_part_floats(m), m->pb_fb, m->n_cus);
+  if (pieces == 2 && small_attn(m, n))
+    return launch_attn_small(m->stream, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n,
+                             m->pb_fb, m->n_cus);
+  return launch_attn_prefill(m->stream, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n,
+                             pieces, m->pb_fb, m->n_cus, m->opt_prefill_attn);
+}
+
 // Prompt pass over one short block (two pieces per activation) with the kernels of nnc_small.hip.
 static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t* tokens, uint32_t n, uint32_t pos0,
                                       bool want_head, float* logits_out, int32_t* next_dev) {
@@ -1253,10 +1287,7 @@ static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t
     double rows = 0;
     for (uint32_t i = 0; i < n; ++i) rows += pos0 + i + 1.0;
     RUN(FAM_PATTN, (pos0 + T) * 2.0 * Dkv * w + T * Dq * 6.0, rows * 4.0 * Dq,
-        small_attn(m, n) ? launch_attn_small(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0,
-                                          (int)n, m->pb_fb, m->n_cus)
-                      : launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq,
-                                            pos0, (int)n, 2, m->pb_fb, m->n_cus, m->opt_prefill_attn));
+        prompt_attention(m, L, slot, pos0, n, 2));
     {
       SmallGemmArgs a = gemm(L.wo, L.so, H, Dq, m->pb_fb);
       resid(a, po, L.g_post);
@@ -1406,11 +1437,7 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       double rows = 0;
       for (uint32_t i = 0; i < n; ++i) rows += pos0 + i + 1.0;
       RUN(FAM_PATTN, (pos0 + T) * 2.0 * Dkv * w + T * Dq * 6.0, rows * 4.0 * Dq,
-          pieces == 2 && small_attn(m, n)
-              ? launch_attn_small(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0, (int)n,
-                                  m->pb_fb, m->n_cus)
-              : launch_attn_prefill(s, f16, m->pb_qkv, nq, nkv, L.kc, m->pb_vt, m->pb_vt_stride, slot, c.max_seq, pos0,
-                                    (int)n, pieces, m->pb_fb, m->n_cus, m->opt_prefill_attn));
+          prompt_attention(m, L, slot, pos0, n, pieces));
     }
     {
       PrefillGemmArgs a{};

@@ -247,6 +247,13 @@ hipError_t launch_v_transpose(hipStream_t s, const void* vc, uint32_t slot, int 
 hipError_t launch_attn_prefill(hipStream_t s, bool f16, const float* qkv, int nq, int nkv, const void* kc, const void* vt,
                                uint32_t S, uint32_t slot, uint32_t max_seq, uint32_t pos0, int n, int pieces, void* Of,
                                int n_cus, int shape);
+// The same on 32 x 32 products (nnc_attn.hip).  One piece: splits = 1.  Two pieces: the positions of a token block go to
+// `splits` workgroups, whose partial records (attn_split_floats of them, at most part_floats) a second kernel merges.
+constexpr int ATTN_MAX_SPLITS = 8;
+size_t attn_split_floats(int n, int nq, int splits);
+hipError_t launch_attn_block(hipStream_t s, bool f16, const float* qkv, int nq, int nkv, const void* kc, const void* vt, uint32_t S,
+                             uint32_t slot, uint32_t max_seq, uint32_t pos0, int n, int pieces, int splits, float* part,
+                             size_t part_floats, void* Of, int n_cus);
 hipError_t launch_embed_rows(hipStream_t s, bool f16, const void* Ep, int H, const int32_t* tokens_dev, int n, float* x);
 // finish: also feed the tokens back, advance the positions and log the tokens (greedy loop)
 hipError_t launch_argmax(hipStream_t s, const float* logits, long ld, int V, int ncols,

@@ -442,6 +442,59 @@ def test_resident_greedy_on_the_full_grid(nnc, lens, dtype):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
 
 
+# enough query heads that blocks of more than 512 tokens take the 32 x 32 attention
+HEADS16 = synth.ModelShape("heads16", hidden=256, n_layers=2, n_q_heads=16, n_kv_heads=8, head_dim=128, ffn=512, vocab=1024,
+                           dtype=synth.BF16)
+
+
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
+@pytest.mark.parametrize("n,max_seq", [(530, 546), (641 + 16, 700), (768 + 16, 1000), (1155, 1155)])
+def test_block_attention_on_wide_products(nnc, n, max_seq, dtype):
+    """Single-piece blocks on the 32 x 32 attention: just over its smallest launch, one token past a 128-token block, whole
+    blocks (both halves of the launch), a cache that ends inside the last chunk; and a second block that starts
+    mid-context.  Against the oracle, and against the 16 x 16 kernel (forced), which rounds the same values."""
+    print(f"case: 32 x 32 prompt attention, {n} tokens of {max_seq}, dtype {dtype}", flush=True)
+    shape = dataclasses.replace(HEADS16, dtype=dtype)
+    g, o = _pair(nnc, shape, 1, max_seq, exact_prefill=False)
+    toks = synth.tokens(n, shape.vocab, stream=700 + n)
+    lg, ng = g.prefill(0, toks)
+    lo, no = oracle_prefill_like_library(o, 0, toks, shape)
+    _check_logits(shape, lg, lo, BF16_ABS_PROMPT)
+    assert int(ng.item()) == no
+    g.kv_reset(0)
+    g.set_option(nnc.OPT_PREFILL_ATTN, 0)
+    l2, _ = g.prefill(0, toks)
+    assert not np.array_equal(l2.cpu().numpy(), lg.cpu().numpy())      # the other kernel ran
+    _check_logits(shape, l2, lg.double().cpu().numpy(), BF16_ABS_PROMPT)
+
+
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
+@pytest.mark.parametrize("pos0,n,max_seq", [(1599, 9, 1700), (1700, 16, 1716), (1650, 129, 2000), (2000, 333, 2400), (1601, 500, 2101)])
+def test_block_attention_with_split_positions(nnc, pos0, n, max_seq, dtype):
+    """Second turns behind a long context, their positions split over workgroups: the fewest tokens, a cache that ends inside
+    a chunk, one token past a 128-token block, splits that see nothing of the first tokens.  Against the same turn
+    through the 16 x 16 kernel: both carry two pieces, so they agree as closely as two orders of an fp32 sum do."""
+    print(f"case: split prompt attention, {n} tokens behind {pos0} of {max_seq}, dtype {dtype}", flush=True)
+    shape = dataclasses.replace(HEADS16, dtype=dtype)
+    g, _ = _pair(nnc, shape, 1, max_seq, exact_prefill=False)
+    first, more = synth.tokens(pos0, shape.vocab, stream=71), synth.tokens(n, shape.vocab, stream=72)
+    out = []
+    for attn in (-1, 0):
+        g.kv_reset(0)
+        g.set_option(nnc.OPT_PREFILL_ATTN, 0)
+        g.prefill(0, first, want_logits=False)
+        g.set_option(nnc.OPT_PREFILL_ATTN, attn)
+        if attn == 0:
+            g.set_option(nnc.OPT_PLANNER, 0)                           # (the short-block attention stays out of it)
+        lg, nx = g.prefill(0, more)
+        kv = [g.kv_read(1, 0, w, pos0, n).cpu().numpy() for w in (0, 1)]
+        out.append((lg.double().cpu().numpy(), int(nx.item()), kv))
+    (l0, n0, k0), (l1, n1, k1) = out
+    assert np.isfinite(l0).all() and np.abs(l0 - l1).max() <= BF16_ABS_TIGHT and n0 == n1
+    for a, b in zip(k0, k1):
+        assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
+
+
 @pytest.mark.parametrize("ffn", [4864, 8448])
 @pytest.mark.parametrize("batch", [1, 3])
 def test_resident_greedy_with_uneven_units(nnc, batch, ffn):
