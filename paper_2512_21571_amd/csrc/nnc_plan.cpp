@@ -177,7 +177,9 @@ SmallGemmPlan plan_small_gemm(const Machine& mc, int epi, int n_tiles, int KT, i
     // the matrix-core time, the weights from HBM; an epilogue per workgroup; launch
     const double t_cu = rounds * bytes / 100e3;
     const double t_mfma = (double)rounds * KT * xt * nt * ct / 4 * 16 / 2200.0;
-    const double t_hbm = (double)n_tiles * KT * 1024.0 / mc.hbm_bytes_per_us;
+    // (a launch of several rounds starts cold streams several times: 4B gate|up at 24 tokens 37 us in five rounds, 38 in
+    // two, 28 in one)
+    const double t_hbm = (double)n_tiles * KT * 1024.0 / mc.hbm_bytes_per_us * (1.0 + 0.1 * (rounds - 1));
     const double total = std::max(std::max(t_cu, t_mfma), t_hbm) + 0.15 * nt * ct / 2 * rounds + 3.0;
     if (total < best.t_us) {
       best.nt = nt; best.ct = ct; best.workgroups = wgs; best.t_us = total;
