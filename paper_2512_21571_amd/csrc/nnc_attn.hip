@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
   const uint32_t kvoff = krow * 256u + kgrp * 16u, vvoff = vrow * S * 2u + vgrp * 16u;
   // (inline assembly: the compiler would make every later LDS read wait for all copies; the waits are explicit)
   auto copy1 = [&](const char* base, uint32_t voff, uint32_t lds_addr) __attribute__((always_inline)) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(base)
                  : "memory", "m0");

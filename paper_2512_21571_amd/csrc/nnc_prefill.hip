@@ -324,10 +324,11 @@ __global__ __launch_bounds__(256, 2) void k_gemm_prefill_dl(PrefillGemmArgs a) {
   // The copy instruction is written as inline assembly: the compiler, when it sees one, makes
   // every later LDS read wait for all of them (it cannot tell which stage a read touches), which
   // would undo the look-ahead.  Hidden from it, the waits are the explicit ones below.
-  // m0 = LDS byte address of the fragment (wave-uniform); lane l's 16 bytes land at m0 + 16 l.
+  // m0 = LDS byte address of the fragment (wave-uniform); lane l's 16 bytes land at m0 + 16 l.  One wait state
+  // between the scalar write of m0 and the copy that reads it, which the assembler does not put in by itself.
   typedef __attribute__((address_space(3))) void* lptr;
   auto copy1 = [&](const char* base, uint32_t voff, uint32_t lds_addr) __attribute__((always_inline)) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(base)
                  : "memory", "m0");
@@ -486,7 +487,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_prefill_big(PrefillGemmArgs a) 
   for (int j = 0; j < BL; ++j) vob[j] = ((uint32_t)min(tt0 + wave + 4 * j, a.t_tiles - 1) * (uint32_t)a.KT * 64u + lane) * 16u;
   typedef __attribute__((address_space(3))) void* lptr;
   auto copy1 = [&](const char* base, uint32_t voff, uint32_t lds_addr) __attribute__((always_inline)) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(base)
                  : "memory", "m0");
