@@ -149,7 +149,7 @@ struct nnc_model {
 
   bool profiling = false;
   // Long prompts: the fp32-grade tail pass runs on a second stream, one layer behind the last
-  // block (whose layers record layer_done after their cache append); created on first use.
+  // block (whose layers record layer_done after their cache append).
   bool opt_tail_overlap = true;
   hipStream_t tail_stream = nullptr;
   std::vector<hipEvent_t> layer_done;   // one per layer, + [n_layers]: fork point, + [n_layers + 1]: join
@@ -259,6 +259,47 @@ ResidentTurn g_turn;
 bool being_captured(const nnc_model* m) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   return m->stream && hipStreamIsCapturing(m->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+// Whether work on `st` runs while the model's stream is busy.  Streams share a few hardware queues, and two streams of one
+// queue run one after the other.
+bool runs_beside(nnc_model* m, hipStream_t st, uint32_t* words) {
+  uint32_t got[2] = {0, 0};
+  const bool ok = launch_raise_word(st, words) == hipSuccess &&  // (once before, so that its first launch is not what is timed)
+                  hipStreamSynchronize(st) == hipSuccess && launch_zero_words(m->stream, words, 2) == hipSuccess &&
+                  hipStreamSynchronize(m->stream) == hipSuccess && launch_await_word(m->stream, words) == hipSuccess &&
+                  launch_raise_word(st, words) == hipSuccess && hipStreamSynchronize(st) == hipSuccess &&
+                  hipMemcpyAsync(got, words, sizeof got, hipMemcpyDeviceToHost, m->stream) == hipSuccess &&
+                  hipStreamSynchronize(m->stream) == hipSuccess;
+  return ok && got[1] == 1;
+}
+
+// Second stream and per-layer events for the tail of a long prompt; without them the tail follows the last block on the
+// model's stream.  The runtime deals streams to hardware queues in turn, so about one in four met the queue of the model's
+// stream and lost the overlap for the life of the model (4B, 4 layers, 2048 tokens: 2634 us against 2350, as with the
+// overlap switched off); a few are tried, once, when the model is made.
+void make_tail_stream(nnc_model* m, uint32_t* words) {
+  std::vector<hipStream_t> tried;
+  for (int i = 0; i < 4; ++i) {
+    hipStream_t st = nullptr;
+    if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) break;
+    tried.push_back(st);
+    if (runs_beside(m, st, words)) break;
+  }
+  if (tried.empty()) return;
+  m->tail_stream = tried.back();
+  tried.pop_back();
+  for (hipStream_t st : tried) (void)hipStreamDestroy(st);
+  m->layer_done.assign(m->c.n_layers + 2, nullptr);
+  for (auto& e : m->layer_done)
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+      for (hipEvent_t d : m->layer_done)
+        if (d) (void)hipEventDestroy(d);
+      m->layer_done.clear();
+      (void)hipStreamDestroy(m->tail_stream);
+      m->tail_stream = nullptr;
+      return;
+    }
 }
 
 void release_all(nnc_model* m) {
@@ -1036,6 +1077,7 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
   }
   m->len.assign(c.max_batch, 0);
   TRY_OR_BAIL(hipStreamSynchronize(s));
+  if (m->pb_max && c.has_embed_and_head && c.max_seq > 512) make_tail_stream(m, m->tail_counters);  // (cleared before every use)
   (void)st;
 #undef ALLOC
 #undef TRY_OR_BAIL
@@ -1467,25 +1509,6 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
   return want_head ? prefill_head(m, n, pending, logits_out, next_dev) : NNC_OK;
 }
 
-// Second stream and per-layer events for the tail of a long prompt; false if they cannot be had
-// (the tail then follows the last block on the model's stream).
-static bool ensure_tail_stream(nnc_model* m) {
-  if (m->tail_stream) return true;
-  hipStream_t st = nullptr;
-  if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return false;
-  std::vector<hipEvent_t> ev(m->c.n_layers + 2, nullptr);
-  for (auto& e : ev)
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-      for (hipEvent_t d : ev)
-        if (d) (void)hipEventDestroy(d);
-      (void)hipStreamDestroy(st);
-      return false;
-    }
-  m->tail_stream = st;
-  m->layer_done = ev;
-  return true;
-}
-
 // While alive, the model's passes are enqueued on the tail stream and wait, layer by layer, for
 // the last block's cache appends.
 struct TailStreamScope {
@@ -1529,7 +1552,7 @@ static nnc_status prefill_common(nnc_model* m, uint32_t slot, const int32_t* tok
     // The tail pass streams every weight once more at a few percent of the matrix cores' rate,
     // the last block is bound by the matrix cores: the two run side by side, the tail's layer l
     // starting when the block's layer l has appended its K / V rows.
-    overlap = head < n && m->opt_tail_overlap && !m->profiling && ensure_tail_stream(m);
+    overlap = head < n && m->opt_tail_overlap && !m->profiling && m->tail_stream;
     for (uint32_t t0 = 0; t0 < head;) {
       const uint32_t blk = m->opt_prefill_block ? std::min(m->opt_prefill_block, m->pb_max) : m->pb_max;
       const uint32_t nb = std::min(blk, head - t0);

@@ -128,6 +128,10 @@ hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, cons
                                      int H, float eps, int ncols, void* Xp, int NC, int nsplit);
 // n 32-bit words = 0 (a fill kernel: safe under graph capture)
 hipError_t launch_zero_words(hipStream_t s, uint32_t* p, int n);
+// Do two streams run side by side?  w (two words, zero): w[0] is set on one, waited for (about 0.5 ms at most) on the other,
+// which leaves 1 in w[1] if it saw it.
+hipError_t launch_raise_word(hipStream_t s, uint32_t* w);
+hipError_t launch_await_word(hipStream_t s, uint32_t* w);
 // y = x + part[0] + ... + part[nparts - 1], n contiguous floats
 hipError_t launch_fold_residual(hipStream_t s, const float* x, const float* part, int nparts, long part_stride,
                                 float* y, size_t n);

@@ -376,6 +376,25 @@ hipError_t launch_zero_words(hipStream_t s, uint32_t* p, int n) {
   return hipGetLastError();
 }
 
+__global__ void k_raise_word(uint32_t* w) { __hip_atomic_store(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__global__ void k_await_word(uint32_t* w) {
+  for (int polls = 0; polls < 500; ++polls) {  // (about 1 us each; bounded, so that it ends also where the other never comes)
+    if (__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+      w[1] = 1u;
+      return;
+    }
+    __builtin_amdgcn_s_sleep(8);
+  }
+}
+hipError_t launch_raise_word(hipStream_t s, uint32_t* w) {
+  k_raise_word<<<1, 1, 0, s>>>(w);
+  return hipGetLastError();
+}
+hipError_t launch_await_word(hipStream_t s, uint32_t* w) {
+  k_await_word<<<1, 1, 0, s>>>(w);
+  return hipGetLastError();
+}
+
 // y = x + (part[0] + part[1] + ...) for n contiguous floats (all columns), fixed order.
 __global__ __launch_bounds__(256) void k_fold_residual(const float* __restrict__ x, const float* __restrict__ part,
                                                        int nparts, long part_stride, float* __restrict__ y, size_t n) {

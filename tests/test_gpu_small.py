@@ -720,6 +720,24 @@ def test_batched_decode_mixed_lengths_up_to_4k(nnc, shape, fuse):
     assert g.slot_len(1) == 4104
 
 
+@pytest.mark.parametrize("n", [529, 700])
+def test_prompt_tails_of_several_models(nnc, n):
+    """Each model picks a second stream for prompt tails when it is made, by whether that runs beside its own. Six models
+    alive at once, more than there are hardware queues to share, and one made after another went: the
+    same bits as with the tail behind the block."""
+    print(f"case: prompt tails of several models, {n} tokens", flush=True)
+    blob = synth.make_blob(SMALL_G4, weight_std=0.05)
+    models = [nnc.Model(SMALL_G4, blob, 1, 720) for _ in range(6)]
+    del models[2]
+    models.append(nnc.Model(SMALL_G4, blob, 1, 720))
+    toks = synth.tokens(n, SMALL_G4.vocab, stream=5)
+    models[0].set_option(nnc.OPT_TAIL_OVERLAP, 0)
+    outs = [g.prefill(0, toks)[0] for g in models]
+    assert np.abs(outs[0].cpu().numpy()).max() > 0.1
+    for lg in outs[1:]:
+        assert np.array_equal(lg.cpu().numpy(), outs[0].cpu().numpy())
+
+
 def test_prompt_tail_beside_the_last_block_equals_tail_after_it(nnc):
     """The fp32-grade pass over a long prompt's last tokens runs on the library's second stream
     beside the last block (default) or after it on the model's stream: same bits, for one block,
