@@ -65,11 +65,12 @@ __device__ __forceinline__ float pair_sum(uint32_t w, float c, Fp16*) {
   return __builtin_amdgcn_fdot2(__builtin_bit_cast(Fp16::vec2, w), __builtin_bit_cast(Fp16::vec2, Fp16::kOnes2), c, false);
 }
 
-// maxima without the NaN-quieting copies that fmaxf brings (no operand here is a NaN)
+// The maximum of three as one v_maximum3.  It reads fresh matrix products, whose result needs 12 wait states before it may be
+// read, and only the compiler puts those in: not inline assembly (v_max3 written so read two-piece scores after 3).  Not
+// fmaxf either, which first quiets every operand with an instruction of its own.  A NaN score makes the maximum NaN; its
+// token's weights and sums are NaN by the score itself.
 __device__ __forceinline__ float max3(float x, float y, float z) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
-  return r;
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z);
 }
 
 }  // namespace

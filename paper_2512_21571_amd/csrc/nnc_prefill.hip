@@ -951,17 +951,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float* __restrict
     for (int j = 0; j < 4; ++j) Fs[buf][wave + 4 * j][lane] = stage[j];
   };
 
-  // maxima without the NaN-quieting copies that fmaxf brings (no operand here is a NaN)
+  // maxima as single instructions without the NaN-quieting copies that fmaxf brings; not as inline assembly, in front of
+  // which the compiler leaves out the wait states (8) that a fresh matrix product needs before it is read
   auto max3 = [](float x, float y, float z) __attribute__((always_inline)) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
-    return r;
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z);
   };
-  auto max2 = [](float x, float y) __attribute__((always_inline)) {
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-    return r;
-  };
+  auto max2 = [](float x, float y) __attribute__((always_inline)) { return __builtin_elementwise_maximum(x, y); };
   const u32x4 ones = u32x4{HF::kOnes2, HF::kOnes2, HF::kOnes2, HF::kOnes2};  // 1.0 x 8
 
   auto do_chunk = [&](int buf, uint32_t kv0) __attribute__((always_inline)) {

@@ -495,6 +495,32 @@ def test_block_attention_with_split_positions(nnc, pos0, n, max_seq, dtype):
         assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
 
 
+@pytest.mark.parametrize("turns,attn", [((657,), -1), ((657,), 0), ((1600, 60), -1), ((1600, 60), 1)], ids=str)
+def test_attention_scores_ruled_by_the_last_head_dims(nnc, turns, attn):
+    """Scores that head dims 112 .. 127 move by tens (e^11 is binary16's largest weight): a maximum taken before the last
+    products are in overflows the weights to inf / inf.  One and two pieces, the 32 x 32 attention (-1) and the
+    16 x 16 one.  K rows of the second layer, which depend on every row of the first layer's attention, against the oracle: the
+    binary16 rounding of a query moves a score of spread 13 by 3e-3, and its weight by as much."""
+    print(f"case: scores ruled by the last head dims, turns {turns}, attention {attn}", flush=True)
+    shape = dataclasses.replace(HEADS16, dtype=synth.F16)
+    blob = synth.make_blob(shape, weight_std=0.05)
+    for name in ("l0.g_q", "l0.g_k"):
+        synth.blob_tensor(shape, blob, name)[112:] = 6.0
+    g, o, at = nnc.Model(shape, blob, 1, 1700), oracle.from_shape(shape, blob, 1, 1700), 0
+    q, k = (np.random.RandomState(1).randn(2, 500, 16) * 6.0)          # (the scores' spread: 13)
+    assert 10 < np.std((q * k).sum(1) / np.sqrt(128)) < 16
+    for n in turns:
+        toks = synth.tokens(n, shape.vocab, stream=810 + n)
+        g.set_option(nnc.OPT_PREFILL_ATTN, attn)
+        lg, _ = g.prefill(0, toks)
+        assert np.isfinite(lg.cpu().numpy()).all()
+        oracle_prefill_like_library(o, 0, toks, shape)
+        got = g.kv_read(1, 0, 0, at, n).double().cpu().numpy()
+        want = o.kv_rows(1, 0, 0)[at:at + n]
+        assert np.isfinite(got).all() and np.linalg.norm(got - want) <= 1e-2 * np.linalg.norm(want)
+        at += n
+
+
 @pytest.mark.parametrize("ffn", [4864, 8448])
 @pytest.mark.parametrize("batch", [1, 3])
 def test_resident_greedy_with_uneven_units(nnc, batch, ffn):
