@@ -240,8 +240,8 @@ typedef enum {
                                whatever model and stream, take turns on a GPU; nothing orders them with
                                the kernels of other processes, or with kernels of the caller's own that stay
                                on the GPU for as long as that bound: where such share the GPU, set 0.
-                               While the caller captures the model's stream, runs of two to four
-                               sequences are one kernel per stage, as every replay needs tags of its own */
+                               While the caller captures the model's stream, every call is one kernel per
+                               stage, as each replay of a resident launch would need tags of its own */
   NNC_OPT_PREFILL_TILE = 4, /* block tile of the large-block prompt GEMMs: -1 (default) chosen from
                                each launch's size; 0: 64 x 128, 1: 256 x 128, 2: 128 x 128, 3: 64 x 64,
                                4: 192 x 128, 5: 256 x 256, 6: 192 x 256 (rows x operand columns).  Same k order per output

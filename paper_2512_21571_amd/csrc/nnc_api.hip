@@ -619,7 +619,7 @@ nnc_status greedy_step(nnc_model* m, uint32_t batch, int nsplit, int grid_chunks
   p.next = m->next;
   p.finish = true;
   p.grid_chunks = grid_chunks;
-  const bool graph = allow_graph && m->opt_graph && !m->profiling && m->stream != nullptr;
+  const bool graph = allow_graph && m->opt_graph && !m->profiling && m->stream != nullptr && !being_captured(m);
   if (!graph) {
     return run_pass(m, p);
   }
@@ -645,8 +645,10 @@ nnc_status greedy_step(nnc_model* m, uint32_t batch, int nsplit, int grid_chunks
   return NNC_OK;
 }
 
+// Not while the caller captures the stream: a replay would meet the arg-max words of the replay before under its own
+// tags, end its last exchange before all workgroups have read, and empty words that others still wait for.
 bool use_persistent(const nnc_model* m, uint32_t batch) {
-  return m->mk_ok && m->opt_persistent && !m->profiling && batch == 1;
+  return m->mk_ok && m->opt_persistent && !m->profiling && batch == 1 && !being_captured(m);
 }
 // Greedy runs of two to four sequences.  (Single steps of a batch keep the per-stage kernels, whose bits
 // nnc_decode_step_static promises; so do runs that ask for a variant of those kernels.)
@@ -659,10 +661,8 @@ bool use_persistent(const nnc_model* m, uint32_t batch) {
 bool use_persistent_greedy(const nnc_model* m, const uint32_t* slots, uint32_t batch, uint32_t n_steps) {
   if (use_persistent(m, batch)) return true;
   if (!m->mk_ok || !m->opt_persistent || m->profiling || batch > m->mk_seqs || m->opt_fuse_norm || !m->opt_fuse_qk ||
-      m->opt_decode_pieces == 2)
+      m->opt_decode_pieces == 2 || being_captured(m))
     return false;
-  // (a replay of a caller's graph would meet the tags of the replay before)
-  if (being_captured(m)) return false;
   // (a single run beyond the tag space, which the resident kernel would have to refuse)
   if ((uint64_t)n_steps * mk_tags_per_step((int)m->c.n_layers) + 1 >= m->mk_tag_limit) return false;
   long units = 0;
@@ -737,7 +737,7 @@ nnc_status persistent_steps(nnc_model* m, const uint32_t* slots, const int32_t* 
   p.spin_max = m->mk_spin_limit;
   std::unique_lock<std::mutex> turn(g_turn.mutex, std::defer_lock);
   nnc_model** last = nullptr;
-  if (m->device < MAX_DEVICES && !being_captured(m)) {
+  if (m->device < MAX_DEVICES) {
     turn.lock();
     last = &g_turn.last[m->device];
     if (*last && *last != m) HIP_TRY(hipStreamWaitEvent(m->stream, (*last)->mk_error_event, 0));

@@ -650,18 +650,21 @@ def test_resident_grids_of_two_models_take_turns(nnc, batches):
     g.synchronize()
 
 
-def test_greedy_run_of_two_in_a_callers_graph(nnc):
-    """A greedy run of two sequences captured by the caller is one kernel per stage (a replayed resident launch
-    would meet its own tags): every replay gives the tokens and logits of the eager run."""
+@pytest.mark.parametrize("want_logits", [True, False], ids=["logits", "tokens-only"])
+@pytest.mark.parametrize("batch,steps", [(1, 1), (1, 4), (2, 4)])
+def test_greedy_run_in_a_callers_graph(nnc, batch, steps, want_logits):
+    """A greedy run captured by the caller is one kernel per stage (a replayed resident launch would meet its own
+    tags), enqueued one by one (the library's own step graphs cannot be captured inside another): every replay gives the
+    tokens and logits of the eager run, with eager steps of the resident kernel between."""
     import torch
-    print("case: greedy run of two sequences in a caller's graph", flush=True)
-    shape, slots = SMALL_BF16, [0, 1]
-    g = nnc.Model(shape, synth.make_blob(shape, weight_std=0.05), 2, 100)
-    g.set_option(nnc.OPT_GRAPH, 0)
+    print(f"case: greedy run of {batch} sequences, {steps} steps, in a caller's graph", flush=True)
+    shape, slots = SMALL_BF16, list(range(batch))
+    g = nnc.Model(shape, synth.make_blob(shape, weight_std=0.05), batch, 100)
+    g.set_option(nnc.OPT_STAGE_TRACE, 1)                  # stamps only where the resident kernel runs
     prompts = [synth.tokens(21 + s, shape.vocab, stream=s) for s in slots]
     firsts = [int(g.prefill(s, p)[1].item()) for s, p in zip(slots, prompts)]
     g.set_option(nnc.OPT_PERSISTENT, 0)
-    want = [t.cpu().numpy() for t in g.decode_greedy(slots, firsts, 4, want_logits=True)]
+    want = [t.cpu().numpy() for t in g.decode_greedy(slots, firsts, steps, want_logits=True)]
     g.set_option(nnc.OPT_PERSISTENT, 1)
     g.kv_reset()
     for s, p in zip(slots, prompts):
@@ -669,14 +672,50 @@ def test_greedy_run_of_two_in_a_callers_graph(nnc):
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=g.stream):
-        toks, logits = g.decode_greedy(slots, firsts, 4, want_logits=True)
-    for _ in range(3):
-        toks.zero_()
-        logits.zero_()
+        toks, logits = g.decode_greedy(slots, firsts, steps, want_logits=want_logits)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert not g.stage_trace().any()
+    for _ in range(4):                                    # two replays in a row, then a resident run, and again
+        for t in (toks, logits) if want_logits else (toks,):
+            t.zero_()
         torch.cuda.synchronize()
         graph.replay()
+        graph.replay()
         torch.cuda.synchronize()
-        assert np.array_equal(toks.cpu().numpy(), want[0]) and np.array_equal(logits.cpu().numpy(), want[1])
+        assert np.array_equal(toks.cpu().numpy(), want[0])
+        assert not want_logits or np.array_equal(logits.cpu().numpy(), want[1])
+        g.decode_greedy(slots, firsts, 2)
+        g.synchronize()
+    assert g.stage_trace().any()
+
+
+def test_single_step_in_a_callers_graph(nnc):
+    """The same for nnc_decode_step of one sequence, at the library's default of replaying steps as graphs of its own."""
+    import torch
+    print("case: single step in a caller's graph", flush=True)
+    g = nnc.Model(SMALL_BF16, synth.make_blob(SMALL_BF16, weight_std=0.05), 1, 100)
+    g.set_option(nnc.OPT_STAGE_TRACE, 1)
+    prompt = synth.tokens(37, SMALL_BF16.vocab)
+    first = int(g.prefill(0, prompt)[1].item())
+    g.set_option(nnc.OPT_PERSISTENT, 0)
+    want = [t.cpu().numpy() for t in g.decode_step([0], [first])]
+    g.set_option(nnc.OPT_PERSISTENT, 1)
+    g.kv_reset()
+    g.prefill(0, prompt, want_logits=False)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=g.stream):
+        logits, nxt = g.decode_step([0], [first])
+    for _ in range(3):
+        logits.zero_()
+        nxt.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(logits.cpu().numpy(), want[0]) and np.array_equal(nxt.cpu().numpy(), want[1])
+    assert not g.stage_trace().any()
 
 
 @pytest.mark.parametrize("planner", [0, 1], ids=["hand-rules", "planner"])
