@@ -521,6 +521,32 @@ def test_attention_scores_ruled_by_the_last_head_dims(nnc, turns, attn):
         at += n
 
 
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
+@pytest.mark.parametrize("turns", [(657,), (700, 900), (1600, 60)], ids=str)
+def test_wide_attention_never_meets_rows_past_its_tokens(nnc, turns, dtype):
+    """A prompt whose rows are NaN from position 600 on, then others on the same slot: the same bits as on a model that never saw
+    the first, whatever the transposed V copy and the cache still hold past the new tokens (whole 64-position chunks of it
+    are read, with weights of zero)."""
+    print(f"case: prompts {turns} behind one of NaN rows, dtype {dtype}", flush=True)
+    shape = dataclasses.replace(HEADS16, dtype=dtype)
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    synth.blob_tensor(shape, blob, "embed")[1023] = 0x7f80 if dtype == synth.BF16 else 0x7c00    # infinity
+    bad = synth.tokens(1700, 1023, stream=5)
+    bad[600] = 1023
+    out = []
+    for dirty in (True, False):
+        g = nnc.Model(shape, blob, 1, 1700)
+        if dirty:
+            g.prefill(0, bad, want_logits=False)
+            assert np.isnan(g.kv_read(1, 0, 1, 600, 1000).cpu().numpy()).all()
+            g.kv_reset()
+        for i, n in enumerate(turns):
+            g.prefill(0, synth.tokens(n, 1023, stream=6 + i), want_logits=False)
+        out.append([g.kv_read(l, 0, w, 0, sum(turns)).cpu().numpy() for l in (0, 1) for w in (0, 1)])
+    for a, b in zip(*out):
+        assert np.isfinite(b).all() and np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("ffn", [4864, 8448])
 @pytest.mark.parametrize("batch", [1, 3])
 def test_resident_greedy_with_uneven_units(nnc, batch, ffn):
