@@ -976,7 +976,7 @@ nnc_status nnc_model_create(const nnc_config* cfg, const void* blob, size_t blob
     ALLOC(m->pb_part, float*, (size_t)(PB_SPLIT_MAX - 1) * pb * H * 4);
     ALLOC(m->pb_ssq, float*, (H / 16) * (size_t)std::min<uint32_t>(pb, PB_SMALL_TOKENS) * 4);
     // transposed V copy of one slot: [kv head][128][positions, padded to a multiple of 32];
-    // zero-filled once so that positions never written read as finite values
+    // zero-filled once: positions never written read as defined values
     m->pb_vt_stride = (c.max_seq + 31) / 32 * 32;
     ALLOC(m->pb_vt, void*, (size_t)c.n_kv_heads * 128 * m->pb_vt_stride * 2);
     TRY_OR_BAIL(hipMemsetAsync(m->pb_vt, 0, (size_t)c.n_kv_heads * 128 * m->pb_vt_stride * 2, s));

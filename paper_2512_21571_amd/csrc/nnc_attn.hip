@@ -274,16 +274,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      // Columns past the wave's last token: their weights are zero, but V^T may hold anything there (rows of later tokens, of an
-      // earlier prompt), and zero times an infinity would reach every token of the wave.
       if (kv0 + st * 16 + 15 > p_last) {
-        const int keep = (int)p_last - (int)(kv0 + st * 16 + hf * 8);  // last column kept, of this lane's eight
+        const int keep = (int)p_last - (int)(kv0 + st * 16 + hf * 8);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t m = (keep >= 2 * e ? 0xffffu : 0u) | (keep > 2 * e ? 0xffff0000u : 0u);
+        for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-          for (int dt = 0; dt < 4; ++dt) vf[st & 1][dt][e] &= m;
-        }
+          for (int e = 0; e < 4; ++e) vf[st & 1][dt][e] &= column_mask(keep, e);
       }
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)

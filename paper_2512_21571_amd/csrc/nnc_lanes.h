@@ -68,6 +68,13 @@ __device__ __forceinline__ float col4_sum(float v) {
   return a + b;
 }
 
+// Columns past a wave's last token in a fragment of V^T (eight 16-bit positions per lane): their weights are zero, but V^T
+// may hold anything there (rows of later tokens, of an earlier prompt), and zero times an infinity would reach every
+// token of the wave.  Mask of word e of the fragment where `keep` is the last position kept, counted from the lane's first.
+__device__ __forceinline__ uint32_t column_mask(int keep, int e) {
+  return (keep >= 2 * e ? 0xffffu : 0u) | (keep > 2 * e ? 0xffff0000u : 0u);
+}
+
 // Sum / maximum over the whole wave, returned in every lane (wave-uniform).
 __device__ __forceinline__ float wave_sum(float v) {
   v = row16_sum(v);

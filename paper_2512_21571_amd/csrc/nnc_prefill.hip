@@ -857,8 +857,8 @@ hipError_t launch_v_transpose(hipStream_t s, const void* vc, uint32_t slot, int 
 // (double-buffered, one barrier per chunk), and each wave reads them from LDS for its GH heads.
 // A wave keeps only its queries and accumulators in registers, so two workgroups fit on a CU
 // and one wave's softmax arithmetic overlaps another's matrix-core work.
-// Masked positions get weight exp(-inf) = 0; their K / V^T values are finite (the copy and the
-// cache rows read are initialised memory), so 0 x value = 0.
+// Masked positions get weight exp(-inf) = 0, and their V^T columns past the wave's last token are
+// taken as zero (column_mask).
 // PIECES = 2: queries and weights enter the matrix cores as two bf16 pieces (16 significant
 // bits); PIECES = 1: one bf16 each.  The row sum adds the weights as they are multiplied.
 template <int GH, int PIECES, class HF>
@@ -1035,9 +1035,25 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float* __restrict
       }
     }
     // every V^T fragment feeds all GH heads
+    const bool past = kv0 + 31 > p_last;  // columns past the wave's last token
+    const int keep = (int)p_last - (int)(kv0 + g * 8);
+    if constexpr (kVfUpFront) {
+      if (past) {
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) vf[dt][e] &= column_mask(keep, e);
+      }
+    }
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) {
-      if constexpr (!kVfUpFront) vf[dt] = Fs[buf][8 + dt][lane];
+      if constexpr (!kVfUpFront) {
+        vf[dt] = Fs[buf][8 + dt][lane];
+        if (past) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) vf[dt][e] &= column_mask(keep, e);
+        }
+      }
 #pragma unroll
       for (int h = 0; h < GH; ++h)
 #pragma unroll

@@ -556,6 +556,12 @@ __global__ __launch_bounds__(256) void k_attn_small(const float* __restrict__ qk
         lacc[h] = HF::mfma(ones, pf[h][pc], lacc[h]);
       }
     }
+    if (kv0 + 31 > p_last) {
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vf[dt][e] &= column_mask((int)p_last - (int)(kv0 + g * 8), e);
+    }
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt)
 #pragma unroll

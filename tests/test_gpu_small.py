@@ -522,23 +522,29 @@ def test_attention_scores_ruled_by_the_last_head_dims(nnc, turns, attn):
 
 
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
-@pytest.mark.parametrize("turns", [(657,), (700, 900), (1600, 60)], ids=str)
-def test_wide_attention_never_meets_rows_past_its_tokens(nnc, turns, dtype):
-    """A prompt whose rows are NaN from position 600 on, then others on the same slot: the same bits as on a model that never saw
-    the first, whatever the transposed V copy and the cache still hold past the new tokens (whole 64-position chunks of it
+@pytest.mark.parametrize("heads,turns,attn", [
+    (16, (657,), -1), (16, (700, 900), -1), (16, (1600, 60), -1),       # 32 x 32 products, one and two pieces
+    (4, (40,), -1), (4, (37, 90), -1), (4, (600,), 0), (4, (700,), 1), (4, (600,), 2), (4, (700,), 3),
+    (16, (330,), 0), (16, (330,), 2)], ids=str)
+def test_prompt_attention_never_meets_rows_past_its_tokens(nnc, heads, turns, attn, dtype):
+    """A prompt whose rows are NaN from position 30 on, then others on the same slot: the same bits as on a model that never saw
+    the first, whatever the transposed V copy and the cache still hold past the new tokens (whole chunks of positions
     are read, with weights of zero)."""
-    print(f"case: prompts {turns} behind one of NaN rows, dtype {dtype}", flush=True)
-    shape = dataclasses.replace(HEADS16, dtype=dtype)
+    print(f"case: prompts {turns} behind one of NaN rows, {heads} heads, attention {attn}, dtype {dtype}", flush=True)
+    shape = dataclasses.replace(HEADS16 if heads == 16 else SMALL_BF16, dtype=dtype)
     blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
     synth.blob_tensor(shape, blob, "embed")[1023] = 0x7f80 if dtype == synth.BF16 else 0x7c00    # infinity
     bad = synth.tokens(1700, 1023, stream=5)
-    bad[600] = 1023
+    bad[30] = 1023
     out = []
     for dirty in (True, False):
         g = nnc.Model(shape, blob, 1, 1700)
+        g.set_option(nnc.OPT_PREFILL_ATTN, attn)
+        if heads == 16 and turns == (330,):
+            g.set_option(nnc.OPT_PLANNER, 0)                           # (no short-block attention)
         if dirty:
             g.prefill(0, bad, want_logits=False)
-            assert np.isnan(g.kv_read(1, 0, 1, 600, 1000).cpu().numpy()).all()
+            assert np.isnan(g.kv_read(1, 0, 1, 30, 1600).cpu().numpy()).all()
             g.kv_reset()
         for i, n in enumerate(turns):
             g.prefill(0, synth.tokens(n, 1023, stream=6 + i), want_logits=False)
