@@ -448,51 +448,80 @@ HEADS16 = synth.ModelShape("heads16", hidden=256, n_layers=2, n_q_heads=16, n_kv
 
 
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
-@pytest.mark.parametrize("n,max_seq", [(530, 546), (641 + 16, 700), (768 + 16, 1000), (1155, 1155)])
-def test_block_attention_on_wide_products(nnc, n, max_seq, dtype):
-    """Single-piece blocks on the 32 x 32 attention: just over its smallest launch, one token past a 128-token block, whole
-    blocks (both halves of the launch), a cache that ends inside the last chunk; and a second block that starts
-    mid-context.  Against the oracle, and against the 16 x 16 kernel (forced), which rounds the same values."""
-    print(f"case: 32 x 32 prompt attention, {n} tokens of {max_seq}, dtype {dtype}", flush=True)
+@pytest.mark.parametrize("turns,max_seq", [((530,), 540), ((530,), 546), ((641 + 16,), 700), ((768 + 16,), 1000), ((1155,), 1155),
+                                           ((657, 577), 1234), ((101, 545), 646)], ids=str)
+def test_block_attention_on_wide_products(nnc, turns, max_seq, dtype):
+    """Single-piece blocks on the 32 x 32 attention: just over its smallest launch, with a cache (540, 546) and a transposed V
+    copy (540: 544 columns) that end inside the last 64-position chunk, one token past a 128-token block, whole blocks (both halves
+    of the launch), a full cache, and turns that start at odd positions.  Against the oracle, and against the
+    16 x 16 kernel (forced), which rounds the same values."""
+    print(f"case: 32 x 32 prompt attention, turns {turns} of {max_seq}, dtype {dtype}", flush=True)
     shape = dataclasses.replace(HEADS16, dtype=dtype)
     g, o = _pair(nnc, shape, 1, max_seq, exact_prefill=False)
-    toks = synth.tokens(n, shape.vocab, stream=700 + n)
-    lg, ng = g.prefill(0, toks)
-    lo, no = oracle_prefill_like_library(o, 0, toks, shape)
-    _check_logits(shape, lg, lo, BF16_ABS_PROMPT)
-    assert int(ng.item()) == no
+    prompts = [synth.tokens(n, shape.vocab, stream=700 + n) for n in turns]
+    assert len(turns) == 1 or (turns[0] % 2 == 1 and turns[1] - 16 > 512)
+    got = []
+    for toks in prompts:
+        lg, ng = g.prefill(0, toks)
+        lo, no = oracle_prefill_like_library(o, 0, toks, shape)
+        _check_logits(shape, lg, lo, BF16_ABS_PROMPT)
+        assert int(ng.item()) == no
+        got.append(lg.cpu().numpy())
     g.kv_reset(0)
     g.set_option(nnc.OPT_PREFILL_ATTN, 0)
-    l2, _ = g.prefill(0, toks)
-    assert not np.array_equal(l2.cpu().numpy(), lg.cpu().numpy())      # the other kernel ran
-    _check_logits(shape, l2, lg.double().cpu().numpy(), BF16_ABS_PROMPT)
+    for toks, lg in zip(prompts, got):
+        l2, _ = g.prefill(0, toks)
+        if len(toks) > 512:
+            assert not np.array_equal(l2.cpu().numpy(), lg)            # the other kernel ran
+        _check_logits(shape, l2, lg, BF16_ABS_PROMPT)
+
+
+def _attention_splits(shape, pos0, n, max_seq, cus=256):
+    """Workgroups over the positions of a two-piece turn of 16 query heads, as the library documents them: as many as fit the chip
+    twice, each with at least 320 positions, at most 8, and no more records of 132 floats than the three k-slice
+    buffers of a whole block hold."""
+    room = 3 * min(4096, -(-max_seq // 128) * 128) * shape.hidden
+    return min(2 * cus // (-(-n // 128) * 16), 8, (pos0 + n) // 320, room // (n * 16 * 132))
 
 
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
-@pytest.mark.parametrize("pos0,n,max_seq", [(1599, 9, 1700), (1700, 16, 1716), (1650, 129, 2000), (2000, 333, 2400), (1601, 500, 2101)])
-def test_block_attention_with_split_positions(nnc, pos0, n, max_seq, dtype):
-    """Second turns behind a long context, their positions split over workgroups: the fewest tokens, a cache that ends inside
-    a chunk, one token past a 128-token block, splits that see nothing of the first tokens.  Against the same turn
-    through the 16 x 16 kernel: both carry two pieces, so they agree as closely as two orders of an fp32 sum do."""
-    print(f"case: split prompt attention, {n} tokens behind {pos0} of {max_seq}, dtype {dtype}", flush=True)
-    shape = dataclasses.replace(HEADS16, dtype=dtype)
-    g, _ = _pair(nnc, shape, 1, max_seq, exact_prefill=False)
+@pytest.mark.parametrize("hidden,pos0,n,max_seq,splits", [
+    (256, 1599, 9, 1700, 5), (256, 1700, 16, 1716, 5), (256, 1650, 129, 2000, 5), (256, 2000, 333, 2400, 2),
+    (1024, 1601, 500, 2101, 6), (1024, 2000, 333, 2400, 7), (256, 2453, 108, 2600, 8)])
+def test_block_attention_with_split_positions(nnc, hidden, pos0, n, max_seq, splits, dtype):
+    """Second turns behind a long context, their positions split over 2 to 8 workgroups: the fewest tokens, a cache that ends
+    inside a chunk, one token past a 128-token block, four token blocks, and (108 tokens behind 2453) a last split of which the
+    first tokens see nothing.  Against the same turn through the 16 x 16 kernel: both carry two pieces, so they agree as
+    closely as two orders of an fp32 sum do, but not to the bit; and the 8 splits against the oracle."""
+    print(f"case: split prompt attention, {n} tokens behind {pos0} of {max_seq}, hidden {hidden}, dtype {dtype}", flush=True)
+    shape = dataclasses.replace(HEADS16, hidden=hidden, dtype=dtype)
+    assert _attention_splits(shape, pos0, n, max_seq) == splits
+    if splits == 8:                                                    # the last split's first position
+        chunks = (pos0 + n - 1) // 32 + 1
+        assert pos0 < 7 * -(-chunks // 8) * 32 < pos0 + n
+    g, o = _pair(nnc, shape, 1, max_seq, exact_prefill=False)
     first, more = synth.tokens(pos0, shape.vocab, stream=71), synth.tokens(n, shape.vocab, stream=72)
     out = []
-    for attn in (-1, 0):
+    for attn, planner in ((-1, 1), (0, 1), (0, 0)):                     # (0, 1): the short-block attention where it is the choice
         g.kv_reset(0)
         g.set_option(nnc.OPT_PREFILL_ATTN, 0)
         g.prefill(0, first, want_logits=False)
         g.set_option(nnc.OPT_PREFILL_ATTN, attn)
-        if attn == 0:
-            g.set_option(nnc.OPT_PLANNER, 0)                           # (the short-block attention stays out of it)
+        g.set_option(nnc.OPT_PLANNER, planner)
         lg, nx = g.prefill(0, more)
         kv = [g.kv_read(1, 0, w, pos0, n).cpu().numpy() for w in (0, 1)]
         out.append((lg.double().cpu().numpy(), int(nx.item()), kv))
-    (l0, n0, k0), (l1, n1, k1) = out
-    assert np.isfinite(l0).all() and np.abs(l0 - l1).max() <= BF16_ABS_TIGHT and n0 == n1
-    for a, b in zip(k0, k1):
-        assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
+    l0, n0, k0 = out[0]
+    assert np.isfinite(l0).all()
+    assert not np.array_equal(l0, out[1][0])                           # another kernel, the same everywhere else
+    for l1, n1, k1 in out[1:]:
+        assert np.abs(l0 - l1).max() <= BF16_ABS_TIGHT and n0 == n1
+        for a, b in zip(k0, k1):
+            assert np.all(np.abs(a - b) <= np.abs(b) * 2.0 ** -7 + 3e-3)
+    if splits == 8:
+        oracle_prefill_like_library(o, 0, first, shape)
+        lo, _ = oracle_prefill_like_library(o, 0, more, shape)
+        assert np.abs(l0 - lo).max() <= BF16_ABS_PROMPT
 
 
 @pytest.mark.parametrize("turns,attn", [((657,), -1), ((657,), 0), ((1600, 60), -1), ((1600, 60), 1)], ids=str)
