@@ -32,6 +32,8 @@
 #include "nnc_internal.h"
 #include "nnc_lanes.h"
 
+#include <type_traits>
+
 namespace nnc {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -185,7 +187,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
 
   // A chunk.  Fragment reads are issued well before the products that use them, and kept there by scheduling barriers:
   // left alone the compiler reads two fragments, waits for them, multiplies, and pays the LDS latency eight times.
-  auto do_chunk = [&](int buf, uint32_t kv0) __attribute__((always_inline)) {
+  // DIAGONAL: the chunk reaches past the workgroup's first token, and may reach past the wave's.
+  auto do_chunk = [&](auto diagonal, int buf, uint32_t kv0) __attribute__((always_inline)) {
+    constexpr bool DIAGONAL = decltype(diagonal)::value;
     f32x16 sc[SUB];
     u32x4 vf[2][4];  // V^T fragments of two 16-position steps
     auto read_v = [&](int st, u32x4(&v)[4]) __attribute__((always_inline)) {
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (kv0 + CH - 1 > p_first) {  // the chunk reaches past the wave's first token: mask per lane
+    if (DIAGONAL && kv0 + CH - 1 > p_first) {  // mask per lane
 #pragma unroll
       for (int s = 0; s < SUB; ++s)
 #pragma unroll
@@ -256,6 +260,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
 #pragma unroll
     for (int st = 0; st < 2 * SUB; ++st) {
       const int s = st >> 1, ps = st & 1;
+      if (DIAGONAL && kv0 + st * 16 > p_last) break;  // none of the wave's tokens sees these positions
       if (st + 1 < 2 * SUB) read_v(st + 1, vf[(st + 1) & 1]);
       uint32_t pw[PIECES][4];
 #pragma unroll
@@ -274,12 +279,16 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (kv0 + st * 16 + 15 > p_last) {
-        const int keep = (int)p_last - (int)(kv0 + st * 16 + hf * 8);
+      if constexpr (DIAGONAL) {
+        if (kv0 + st * 16 + 15 > p_last) {
+          const int keep = (int)p_last - (int)(kv0 + st * 16 + hf * 8);
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t m = column_mask(keep, e);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) vf[st & 1][dt][e] &= column_mask(keep, e);
+            for (int dt = 0; dt < 4; ++dt) vf[st & 1][dt][e] &= m;
+          }
+        }
       }
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
@@ -298,11 +307,18 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
     copy(kv_begin, 0);
     copied();
     int buf = 0;
-    for (uint32_t kv0 = kv_begin; kv0 < kv_end; kv0 += CH, buf ^= 1) {
-      if (kv0 + CH < kv_end) copy(kv0 + CH, buf ^ 1);  // (uniform over the workgroup)
-      if (active && kv0 <= p_last) do_chunk(buf, kv0);
-      copied();
-    }
+    uint32_t kv0 = kv_begin;
+    auto chunks_to = [&](auto diagonal, uint32_t end) __attribute__((always_inline)) {
+      for (; kv0 < end; kv0 += CH, buf ^= 1) {
+        if (kv0 + CH < kv_end) copy(kv0 + CH, buf ^ 1);  // (uniform over the workgroup)
+        if (active && kv0 <= p_last) do_chunk(diagonal, buf, kv0);
+        copied();
+      }
+    };
+    // whole chunks that every token of the workgroup sees, then the others
+    const uint32_t seen = (pos0 + (uint32_t)(tb * AB_TOKENS) + 1) / CH * CH;
+    chunks_to(std::false_type{}, min(seen, kv_end));
+    chunks_to(std::true_type{}, kv_end);
   }
   if (!active || t0 + r32 >= n) return;
   const float l = lrun + __shfl_xor(lrun, 32, 64);
