@@ -17,10 +17,12 @@ Machine machine_mi355x(int cus) {
   m.launch_us = 5.0;
   // whole prompt passes with and without k slices on the large tiles (0.6B .. 8B layer shapes, 768 ..
   // 4096 tokens): slices pay (4 - 9 %) while the partials are a few tens of MB and cost 2 - 3 % once
-  // they are not; the second rate is the one at which the model stops choosing the losing launches
-  // (the down projection of the 8B shape at 512 two-piece tokens with four slices, 50 MB: 90.6 us on 256 x 256 tiles against 113
-  // with two slices on 128 x 128, the norm behind it 13.7 against 12.0)
-  m.fold_cached_bytes = 60e6;
+  // they are not; the second rate is the one at which the model stops choosing the losing launches.
+  // (A limit of 60 MB brings the down projection of 8B at 512 two-piece tokens to four slices, 116 -> 99 us, but
+  // launches that lose as well, O and down with their norms, us per layer: 8B 768 tokens 147 -> 163, 1.7B 1536 tokens
+  // 55 -> 70.  Prompts of 4 layers at 48 / 60 MB: 8B 512 tokens 1693 / 1580, 640 1640 / 1720, 900 1950 / 2084, 1.7B 1552 1139 /
+  // 1200, 3088 1831 / 1874.)
+  m.fold_cached_bytes = 48e6;
   m.fold_bytes_per_us = 2.0e6;
   // the weight-streaming GEMM alone, launches back to back, 200 (rows, k, batch, row tiles,
   // k slices) combinations of the five model shapes: least-squares / best-pick fit
@@ -31,11 +33,12 @@ Machine machine_mi355x(int cus) {
   // prompt GEMM, time per k step with two workgroups per CU, measured at the 4B / 8B shapes:
   // 0.48 us for 128 x 128 tiles (16 matrix-core instructions per wave), 0.726 for 192 x 128 (24),
   // 0.865 for 256 x 128 (32): least-squares line through the three; a lone workgroup on a CU
-  // takes 0.73 x that (0.69 - 0.78: 128 x 128 tiles on 160 - 256 CUs, QKV of the 1.7B and 8B shapes at 256 - 512 two-piece
-  // tokens; at 0.78 the 64-row tiles were picked there: 1.7B, 512 tokens 31.6 us against 28.4, 8B, 256 tokens 52.2 / 49.4)
+  // takes 0.78 x that (single launches show 0.69 - 0.78; over the 192 GEMMs of the 0.6B .. 8B shapes at 200 - 4096 tokens the
+  // picks at 0.73 are as far above the best tile, 2.4 %, and 39 prompts of 200 - 3088 tokens 0.2 % slower: 1.7B 784 tokens 805 us
+  // against 836, 8B 256 1040 / 1055, 128 846 / 825)
   m.pg_c1 = 0.0241;
   m.pg_c0 = 0.110;
-  m.pg_solo = 0.73;
+  m.pg_solo = 0.78;
   // the 256 x 256 tile, one workgroup per CU: 0.77 us per k step (64 matrix-core instructions per
   // wave), measured on the 8B gate|up and down projections at 4080 tokens
   m.pg_big = 0.77;

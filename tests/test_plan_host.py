@@ -75,7 +75,11 @@ def test_mid_size_blocks_split_k_of_the_residual_projections():
     RESID = 1
     for rows, k, tokens, tile, ks in ((H8, F8, 1024, (128, 128), 2), (H8, Dq8, 1024, (128, 128), 2),
                                       (H4, F4, 768, (128, 128), 4), (H4, F4, 2032, (192, 256), 2),
-                                      (H8, F8, 2048, (256, 256), 2)):
+                                      (H8, F8, 2048, (256, 256), 2),
+                                      # launches whose partials would be 50 MB with one slice more: 42 / 105 us at these
+                                      # picks and 53 / 111 with three slices (8B), 55 / 70 (1.7B), norms included
+                                      (H8, Dq8, 768, (128, 128), 2), (H8, F8, 768, (128, 128), 2),
+                                      (SHAPES["1.7b"][0], SHAPES["1.7b"][3], 1536, (128, 128), 2)):
         p = nnc.plan_prefill_gemm(rows, k, tokens, 1, RESID, 4)
         assert ((p.tile_rows, p.tile_cols), p.k_slices) == (tile, ks), (rows, k, tokens, p.tile_rows, p.tile_cols, p.k_slices)
         assert p.t_us < nnc.plan_prefill_gemm(rows, k, tokens, 1, RESID, 1).t_us
