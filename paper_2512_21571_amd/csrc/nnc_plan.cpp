@@ -180,8 +180,11 @@ SmallGemmPlan plan_small_gemm(const Machine& mc, int epi, int n_tiles, int KT, i
     // the matrix-core time, the weights from HBM; an epilogue per workgroup; launch
     const double t_cu = rounds * bytes / 100e3;
     const double t_mfma = (double)rounds * KT * xt * nt * ct / 4 * 16 / 2200.0;
-    // (a launch of several rounds starts cold streams several times: 4B gate|up at 24 tokens 37 us in five rounds, 38 in
-    // two, 28 in one)
+    // (Every round starts cold streams anew.  A slope, not a step at the second round: it has to tell one round from
+    // two and two from ten.  Every tile forced in turn at 55 prompt shapes (0.6B .. 8B, bf16, binary16, bytes, 9 - 512 tokens):
+    // the picks' GEMM time is 2.9 % above the best tiles' without the term, 2.1 % with it (any slope of 0.05 - 0.3), 2.8 - 3.3 %
+    // with a step of 0.1 - 0.6.  gate|up of 4B, us and rounds by tile (rows / 16 x columns / 16): 24 tokens 2 x 2 38.6 in 5, 4 x 2
+    // 40.8 in 3, 4 x 4 35.3 in 2, 6 x 4 28.2 in 1; 64 tokens 60.4 in 10, 55.9 in 5, 46.0 in 3, 42.8 in 2.)
     const double t_hbm = (double)n_tiles * KT * 1024.0 / mc.hbm_bytes_per_us * (1.0 + 0.1 * (rounds - 1));
     const double total = std::max(std::max(t_cu, t_mfma), t_hbm) + 0.15 * nt * ct / 2 * rounds + 3.0;
     if (total < best.t_us) {
