@@ -81,9 +81,11 @@ def counter_traffic(workload: str, kernel: str, decode_steps: int):
 # the block-tile prompt GEMM: the 256 x 256 tile kernel (k_gemm_prefill_big) or the 256 / 192 / 128 x 128 one
 # (k_gemm_prefill_dl), chosen per launch by the library's tile chooser; timed together as one family
 PG_KERNELS = "k_gemm_prefill_big|k_gemm_prefill_dl"
+# prompt attention: k_attn_block from 80 workgroups of 128 tokens on, else k_attn_prefill or (short blocks) k_attn_small
+PA_KERNELS = "k_attn_block|k_attn_prefill|k_attn_small"
 KERNEL_OF_FAMILY = {"gemm_skinny": "k_gemm_skinny", "attn_partial": "k_attn_partial_mc",
                     "rmsnorm_pack": "k_rmsnorm_pack", "attn_combine": "k_attn_combine",
-                    "gemm_prefill": PG_KERNELS, "attn_prefill": "k_attn_prefill"}
+                    "gemm_prefill": PG_KERNELS, "attn_prefill": PA_KERNELS}
 GOLDEN = {"qwen3-4b-bf16-b1-c2048-d128": "cfg3", "qwen3-4b-bf16-b8-c2048-d128": "cfg3",
           "qwen3-8b-bf16-b16-c4096-d128": "cfg4"}
 

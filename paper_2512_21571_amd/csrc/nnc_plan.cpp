@@ -34,7 +34,7 @@ Machine machine_mi355x(int cus) {
   // 0.48 us for 128 x 128 tiles (16 matrix-core instructions per wave), 0.726 for 192 x 128 (24),
   // 0.865 for 256 x 128 (32): least-squares line through the three; a lone workgroup on a CU
   // takes 0.78 x that (single launches show 0.69 - 0.78; over the 192 GEMMs of the 0.6B .. 8B shapes at 200 - 4096 tokens the
-  // picks at 0.73 are as far above the best tile, 2.4 %, and 39 prompts of 200 - 3088 tokens 0.2 % slower: 1.7B 784 tokens 805 us
+  // picks at 0.73 are as far above the best tile, 2.4 %, and 43 prompts of 128 - 3088 tokens 0.2 % slower: 1.7B 784 tokens 805 us
   // against 836, 8B 256 1040 / 1055, 128 846 / 825)
   m.pg_c1 = 0.0241;
   m.pg_c0 = 0.110;
