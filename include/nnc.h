@@ -255,12 +255,18 @@ typedef enum {
   NNC_OPT_PREFILL_KSLICES = 13, /* with a forced NNC_OPT_PREFILL_TILE: k slices (1 .. 4) of the output and
                                down projections of a large prompt block, 0 (default): by the rule above.
                                Without a forced tile the tile model picks tile and slices together */
-  NNC_OPT_PREFILL_ATTN = 6, /* launch shape of the large-block prompt attention: -1 (default) chosen
-                               from each launch's size; else bit 0: every workgroup takes a long
-                               and a short 64-token block, bit 1: two query heads per wave; results
-                               are bit-identical for all (a wave's arithmetic per head is the same).
-                               Short blocks with few workgroups use a kernel of their own, whatever
-                               this says, while NNC_OPT_PLANNER is 1 */
+  NNC_OPT_PREFILL_ATTN = 6, /* attention of large prompt blocks.  0 .. 3: the kernel of 16 x 16 products, bit 0:
+                               every workgroup takes a long and a short 64-token block, bit 1: two query
+                               heads per wave; bit-identical for 0 .. 3 (a wave's arithmetic per head is the
+                               same).  -1 (default): chosen from each launch's size: that kernel, or, while
+                               NNC_OPT_PLANNER is 1, one of 32 x 32 products for blocks of one piece with at least
+                               80 pairs of (128 tokens, query head), and for two-piece blocks that end at position
+                               1600 or later and leave compute units idle, their positions split over up to 8
+                               workgroups.  Its results differ from those of 0 .. 3: with one piece the
+                               softmax weights are rounded to 16 bits against another running maximum, with two
+                               the sums run in another order.
+                               Short blocks with few workgroups that -1 does not split use a kernel of their
+                               own, whatever this says, while NNC_OPT_PLANNER is 1 */
   NNC_OPT_FUSE_QK = 7,      /* 1 (default): per-stage decode passes of bf16 models do QK-norm, RoPE and
                                the cache append inside the attention kernel (one kernel less per
                                layer); 0: in a kernel of their own.  Bit-identical results */

@@ -315,7 +315,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(const float* __restrict__
         copied();
       }
     };
-    // whole chunks that every token of the workgroup sees, then the others
+    // Whole chunks that every token of the workgroup sees, then the others.  (One loop with the column mask in it costs a 4B
+    // prompt of 1040 tokens, 4 layers, 1 %: 1443 us without a mask, 1458 so, 1449 as it is.)
     const uint32_t seen = (pos0 + (uint32_t)(tb * AB_TOKENS) + 1) / CH * CH;
     chunks_to(std::false_type{}, min(seen, kv_end));
     chunks_to(std::true_type{}, kv_end);

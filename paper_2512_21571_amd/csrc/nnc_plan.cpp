@@ -18,11 +18,12 @@ Machine machine_mi355x(int cus) {
   // whole prompt passes with and without k slices on the large tiles (0.6B .. 8B layer shapes, 768 ..
   // 4096 tokens): slices pay (4 - 9 %) while the partials are a few tens of MB and cost 2 - 3 % once
   // they are not; the second rate is the one at which the model stops choosing the losing launches.
-  // (A limit of 60 MB brings the down projection of 8B at 512 two-piece tokens to four slices, 116 -> 99 us, but
-  // launches that lose as well, O and down with their norms, us per layer: 8B 768 tokens 147 -> 163, 1.7B 1536 tokens
-  // 55 -> 70.  Prompts of 4 layers at 48 / 60 MB: 8B 512 tokens 1693 / 1580, 640 1640 / 1720, 900 1950 / 2084, 1.7B 1552 1139 /
-  // 1200, 3088 1831 / 1874.)
+  // A limit of 60 MB for every block picks launches that lose, O and down with their norms, us per layer: 8B 768 tokens
+  // 147 -> 163, 1.7B 1536 55 -> 70 (prompts of 4 layers: 8B 640 tokens 1640 -> 1720, 900 1950 -> 2084, 1.7B 3088 1831 -> 1874).
+  // Two-piece blocks of up to 512 tokens have it: there only O and down of 4096-wide models at 489 - 512 tokens lie
+  // between, with four slices (8B 512: down 116 -> 99, O 46 -> 48, the prompt 1693 -> 1580)
   m.fold_cached_bytes = 48e6;
+  m.fold_cached_short_bytes = 60e6;
   m.fold_bytes_per_us = 2.0e6;
   // the weight-streaming GEMM alone, launches back to back, 200 (rows, k, batch, row tiles,
   // k slices) combinations of the five model shapes: least-squares / best-pick fit
@@ -33,12 +34,15 @@ Machine machine_mi355x(int cus) {
   // prompt GEMM, time per k step with two workgroups per CU, measured at the 4B / 8B shapes:
   // 0.48 us for 128 x 128 tiles (16 matrix-core instructions per wave), 0.726 for 192 x 128 (24),
   // 0.865 for 256 x 128 (32): least-squares line through the three; a lone workgroup on a CU
-  // takes 0.78 x that (single launches show 0.69 - 0.78; over the 192 GEMMs of the 0.6B .. 8B shapes at 200 - 4096 tokens the
-  // picks at 0.73 are as far above the best tile, 2.4 %, and 43 prompts of 128 - 3088 tokens 0.2 % slower: 1.7B 784 tokens 805 us
-  // against 836, 8B 256 1040 / 1055, 128 846 / 825)
+  // takes 0.73 x that (single launches show 0.69 - 0.78), 0.78 in one-piece residual projections, whose epilogue reads and
+  // writes twice the outputs per tile with no other workgroup to hide it.  Over the 192 GEMMs of the 0.6B .. 8B shapes at 200 - 4096 tokens
+  // the picks are 2.22 % above the best tiles in the sum, 31 in 1000 in the mean (0.78 throughout: 2.35 %, 35; 0.73: 2.36 %, 35).  us, 0.78 / 0.73:
+  // QKV of 1.7B at 512 tokens 29.3 / 28.1, of 8B at 320 51.5 / 48.8, at 256 45.7 / 48.7, down of 4B at 256 47.7 / 44.4; O of 1.7B at 768 21.6 /
+  // 25.1, of 0.6B 17.6 / 19.7.
   m.pg_c1 = 0.0241;
   m.pg_c0 = 0.110;
-  m.pg_solo = 0.78;
+  m.pg_solo = 0.73;
+  m.pg_solo_resid1 = 0.78;
   // the 256 x 256 tile, one workgroup per CU: 0.77 us per k step (64 matrix-core instructions per
   // wave), measured on the 8B gate|up and down projections at 4080 tokens
   m.pg_big = 0.77;
@@ -103,12 +107,13 @@ PrefillGemmPlan plan_prefill_gemm(const Machine& mc, int n_tiles, int KT, int co
       const double t2 = wgs_per_cu == 1 ? (t.nt == 16 ? mc.pg_big : mc.pg_big12)
                         : t.lds_direct  ? mc.pg_c0 + mc.pg_c1 * wi * wj
                                         : mc.rg_c0 + mc.rg_c1 * wi * wj;
-      const double t1 = mc.pg_solo * t2;
+      const double t1 = (epi == PLAN_EPI_RESID && pieces == 1 ? mc.pg_solo_resid1 : mc.pg_solo) * t2;
       const double t_comp = wgs_per_cu == 1 ? kts * t2 * (full + (rem ? 1 : 0))
                                             : kts * (full * t2 + (rem == 0 ? 0.0 : rem <= mc.cus ? t1 : t2));
       const double fold = (slices - 1) * n_tokens * N * 4.0 * 2.0;  // partials written, then read by the norm kernel
       const double t_mem = (W + X) / mc.hbm_bytes_per_us;
-      const double t_fold = fold / (fold <= mc.fold_cached_bytes ? mc.hbm_bytes_per_us : mc.fold_bytes_per_us);
+      const double cached = pieces == 2 && n_tokens <= 512 ? mc.fold_cached_short_bytes : mc.fold_cached_bytes;
+      const double t_fold = fold / (fold <= cached ? mc.hbm_bytes_per_us : mc.fold_bytes_per_us);
       const double total = std::max(t_comp, t_mem) + out_bytes / mc.hbm_bytes_per_us + t_fold + mc.launch_us;
       if (total < best.t_us * 0.999) {
         best.tile = t.code; best.nt = t.nt; best.tt = t.tt;

@@ -29,7 +29,7 @@ struct Machine {
   double launch_us;       // start-to-end time of a kernel with nothing to do
   // k-slice partials of a prompt GEMM (written by its epilogue, read back by the next norm kernel):
   // at the streaming rate while all of them stay in the caches, at fold_bytes_per_us beyond that
-  double fold_cached_bytes, fold_bytes_per_us;
+  double fold_cached_bytes, fold_cached_short_bytes, fold_bytes_per_us;
   // the weight-streaming GEMM of decode passes: streaming rate of the whole chip, bytes a CU moves
   // through its vector memory path (weights + operand), launch-to-launch overhead, one round of
   // the cross-wave reduction in the epilogue
@@ -37,7 +37,7 @@ struct Machine {
   // micro-kernel regression of the LDS-staged prompt GEMM, per k step of 32 with two workgroups per
   // CU: c0 + c1 * (matrix-core instructions per wave and k step) microseconds; one workgroup
   // alone on a CU takes `solo` times that
-  double pg_c0, pg_c1, pg_solo;
+  double pg_c0, pg_c1, pg_solo, pg_solo_resid1;  // (resid1: one-piece residual projections)
   double pg_big, pg_big12;  // microseconds per k step of the 256 x 256 / 192 x 256 tile (one workgroup per CU)
   double rg_c0, rg_c1;  // the same regression for the register-ring kernel of the 64-row tiles
 };

@@ -861,6 +861,9 @@ hipError_t launch_v_transpose(hipStream_t s, const void* vc, uint32_t slot, int 
 // taken as zero (column_mask).
 // PIECES = 2: queries and weights enter the matrix cores as two bf16 pieces (16 significant
 // bits); PIECES = 1: one bf16 each.  The row sum adds the weights as they are multiplied.
+// With one piece it serves models of fewer than 16 query heads (fewer than 80 workgroups of k_attn_block), forced launch shapes
+// (NNC_OPT_PREFILL_ATTN) and NNC_OPT_PLANNER 0; models of 16 or 32 heads meet it with two pieces only: blocks too large
+// for k_attn_small that do not end far enough out for k_attn_block to split them.
 template <int GH, int PIECES, class HF>
 __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float* __restrict__ qkv, int nq, int nkv,
                                                          const uint16_t* __restrict__ kc,
