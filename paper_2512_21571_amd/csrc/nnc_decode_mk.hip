@@ -1305,7 +1305,8 @@ __global__ __launch_bounds__(MK_THREADS, 1) void k_decode_resident(MkArgs a) {
     stamp(step);  // token known
   }
 
-  // all winners are in, so every workgroup has read every vector: leave the untagged words empty
+  // All winners are in, so every workgroup has read every vector: leave the untagged words empty.  (The winners' tags tell this
+  // launch's from earlier ones; a replay would not have tags of its own, so a launch is never captured by a caller.)
   for (int r = 0; r < MK_ROT; ++r) {
     if (tid < 128)
       for (int h = nwg - 1 - wg_att; h < ns * nq; h += nwg) st_empty(a.xo + r * a.s_o + (size_t)h * 128 + tid);
