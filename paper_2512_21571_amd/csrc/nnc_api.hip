@@ -1459,7 +1459,7 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       if (nnc_status st_ = weights_of(a, L.wqkv, L.sqkv, Nqkv, H)) return st_;
       a.n_tiles = Nqkv / 16; a.KT = H / 32; a.Xf = m->pb_fa; a.t_tiles = ct;
       a.out = m->pb_qkv; a.ldo = Nqkv;
-      RUN(FAM_PGEMM, (double)Nqkv * H * w, 2.0 * Nqkv * H * T, launch_gemm_prefill(s, f16, EPI_STORE, a, pieces, plan_gemm(a, EPI_STORE, nullptr)));
+      RUN(FAM_PGEMM, (double)Nqkv * H * w, 2.0 * Nqkv * H * T, launch_gemm_prefill(s, f16, EPI_STORE, a, pieces, plan_gemm(a, EPI_STORE, nullptr), m->n_cus));
     }
     {
       // Transposed copy of the V rows of earlier calls and blocks, from the cache.  Before the append
@@ -1487,7 +1487,7 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       a.n_tiles = H / 16; a.KT = Dq / 32; a.Xf = m->pb_fb; a.t_tiles = ct;
       a.out = m->pb_x; a.ldo = H;
       const int shape = plan_gemm(a, EPI_RESID, &pending);
-      RUN(FAM_PGEMM_O, (double)H * Dq * w, 2.0 * H * Dq * T, launch_gemm_prefill(s, f16, EPI_RESID, a, pieces, shape));
+      RUN(FAM_PGEMM_O, (double)H * Dq * w, 2.0 * H * Dq * T, launch_gemm_prefill(s, f16, EPI_RESID, a, pieces, shape, m->n_cus));
     }
     RUN(FAM_NORM, T * H * 6.0, 0, launch_rmsnorm_frag(s, f16, m->pb_x, m->pb_part, pending, part_stride, L.g_post, H, c.rms_eps, (int)n, tt, pieces, m->pb_fa));
     {
@@ -1495,7 +1495,7 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       if (nnc_status st_ = weights_of(a, L.wgu, L.sgu, 2 * F, H)) return st_;
       a.n_tiles = 2 * F / 16; a.KT = H / 32; a.Xf = m->pb_fa; a.t_tiles = ct;
       a.packed_out = m->pb_fb;
-      RUN(FAM_PGEMM_GU, 2.0 * F * H * w, 4.0 * F * H * T, launch_gemm_prefill(s, f16, EPI_SWIGLU, a, pieces, plan_gemm(a, EPI_SWIGLU, nullptr)));
+      RUN(FAM_PGEMM_GU, 2.0 * F * H * w, 4.0 * F * H * T, launch_gemm_prefill(s, f16, EPI_SWIGLU, a, pieces, plan_gemm(a, EPI_SWIGLU, nullptr), m->n_cus));
     }
     {
       PrefillGemmArgs a{};
@@ -1503,7 +1503,7 @@ static nnc_status prefill_block(nnc_model* m, uint32_t slot, const int32_t* toke
       a.n_tiles = H / 16; a.KT = F / 32; a.Xf = m->pb_fb; a.t_tiles = ct;
       a.out = m->pb_x; a.ldo = H;
       const int shape = plan_gemm(a, EPI_RESID, &pending);
-      RUN(FAM_PGEMM_D, (double)H * F * w, 2.0 * H * F * T, launch_gemm_prefill(s, f16, EPI_RESID, a, pieces, shape));
+      RUN(FAM_PGEMM_D, (double)H * F * w, 2.0 * H * F * T, launch_gemm_prefill(s, f16, EPI_RESID, a, pieces, shape, m->n_cus));
     }
   }
   return want_head ? prefill_head(m, n, pending, logits_out, next_dev) : NNC_OK;

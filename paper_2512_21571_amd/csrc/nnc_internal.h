@@ -190,7 +190,7 @@ struct PrefillGemmArgs {
   float* part = nullptr;
   long part_stride = 0;
 };
-hipError_t launch_gemm_prefill(hipStream_t s, bool f16, int epi, const PrefillGemmArgs& a, int pieces, int shape);
+hipError_t launch_gemm_prefill(hipStream_t s, bool f16, int epi, const PrefillGemmArgs& a, int pieces, int shape, int n_cus);
 
 // ---- prompt GEMMs of short blocks (two pieces per activation; nnc_small.hip) ----
 // Y[t, n] = sum_k X[t, k] W[n, k], X in fragment order with two pieces per activation, W packed

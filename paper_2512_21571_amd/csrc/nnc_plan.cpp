@@ -46,6 +46,7 @@ Machine machine_mi355x(int cus) {
   // the 256 x 256 tile, one workgroup per CU: 0.77 us per k step (64 matrix-core instructions per
   // wave), measured on the 8B gate|up and down projections at 4080 tokens
   m.pg_big = 0.77;
+  m.pg_half = 0.547;  // a last round of its 128 x 256 halves (0.65 - 0.79 of the whole block's time as the only round)
   m.pg_big12 = 0.62;  // the 192 x 256 tile (48 per wave): the 8B QKV projection
   // the register-ring kernel of the 64-row tiles: 0.26 us per k step with 4 matrix-core
   // instructions per wave (64 x 64), 0.37 with 8 (64 x 128)
@@ -108,7 +109,8 @@ PrefillGemmPlan plan_prefill_gemm(const Machine& mc, int n_tiles, int KT, int co
                         : t.lds_direct  ? mc.pg_c0 + mc.pg_c1 * wi * wj
                                         : mc.rg_c0 + mc.rg_c1 * wi * wj;
       const double t1 = (epi == PLAN_EPI_RESID && pieces == 1 ? mc.pg_solo_resid1 : mc.pg_solo) * t2;
-      const double t_comp = wgs_per_cu == 1 ? kts * t2 * (full + (rem ? 1 : 0))
+      const double t_last = t.nt == 16 && 2 * rem <= mc.cus ? mc.pg_half : t2;  // one workgroup per CU: the last round
+      const double t_comp = wgs_per_cu == 1 ? kts * (full * t2 + (rem ? t_last : 0.0))
                                             : kts * (full * t2 + (rem == 0 ? 0.0 : rem <= mc.cus ? t1 : t2));
       const double fold = (slices - 1) * n_tokens * N * 4.0 * 2.0;  // partials written, then read by the norm kernel
       const double t_mem = (W + X) / mc.hbm_bytes_per_us;

@@ -38,7 +38,7 @@ struct Machine {
   // CU: c0 + c1 * (matrix-core instructions per wave and k step) microseconds; one workgroup
   // alone on a CU takes `solo` times that
   double pg_c0, pg_c1, pg_solo, pg_solo_resid1;  // (resid1: one-piece residual projections)
-  double pg_big, pg_big12;  // microseconds per k step of the 256 x 256 / 192 x 256 tile (one workgroup per CU)
+  double pg_big, pg_half, pg_big12;  // microseconds per k step of the 256 x 256 tile (one workgroup per CU), a last round of its halves, the 192 x 256 tile
   double rg_c0, rg_c1;  // the same regression for the register-ring kernel of the 64-row tiles
 };
 Machine machine_mi355x(int cus);

@@ -325,6 +325,27 @@ def test_large_block_prefill_k_slices_on_every_block_tile(nnc, tile, ks):
     assert int(n2.item()) == no2
 
 
+@pytest.mark.parametrize("n", [300, 512, 1040])
+def test_square_block_tiles_with_a_ragged_last_round(nnc, n):
+    """gate|up of 1124 row tiles: 71 row blocks of 256, the last one with 4 tiles.  At 300 tokens 213 blocks, all whole (more than
+    half the CUs); at 512 (two pieces) and 1040 (one piece) 284: one round of whole blocks, then 28 as halves, among
+    them halves without a row.  Bit-identical to the 256 x 128 and 128 x 128 tiles; matches the oracle."""
+    shape = synth.ModelShape("rounds", hidden=256, n_layers=1, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn=8992, vocab=512,
+                             dtype=synth.BF16)
+    g, o = _pair(nnc, shape, 1, 1088, weight_std=0.02, exact_prefill=False)
+    toks = synth.tokens(n, shape.vocab, stream=77)
+    got = {}
+    for tile in (1, 2, 5):
+        g.kv_reset(0)
+        g.set_option(nnc.OPT_PREFILL_TILE, tile)
+        lg, ng = g.prefill(0, toks)
+        got[tile] = lg.cpu().numpy()
+    assert np.array_equal(got[5], got[1]) and np.array_equal(got[2], got[1])
+    lo, no = oracle_prefill_like_library(o, 0, toks, shape)
+    _check_logits(shape, lg, lo, BF16_ABS_PROMPT if n > 512 else BF16_ABS_TIGHT)
+    assert int(ng.item()) == no
+
+
 @pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4, 5, 6])
 def test_large_block_prefill_short_k_loops(nnc, tile):
     """A model so narrow that the GEMM k loops have 2 (QKV, gate|up) and 3 (down) steps:
