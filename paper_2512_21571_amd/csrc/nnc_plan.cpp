@@ -31,27 +31,24 @@ Machine machine_mi355x(int cus) {
   m.cu_bytes_per_us = 58e3;
   m.skinny_launch_us = 2.5;
   m.skinny_round_us = 0.6;
-  // prompt GEMM, time per k step with two workgroups per CU, measured at the 4B / 8B shapes:
-  // 0.48 us for 128 x 128 tiles (16 matrix-core instructions per wave), 0.726 for 192 x 128 (24),
-  // 0.865 for 256 x 128 (32): least-squares line through the three; a lone workgroup on a CU
-  // takes 0.73 x that (single launches show 0.69 - 0.78), 0.78 in one-piece residual projections, whose epilogue reads and
-  // writes twice the outputs per tile with no other workgroup to hide it.  Over the 192 GEMMs of the 0.6B .. 8B shapes at 200 - 4096 tokens
-  // the picks are 2.22 % above the best tiles in the sum, 31 in 1000 in the mean (0.78 throughout: 2.35 %, 35; 0.73: 2.36 %, 35).  us, 0.78 / 0.73:
-  // QKV of 1.7B at 512 tokens 29.3 / 28.1, of 8B at 320 51.5 / 48.8, at 256 45.7 / 48.7, down of 4B at 256 47.7 / 44.4; O of 1.7B at 768 21.6 /
-  // 25.1, of 0.6B 17.6 / 19.7.
-  m.pg_c1 = 0.0241;
-  m.pg_c0 = 0.110;
-  m.pg_solo = 0.73;
-  m.pg_solo_resid1 = 0.78;
-  // the 256 x 256 tile, one workgroup per CU: 0.77 us per k step (64 matrix-core instructions per
-  // wave), measured on the 8B gate|up and down projections at 4080 tokens
+  // prompt GEMM with direct copies, us per k step of the 256 / 192 / 128 x 128 tiles: two workgroups per CU, and a lone one as a
+  // share of that, a tenth more in one-piece residual projections, whose epilogue reads and writes twice the outputs per tile with
+  // no other workgroup to hide it; of the 256 x 256 and 192 x 256 tiles, one workgroup per CU, and of a last round of 128 x 256 halves of the former.
+  // Fitted to every tile and slice count at 14 sizes of 200 - 4096 tokens of the 0.6B .. 8B shapes (224 GEMMs, the norms' share of the
+  // slices included): the picks are 2.4 % above the best tiles in the sum, 32 in 1000 in the mean
+  m.pg_pair[0] = 0.844; m.pg_solo[0] = 0.585;
+  m.pg_pair[1] = 0.631; m.pg_solo[1] = 0.727;
+  m.pg_pair[2] = 0.482; m.pg_solo[2] = 0.552;
+  m.pg_solo_resid1 = 1.086;
   m.pg_big = 0.77;
-  m.pg_half = 0.547;  // a last round of its 128 x 256 halves (0.65 - 0.79 of the whole block's time as the only round)
-  m.pg_big12 = 0.62;  // the 192 x 256 tile (48 per wave): the 8B QKV projection
+  m.pg_half = 0.547;
+  m.pg_big12 = 0.63;
   // the register-ring kernel of the 64-row tiles: 0.26 us per k step with 4 matrix-core
   // instructions per wave (64 x 64), 0.37 with 8 (64 x 128)
   m.rg_c1 = 0.0275;
   m.rg_c0 = 0.150;
+  m.rg_solo = 0.73;
+  m.rg_solo_resid1 = 0.78;
   return m;
 }
 
@@ -60,7 +57,7 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 struct PgTile {
   int code, nt, tt;
-  bool lds_direct;  // three LDS stages filled by direct copies; else register ring, two stages
+  bool lds_direct;  // LDS stages (three, 128 x 128: four) filled by direct copies; else register ring, two stages
   int wgs_per_cu;   // resident workgroups per CU the kernel is built for
 };
 // every block tile the prompt GEMM kernels are instantiated for, plus one that is not (256 x 256
@@ -84,7 +81,7 @@ PrefillGemmPlan plan_prefill_gemm(const Machine& mc, int n_tiles, int KT, int co
     ++best.candidates;
     // capacity: staged operands of the resident workgroups in LDS; accumulators and two sets of
     // fragments (one for the ring kernels) in the wave's registers
-    const int stages = t.lds_direct ? 3 : 2;
+    const int stages = t.lds_direct ? t.nt == 8 ? 4 : 3 : 2;
     const int lds = stages * (t.nt + t.tt) * 1024 * wgs_per_cu;
     const int wi = t.nt / 2, wj = t.tt / 2;
     const int regs = wi * wj * 4 + (t.lds_direct ? 2 : 1) * (wi + wj) * 4 + (t.lds_direct ? 0 : 8 * (t.nt / 4 + t.tt / 4) * 4);
@@ -105,13 +102,17 @@ PrefillGemmPlan plan_prefill_gemm(const Machine& mc, int n_tiles, int KT, int co
       const int wgs = ceil_div(n_tiles, t.nt) * ceil_div(col_tiles, t.tt) * slices;
       const int slots = wgs_per_cu * mc.cus;
       const int full = wgs / slots, rem = wgs - full * slots;
-      const double t2 = wgs_per_cu == 1 ? (t.nt == 16 ? mc.pg_big : mc.pg_big12)
-                        : t.lds_direct  ? mc.pg_c0 + mc.pg_c1 * wi * wj
-                                        : mc.rg_c0 + mc.rg_c1 * wi * wj;
-      const double t1 = (epi == PLAN_EPI_RESID && pieces == 1 ? mc.pg_solo_resid1 : mc.pg_solo) * t2;
-      const double t_last = t.nt == 16 && 2 * rem <= mc.cus ? mc.pg_half : t2;  // one workgroup per CU: the last round
-      const double t_comp = wgs_per_cu == 1 ? kts * (full * t2 + (rem ? t_last : 0.0))
-                                            : kts * (full * t2 + (rem == 0 ? 0.0 : rem <= mc.cus ? t1 : t2));
+      const bool resid1 = epi == PLAN_EPI_RESID && pieces == 1;
+      double t_comp;
+      if (wgs_per_cu == 1) {
+        const double t_last = t.nt == 16 && 2 * rem <= mc.cus ? mc.pg_half : t.nt == 16 ? mc.pg_big : mc.pg_big12;
+        t_comp = kts * (full * (t.nt == 16 ? mc.pg_big : mc.pg_big12) + (rem ? t_last : 0.0));
+      } else {
+        const int q = t.nt == 16 ? 0 : t.nt == 12 ? 1 : 2;
+        const double t2 = t.lds_direct ? mc.pg_pair[q] : mc.rg_c0 + mc.rg_c1 * wi * wj;
+        const double t1 = t2 * (t.lds_direct ? mc.pg_solo[q] * (resid1 ? mc.pg_solo_resid1 : 1.0) : resid1 ? mc.rg_solo_resid1 : mc.rg_solo);
+        t_comp = kts * (full * t2 + (rem == 0 ? 0.0 : rem <= mc.cus ? t1 : t2));
+      }
       const double fold = (slices - 1) * n_tokens * N * 4.0 * 2.0;  // partials written, then read by the norm kernel
       const double t_mem = (W + X) / mc.hbm_bytes_per_us;
       const double cached = pieces == 2 && n_tokens <= 512 ? mc.fold_cached_short_bytes : mc.fold_cached_bytes;

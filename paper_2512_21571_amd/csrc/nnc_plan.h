@@ -10,8 +10,8 @@
 //   variables    block tile (NT x TT 16-row / 16-column tiles at the LDS level), k slices
 //   constraints  LDS bytes of the staged operands x resident workgroups <= LDS per CU;
 //                accumulator + fragment registers per wave <= the register file share
-//   T_comp       k steps x micro-kernel time per k step (linear in the matrix-core
-//                instructions per wave: c0 + c1 x WI x WJ, measured), summed over the rounds in
+//   T_comp       k steps x micro-kernel time per k step (measured per tile; for the 64-row tiles linear in
+//                the matrix-core instructions per wave, c0 + c1 x WI x WJ), summed over the rounds in
 //                which the launch's workgroups occupy the chip (a last round with at most one
 //                workgroup per CU runs faster per step than a full one)
 //   T_mem        (weights + activations + outputs + k-slice partials) / streaming bandwidth
@@ -34,12 +34,13 @@ struct Machine {
   // through its vector memory path (weights + operand), launch-to-launch overhead, one round of
   // the cross-wave reduction in the epilogue
   double stream_bytes_per_us, cu_bytes_per_us, skinny_launch_us, skinny_round_us;
-  // micro-kernel regression of the LDS-staged prompt GEMM, per k step of 32 with two workgroups per
-  // CU: c0 + c1 * (matrix-core instructions per wave and k step) microseconds; one workgroup
-  // alone on a CU takes `solo` times that
-  double pg_c0, pg_c1, pg_solo, pg_solo_resid1;  // (resid1: one-piece residual projections)
-  double pg_big, pg_half, pg_big12;  // microseconds per k step of the 256 x 256 tile (one workgroup per CU), a last round of its halves, the 192 x 256 tile
-  double rg_c0, rg_c1;  // the same regression for the register-ring kernel of the 64-row tiles
+  // micro-kernel times of the LDS-staged prompt GEMM, microseconds per k step of 32: the 256 / 192 / 128 x 128 tiles with two
+  // workgroups per CU, and a lone one as a share of that (resid1: more in one-piece residual projections)
+  double pg_pair[3], pg_solo[3], pg_solo_resid1;
+  double pg_big, pg_half, pg_big12;  // the 256 x 256 tile (one workgroup per CU), a last round of its halves, the 192 x 256 tile
+  // the register-ring kernel of the 64-row tiles: c0 + c1 * (matrix-core instructions per wave and k step) with two workgroups
+  // per CU, and a lone one as a share of that
+  double rg_c0, rg_c1, rg_solo, rg_solo_resid1;
 };
 Machine machine_mi355x(int cus);
 

@@ -46,8 +46,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // 32.  4 waves in a 2 x 2 arrangement, each NT/2 x TT/2 accumulator tiles.
 //   NT = 16, TT = 8  (256 x 128, 128 x 64 per wave): the matrix-core-bound shape; per k step a
 //                    wave reads 12 fragments from LDS for 32 matrix-core instructions.
-//   NT = 12, TT = 8  (192 x 128) and NT = 8, TT = 8 (128 x 128): launches whose 256 x 128
-//                    workgroups would fill the last round of two per CU badly.
+//   NT = 12, TT = 8  (192 x 128): launches whose 256 x 128 workgroups would fill the last round of
+//                    two per CU badly, and NT = 8 (128 x 128).
 //   NT = 4,  TT = 8  (64 x 128): short prompts, where the launch would otherwise leave most of
 //                    the chip idle.
 //   NT = 4,  TT = 4  (64 x 64): the same, for launches that even so have fewer workgroups than CUs.
@@ -285,18 +285,24 @@ __global__ __launch_bounds__(256, 2) void k_gemm_prefill(PrefillGemmArgs a) {
 
 // The same GEMM with the operands copied global -> LDS directly (16 bytes per lane, a wave's 64
 // lanes land on 1 KiB contiguous: exactly one fragment), without passing through registers.
-// Three LDS stages and two register sets of fragments: when step kt starts, the copies of step
-// kt + 3 are issued into the stage whose fragments step kt already holds in registers, and the
-// fragments of step kt + 1 are read while the matrix cores work on step kt; one barrier per k
-// step.
-template <int EPI, int NT, int TT, int PIECES, class HF>
+// ST LDS stages and two register sets of fragments: while the matrix cores work on step kt, the fragments of step
+// kt + 1 are read into the other set and the copies of step kt + ST are issued into the stage whose fragments
+// step kt already holds in registers; one barrier per k step.
+// Fragment reads and copies stand behind single products, in an order that scheduling barriers keep: behind each
+// product of a step's first part one read, in the rest the copies, evenly spaced.  Issued in front of the
+// products they cost a k step of the 128 x 128 tile alone on its CU 860 cycles for 256 of products (one wave per SIMD hides nothing).
+// What bounds the kernel now is what a CU draws out of L2: 52 - 64 GB/s of operands (16 KiB per k step at 128 x 128).
+// us per launch, before / now (every second k slice count, 0.6B .. 8B shapes, 200 - 4096 tokens): 128 x 128, one
+// workgroup per CU: 8B, 256 tokens in two pieces, QKV 49.7 / 39.6, down 138 / 109; 1.7B, 512 tokens, QKV 28.2 / 23.4; two per CU: 8B,
+// 512 tokens, O in two k slices 42.3 / 40.4; 256 x 128: 4B, 2048 tokens, gate|up 186 / 173, launches of up to one workgroup per CU 0.89 x, of more
+// 0.90 - 1.0; 192 x 128 0.87 and 0.93 - 1.0.
+// Stages: as many as two workgroups per CU have room for, and for 128 and 192 rows one more where a CU holds one only (128 x 128, 8B QKV at
+// 256 tokens with 3 / 4 / 5 / 8 stages: 51.0 / 40.4 / 39.6 / 40.6; 4B down at 333: 108 / 79 / 70 / 69).
+template <int EPI, int NT, int PIECES, class HF, int ST>
 __global__ __launch_bounds__(256, 2) void k_gemm_prefill_dl(PrefillGemmArgs a) {
-  constexpr int WI = NT / 2, AL = NT / 4, WJ = TT / 2, BL = TT / 4;
-  constexpr int ST = 3;
+  constexpr int TT = 8, WI = NT / 2, WJ = TT / 2, AL = NT / 4, L = NT / 4 + TT / 4;
   __shared__ u32x4 As[ST][NT][64];
   __shared__ u32x4 Bs[ST][TT][64];
-  // (the wave index as a scalar: the LDS addresses of the copies below are then scalar arithmetic
-  // instead of a vector op + lane read in front of every copy)
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wn = wave >> 1, wt = wave & 1;
   // blockIdx.z = k slice (residual projections whose tiles alone would leave CUs idle)
@@ -313,14 +319,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm_prefill_dl(PrefillGemmArgs a) {
 #pragma unroll
     for (int j = 0; j < WJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // wave w copies fragments w, w + 4, ...; per-thread byte offsets are fixed for the kernel
-  // (tile indices clamped to the last valid one: rows / columns past the edge compute garbage
-  // that is never stored)
-  uint32_t voa[AL], vob[BL];
+  // wave w copies fragments w, w + 4, ... of either operand; per-thread byte offsets are fixed for the kernel
+  // (tile indices clamped to the last valid one: rows / columns past the edge compute garbage that is never stored)
+  uint32_t vo[L];
 #pragma unroll
-  for (int j = 0; j < AL; ++j) voa[j] = ((uint32_t)min(nt0 + wave + 4 * j, a.n_tiles - 1) * (uint32_t)a.KT * 64u + lane) * 16u;
-#pragma unroll
-  for (int j = 0; j < BL; ++j) vob[j] = ((uint32_t)min(tt0 + wave + 4 * j, a.t_tiles - 1) * (uint32_t)a.KT * 64u + lane) * 16u;
+  for (int c = 0; c < L; ++c) {
+    const int t = c < AL ? min(nt0 + wave + 4 * c, a.n_tiles - 1) : min(tt0 + wave + 4 * (c - AL), a.t_tiles - 1);
+    vo[c] = ((uint32_t)t * (uint32_t)a.KT * 64u + lane) * 16u;
+  }
   // The copy instruction is written as inline assembly: the compiler, when it sees one, makes
   // every later LDS read wait for all of them (it cannot tell which stage a read touches), which
   // would undo the look-ahead.  Hidden from it, the waits are the explicit ones below.
@@ -333,63 +339,71 @@ __global__ __launch_bounds__(256, 2) void k_gemm_prefill_dl(PrefillGemmArgs a) {
                  : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(base)
                  : "memory", "m0");
   };
-  auto issue = [&](int kt, int st) __attribute__((always_inline)) {
+  // copy number c of k step kt into stage st: weight fragments, then operand fragments
+  auto issue1 = [&](auto cc, int kt, int st) __attribute__((always_inline)) {
+    constexpr int c = decltype(cc)::value;
     const size_t ko = (size_t)kt * 1024;
-#pragma unroll
-    for (int j = 0; j < AL; ++j) copy1(W + ko, voa[j], (uint32_t)(size_t)(lptr)&As[st][wave + 4 * j][0]);
-#pragma unroll
-    for (int j = 0; j < BL; ++j) copy1(X + ko, vob[j], (uint32_t)(size_t)(lptr)&Bs[st][wave + 4 * j][0]);
+    if constexpr (c < AL) copy1(W + ko, vo[c], (uint32_t)(size_t)(lptr)&As[st][wave + 4 * c][0]);
+    else copy1(X + ko, vo[c], (uint32_t)(size_t)(lptr)&Bs[st][wave + 4 * (c - AL)][0]);
   };
-  // s_waitcnt vmcnt(n) with the other counters left alone
-  constexpr int L = AL + BL;  // copy instructions per wave and k step
-  auto wait_vm = [](auto nc) __attribute__((always_inline)) {
-    constexpr int n = decltype(nc)::value;
-    __builtin_amdgcn_s_waitcnt((n & 0xf) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
+  // wait until at most r whole steps of copies (r < ST) are still in flight
+  auto wait_steps = [&](int r) __attribute__((always_inline)) {
+    static_for<ST>([&](auto rc) __attribute__((always_inline)) {
+      constexpr int n = decltype(rc)::value * L;
+      if (r == decltype(rc)::value) __builtin_amdgcn_s_waitcnt((n & 0xf) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
+    });
   };
-  // Fragments live in two register sets: while the matrix cores work on step kt (set kt & 1),
-  // the fragments of step kt + 1 are read from LDS into the other set.
-  u32x4 af[2][WI], bf[2][WJ];
-  auto read_frags = [&](auto setc, int st) __attribute__((always_inline)) {
-    constexpr int P = decltype(setc)::value;
-#pragma unroll
-    for (int i = 0; i < WI; ++i) af[P][i] = As[st][wn * WI + i][lane];
-#pragma unroll
-    for (int j = 0; j < WJ; ++j) bf[P][j] = Bs[st][wt * WJ + j][lane];
-  };
+  u32x4 af[2][WI], bf[2][WJ];  // fragments of the step in work and of the next
   constexpr std::integral_constant<int, 0> c0{};
   constexpr std::integral_constant<int, 1> c1{};
-  constexpr std::integral_constant<int, L> cL{};
-  constexpr std::integral_constant<int, 2 * L> c2L{};
-  // Step kt: stage kt % 3 is already in registers and free again, stage (kt + 1) % 3 must have
-  // landed (its copies were issued two steps ago), stage (kt + 2) % 3 is in flight.
-  auto step = [&](auto setc, int kt, int st) __attribute__((always_inline)) {
+  // Step kt (fragments in register set P): stage kt % ST is in registers and free, stage (kt + 1) % ST must have
+  // landed, the stages behind it are in flight.  (Behind the last step the reads fetch what nobody uses.)
+  // ALL: step kt + ST exists.  (Asked per copy in the last steps only; a step specialised for each of its ends instead made the
+  // compiler keep a second set of accumulators, 199 registers instead of 137 at 128 x 128, scratch at 256 x 128.)
+  auto step = [&](auto setc, auto allc, int kt, int st) __attribute__((always_inline)) {
     constexpr int P = decltype(setc)::value;
-    if (kt + 2 < KT) wait_vm(cL);  // all but the newest issue
-    else wait_vm(c0);
+    const bool more = decltype(allc)::value || kt + ST < KT;
+    if (more) wait_steps(ST - 2);
+    else wait_steps(min(max(KT - kt - 2, 0), ST - 2));
     lds_sync();
-    if (kt + 3 < KT) issue(kt + 3, st);
-    if (kt + 1 < KT) read_frags(std::integral_constant<int, 1 - P>{}, st == 2 ? 0 : st + 1);
-#pragma unroll
-    for (int i = 0; i < WI; ++i)
-#pragma unroll
-      for (int j = 0; j < WJ; ++j)
-        acc[i][j] = HF::mfma(af[P][i], bf[P][j], acc[i][j]);
+    const int nx = st == ST - 1 ? 0 : st + 1;
+    constexpr int R = WI + WJ, SP = (WI * WJ - R) / L;  // fragment reads; products from one copy to the next
+    static_for<WI * WJ>([&](auto mc) __attribute__((always_inline)) {
+      constexpr int m = decltype(mc)::value, i = m / WJ, j = m % WJ;
+      acc[i][j] = HF::mfma(af[P][i], bf[P][j], acc[i][j]);
+      if constexpr (m < R) {
+        if constexpr (m < WI) af[1 - P][m] = As[nx][wn * WI + m][lane];
+        else bf[1 - P][m - WI] = Bs[nx][wt * WJ + m - WI][lane];
+      }
+      if constexpr (m >= R && (m - R) % SP == 0 && (m - R) / SP < L) {
+        if (more) issue1(std::integral_constant<int, (m - R) / SP>{}, kt + ST, st);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
-  issue(0, 0);
-  if (KT > 1) issue(1, 1);
-  if (KT > 2) issue(2, 2);
-  if (KT > 2) wait_vm(c2L);
-  else if (KT > 1) wait_vm(cL);
-  else wait_vm(c0);
+#pragma unroll
+  for (int q = 0; q < ST; ++q)
+    if (q < KT) static_for<L>([&](auto cc) __attribute__((always_inline)) { issue1(cc, q, q); });
+  wait_steps(min(KT, ST) - 1);
   lds_sync();
-  read_frags(c0, 0);
-  int st = 0;
-  for (int kt = 0; kt < KT; kt += 2) {
-    step(c0, kt, st);
-    st = st == 2 ? 0 : st + 1;
+#pragma unroll
+  for (int i = 0; i < WI; ++i) af[0][i] = As[0][wn * WI + i][lane];
+#pragma unroll
+  for (int j = 0; j < WJ; ++j) bf[0][j] = Bs[0][wt * WJ + j][lane];
+  int st = 0, kt = 0;
+  auto next_stage = [&]() __attribute__((always_inline)) { st = st == ST - 1 ? 0 : st + 1; };
+  for (; kt + 1 + ST < KT; kt += 2) {
+    step(c0, std::true_type{}, kt, st);
+    next_stage();
+    step(c1, std::true_type{}, kt + 1, st);
+    next_stage();
+  }
+  for (; kt < KT; kt += 2) {
+    step(c0, std::false_type{}, kt, st);
+    next_stage();
     if (kt + 1 < KT) {
-      step(c1, kt + 1, st);
-      st = st == 2 ? 0 : st + 1;
+      step(c1, std::false_type{}, kt + 1, st);
+      next_stage();
     }
   }
   pg_epilogue<EPI, NT, TT, PIECES, HF>(a, acc, nt0, tt0, wn, wt, lane, (int)blockIdx.z);
@@ -671,6 +685,7 @@ hipError_t launch_gemm_prefill(hipStream_t s, bool f16, int epi, const PrefillGe
     ksplit = (a.KT + a.kts_per_split - 1) / a.kts_per_split;
   }
   dim3 grid((a.n_tiles + NT - 1) / NT, (a.t_tiles + TT - 1) / TT, ksplit);
+  const bool lone = (long)grid.x * grid.y * grid.z <= n_cus;
   // 256 x 256: a last round of at most half the CUs is done as blocks of 128 x 256, twice as many on as many CUs more.  Against
   // whole blocks: 0.65 - 0.79 of the time where it is the only round, 0.96 in the median behind others (4B, 2048 tokens, gate|up = 2.4 rounds 200 -> 186 us)
   const int blocks = (int)(grid.x * grid.y * grid.z), rest = blocks % n_cus;
@@ -678,9 +693,11 @@ hipError_t launch_gemm_prefill(hipStream_t s, bool f16, int epi, const PrefillGe
 #define PG_LAUNCH_H(E, P, HF)                                                          \
   do {                                                                                 \
     if (shape == 0) k_gemm_prefill<E, 4, 8, P, HF><<<grid, 256, 0, s>>>(a);            \
-    else if (shape == 1) k_gemm_prefill_dl<E, 16, 8, P, HF><<<grid, 256, 0, s>>>(a);   \
-    else if (shape == 2) k_gemm_prefill_dl<E, 8, 8, P, HF><<<grid, 256, 0, s>>>(a);    \
-    else if (shape == 4) k_gemm_prefill_dl<E, 12, 8, P, HF><<<grid, 256, 0, s>>>(a);   \
+    else if (shape == 1) k_gemm_prefill_dl<E, 16, P, HF, 3><<<grid, 256, 0, s>>>(a); \
+    else if (shape == 2 && lone) k_gemm_prefill_dl<E, 8, P, HF, 5><<<grid, 256, 0, s>>>(a); \
+    else if (shape == 2) k_gemm_prefill_dl<E, 8, P, HF, 4><<<grid, 256, 0, s>>>(a);      \
+    else if (shape == 4 && lone) k_gemm_prefill_dl<E, 12, P, HF, 4><<<grid, 256, 0, s>>>(a); \
+    else if (shape == 4) k_gemm_prefill_dl<E, 12, P, HF, 3><<<grid, 256, 0, s>>>(a);  \
     else if (shape == 5) k_gemm_prefill_big<E, P, HF, 16><<<bigs, 256, 0, s>>>(a, grid.x, grid.y, whole); \
     else if (shape == 6) k_gemm_prefill_big<E, P, HF, 12><<<bigs, 256, 0, s>>>(a, grid.x, grid.y, whole); \
     else k_gemm_prefill<E, 4, 4, P, HF><<<grid, 256, 0, s>>>(a);                       \
