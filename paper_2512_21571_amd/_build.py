@@ -48,7 +48,7 @@ def build(force: bool = True) -> str:
     """force: compile every source; otherwise only the sources newer than their object file
     (the sources are compiled side by side, one hipcc each, then linked)."""
     os.makedirs(OBJ_DIR, exist_ok=True)
-    hdr_time = max(os.path.getmtime(h) for h in HEADERS + [os.path.join(CSRC, n) for n in ("nnc_lanes.h", "nnc_half.h", "nnc_plan.h")])
+    hdr_time = max(os.path.getmtime(h) for h in HEADERS + [os.path.join(CSRC, n) for n in ("nnc_lanes.h", "nnc_half.h", "nnc_plan.h", "nnc_ahead.h")])
     jobs = []
     for src in SOURCES:
         sp, op = os.path.join(CSRC, src), os.path.join(OBJ_DIR, src + ".o")

@@ -1201,7 +1201,7 @@ static nnc_status prefill_head(nnc_model* m, uint32_t n, int pending, float* log
 
 // Whether a block of n tokens runs through the kernels of nnc_small.hip.  They save three kernels per
 // layer but re-read the weights from L2 once per 32 - 64 operand columns, which costs more than that from
-// n * H^2 = 2^29 on, in binary16 (which keeps its norm kernels) 2^28.  Measured, us per layer, block tiles /
+// n * H^2 = 2^29 on (at 0.6B the two are within 3 % of each other from 272 tokens on), in binary16 (which keeps its norm kernels) 2^28.  Measured, us per layer, block tiles /
 // short-block kernels: 0.6B 55.2 / 44.3 at 128 tokens, 96.4 / 90.5 at 512; 1.7B 92.2 / 87.9 at 128, 99.8 / 102.0 at
 // 144, 116.6 / 119.0 at 256; 4B 114.3 / 104.8 at 33, 118.3 / 118.4 at 79, 129.9 / 145.4 at 112; binary16: 0.6B 69.5 / 62.8
 // at 256, 78.6 / 79.1 at 288; 1.7B 77.4 / 73.4 at 64, 86.9 / 90.9 at 79; 4B 115.1 / 106.1 at 39, 119.0 / 123.1 at 80.
@@ -1209,10 +1209,10 @@ static nnc_status prefill_head(nnc_model* m, uint32_t n, int pending, float* log
 // tiles): hidden sizes up to 2560.
 // Byte weights need no widened copy here, so the limit lies further out and depends on how many rounds
 // of workgroups the short GEMMs take; the tile models know that.  A layer takes 1.75 - 2 times the short GEMMs'
-// model time, against the block-tile GEMMs' model time + 25 us + a pass over the weights at 2.4 TB/s.
+// model time, against the block-tile GEMMs' model time + 35 us + a pass over the weights at 2.4 TB/s.
 // Measured as above: 0.6B 86.0 / 63.8 at 256; 1.7B 144.6 / 122.9 at 256, 165.4 / 169.1 at 300; 4B 206.8 / 190.7 at 192,
 // 219.6 / 228.6 at 208, 226.1 / 243.0 at 256; 8B 288 / 197 at 128, 337 / 307 at 192, 338 / 324 at 208, 344 - 370 (three cards) /
-// 357 at 256, 417 / 424 at 288.
+// 357 at 256, 417 / 424 at 288.  With the block tiles as they are since, 8B 344 / 335 at 200, 355 / 366 at 250; 4B 219 / 207 at 192, 220 / 245 at 208.
 static bool short_block(const nnc_model* m, uint32_t n) {
   if (n > PB_SMALL_TOKENS || m->opt_prefill_exact == 1) return false;
   const double H = m->H();
@@ -1223,7 +1223,7 @@ static bool short_block(const nnc_model* m, uint32_t n) {
   const struct { int small, block, rows, K; } gemms[4] = {
       {SEPI_QKV, PLAN_EPI_STORE, (int)(m->Dq() + 2 * m->Dkv()), (int)m->H()}, {SEPI_RESID, PLAN_EPI_RESID, (int)m->H(), (int)m->Dq()},
       {SEPI_SWIGLU, PLAN_EPI_SWIGLU, (int)(2 * m->F()), (int)m->H()}, {SEPI_RESID, PLAN_EPI_RESID, (int)m->H(), (int)m->F()}};
-  double small = 0.0, block = 25.0;
+  double small = 0.0, block = 35.0;
   for (const auto& g : gemms) {
     small += 1.75 * plan_small_gemm(mc, g.small, g.rows / 16, g.K / 64, tt, 2).t_us;
     block += plan_prefill_gemm(mc, g.rows / 16, g.K / 32, tt, (int)n, 2, g.block, g.block == PLAN_EPI_RESID ? PB_SPLIT_MAX : 1).t_us +
@@ -1288,6 +1288,12 @@ static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t
                       po = plan_small_gemm(mc, SEPI_RESID, H / 16, Dq / kt, 2 * tt, xt),
                       pg = plan_small_gemm(mc, SEPI_SWIGLU, 2 * F / 16, H / kt, 2 * tt, xt),
                       pd = plan_small_gemm(mc, SEPI_RESID, H / 16, F / kt, 2 * tt, xt);
+  // Every launch brings what its threads can of the next GEMM's weights into L2.  Not with one or two token tiles, whose launches read each
+  // weight once, at the rate of HBM (16 tokens: 0.98 - 1.01 x), nor with byte weights (0.98 - 1.02 x).
+  const long lines = (long)m->n_cus / 8 * 256 * SMALL_AHEAD;  // per XCD
+  auto ahead = [&](const void* W, int rows, int K, const SmallGemmPlan& p) {
+    return m->w8 || tt < 3 ? WeightAhead() : weight_ahead(W, rows / 16, K / kt, p.nt, lines);
+  };
   int blocks = 1;  // partial sums of squares per token that the next GEMM adds up
   auto gemm = [&](const void* W, const float* scale, int rows, int K, const void* X) {
     SmallGemmArgs a;
@@ -1323,6 +1329,7 @@ static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t
       normed_by(a);
       a.gq = L.g_q; a.gk = L.g_k; a.rope = m->rope; a.slot = slot; a.pos0 = pos0; a.max_seq = c.max_seq;
       a.nq = nq; a.nkv = nkv; a.q = m->pb_qkv; a.ldq = Nqkv; a.kc = L.kc; a.vc = L.vc; a.vt = m->pb_vt; a.vt_stride = m->pb_vt_stride;
+      a.ahead = ahead(L.wo, H, Dq, po);
       RUN(FAM_PGEMM, (double)Nqkv * H * lw, 2.0 * Nqkv * H * T, launch_gemm_small(s, f16, SEPI_QKV, a, pq.nt, pq.ct));
     }
     if (m->record_layers) HIP_TRY(hipEventRecord(m->layer_done[li], s));
@@ -1333,6 +1340,7 @@ static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t
     {
       SmallGemmArgs a = gemm(L.wo, L.so, H, Dq, m->pb_fb);
       resid(a, po, L.g_post);
+      a.ahead = ahead(L.wgu, 2 * F, H, pg);
       RUN(FAM_PGEMM_O, (double)H * Dq * lw, 2.0 * H * Dq * T, launch_gemm_small(s, f16, SEPI_RESID, a, po.nt, po.ct));
     }
     if (f16) RUN(FAM_NORM, T * H * 6.0, 0, launch_rmsnorm_frag(s, f16, m->pb_x, nullptr, 0, 0, L.g_post, H, c.rms_eps, (int)n, tt, 2, m->pb_fa));
@@ -1340,11 +1348,13 @@ static nnc_status prefill_block_small(nnc_model* m, uint32_t slot, const int32_t
       SmallGemmArgs a = gemm(L.wgu, L.sgu, 2 * F, H, m->pb_fa);
       normed_by(a);
       a.packed_out = m->pb_fb;
+      a.ahead = ahead(L.wd, H, F, pd);
       RUN(FAM_PGEMM_GU, 2.0 * F * H * lw, 4.0 * F * H * T, launch_gemm_small(s, f16, SEPI_SWIGLU, a, pg.nt, pg.ct));
     }
     {
       SmallGemmArgs a = gemm(L.wd, L.sd, H, F, m->pb_fb);
       resid(a, pd, li + 1 < c.n_layers ? m->L[li + 1].g_in : nullptr);
+      if (li + 1 < c.n_layers) a.ahead = ahead(m->L[li + 1].wqkv, Nqkv, H, pq);
       RUN(FAM_PGEMM_D, (double)H * F * lw, 2.0 * H * F * T, launch_gemm_small(s, f16, SEPI_RESID, a, pd.nt, pd.ct));
     }
   }

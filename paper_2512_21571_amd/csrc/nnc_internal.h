@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "nnc_ahead.h"
+
 namespace nnc {
 
 // `dt` arguments of the launchers: the model's element type, 0 = fp32, 1 = bf16, 2 = binary16
@@ -227,7 +229,10 @@ struct SmallGemmArgs {
   float* ssq_out = nullptr;
   // SEPI_SWIGLU: silu(gate) * up in fragment order, two pieces
   void* packed_out = nullptr;
+  WeightAhead ahead;  // the next GEMM's weights
+  int wgs = 0;        // workgroups of the launch (filled in by the launcher)
 };
+constexpr int SMALL_AHEAD = 2;  // lines of the next GEMM's weights that a thread touches at most
 // nt x ct: row tiles x column tiles per workgroup
 hipError_t launch_gemm_small(hipStream_t s, bool f16, int epi, const SmallGemmArgs& a, int nt, int ct);
 int attn_small_heads(int nq, int nkv, int n, int n_cus);

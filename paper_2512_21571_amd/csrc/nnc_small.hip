@@ -11,6 +11,7 @@
 // epilogue writes gain * x as the next operand and, per row block and token, the sum of x^2; the
 // next GEMM multiplies its outputs by 1 / rms, which is exact because the matmul is linear.
 // (binary16 models: an un-normalised row may leave the format's range, so there the norm kernel stays.)
+#include "nnc_ahead.h"
 #include "nnc_half.h"
 #include "nnc_internal.h"
 #include "nnc_lanes.h"
@@ -25,7 +26,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // the loop: both operands lie in fragment order in memory, a wave's load is 1 KiB contiguous, and
 // with two register sets of U k tiles a workgroup keeps 4 U (NT + CT) KiB in flight, which is what
 // bounds a launch this short.
-template <int EPI, int NT, int CT, int U, class HF>
+// AHEAD: it touches the next GEMM's weights too (not for bytes, nor where a launch has only one or two token tiles).
+template <int EPI, int NT, int CT, int U, class HF, bool AHEAD>
 __global__ __launch_bounds__(256) void k_gemm_small(SmallGemmArgs a) {
   constexpr bool W8 = HF::kW8;      // byte weights: two operand k tiles per weight tile
   constexpr int XT = W8 ? 2 : 1;
@@ -136,8 +138,10 @@ __global__ __launch_bounds__(256) void k_gemm_small(SmallGemmArgs a) {
     for (int u = 0; u < U; ++u) mma_tile(av[u], bv[u]);
   };
   const int n_groups = n_mine / U;
+  if (n_groups > 0) load_group(0, avA, bvA);
+  Ahead<SMALL_AHEAD> ahead;
+  if constexpr (AHEAD) ahead.prepare(a.ahead, blockIdx.x, a.wgs);
   if (n_groups > 0) {
-    load_group(0, avA, bvA);
     // (scheduling barriers: the next set's loads are issued before the products on the current one)
     for (int gi = 0;;) {
       load_group((gi + 1) * U, avB, bvB);
@@ -156,6 +160,8 @@ __global__ __launch_bounds__(256) void k_gemm_small(SmallGemmArgs a) {
     load_tile(wave + 4 * t, avA[0], bvA[0]);
     mma_tile(avA[0], bvA[0]);
   }
+
+  if constexpr (AHEAD) ahead.issue(a.ahead);  // in flight during the epilogue
 
   // the two pieces of a token are added in the wave, the four waves' sums in LDS (fixed order)
 #pragma unroll
@@ -338,6 +344,7 @@ __global__ __launch_bounds__(256) void k_gemm_small(SmallGemmArgs a) {
       }
     }
   }
+  if constexpr (AHEAD) ahead.done();
 }
 
 hipError_t launch_gemm_small(hipStream_t s, bool f16, int epi, const SmallGemmArgs& a, int nt, int ct) {
@@ -352,12 +359,17 @@ hipError_t launch_gemm_small(hipStream_t s, bool f16, int epi, const SmallGemmAr
     return hipErrorInvalidValue;
   const int gx = (a.n_tiles + nt - 1) / nt, gy = (a.t_tiles + ct - 1) / ct;
   const unsigned grid = (unsigned)((gx + 7) / 8 * 8 * gy);
-#define SG_HF(E, NT, CT, U)                                                   \
-  do {                                                                        \
-    if (a.wscale) k_gemm_small<E, NT, CT, 2, Bf16W8><<<grid, 256, 0, s>>>(a); \
-    else if (f16) k_gemm_small<E, NT, CT, U, Fp16><<<grid, 256, 0, s>>>(a);   \
-    else k_gemm_small<E, NT, CT, U, Bf16><<<grid, 256, 0, s>>>(a);            \
-    return hipGetLastError();                                                 \
+  SmallGemmArgs b = a;
+  b.wgs = (int)grid;
+  const bool ahead = a.ahead.W != nullptr;
+#define SG_HF(E, NT, CT, U)                                                             \
+  do {                                                                                  \
+    if (a.wscale) k_gemm_small<E, NT, CT, 2, Bf16W8, false><<<grid, 256, 0, s>>>(b);    \
+    else if (f16 && ahead) k_gemm_small<E, NT, CT, U, Fp16, true><<<grid, 256, 0, s>>>(b); \
+    else if (f16) k_gemm_small<E, NT, CT, U, Fp16, false><<<grid, 256, 0, s>>>(b);      \
+    else if (ahead) k_gemm_small<E, NT, CT, U, Bf16, true><<<grid, 256, 0, s>>>(b);     \
+    else k_gemm_small<E, NT, CT, U, Bf16, false><<<grid, 256, 0, s>>>(b);               \
+    return hipGetLastError();                                                           \
   } while (0)
 #define SG(E, NT, CT, U) \
   if (epi == E && nt == NT && ct == CT) SG_HF(E, NT, CT, U)
