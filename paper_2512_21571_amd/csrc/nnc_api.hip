@@ -420,6 +420,7 @@ struct Pass {
   int grid_chunks = 1;
   double kv_rows = 0;       // sum over columns of (position + 1): cached rows attention must read
   bool one_slot = false;    // the columns are consecutive positions of one slot (prompt chunk)
+  bool begun = false;       // hidden-state steps: x, the columns' state and the first layer's operand are there already
   int* pending_out = nullptr;  // hidden-state models: leave the last projection's partials unadded and say how many
   bool decode = false;      // every column is a different slot: QK-norm, RoPE and the cache append may run inside the attention kernel
 };
@@ -446,7 +447,7 @@ nnc_status run_pass(nnc_model* m, const Pass& p) {
   // (NormTail): two kernels less per layer.  The head's norm stays a kernel when the head takes
   // a sub-range of the columns.
   const bool fuse_norm = p.decode && m->opt_fuse_norm && m->tail_counters && m->mk_error && H % 4 == 0 && H <= 8192;
-  bool normed = false;  // Xp already holds the normed input of the next GEMM
+  bool normed = p.begun;  // Xp already holds the normed input of the next GEMM
   int tails = 0;
   auto norm_tail = [&](GemmArgs& a, const float* gain) {
     a.tail.counter = m->tail_counters + tails++;
@@ -483,10 +484,13 @@ nnc_status run_pass(nnc_model* m, const Pass& p) {
       RUN(FAM_QKROPE, n * Nqkv * 4.0, 0,
           launch_qknorm_rope_append(s, dt, m->qkv, nq, nkv, L.g_q, L.g_k, c.rms_eps, m->rope, cm, n,
                                     L.kc, L.vc, c.max_batch, c.max_seq, m->qsplit));
+    // (fp32 attention over one chunk writes the operand of the output projection itself)
+    const bool direct = m->f32 && p.grid_chunks == 1;
     RUN(FAM_ATTN, p.kv_rows * 2.0 * Dkv * hw, p.kv_rows * 4.0 * Dq,
         launch_attn_partial(s, dt, m->qkv, m->qsplit, nq, nkv, L.kc, L.vc, c.max_batch, c.max_seq, cm, n,
-                            p.grid_chunks, m->partial, m->max_chunks, fuse ? &fz : nullptr, p.one_slot));
-    RUN(FAM_COMBINE, 0, 0,
+                            p.grid_chunks, m->partial, m->max_chunks, fuse ? &fz : nullptr, p.one_slot,
+                            direct ? m->Ap : nullptr, nc, ns));
+    if (!direct) RUN(FAM_COMBINE, 0, 0,
         launch_attn_combine(s, dt, m->partial, m->max_chunks, nq, cm, n, m->Ap, nc, ns));
     {
       GemmArgs a{};
@@ -566,8 +570,10 @@ int decode_nsplit(const nnc_model* m, uint32_t batch) {
 // Chunk count of an attention launch, rounded up to a multiple of 8 (the captured decode graphs
 // are keyed by it: a new one every 512 positions, and at most 7 idle workgroups per sequence
 // and kv head instead of up to half of them).
-int chunks_grid(uint32_t max_pos) {
+// One chunk of an fp32 model stays one: its attention needs no merge.
+int chunks_grid(uint32_t max_pos, bool f32 = false) {
   const int need = (int)(max_pos / ATT_CHUNK) + 1;
+  if (f32 && need == 1) return 1;
   return (need + 7) / 8 * 8;
 }
 
@@ -588,7 +594,7 @@ nnc_status check_slots(const nnc_model* m, const uint32_t* slots, uint32_t batch
 }
 
 nnc_status set_decode_state(nnc_model* m, const uint32_t* slots, const int32_t* tokens, uint32_t batch,
-                            uint32_t* max_pos_out, double* kv_rows_out, const float* x_rows = nullptr) {
+                            uint32_t* max_pos_out, double* kv_rows_out) {
   uint32_t pos[MAX_COLS];
   uint32_t mx = 0;
   double rows = 0;
@@ -599,8 +605,21 @@ nnc_status set_decode_state(nnc_model* m, const uint32_t* slots, const int32_t* 
   }
   *max_pos_out = mx;
   *kv_rows_out = rows;
-  // (x_rows: hidden-state input, copied to x by the same launch)
-  HIP_TRY(launch_set_state(m->stream, m->st, (int)batch, tokens, slots, pos, 0, x_rows, m->x, x_rows ? (size_t)batch * m->H() : 0));
+  HIP_TRY(launch_set_state(m->stream, m->st, (int)batch, tokens, slots, pos, 0));
+  return NNC_OK;
+}
+
+// Start of a hidden-state pass of p.ncols rows: the residual stream, the columns' state and the first layer's normed operand in one
+// launch (where the rows can be read sixteen bytes at a time).
+nnc_status begin_hidden(nnc_model* m, Pass& p, const float* rows, const uint32_t* slots, const uint32_t* pos) {
+  const int H = (int)m->H(), n = p.ncols;
+  p.begun = m->c.n_layers > 0 && H <= 8192 && reinterpret_cast<uintptr_t>(rows) % 16 == 0;
+  if (p.begun)
+    RUN(FAM_NORM, n * H * 12.0, 0,
+        launch_rows_rmsnorm_pack(m->stream, m->dt, rows, slots, pos, m->st, m->x, m->L[0].g_in, H, m->c.rms_eps, n, m->Xp, n * p.nsplit,
+                                 p.nsplit));
+  else
+    HIP_TRY(launch_set_state(m->stream, m->st, n, nullptr, slots, pos, 0, rows, m->x, (size_t)n * H));
   return NNC_OK;
 }
 
@@ -1600,18 +1619,19 @@ static nnc_status prefill_common(nnc_model* m, uint32_t slot, const int32_t* tok
       slots[i] = slot;
       pos[i] = len0 + t0 + i;
     }
-    HIP_TRY(launch_set_state(m->stream, m->st, (int)nc, tokens ? tokens + t0 : nullptr, slots, pos, 0));
     Pass p;
     p.ncols = (int)nc;
     p.nsplit = nsplit;
     p.tokens = tokens != nullptr;
-    p.grid_chunks = chunks_grid(pos[nc - 1]);
+    p.grid_chunks = chunks_grid(pos[nc - 1], m->f32);
     p.one_slot = true;
     for (uint32_t i = 0; i < nc; ++i) p.kv_rows += pos[i] + 1.0;
     const bool last = t0 + nc == n;
     int pending = 0;
-    if (!tokens) {
-      HIP_TRY(launch_copy_rows(m->stream, x + (size_t)t0 * H, m->x, (size_t)nc * H));
+    if (tokens) {
+      HIP_TRY(launch_set_state(m->stream, m->st, (int)nc, tokens + t0, slots, pos, 0));
+    } else {
+      if (nnc_status st = begin_hidden(m, p, x + (size_t)t0 * H, slots, pos)) return st;
       p.pending_out = &pending;
     }
     if (last && tokens && (logits_out || next_out)) {
@@ -1679,11 +1699,11 @@ nnc_status nnc_decode_step(nnc_model* m, const uint32_t* slots, const int32_t* t
     p.logits = logits_out;
     p.logits_ld = m->V();
     p.next = next_out ? m->next : nullptr;
-    p.grid_chunks = chunks_grid(max_pos);
+    p.grid_chunks = chunks_grid(max_pos, m->f32);
     p.kv_rows = kv_rows;
     if (nnc_status st = run_pass(m, p)) return st;
   } else {
-    if (nnc_status st = greedy_step(m, batch, nsplit, chunks_grid(max_pos), true, kv_rows)) return st;
+    if (nnc_status st = greedy_step(m, batch, nsplit, chunks_grid(max_pos, m->f32), true, kv_rows)) return st;
   }
   if (next_out) HIP_TRY(hipMemcpyAsync(next_out, m->next, batch * 4, hipMemcpyDeviceToDevice, m->stream));
   for (uint32_t i = 0; i < batch; ++i) m->len[slots[i]] += 1;
@@ -1738,7 +1758,7 @@ nnc_status nnc_decode_step_static(nnc_model* m, const uint32_t* slots, const int
   // carve the workspace; sizes follow this call's batch and longest context, not max_seq
   uint32_t max_pos = 0;
   for (uint32_t i = 0; i < batch; ++i) max_pos = std::max(max_pos, m->len[slots[i]]);
-  const int nsplit = decode_nsplit(m, batch), grid_chunks = chunks_grid(max_pos);
+  const int nsplit = decode_nsplit(m, batch), grid_chunks = chunks_grid(max_pos, m->f32);
   const size_t H = m->H(), Dq = m->Dq(), Dkv = m->Dkv(), F = m->F(), V = m->V(), w = m->esz(), B = batch;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -1818,7 +1838,7 @@ nnc_status nnc_decode_greedy(nnc_model* m, const uint32_t* slots, const int32_t*
     return NNC_OK;
   }
   for (uint32_t step = 0; step < n_steps; ++step) {
-    const int gc = chunks_grid(max_pos + step);
+    const int gc = chunks_grid(max_pos + step, m->f32);
     if (logits_out) {
       Pass p;
       p.decode = true;
@@ -1846,21 +1866,27 @@ nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const flo
   if (m->c.has_embed_and_head) return fail(NNC_E_STATE, "model takes tokens; use nnc_decode_step");
   if (nnc_status st = check_slots(m, slots, batch, 1)) return st;
   uint32_t max_pos = 0;
-  double kv_rows = 0;
-  if (nnc_status st = set_decode_state(m, slots, nullptr, batch, &max_pos, &kv_rows, x)) return st;
   Pass p;
   p.decode = true;
-  p.kv_rows = kv_rows;
   p.ncols = (int)batch;
   p.nsplit = decode_nsplit(m, batch);
   p.tokens = false;
-  p.grid_chunks = chunks_grid(max_pos);
+  {
+    uint32_t pos[MAX_COLS];
+    for (uint32_t i = 0; i < batch; ++i) {
+      pos[i] = m->len[slots[i]];
+      max_pos = std::max(max_pos, pos[i]);
+      p.kv_rows += pos[i] + 1.0;
+    }
+    if (nnc_status st = begin_hidden(m, p, x, slots, pos)) return st;
+  }
+  p.grid_chunks = chunks_grid(max_pos, m->f32);
   int pending = 0;
   p.pending_out = &pending;
-  // One small layer is eight kernels of a few microseconds: launched one by one they are bound by the
-  // host (41 us per call), replayed as a graph by the GPU.
+  // One small layer is six kernels of a few microseconds here, one before and one behind: launched one by one they are bound by
+  // the host (1110 - 1390 us for sixteen steps, by the box), as a graph less so (1104 - 1190; 36 us of the GPU per step, 69 of the host).
   const bool graph = m->opt_graph && !m->profiling && m->stream != nullptr && !being_captured(m);
-  nnc_model::HiddenGraph* hg = graph ? &m->hidden_graphs[std::make_tuple((int)batch, p.nsplit, p.grid_chunks)] : nullptr;
+  nnc_model::HiddenGraph* hg = graph ? &m->hidden_graphs[std::make_tuple((int)batch, p.nsplit, p.begun ? p.grid_chunks : -p.grid_chunks)] : nullptr;
   if (hg && !hg->exec && ++hg->uses > 2) {
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));

@@ -126,8 +126,10 @@ hipError_t launch_embed(hipStream_t s, int dt, const void* Ep, int H, const ColS
 hipError_t launch_rmsnorm_pack(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
                                long part_stride, const float* gain, int H, float eps, int ncols, void* Xp,
                                int NC, int nsplit);
-hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, const ColState* st, float* x, const float* gain,
+hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, ColState* st, float* x, const float* gain,
                                      int H, float eps, int ncols, void* Xp, int NC, int nsplit);
+hipError_t launch_rows_rmsnorm_pack(hipStream_t s, int dt, const float* rows, const uint32_t* slot, const uint32_t* pos, ColState* st,
+                                    float* x, const float* gain, int H, float eps, int ncols, void* Xp, int NC, int nsplit);
 // n 32-bit words = 0 (a fill kernel: safe under graph capture)
 hipError_t launch_zero_words(hipStream_t s, uint32_t* p, int n);
 // Do two streams run side by side?  w (two words, zero): w[0] is set on one, waited for (about 0.5 ms at most) on the other,
@@ -162,7 +164,7 @@ bool attn_partial_can_fuse(int dt, int nq, int nkv);
 hipError_t launch_attn_partial(hipStream_t s, int dt, const float* qkv, const void* qsplit, int nq, int nkv,
                                void* kc, void* vc, uint32_t max_batch, uint32_t max_seq, const ColMap& cm,
                                int ncols, int grid_chunks, float* partial, int max_chunks,
-                               const AttnFuseArgs* fuse, bool one_slot = false);
+                               const AttnFuseArgs* fuse, bool one_slot = false, void* out = nullptr, int NC = 0, int nsplit = 1);
 hipError_t launch_attn_combine(hipStream_t s, int dt, const float* partial, int max_chunks, int nq,
                                const ColMap& cm, int ncols, void* Op, int NC, int nsplit);
 
@@ -271,7 +273,6 @@ hipError_t launch_argmax(hipStream_t s, const float* logits, long ld, int V, int
                          int32_t* token_log = nullptr);
 hipError_t launch_kv_read(hipStream_t s, int dt, const void* cache, uint32_t max_seq, int nkv,
                           uint32_t pos0, uint32_t n, float* out);
-hipError_t launch_copy_rows(hipStream_t s, const float* src, float* dst, size_t n);
 
 // ---- resident whole-step decode kernel (16-bit models, one to four sequences) ----
 constexpr int MK_MAX_SEQ = 4;  // 3 pieces each: 12 of the 16 operand columns of a matrix-core instruction

@@ -165,15 +165,20 @@ __global__ __launch_bounds__(256) void k_set_state(ColState* st, StateInit init,
   if (i == 0) st->step = step;
 }
 
-hipError_t launch_set_state(hipStream_t s, ColState* st, int ncols, const int32_t* tok,
-                            const uint32_t* slot, const uint32_t* pos, uint32_t step, const float* rows, float* x,
-                            size_t n) {
+static StateInit state_init(int ncols, const int32_t* tok, const uint32_t* slot, const uint32_t* pos) {
   StateInit init;
   for (int i = 0; i < MAX_COLS; ++i) {
     init.tok[i] = (i < ncols && tok) ? tok[i] : 0;
     init.slot[i] = i < ncols ? slot[i] : 0;
     init.pos[i] = i < ncols ? pos[i] : 0;
   }
+  return init;
+}
+
+hipError_t launch_set_state(hipStream_t s, ColState* st, int ncols, const int32_t* tok,
+                            const uint32_t* slot, const uint32_t* pos, uint32_t step, const float* rows, float* x,
+                            size_t n) {
+  const StateInit init = state_init(ncols, tok, slot, pos);
   if (!rows) n = 0;
   const unsigned grid = (unsigned)((n + 255) / 256 < 256 ? (n + 255) / 256 : 256);
   k_set_state<<<grid ? grid : 1, n ? 256 : MAX_COLS, 0, s>>>(st, init, ncols, step, rows, x, n);
@@ -279,15 +284,28 @@ __device__ __forceinline__ void store_normed4(void* Xp, int NC, int nsplit, int 
 // 4.8 us for 8 rows of 2560 with three partials: the kernel is memory latency from start to end.)
 // EMB: the row comes from the packed embedding matrix (token of the column) and is written to x; a
 // gather kernel of its own in front of the first layer cost a greedy step 6.5 us (8 x 2560).
-template <bool F32, int NV, bool EMB, class HF>
+// ROWS: the row comes from the caller's rows (hidden-state steps) and is written to x, and the first workgroup
+// sets the columns' state: one kernel less than with k_set_state in front (2.5 us of it, 3 on the host).
+struct NoState {};
+enum { NORM_PLAIN, NORM_EMB, NORM_ROWS };
+template <bool F32, int NV, int MODE, class HF, class INIT>
 __global__ __launch_bounds__(256) void k_rmsnorm_pack(float* __restrict__ x, long ldx,
                                                       const float* __restrict__ part, int nparts,
                                                       long part_stride, const float* __restrict__ gain,
                                                       int H, float eps, void* __restrict__ Xp, int NC,
                                                       int nsplit, const void* __restrict__ Ep,
-                                                      const ColState* __restrict__ st) {
+                                                      ColState* __restrict__ st, INIT init) {
   __shared__ float sm[4];
   const int seq = blockIdx.x;
+  if constexpr (MODE == NORM_ROWS) {
+    const int i = threadIdx.x;
+    if (seq == 0 && i < (int)gridDim.x) {
+      st->tok[i] = init.tok[i];
+      st->slot[i] = init.slot[i];
+      st->pos[i] = init.pos[i];
+    }
+    if (seq == 0 && i == 0) st->step = 0;
+  }
   float* xr = x + (size_t)seq * ldx;
   constexpr int MAXP = 8;  // most k slices a projection is split into
   float4 v[NV], g[NV], pp[NV][MAXP];
@@ -296,7 +314,10 @@ __global__ __launch_bounds__(256) void k_rmsnorm_pack(float* __restrict__ x, lon
     const int i = (threadIdx.x + 256 * q) * 4;
     v[q] = g[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < H) {
-      if constexpr (EMB) {
+      if constexpr (MODE == NORM_ROWS) {
+        v[q] = *reinterpret_cast<const float4*>(static_cast<const float*>(Ep) + (size_t)seq * H + i);
+        *reinterpret_cast<float4*>(xr + i) = v[q];
+      } else if constexpr (MODE == NORM_EMB) {
         const int r = st->tok[seq];
         if constexpr (F32) {
           v[q] = static_cast<const float4*>(Ep)[((size_t)(r >> 4) * (H / 16) + (i >> 4)) * 64 + (r & 15) + 16 * ((i & 15) >> 2)];
@@ -339,14 +360,14 @@ __global__ __launch_bounds__(256) void k_rmsnorm_pack(float* __restrict__ x, lon
   }
 }
 
-template <bool EMB>
+template <int MODE, class INIT>
 static hipError_t rmsnorm_pack_dispatch(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
                                         long part_stride, const float* gain, int H, float eps, int ncols, void* Xp,
-                                        int NC, int nsplit, const void* Ep, const ColState* st) {
+                                        int NC, int nsplit, const void* Ep, ColState* st, const INIT& init) {
   if (H % 4 || H > 8192 || nparts > 8 || nparts < 0 || ldx % 4) return hipErrorInvalidValue;
-#define RN_LAUNCH(NV)                                                                                                 \
-  NNC_FOR_DTYPE(dt, k_rmsnorm_pack<F32, NV, EMB, HF><<<ncols, 256, 0, s>>>(x, ldx, part, nparts, part_stride, gain, H, eps, \
-                                                                           Xp, NC, nsplit, Ep, st))
+#define RN_LAUNCH(NV)                                                                                                       \
+  NNC_FOR_DTYPE(dt, k_rmsnorm_pack<F32, NV, MODE, HF, INIT><<<ncols, 256, 0, s>>>(x, ldx, part, nparts, part_stride, gain, H, \
+                                                                                 eps, Xp, NC, nsplit, Ep, st, init))
   if (H <= 1024) RN_LAUNCH(1);
   else if (H <= 2048) RN_LAUNCH(2);
   else if (H <= 4096) RN_LAUNCH(4);
@@ -358,13 +379,21 @@ static hipError_t rmsnorm_pack_dispatch(hipStream_t s, int dt, float* x, long ld
 hipError_t launch_rmsnorm_pack(hipStream_t s, int dt, float* x, long ldx, const float* part, int nparts,
                                long part_stride, const float* gain, int H, float eps, int ncols, void* Xp,
                                int NC, int nsplit) {
-  return rmsnorm_pack_dispatch<false>(s, dt, x, ldx, part, nparts, part_stride, gain, H, eps, ncols, Xp, NC, nsplit, nullptr, nullptr);
+  return rmsnorm_pack_dispatch<NORM_PLAIN>(s, dt, x, ldx, part, nparts, part_stride, gain, H, eps, ncols, Xp, NC, nsplit, nullptr,
+                                           nullptr, NoState{});
 }
 
 // the same with x[col] = E[tok[col]] first (x is written)
-hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, const ColState* st, float* x, const float* gain,
+hipError_t launch_embed_rmsnorm_pack(hipStream_t s, int dt, const void* Ep, ColState* st, float* x, const float* gain,
                                      int H, float eps, int ncols, void* Xp, int NC, int nsplit) {
-  return rmsnorm_pack_dispatch<true>(s, dt, x, H, nullptr, 0, 0, gain, H, eps, ncols, Xp, NC, nsplit, Ep, st);
+  return rmsnorm_pack_dispatch<NORM_EMB>(s, dt, x, H, nullptr, 0, 0, gain, H, eps, ncols, Xp, NC, nsplit, Ep, st, NoState{});
+}
+
+// the same with x[col] = rows[col] (16-byte aligned) and the columns' state set first
+hipError_t launch_rows_rmsnorm_pack(hipStream_t s, int dt, const float* rows, const uint32_t* slot, const uint32_t* pos, ColState* st,
+                                    float* x, const float* gain, int H, float eps, int ncols, void* Xp, int NC, int nsplit) {
+  return rmsnorm_pack_dispatch<NORM_ROWS>(s, dt, x, H, nullptr, 0, 0, gain, H, eps, ncols, Xp, NC, nsplit, rows, st,
+                                          state_init(ncols, nullptr, slot, pos));
 }
 
 __global__ void k_zero_words(uint32_t* p, int n) {
@@ -1059,14 +1088,29 @@ __device__ __forceinline__ void widen_row8(const Row8Raw<F32>& r, float* v) {
   }
 }
 
-template <bool F32, int GH, class HF>
+struct AttnFuse {
+  const float* qkv;   // [slices][columns][(nq + 2 nkv) * 128] raw q | k | v, as k-slice partial sums
+  const float* gq;    // QK-norm gains
+  const float* gk;
+  float eps;
+  const float2* rope;
+  int slices;         // partial sums to add, in slice order (>= 1)
+  long slice_stride;  // floats between them
+};
+// FUSED (fp32 decode passes): QK norm, rotary embedding and append run here too, as in k_attn_partial_mc below.
+// out != NULL: the chunk is the only one of every column, and the workgroup writes the operand of the output projection itself (the bits
+// that k_attn_combine would make of one record).  A layer of the 0.6B shape at 32 positions is ten kernels of 2 - 7 us without
+// these two and eight with them.
+template <bool F32, int GH, bool FUSED, class HF>
 __global__ __launch_bounds__(256) void k_attn_partial(
-    const float* __restrict__ qkv, int nq, int nkv, const void* __restrict__ kc,
-    const void* __restrict__ vc, uint32_t max_seq, ColMap cm,
-    float* __restrict__ partial, int max_chunks) {
+    const float* __restrict__ qkv, AttnFuse fz, int nq, int nkv, void* __restrict__ kc,
+    void* __restrict__ vc, uint32_t max_seq, ColMap cm,
+    float* __restrict__ partial, int max_chunks, void* __restrict__ out, int NC, int nsplit) {
+  static_assert(F32 || !FUSED, "16-bit caches have a fused kernel of their own");
   __shared__ float sc[GH][ATT_CHUNK];      // scores, then softmax weights
   __shared__ float red[4][4][GH][128];     // value sums per wave and per row group of 16 lanes
   __shared__ float sm_m[GH], sm_l[GH];
+  __shared__ __attribute__((aligned(16))) float fresh[FUSED ? GH + 2 : 1][128];  // rotated queries, the new K row, the new V row
   const int chunk = blockIdx.x, col = blockIdx.z;
   const int G = nq / nkv;
   const int groups = G / GH;
@@ -1080,25 +1124,62 @@ __global__ __launch_bounds__(256) void k_attn_partial(
   const int ld = (nq + 2 * nkv) * 128;
   const size_t base = ((size_t)slot * nkv + kvh) * max_seq * 128;
 
-  // this lane's 8-element slice of each query head
-  float q[GH][8];
-#pragma unroll
-  for (int h = 0; h < GH; ++h) {
-    const float* qp = qkv + (size_t)(cm.row0 + col) * ld + (size_t)(head0 + h) * 128 + c16 * 8;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) q[h][e] = qp[e];
-  }
-  const float scale = 0.08838834764831845f;  // 1 / sqrt(128)
-
-  // all K and V rows of the chunk that this lane group touches, loaded up front (rows past
-  // `pos` re-read row `pos`: valid memory, masked below)
+  // all K and V rows of the chunk that this lane group touches, loaded up front (rows past the last
+  // cached one re-read it: valid memory, masked below; fused: row `pos` is not cached yet)
+  const uint32_t jlast = FUSED ? (pos > 0 ? pos - 1 : 0) : pos;
   Row8Raw<F32> kraw[ATT_CHUNK / 16], vraw[ATT_CHUNK / 16];
 #pragma unroll
   for (int it = 0; it < ATT_CHUNK / 16; ++it) {
-    const uint32_t j = min(j0 + (uint32_t)(it * 16 + wave * 4 + jj), pos);
+    const uint32_t j = min(j0 + (uint32_t)(it * 16 + wave * 4 + jj), jlast);
     kraw[it] = load_row8_raw<F32>(kc, base + (size_t)j * 128 + c16 * 8);
     vraw[it] = load_row8_raw<F32>(vc, base + (size_t)j * 128 + c16 * 8);
   }
+
+  // this lane's 8-element slice of each query head
+  float q[GH][8];
+  if constexpr (FUSED) {
+    const bool owns_new = pos - j0 < (uint32_t)ATT_CHUNK;
+    const float* row = fz.qkv + (size_t)col * ld;
+    for (int role = wave; role < GH + 2; role += 4) {
+      if (role >= GH && !owns_new) continue;
+      const float* p = row + (size_t)(role < GH ? head0 + role : nq + (role == GH ? 0 : nkv) + kvh) * 128;
+      float a = p[lane], b = p[lane + 64];
+      for (int sl = 1; sl < fz.slices; ++sl) {
+        a += p[(size_t)sl * fz.slice_stride + lane];
+        b += p[(size_t)sl * fz.slice_stride + lane + 64];
+      }
+      if (role <= GH) {
+        const float* gg = role < GH ? fz.gq : fz.gk;
+        qk_norm_rope(a, b, fz.eps, gg[lane], gg[lane + 64], fz.rope[(size_t)pos * 64 + lane]);
+      }
+      fresh[role][lane] = a;
+      fresh[role][lane + 64] = b;
+      if (role >= GH && hg == 0) {  // (the head groups of a kv head share the row)
+        float* dst = static_cast<float*>(role == GH ? kc : vc) + base + (size_t)pos * 128;
+        dst[lane] = a;
+        dst[lane + 64] = b;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < GH; ++h)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) q[h][e] = fresh[h][c16 * 8 + e];
+#pragma unroll
+    for (int it = 0; it < ATT_CHUNK / 16; ++it)
+      if (j0 + (uint32_t)(it * 16 + wave * 4 + jj) == pos) {
+        kraw[it] = load_row8_raw<F32>(fresh[GH], c16 * 8);
+        vraw[it] = load_row8_raw<F32>(fresh[GH + 1], c16 * 8);
+      }
+  } else {
+#pragma unroll
+    for (int h = 0; h < GH; ++h) {
+      const float* qp = qkv + (size_t)(cm.row0 + col) * ld + (size_t)(head0 + h) * 128 + c16 * 8;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) q[h][e] = qp[e];
+    }
+  }
+  const float scale = 0.08838834764831845f;  // 1 / sqrt(128)
 
   // scores s[h][j] = <q_h, K_j> / sqrt(d); positions beyond `pos` get -inf
 #pragma unroll
@@ -1164,6 +1245,10 @@ __global__ __launch_bounds__(256) void k_attn_partial(
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) v += (red[w][0][h][i] + red[w][1][h][i]) + (red[w][2][h][i] + red[w][3][h][i]);
+    if (out) {
+      store_packed<F32, HF>(out, NC, nsplit, col, (head0 + h) * 128 + i, v / sm_l[h]);
+      continue;
+    }
     float* rec = partial + (((size_t)col * nq + head0 + h) * max_chunks + chunk) * 132;
     rec[i] = v;
     if (i == 0) {
@@ -1190,15 +1275,6 @@ __global__ __launch_bounds__(256) void k_attn_partial(
 // to the cache together with the V row and patches into its own operands (the row is not in the
 // cache when the loads are issued).  One kernel less per layer.
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-struct AttnFuse {
-  const float* qkv;   // [slices][columns][(nq + 2 nkv) * 128] raw q | k | v, as k-slice partial sums
-  const float* gq;    // QK-norm gains
-  const float* gk;
-  float eps;
-  const float2* rope;
-  int slices;         // partial sums to add, in slice order (>= 1)
-  long slice_stride;  // floats between them
-};
 template <bool FUSED, class HF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FUSED ? 6 : 5, FUSED ? 6 : 5))) void k_attn_partial_mc(const uint16_t* __restrict__ qsplit, AttnFuse fz, int nq,
                                                          int nkv, uint16_t* __restrict__ kc,
@@ -1538,15 +1614,16 @@ __global__ __launch_bounds__(256) void k_attn_partial_shared(const uint16_t* __r
   }
 }
 
-bool attn_partial_can_fuse(int dt, int nq, int nkv) { return dt != DT_F32 && nq / nkv <= 8; }
+bool attn_partial_can_fuse(int dt, int nq, int nkv) { return dt == DT_F32 || nq / nkv <= 8; }
 
 // fuse != NULL: raw projection output, gains and rotary table for the fused variant (the caller
 // then does not launch k_qknorm_rope_append; columns must be different slots).
 hipError_t launch_attn_partial(hipStream_t s, int dt, const float* qkv, const void* qsplit, int nq, int nkv,
                                void* kc, void* vc, uint32_t max_batch, uint32_t max_seq,
                                const ColMap& cm, int ncols, int grid_chunks, float* partial,
-                               int max_chunks, const AttnFuseArgs* fuse, bool one_slot) {
+                               int max_chunks, const AttnFuseArgs* fuse, bool one_slot, void* out, int NC, int nsplit) {
   (void)max_batch;
+  if (out && (dt != DT_F32 || grid_chunks != 1)) return hipErrorInvalidValue;
   const int G = nq / nkv;
   const bool f32 = dt == DT_F32, f16 = dt == DT_F16;
   if (fuse) {
@@ -1554,7 +1631,13 @@ hipError_t launch_attn_partial(hipStream_t s, int dt, const float* qkv, const vo
     dim3 grid(grid_chunks, nkv, ncols);
     const AttnFuse fz{qkv, fuse->gq, fuse->gk, fuse->eps, fuse->rope, fuse->qkv_slices > 1 ? fuse->qkv_slices : 1,
                       fuse->qkv_slice_stride};
-    if (f16)
+    if (f32) {
+      const int GH = (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
+      grid.y = nkv * (G / GH);
+#define NNC_ATT(H) k_attn_partial<true, H, true, Bf16><<<grid, 256, 0, s>>>(qkv, fz, nq, nkv, kc, vc, max_seq, cm, partial, max_chunks, out, NC, nsplit)
+      if (GH == 4) NNC_ATT(4); else if (GH == 2) NNC_ATT(2); else NNC_ATT(1);
+#undef NNC_ATT
+    } else if (f16)
       k_attn_partial_mc<true, Fp16><<<grid, 256, 0, s>>>(nullptr, fz, nq, nkv, static_cast<uint16_t*>(kc),
                                                          static_cast<uint16_t*>(vc), max_seq, cm, partial, max_chunks);
     else
@@ -1590,7 +1673,7 @@ hipError_t launch_attn_partial(hipStream_t s, int dt, const float* qkv, const vo
   const int GH = (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
   dim3 grid(grid_chunks, nkv * (G / GH), ncols);
 #define NNC_ATT(H) \
-  NNC_FOR_DTYPE(dt, k_attn_partial<F32, H, HF><<<grid, 256, 0, s>>>(qkv, nq, nkv, kc, vc, max_seq, cm, partial, max_chunks))
+  NNC_FOR_DTYPE(dt, k_attn_partial<F32, H, false, HF><<<grid, 256, 0, s>>>(qkv, AttnFuse{}, nq, nkv, kc, vc, max_seq, cm, partial, max_chunks, out, NC, nsplit))
   if (GH == 4) NNC_ATT(4); else if (GH == 2) NNC_ATT(2); else NNC_ATT(1);
 #undef NNC_ATT
   return hipGetLastError();
@@ -1755,16 +1838,6 @@ hipError_t launch_kv_read(hipStream_t s, int dt, const void* cache, uint32_t max
                           uint32_t pos0, uint32_t n, float* out) {
   dim3 grid(nkv, n);
   NNC_FOR_DTYPE(dt, k_kv_read<F32, HF><<<grid, 128, 0, s>>>(cache, max_seq, nkv, pos0, out));
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_copy(const float* __restrict__ src, float* __restrict__ dst, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
-}
-
-hipError_t launch_copy_rows(hipStream_t s, const float* src, float* dst, size_t n) {
-  const unsigned grid = (unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-  k_copy<<<grid ? grid : 1, 256, 0, s>>>(src, dst, n);
   return hipGetLastError();
 }
 

@@ -838,6 +838,44 @@ def test_fused_qk_norm_rope_append_equals_separate_kernel(nnc, batch, planner):
         assert np.all(np.abs(a - b) <= np.abs(a) * 2.0 ** -7 + 1e-30) and np.mean(a != b) < 0.02
 
 
+@pytest.mark.parametrize("planner", [0, 1], ids=["hand-rules", "planner"])
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("heads", [(4, 2), (3, 3), (6, 2), (8, 2)], ids=str)
+def test_fused_fp32_attention_equals_separate_kernels(nnc, heads, batch, planner):
+    """fp32 decode steps with QK-norm / RoPE / append inside the attention kernel (one, two or four heads per workgroup, one to
+    three workgroups per kv head) and in a kernel of their own, from an empty slot past position 64, where the attention stops
+    writing the projection's operand itself.  The same bits, up to the QKV projection's k slices; both match the oracle."""
+    shape = synth.ModelShape("f32-heads", hidden=256, n_layers=2, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, ffn=512, vocab=0,
+                             has_embed_and_head=False, tied_lm_head=False, dtype=synth.F32)
+    rows = synth.activations(70 * batch, shape.hidden)
+    out = []
+    for fused in (0, 1):
+        g, o = _pair(nnc, shape, batch, 80)
+        g.set_option(nnc.OPT_PLANNER, planner)
+        g.set_option(nnc.OPT_FUSE_QK, fused)
+        slots = list(range(batch))[::-1]
+        out.append([g.decode_step_hidden(slots, rows[i * batch:(i + 1) * batch]).cpu().numpy() for i in range(70)])
+        out[-1].append(g.kv_read(1, 0, 0, 0, 70).cpu().numpy())
+    for i, (x, y) in enumerate(zip(*out)):
+        assert np.array_equal(x, y) if not planner else np.abs(x - y).max() <= 1e-5 * np.abs(y).max(), i
+    for i in range(70):
+        want = o.step_hidden(0, rows[i * batch + batch - 1].astype(np.float64))
+        assert rel_inf(out[1][i][batch - 1].astype(np.float64), want) <= F32_REL
+
+
+def test_hidden_rows_at_any_float_address(nnc):
+    """Rows that start between two sixteen-byte boundaries take the separate copy and norm: the same bits, prompt and step."""
+    import torch
+    x = torch.from_numpy(synth.activations(24, SMALL_LAYER_F32.hidden)).cuda()
+    shifted = torch.empty(x.numel() + 1, dtype=torch.float32, device="cuda")[1:].view(x.shape).copy_(x)
+    assert x.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 == 4 and shifted.is_contiguous()
+    out = []
+    for rows in (x, shifted):
+        g, _ = _pair(nnc, SMALL_LAYER_F32, 2, 64)
+        out.append([g.prefill_hidden(1, rows[:20])] + [g.decode_step_hidden([1], rows[i:i + 1]) for i in range(20, 24)])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
 @pytest.mark.parametrize("shape,fuse", [(SMALL_BF16, 1), (SMALL_G4, 0)], ids=["small-bf16-fused", "small-g4-separate"])
 def test_batched_decode_mixed_lengths_up_to_4k(nnc, shape, fuse):
     """Three slots of one batch at very different lengths (100, 2040 and 4090 cached positions,
