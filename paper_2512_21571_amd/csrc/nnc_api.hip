@@ -389,9 +389,12 @@ constexpr int MAX_QKV_SLICES = 4;  // k slices of the QKV projection that the fu
 // wide: launches that may run alone on the chip (decode passes).  The chunk pass behind a long
 // prompt runs beside the prompt's last block on a second stream; workgroups of 6 or 8 row tiles
 // (240 registers per wave) do not fit next to that block's GEMM workgroups and cost the prompt 5 %.
-int skinny_rt_choices(int dt, int epi, bool wide = true) {
-  if (dt == (int)NNC_F32 || !wide) return epi == EPI_SWIGLU ? ((1 << 2) | (1 << 4)) : ((1 << 1) | (1 << 2) | (1 << 4));
-  return epi == EPI_SWIGLU ? ((1 << 2) | (1 << 4) | (1 << 6) | (1 << 8)) : ((1 << 1) | (1 << 2) | (1 << 3) | (1 << 4) | (1 << 6));
+// Bit 0: the last workgroup may have fewer row tiles.  For plain 16- and 32-bit stores without slices, which is the LM head: 1055 tiles of an 8B head
+// are 1055 workgroups of one, each reading twice as much operand as weights at 32 columns, or 352 of three.
+int skinny_rt_choices(int dt, int epi, int max_slices, bool wide = true, bool w8 = false) {
+  const int ragged = epi == EPI_STORE && max_slices == 1 && !w8;
+  if (dt == (int)NNC_F32 || !wide) return epi == EPI_SWIGLU ? ((1 << 2) | (1 << 4)) : ((1 << 1) | (1 << 2) | (1 << 4) | ragged);
+  return epi == EPI_SWIGLU ? ((1 << 2) | (1 << 4) | (1 << 6) | (1 << 8)) : ((1 << 1) | (1 << 2) | (1 << 3) | (1 << 4) | (1 << 6) | ragged);
 }
 void plan_skinny(const nnc_model* m, GemmArgs& a, int epi, int max_slices, bool wide) {
   if (!m->opt_planner) return;
@@ -399,7 +402,7 @@ void plan_skinny(const nnc_model* m, GemmArgs& a, int epi, int max_slices, bool 
   // byte weights: a weight tile meets two operand k tiles
   const bool w8 = a.wscale != nullptr;
   const SkinnyGemmPlan pl = plan_skinny_gemm(mc, a.n_tiles, a.KT, w8 ? 2 * a.ncols : a.ncols, a.nseq,
-                                             skinny_rt_choices(m->dt, epi, wide), max_slices);
+                                             skinny_rt_choices(m->dt, epi, max_slices, wide, w8), max_slices);
   if (pl.rt <= 0) return;
   a.rt = pl.rt;
   a.kts_per_split = pl.kts_per_split;
@@ -1965,7 +1968,7 @@ nnc_status nnc_plan_skinny_gemm_query(uint32_t rows, uint32_t k, uint32_t n_seq,
     return fail(NNC_E_ARG, "bad GEMM shape for the planner");
   const Machine mc = machine_mi355x((int)n_cus);
   const SkinnyGemmPlan p = plan_skinny_gemm(mc, (int)(rows / 16), (int)(k / 32), (int)(n_seq * pieces), (int)n_seq,
-                                            skinny_rt_choices((int)NNC_BF16, (int)epilogue),
+                                            skinny_rt_choices((int)NNC_BF16, (int)epilogue, (int)max_k_slices),
                                             (int)std::min<uint32_t>(max_k_slices, MAX_KSPLIT));
   nnc_gemm_plan o{};
   o.tile_rows = (uint32_t)p.rt * 16; o.tile_cols = n_seq * pieces; o.tile_code = p.rt;

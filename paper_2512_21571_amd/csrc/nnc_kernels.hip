@@ -548,6 +548,10 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a) {
   const uint4* __restrict__ W = static_cast<const uint4*>(a.Wp);
   const uint4* __restrict__ X = static_cast<const uint4*>(a.Xp);
   const size_t tile0 = (size_t)blockIdx.x * RT;
+  // The last workgroup of a plain store may have fewer than RT row tiles (LM heads of an odd number of tiles): it reads its last one
+  // again in their place and stores nothing for them.
+  constexpr bool RAGGED = EPI == EPI_STORE && RT > 1 && !W8;
+  const int tiles = RAGGED ? min(RT, a.n_tiles - (int)tile0) : RT;
 
   f32x4 acc[RT][NCB];
 #pragma unroll
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a) {
   // inside the loop.  (With 64-bit vector addresses the compiler recycled registers of earlier
   // load results for them and waited for every outstanding load before it issued the next set.)
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<u32x4*>(Wv + tile0 * KT * 64), 0, RT * KT * 1024, 0x00020000);
+      const_cast<u32x4*>(Wv + tile0 * KT * 64), 0, tiles * KT * 1024, 0x00020000);
   const __amdgpu_buffer_rsrc_t xres =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(Xv), 0, KT * XT * 64 * a.NC, 0x00020000);
   const uint32_t wvoff = (uint32_t)lane * 16u;
@@ -586,7 +590,7 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a) {
   auto load_tile = [&](int kt, u32x4(&av)[RT], u32x4(&bv)[XT * NCB]) __attribute__((always_inline)) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)  // aux 2: non-temporal, each weight byte is used once per pass
-      av[rt] = __builtin_amdgcn_raw_buffer_load_b128(wres, wvoff, (rt * KT + kt) * 1024, 2);
+      av[rt] = __builtin_amdgcn_raw_buffer_load_b128(wres, wvoff, ((RAGGED ? min(rt, tiles - 1) : rt) * KT + kt) * 1024, 2);
 #pragma unroll
     for (int x = 0; x < XT; ++x)
 #pragma unroll
@@ -696,7 +700,7 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a) {
         store_packed<F32, HF>(a.packed_out, a.NC_out, a.nsplit_out, seq, f, act);
       }
     } else {
-      for (int o = tid; o < RC * 16 * nseq; o += 256) {
+      for (int o = tid; o < min(RC, tiles - ch * RC) * 16 * nseq; o += 256) {
         const int r = o / (16 * nseq);
         const int rem = o - r * 16 * nseq;
         const int seq = rem >> 4, row = rem & 15;
@@ -720,7 +724,7 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a) {
 template <bool F32, int NCB, int RT, int EPI, class HF>
 static hipError_t gemm_dispatch(hipStream_t s, const GemmArgs& a) {
   const int ksplit = (a.KT + a.kts_per_split - 1) / a.kts_per_split;
-  dim3 grid(a.n_tiles / RT, ksplit);
+  dim3 grid((a.n_tiles + RT - 1) / RT, ksplit);
   constexpr int U = (RT * NCB <= 2) ? 4 : 2;
   k_gemm_skinny<F32, NCB, RT, EPI, U, HF><<<grid, 256, 0, s>>>(a);
   return hipGetLastError();
@@ -800,7 +804,8 @@ hipError_t launch_gemm(hipStream_t s, int dt, int epi, const GemmArgs& a) {
     return hipErrorInvalidValue;
   }
   if (a.rt > 0) {  // row tiles per workgroup chosen by the caller (the analytic planner)
-    if (a.n_tiles % a.rt || (epi == EPI_SWIGLU && a.rt % 2)) return hipErrorInvalidValue;
+    if (a.n_tiles % a.rt && (epi != EPI_STORE || a.tail.counter)) return hipErrorInvalidValue;
+    if (epi == EPI_SWIGLU && a.rt % 2) return hipErrorInvalidValue;
     if (epi == EPI_SWIGLU) {
       if (a.rt == 2) NNC_FOR_DTYPE(dt, return gemm_dispatch_ncb<F32, EPI_SWIGLU, 2, HF>(s, a));
       if (a.rt == 4) NNC_FOR_DTYPE(dt, return gemm_dispatch_ncb<F32, EPI_SWIGLU, 4, HF>(s, a));

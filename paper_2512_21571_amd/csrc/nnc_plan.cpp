@@ -139,13 +139,13 @@ SkinnyGemmPlan plan_skinny_gemm(const Machine& mc, int n_tiles, int KT, int ncol
   // column, and the kernel loads whole blocks of 16 columns
   const double x_per_kt = 64.0 * ((ncols + 15) / 16 * 16);
   for (int rt = 1; rt <= 8; ++rt) {
-    if (!((rt_choices >> rt) & 1) || n_tiles % rt) continue;
+    if (!((rt_choices >> rt) & 1) || (n_tiles % rt && !(rt_choices & 1))) continue;
     for (int ks = 1; ks <= std::max(1, max_k_slices); ++ks) {
       const int kts = ceil_div(KT, ks);
       if (ks > 1 && kts < 8) break;  // at least two k tiles per wave
       const int slices = ceil_div(KT, kts);
       if (slices != ks) continue;
-      const int wgs = n_tiles / rt * slices;
+      const int wgs = ceil_div(n_tiles, rt) * slices;
       // T_mem, level 1: what the busiest CU pulls through its vector memory path.  A workgroup
       // reads its rt x kts weight tiles once, and the operand of its k slice once for all its
       // row tiles; the operand comes from L2, but it crosses the same per-CU path as the

@@ -1086,6 +1086,23 @@ def test_batched_decode_long_contexts(nnc):
         t = nxt
 
 
+@pytest.mark.parametrize("vocab_tiles,hidden,batch,dtype", [(1055, 256, 11, synth.BF16), (791, 1024, 16, synth.F16), (1055, 4096, 16, synth.BF16),
+                                                            (515, 256, 3, synth.BF16), (1057, 256, 6, synth.F32)])
+def test_head_whose_last_workgroup_has_fewer_row_tiles(nnc, vocab_tiles, hidden, batch, dtype):
+    """LM heads of a number of 16-row tiles that the planner's row tiles per workgroup don't divide: the same logits and tokens as
+    with one row tile per workgroup (each row's sum runs in the same k order), and nothing stored behind a row's end."""
+    shape = synth.ModelShape("head", hidden=hidden, n_layers=0, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=64, vocab=16 * vocab_tiles, dtype=dtype)
+    if dtype != synth.F32:
+        assert vocab_tiles % nnc.plan_skinny_gemm(shape.vocab, hidden, batch, 3 if batch < 6 else 2, 0).tile_code
+    t = [(977 * b + 5) % shape.vocab for b in range(batch)]
+    out = []
+    for planner in (0, 1):
+        g, _ = _pair(nnc, shape, batch, 16)
+        g.set_option(nnc.OPT_PLANNER, planner)
+        out.append([x.cpu() for x in g.decode_step(list(range(batch)), t)])
+    assert np.array_equal(out[0][0].numpy(), out[1][0].numpy()) and out[0][1].tolist() == out[1][1].tolist()
+
+
 def test_multi_block_prefill_long_context(nnc):
     print("case: prompt of several blocks (2048 + 736 single-piece, 16 fp32-grade)", flush=True)
     shape = SMALL_BF16
