@@ -1886,8 +1886,8 @@ nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const flo
   p.grid_chunks = chunks_grid(max_pos, m->f32);
   int pending = 0;
   p.pending_out = &pending;
-  // One small layer is six kernels of a few microseconds here, one before and one behind: launched one by one they are bound by
-  // the host (1110 - 1390 us for sixteen steps, by the box), as a graph less so (1104 - 1190; 36 us of the GPU per step, 69 of the host).
+  // One small layer is six kernels of a few microseconds here, one before and one behind, 36 us of the GPU per step against 69 of the
+  // host.  Launched one by one they take 1036 or 1368 us for a prompt and sixteen steps, by the run; as a graph 1084 - 1190, one run in five 1343.
   const bool graph = m->opt_graph && !m->profiling && m->stream != nullptr && !being_captured(m);
   nnc_model::HiddenGraph* hg = graph ? &m->hidden_graphs[std::make_tuple((int)batch, p.nsplit, p.begun ? p.grid_chunks : -p.grid_chunks)] : nullptr;
   if (hg && !hg->exec && ++hg->uses > 2) {
