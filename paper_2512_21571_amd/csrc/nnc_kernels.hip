@@ -1130,7 +1130,8 @@ __global__ __launch_bounds__(256) void k_attn_partial(
   const size_t base = ((size_t)slot * nkv + kvh) * max_seq * 128;
 
   // all K and V rows of the chunk that this lane group touches, loaded up front (rows past the last
-  // cached one re-read it: valid memory, masked below; fused: row `pos` is not cached yet)
+  // cached one re-read it: valid memory, masked below; fused: row `pos` is not cached yet, and at position 0 no
+  // row of this sequence is: row 0 then holds what an earlier sequence left, which may not be finite)
   const uint32_t jlast = FUSED ? (pos > 0 ? pos - 1 : 0) : pos;
   Row8Raw<F32> kraw[ATT_CHUNK / 16], vraw[ATT_CHUNK / 16];
 #pragma unroll
@@ -1171,11 +1172,15 @@ __global__ __launch_bounds__(256) void k_attn_partial(
 #pragma unroll
       for (int e = 0; e < 8; ++e) q[h][e] = fresh[h][c16 * 8 + e];
 #pragma unroll
-    for (int it = 0; it < ATT_CHUNK / 16; ++it)
-      if (j0 + (uint32_t)(it * 16 + wave * 4 + jj) == pos) {
+    for (int it = 0; it < ATT_CHUNK / 16; ++it) {
+      const uint32_t j = j0 + (uint32_t)(it * 16 + wave * 4 + jj);
+      if (j == pos) {
         kraw[it] = load_row8_raw<F32>(fresh[GH], c16 * 8);
         vraw[it] = load_row8_raw<F32>(fresh[GH + 1], c16 * 8);
+      } else if (j > pos) {
+        vraw[it].a = vraw[it].b = make_float4(0.f, 0.f, 0.f, 0.f);
       }
+    }
   } else {
 #pragma unroll
     for (int h = 0; h < GH; ++h) {
@@ -1229,7 +1234,7 @@ __global__ __launch_bounds__(256) void k_attn_partial(
   for (int it = 0; it < ATT_CHUNK / 16; ++it) {
     const int jl = it * 16 + wave * 4 + jj;
     float vv[8];
-    widen_row8<F32, HF>(vraw[it], vv);  // masked positions have weight 0 and hold row `pos` (finite)
+    widen_row8<F32, HF>(vraw[it], vv);  // masked positions have weight 0 and hold row `pos` (fused: zeros)
 #pragma unroll
     for (int h = 0; h < GH; ++h) {
       const float w = sc[h][jl];
@@ -1312,8 +1317,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FUSED ? 6 :
   const int c16 = lane & 15, g = lane >> 4;
   const size_t base = ((size_t)slot * nkv + kvh) * max_seq * 128;
 
-  // rows past the last cached one re-read it: valid memory, finite values, masked / weight 0
-  // below (fused: row `pos` is not cached yet; it is patched in from the role waves)
+  // rows past the last cached one re-read it: valid memory, masked / weight 0 below (fused: row `pos` is not
+  // cached yet, it is patched in from the role waves, and V rows past it count as zero: at position 0 the row read
+  // in their place is an earlier sequence's, which may not be finite)
   const uint32_t jlast = FUSED ? (pos > 0 ? pos - 1 : 0) : pos;
   const bool owns_new = pos - j0 < (uint32_t)ATT_CHUNK;
   uint2 vreg[4][2];
@@ -1412,13 +1418,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FUSED ? 6 :
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       uint2* d = reinterpret_cast<uint2*>(&Vs[(tid >> 4) + 16 * i][(tid & 15) * 4]);
-      if (FUSED && j0 + (uint32_t)((tid >> 4) + 16 * i) == pos) {
+      const uint32_t j = j0 + (uint32_t)((tid >> 4) + 16 * i);
+      if (FUSED && j == pos) {
         const uint2* nv = reinterpret_cast<const uint2*>(&vnew[(tid & 15) * 8]);
         d[0] = nv[0];
         d[1] = nv[1];
       } else {
-        d[0] = vreg[i][0];
-        d[1] = vreg[i][1];
+        const bool past = FUSED && j > pos;
+        d[0] = past ? make_uint2(0, 0) : vreg[i][0];
+        d[1] = past ? make_uint2(0, 0) : vreg[i][1];
       }
     }
     __syncthreads();  // (fused: every wave holds its query fragments in registers; the LDS behind them becomes pw)

@@ -603,6 +603,52 @@ def test_prompt_attention_never_meets_rows_past_its_tokens(nnc, heads, turns, at
         assert np.isfinite(b).all() and np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("dtype,heads", [(synth.F32, (4, 2)), (synth.F32, (3, 3)), (synth.F32, (8, 2)), (synth.BF16, (4, 2)), (synth.BF16, (16, 2)),
+                                         (synth.F16, (4, 2))], ids=str)
+def test_decode_from_an_empty_slot_never_meets_older_rows(nnc, dtype, heads, batch):
+    """Sequences of NaN rows, then others that begin on the same slots with decode steps (one kernel per stage): the same bits as on a
+    model that never saw the first.  At position 0 nothing of the cache belongs to the sequence, and the attention reads whole
+    chunks of positions, with weights of zero past the newest."""
+    print(f"case: decode steps from empty slots behind NaN rows, dtype {dtype}, heads {heads}, B={batch}", flush=True)
+    shape = dataclasses.replace(SMALL_BF16, dtype=dtype, n_q_heads=heads[0], n_kv_heads=heads[1])
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    synth.blob_tensor(shape, blob, "embed")[1023] = {synth.BF16: 0x7f80, synth.F16: 0x7c00, synth.F32: np.inf}[dtype]
+    slots, out = list(range(batch))[::-1], []
+    for dirty in (True, False):
+        g = nnc.Model(shape, blob, batch, 80)
+        g.set_option(nnc.OPT_PERSISTENT, 0)
+        if dirty:
+            for sl in slots:
+                g.prefill(sl, [1023] * 80, want_logits=False)
+                assert np.isnan(g.kv_read(1, sl, 1, 0, 80).cpu().numpy()).all()
+            g.kv_reset()
+        toks = synth.tokens(3 * batch, 1023, stream=11).reshape(3, batch)
+        out.append([g.decode_step(slots, t)[0].cpu().numpy()[:, :1023] for t in toks])
+        out[-1] += [g.kv_read(l, sl, w, 0, 3).cpu().numpy() for l in (0, 1) for sl in slots for w in (0, 1)]
+    for a, b in zip(*out):
+        assert np.isfinite(b).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("batch", [1, 2])
+def test_hidden_steps_from_an_empty_slot_never_meet_older_rows(nnc, batch):
+    """The same for single layers without embedding: rows of NaN in the cache, then steps from position 0, past the one that is
+    captured, and past the first chunk of positions."""
+    shape, slots, out = SMALL_LAYER_F32, list(range(batch)), []
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    rows = synth.activations(67 * batch, shape.hidden).reshape(67, batch, -1)
+    for dirty in (True, False):
+        g = nnc.Model(shape, blob, batch, 80)
+        if dirty:
+            for sl in slots:
+                g.prefill_hidden(sl, np.full((80, shape.hidden), np.nan, np.float32))
+                assert np.isnan(g.kv_read(0, sl, 1, 0, 80).cpu().numpy()).all()
+            g.kv_reset()
+        out.append([g.decode_step_hidden(slots, r).cpu().numpy() for r in rows])
+    for a, b in zip(*out):
+        assert np.isfinite(b).all() and np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("ffn", [4864, 8448])
 @pytest.mark.parametrize("batch", [1, 3])
 def test_resident_greedy_with_uneven_units(nnc, batch, ffn):
