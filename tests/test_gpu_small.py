@@ -910,16 +910,43 @@ def test_fused_fp32_attention_equals_separate_kernels(nnc, heads, batch, planner
 
 
 def test_hidden_rows_at_any_float_address(nnc):
-    """Rows that start between two sixteen-byte boundaries take the separate copy and norm: the same bits, prompt and step."""
+    """Rows that start between two sixteen-byte boundaries take the separate copy and norm: the same bits, prompt and steps, on a
+    model of their own and in turn with aligned rows on one model.  Its steps are replayed from two graphs by then, the aligned
+    rows' without the first norm: a step that replayed the other one would use the last step's operand."""
     import torch
-    x = torch.from_numpy(synth.activations(24, SMALL_LAYER_F32.hidden)).cuda()
+    x = torch.from_numpy(synth.activations(44, SMALL_LAYER_F32.hidden)).cuda()
     shifted = torch.empty(x.numel() + 1, dtype=torch.float32, device="cuda")[1:].view(x.shape).copy_(x)
     assert x.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 == 4 and shifted.is_contiguous()
     out = []
-    for rows in (x, shifted):
+    for rows in ([x], [shifted], [x, shifted], [shifted, x, x]):
         g, _ = _pair(nnc, SMALL_LAYER_F32, 2, 64)
-        out.append([g.prefill_hidden(1, rows[:20])] + [g.decode_step_hidden([1], rows[i:i + 1]) for i in range(20, 24)])
-    assert all(torch.equal(a, b) for a, b in zip(*out))
+        out.append([g.prefill_hidden(1, rows[0][:20])] + [g.decode_step_hidden([1], rows[i % len(rows)][i:i + 1]) for i in range(20, 44)])
+    for got in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], got))
+
+
+@pytest.mark.parametrize("heads", [(4, 2), (3, 3), (6, 2), (8, 2)], ids=str)
+def test_fp32_attention_of_one_chunk_equals_the_merge(nnc, heads):
+    """While every sequence of a pass has at most 64 positions, the fp32 attention writes the output projection's operand itself; with
+    a longer one beside it the same sequence's steps go through the merge kernel: the same bits, with QK-norm inside the
+    attention and without."""
+    shape = synth.ModelShape("f32-heads", hidden=256, n_layers=2, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, ffn=512, vocab=0,
+                             has_embed_and_head=False, tied_lm_head=False, dtype=synth.F32)
+    rows = synth.activations(90, shape.hidden)
+    for fused in (0, 1):
+        out = []
+        for other in (3, 64):
+            g, o = _pair(nnc, shape, 2, 80)
+            g.set_option(nnc.OPT_FUSE_QK, fused)
+            first = [g.prefill_hidden(0, rows[:5]).cpu().numpy()]
+            g.prefill_hidden(1, rows[20:20 + other])
+            out.append(first + [g.decode_step_hidden([0, 1], rows[[i, i + 5]]).cpu().numpy()[0] for i in range(5, 13)])
+            assert g.slot_len(1) == other + 8
+        for a, b in zip(*out):
+            assert np.array_equal(a, b)
+        for i in range(13):
+            want = o.step_hidden(0, rows[i].astype(np.float64))
+            assert rel_inf((out[0][0][i] if i < 5 else out[0][i - 4]).astype(np.float64), want) <= F32_REL
 
 
 @pytest.mark.parametrize("shape,fuse", [(SMALL_BF16, 1), (SMALL_G4, 0)], ids=["small-bf16-fused", "small-g4-separate"])
