@@ -267,9 +267,12 @@ typedef enum {
                                the sums run in another order.
                                Short blocks with few workgroups that -1 does not split use a kernel of their
                                own, whatever this says, while NNC_OPT_PLANNER is 1 */
-  NNC_OPT_FUSE_QK = 7,      /* 1 (default): per-stage decode passes of bf16 models do QK-norm, RoPE and
-                               the cache append inside the attention kernel (one kernel less per
-                               layer); 0: in a kernel of their own.  Bit-identical results */
+  NNC_OPT_FUSE_QK = 7,      /* 1 (default): per-stage decode passes (fp32 models, 16-bit models of at most
+                               eight query heads per kv head) do QK-norm, RoPE and the cache append inside
+                               the attention kernel (one kernel less per layer); 0: in a kernel of their
+                               own.  Bit-identical results while the QKV projection has one k slice (with
+                               NNC_OPT_PLANNER 0 always); the planner may give the attention kernel up to
+                               four partial sums of it, whose order of addition is another (fp32 rounding) */
   NNC_OPT_TAIL_OVERLAP = 8, /* 1 (default): the fp32-grade pass over the last tokens of a long prompt is
                                enqueued on a second stream of the library's own and runs beside the
                                prompt's last block, each of its layers waiting (event) for that
@@ -357,7 +360,9 @@ nnc_status nnc_stage_trace(nnc_model *m, uint64_t *out, uint32_t cap, uint32_t *
  *                                weights from HBM, t_comp_us = what the busiest compute unit moves
  *                                through its vector memory path (its workgroups' weight tiles and
  *                                operand reads); tile_rows = rows per workgroup (16 x 1, 2, 3, 4, 6
- *                                or 8 row tiles); max_k_slices = partial sums the consumer can add
+ *                                or 8 row tiles; with epilogue 0 and max_k_slices 1 they need not divide
+ *                                `rows`: the last workgroup then has fewer); max_k_slices = partial sums
+ *                                the consumer can add
  */
 typedef struct {
   uint32_t tile_rows, tile_cols;  /* block tile (rows x operand columns) */
