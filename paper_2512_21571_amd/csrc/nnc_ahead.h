@@ -20,7 +20,7 @@ namespace nnc {
 struct WeightAhead {
   const void* W = nullptr;  // NULL: nothing to do
   int n_tiles = 0, KT = 0, nt = 1;
-  uint32_t nt_inv = 0;      // row / nt = row * nt_inv >> 16 for row < 32768
+  uint32_t nt_inv = 0;      // row / nt = row * nt_inv >> 16 for row < 65536 / nt (past that one too many for some rows: another line is touched)
   int lines_log2 = 0;       // 128-byte lines touched per row tile, from its start
 };
 

@@ -1234,7 +1234,9 @@ static nnc_status prefill_head(nnc_model* m, uint32_t n, int pending, float* log
 // model time, against the block-tile GEMMs' model time + 35 us + a pass over the weights at 2.4 TB/s.
 // Measured as above: 0.6B 86.0 / 63.8 at 256; 1.7B 144.6 / 122.9 at 256, 165.4 / 169.1 at 300; 4B 206.8 / 190.7 at 192,
 // 219.6 / 228.6 at 208, 226.1 / 243.0 at 256; 8B 288 / 197 at 128, 337 / 307 at 192, 338 / 324 at 208, 344 - 370 (three cards) /
-// 357 at 256, 417 / 424 at 288.  With the block tiles as they are since, 8B 344 / 335 at 200, 355 / 366 at 250; 4B 219 / 207 at 192, 220 / 245 at 208.
+// 357 at 256, 417 / 424 at 288.  The block tiles have become faster since: 8B 344 / 335 at 200, 355 / 366 at 250; 4B 219 / 207 at 192, 220 / 245 at
+// 208.  With 35 us (25 before) the lines stay where they were: 4B at 192 tokens, the others at 256.  That is late for 8B, whose short-block
+// kernels are 3 % the slower ones at 250; with 25 its line would be at 192, where they are 3 % the faster ones.
 static bool short_block(const nnc_model* m, uint32_t n) {
   if (n > PB_SMALL_TOKENS || m->opt_prefill_exact == 1) return false;
   const double H = m->H();
@@ -1887,7 +1889,9 @@ nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const flo
   int pending = 0;
   p.pending_out = &pending;
   // One small layer is six kernels of a few microseconds here, one before and one behind, 36 us of the GPU per step against 69 of the
-  // host.  Launched one by one they take 1036 or 1368 us for a prompt and sixteen steps, by the run; as a graph 1084 - 1190, one run in five 1343.
+  // host.  A prompt and steps behind it as a graph / launched one by one, us, medians of seven processes each in turn: 0.6B, sixteen steps
+  // 1226 (1093 - 1422) / 1390 (1078 - 1574), one step 161 / 175, two layers, fifteen steps across position 64 1693 / 1818; 1.7B, sixteen steps 1480 /
+  // 1464.  (The first pass on a new model pays for the capture: 2051 / 1804, 2340 / 2387, 2174 / 1936.)
   const bool graph = m->opt_graph && !m->profiling && m->stream != nullptr && !being_captured(m);
   nnc_model::HiddenGraph* hg = graph ? &m->hidden_graphs[std::make_tuple((int)batch, p.nsplit, p.begun ? p.grid_chunks : -p.grid_chunks)] : nullptr;
   if (hg && !hg->exec && ++hg->uses > 2) {

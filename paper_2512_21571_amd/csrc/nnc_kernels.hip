@@ -1104,8 +1104,8 @@ struct AttnFuse {
 };
 // FUSED (fp32 decode passes): QK norm, rotary embedding and append run here too, as in k_attn_partial_mc below.
 // out != NULL: the chunk is the only one of every column, and the workgroup writes the operand of the output projection itself (the bits
-// that k_attn_combine would make of one record).  A layer of the 0.6B shape at 32 positions is ten kernels of 2 - 7 us without
-// these two and eight with them.
+// that k_attn_combine would make of one record; fp32 only).  A hidden-state step of one 0.6B layer at 32 positions is ten kernels of
+// 2 - 7 us without these two, k_qknorm_rope_append and k_attn_combine, and eight with them.
 template <bool F32, int GH, bool FUSED, class HF>
 __global__ __launch_bounds__(256) void k_attn_partial(
     const float* __restrict__ qkv, AttnFuse fz, int nq, int nkv, void* __restrict__ kc,
@@ -1255,9 +1255,11 @@ __global__ __launch_bounds__(256) void k_attn_partial(
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) v += (red[w][0][h][i] + red[w][1][h][i]) + (red[w][2][h][i] + red[w][3][h][i]);
-    if (out) {
-      store_packed<F32, HF>(out, NC, nsplit, col, (head0 + h) * 128 + i, v / sm_l[h]);
-      continue;
+    if constexpr (F32) {
+      if (out) {
+        store_packed<F32, HF>(out, NC, nsplit, col, (head0 + h) * 128 + i, v / sm_l[h]);
+        continue;
+      }
     }
     float* rec = partial + (((size_t)col * nq + head0 + h) * max_chunks + chunk) * 132;
     rec[i] = v;
