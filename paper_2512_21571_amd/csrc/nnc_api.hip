@@ -1889,9 +1889,9 @@ nnc_status nnc_decode_step_hidden(nnc_model* m, const uint32_t* slots, const flo
   int pending = 0;
   p.pending_out = &pending;
   // One small layer is six kernels of a few microseconds here, one before and one behind, 36 us of the GPU per step against 69 of the
-  // host.  A prompt and steps behind it as a graph / launched one by one, us, medians of seven processes each in turn: 0.6B, sixteen steps
-  // 1226 (1093 - 1422) / 1390 (1078 - 1574), one step 161 / 175, two layers, fifteen steps across position 64 1693 / 1818; 1.7B, sixteen steps 1480 /
-  // 1464.  (The first pass on a new model pays for the capture: 2051 / 1804, 2340 / 2387, 2174 / 1936.)
+  // host.  A prompt and steps behind it, us, processes in turn, as a graph / launched one by one: 0.6B, sixteen steps, twenty processes
+  // 1085 - 1254, median 1180 / nine 1033 - 1081, eleven 1315 - 1426; medians of seven: one step 161 / 175, two layers and fifteen steps
+  // across position 64 1693 / 1818; 1.7B, sixteen steps 1480 / 1464.  (The first pass on a new model pays for the capture: 1985 / 1667.)
   const bool graph = m->opt_graph && !m->profiling && m->stream != nullptr && !being_captured(m);
   nnc_model::HiddenGraph* hg = graph ? &m->hidden_graphs[std::make_tuple((int)batch, p.nsplit, p.begun ? p.grid_chunks : -p.grid_chunks)] : nullptr;
   if (hg && !hg->exec && ++hg->uses > 2) {
