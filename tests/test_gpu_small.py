@@ -603,6 +603,22 @@ def test_prompt_attention_never_meets_rows_past_its_tokens(nnc, heads, turns, at
         assert np.isfinite(b).all() and np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("shape", [SMALL_BF16, SMALL_G4, SMALL_F16, dataclasses.replace(HEADS16, dtype=synth.F16, ffn=3072)], ids=lambda s: s.name)
+def test_short_blocks_with_weights_touched_ahead_equal_those_without(nnc, shape):
+    """Blocks of three and more token tiles bring the next GEMM's weights into L2, of one or two they don't: the first 32 tokens
+    get the same cache rows in either (a token's sums don't depend on the others of its block; the shapes keep the row tiles per
+    workgroup, by which bf16 models group a row's sum of squares)."""
+    blob = synth.make_blob(shape, weight_std=0.05, gain_jitter=0.1)
+    toks, out = synth.tokens(96, shape.vocab, stream=3), []
+    for n in (32, 33, 96):
+        g = nnc.Model(shape, blob, 1, 128)
+        g.prefill(0, toks[:n], want_logits=False)
+        out.append([g.kv_read(l, 0, w, 0, 32).cpu().numpy() for l in (0, 1) for w in (0, 1)])
+    for got in out[1:]:
+        for a, b in zip(out[0], got):
+            assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("batch", [1, 3])
 @pytest.mark.parametrize("dtype,heads", [(synth.F32, (4, 2)), (synth.F32, (3, 3)), (synth.F32, (8, 2)), (synth.BF16, (4, 2)), (synth.BF16, (16, 2)),
                                          (synth.F16, (4, 2))], ids=str)
