@@ -926,15 +926,28 @@ def test_fused_fp32_attention_equals_separate_kernels(nnc, heads, batch, planner
 
 
 def test_hidden_rows_at_any_float_address(nnc):
-    """Rows that start between two sixteen-byte boundaries take the separate copy and norm: the same bits, prompt and steps, on a
-    model of their own and in turn with aligned rows on one model.  Its steps are replayed from two graphs by then, the aligned
-    rows' without the first norm: a step that replayed the other one would use the last step's operand."""
+    """Rows that start between two sixteen-byte boundaries take the separate copy and norm: the same bits, prompt and step."""
+    import torch
+    x = torch.from_numpy(synth.activations(24, SMALL_LAYER_F32.hidden)).cuda()
+    shifted = torch.empty(x.numel() + 1, dtype=torch.float32, device="cuda")[1:].view(x.shape).copy_(x)
+    assert x.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 == 4 and shifted.is_contiguous()
+    out = []
+    for rows in (x, shifted):
+        g, _ = _pair(nnc, SMALL_LAYER_F32, 2, 64)
+        out.append([g.prefill_hidden(1, rows[:20])] + [g.decode_step_hidden([1], rows[i:i + 1]) for i in range(20, 24)])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+def test_hidden_rows_of_both_alignments_on_one_model(nnc):
+    """Steps on rows at either kind of address in turn, past the ones that are captured: the bits of a model that gets aligned rows only.
+    The model then has two graphs, the aligned rows' without the first norm: a step that replayed the other one would
+    use the last step's operand."""
     import torch
     x = torch.from_numpy(synth.activations(44, SMALL_LAYER_F32.hidden)).cuda()
     shifted = torch.empty(x.numel() + 1, dtype=torch.float32, device="cuda")[1:].view(x.shape).copy_(x)
     assert x.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 == 4 and shifted.is_contiguous()
     out = []
-    for rows in ([x], [shifted], [x, shifted], [shifted, x, x]):
+    for rows in ([x], [x, shifted], [shifted, x, x]):
         g, _ = _pair(nnc, SMALL_LAYER_F32, 2, 64)
         out.append([g.prefill_hidden(1, rows[0][:20])] + [g.decode_step_hidden([1], rows[i % len(rows)][i:i + 1]) for i in range(20, 44)])
     for got in out[1:]:
